@@ -636,13 +636,15 @@ __global__ __launch_bounds__(64) void k_batch_band(FinalArgs f, int rows_max, in
     if (lane == 0) pre[0] = 0;
     __syncthreads();
     if (total == 0) return;
-    double* lobs = lds_band;
+    Math64& tab = *reinterpret_cast<Math64*>(lds_band);
+    double* lobs = lds_band + sizeof(Math64) / sizeof(double);
     double* zs = lobs + 3 * max_T;
-    uint64_t* rix = reinterpret_cast<uint64_t*>(zs + (size_t)5 * ROW_WINDOW * rows_max);
-    int32_t* rq = reinterpret_cast<int32_t*>(rix + rows_max);
-    RowWalk* rw = reinterpret_cast<RowWalk*>(rq + 2 * rows_max);  // rq padded to 8 B per row
-    int32_t* xs = reinterpret_cast<int32_t*>(rw + rows_max);
-    float* rth = reinterpret_cast<float*>(xs + (size_t)3 * ROW_WINDOW * rows_max);
+    uint64_t* rix = reinterpret_cast<uint64_t*>(zs + 5 * ROW_PAIRS);
+    int32_t* rq = reinterpret_cast<int32_t*>(rix + ROWS_PER_WAVE_MAX);
+    int32_t* xs = rq + ROWS_PER_WAVE_MAX;
+    float* rth = reinterpret_cast<float*>(xs + 4 * ROW_PAIRS);
+    stage_math64(tab);
+    __syncthreads();
     int staged = -1;
     for (;;) {
         int c = 0;
@@ -664,7 +666,7 @@ __global__ __launch_bounds__(64) void k_batch_band(FinalArgs f, int rows_max, in
         int64_t* cidx = a.cand_idx + (int64_t)s * a.cand_cap;
         float* cdist = a.cand_dist + (int64_t)s * a.cand_cap;
         if (staged != s) {
-            stage_obs_f64<0>(f.obs[s], d.T, lobs);
+            stage_obs_f64<0>(f.obs[s], d.T, lobs, tab);
             staged = s;
         }
         if (lane < nr) {
@@ -679,8 +681,8 @@ __global__ __launch_bounds__(64) void k_batch_band(FinalArgs f, int rows_max, in
         }
         __syncthreads();
         const double d64 = simulate_rows_f64_wave<0, 0>(nr, rth, rix, a.key, d.series_id, a.domain, d.P,
-                                                       d.A0, d.R0, d.D0, d.T, (double)a.scale, lobs, zs,
-                                                       xs, rw);
+                                                       d.A0, d.R0, d.D0, d.T, (double)a.scale, lobs, tab,
+                                                       zs, xs);
         if (lane < nr) {
             const int q = rq[lane];
             cdist[q] = (float)d64;
@@ -691,11 +693,10 @@ __global__ __launch_bounds__(64) void k_batch_band(FinalArgs f, int rows_max, in
     }
 }
 
-static size_t band_lds_bytes(int maxT, int R)
+static size_t band_lds_bytes(int maxT)
 {
-    return sizeof(double) * 3 * (size_t)maxT +
-           (size_t)R * (sizeof(double) * 5 * ROW_WINDOW + sizeof(uint64_t) + 2 * sizeof(int32_t) +
-                        sizeof(RowWalk) + sizeof(int32_t) * 3 * ROW_WINDOW + sizeof(float) * 8);
+    return sizeof(Math64) + sizeof(double) * (3 * (size_t)maxT + 5 * ROW_PAIRS) + sizeof(int32_t) * 4 * ROW_PAIRS +
+           (size_t)ROWS_PER_WAVE_MAX * (sizeof(uint64_t) + sizeof(int32_t) + sizeof(float) * 8);
 }
 
 // Finalisation: one workgroup per series sorts its candidates by index and
@@ -1131,8 +1132,8 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     const int npow = npow_cap;
     const size_t lds_f = sizeof(int64_t) * npow + sizeof(float) * (npow + 1) + 16;
     ABC_REQUIRE(lds_f <= (size_t)max_lds, "quota too large for the finalisation");
-    const int band_rows = ROWS_PER_WAVE_MAX;
-    const size_t lds_band = band_lds_bytes(maxT, band_rows);
+    const int band_rows = 12;  // 8 and 16 a few percent slower: the longest walk sets the time
+    const size_t lds_band = band_lds_bytes(maxT);
     ABC_REQUIRE(lds_band <= (size_t)max_lds, "horizon too long for the band decision");
     // A series stops taking samples once its float32 accepts (d <= eps)
     // reach its target, first Q + margin. Float64 decisions of band rows can

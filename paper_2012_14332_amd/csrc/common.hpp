@@ -13,12 +13,6 @@ namespace abc {
 
 abc_status set_error(abc_status st, const char* fmt, ...);
 
-// LDS budget of a float64 row workgroup (several rows side by side per
-// wavefront): small where the rows run beside a float32 launch, so that they
-// do not crowd its workgroups out of the CU (the plain band decision), larger
-// where they run alone (the SMC band decision, float64 row distances).
-constexpr size_t ROW_LDS_BESIDE = 8192;
-constexpr size_t ROW_LDS_ALONE = 20480;
 // Float64 row wavefronts that spread rows over all SIMDs (one per SIMD) when
 // the row kernel runs alone; beside a float32 launch the band decision
 // spreads over up to twice as many.
@@ -30,17 +24,15 @@ constexpr int64_t ROW_WAVE_TARGET = 1024;
 // (packed wavefronts live longer); alone the rows are spread for the
 // shortest latency.
 constexpr int32_t ROW_SCAN_BESIDE = 8;
-constexpr int32_t ROW_SCAN_ALONE = 1;
+constexpr int32_t ROW_SCAN_ALONE = 4;
 
-// abc_recheck_band with a chosen LDS budget per row workgroup, grid cap and
-// candidates per wavefront; with all_rows every candidate (not only those in
+// abc_recheck_band with a chosen grid cap and candidates per wavefront; with all_rows every candidate (not only those in
 // the band) is decided by its float64 distance, and dist64 (nullable,
 // [capacity]) receives that distance for each row, compacted with the rows.
 abc_status recheck_band(const abc_series* ser, const abc_model* model, const abc_stream* st,
                         float eps, float band_w, int64_t capacity, int64_t* idx, float* theta,
                         float* dist, float* weight, int64_t* count, int32_t* rechecked,
-                        void* stream, size_t lds_budget, int64_t grid_max, int32_t scan_min,
-                        double* dist64, bool all_rows);
+                        void* stream, int64_t grid_max, int32_t scan_min, double* dist64, bool all_rows);
 
 #define ABC_REQUIRE(cond, ...)                                 \
     do {                                                       \

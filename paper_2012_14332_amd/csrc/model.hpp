@@ -18,6 +18,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "math64.hpp"
 #include "philox.hpp"
 
 namespace abc {
@@ -184,10 +185,10 @@ __device__ __forceinline__ float log2p1_count_f32(int32_t X)
 
 // ---------------------------------------------------------------------------
 // float64 path: the same definitions evaluated in the order the oracle writes
-// them (no contraction), with the device math library's log/sin/cos/pow/log1p.
+// them (no contraction), with the functions of math64.hpp.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ void normals_f64(uint4 w, double z[5])
+__device__ __forceinline__ void normals_f64(uint4 w, const Math64& tab, double z[5])
 {
 #pragma clang fp contract(off)
     uint32_t f[6];
@@ -196,45 +197,81 @@ __device__ __forceinline__ void normals_f64(uint4 w, double z[5])
 #pragma unroll
     for (int k = 0; k < 6; ++k) u[k] = ((double)f[k] + 0.5) * 0x1p-21;
     const double two_pi = 2.0 * 3.14159265358979323846;
-    const double r0 = sqrt(-2.0 * log(u[0]));
-    const double r1 = sqrt(-2.0 * log(u[2]));
-    const double r2 = sqrt(-2.0 * log(u[4]));
-    z[0] = r0 * cos(two_pi * u[1]);
-    z[1] = r0 * sin(two_pi * u[1]);
-    z[2] = r1 * cos(two_pi * u[3]);
-    z[3] = r1 * sin(two_pi * u[3]);
-    z[4] = r2 * cos(two_pi * u[5]);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const double r = sqrt_mid(-2.0 * log_mid(u[2 * j], tab));
+        double sn, cs;
+        sincos_turn(two_pi * u[2 * j + 1], sn, cs);
+        z[2 * j] = r * cs;
+        if (j < 2) z[2 * j + 1] = r * sn;
+    }
+}
+
+// Quotient and power for parameters outside math64.hpp's ranges (n above
+// POW_N_MAX, or a parameter that is not finite): the library's own, out of line.
+__device__ __attribute__((noinline)) double force_general(double M, double n, double a0, double al)
+{
+#pragma clang fp contract(off)
+    return a0 + al / (1.0 + pow(M, n));
+}
+
+__device__ __attribute__((noinline)) double div_general(double x, double y) { return x / y; }
+
+__device__ __forceinline__ bool theta_mid(const float t[8])
+{
+    bool ok = t[2] >= 0.0f && t[2] <= POW_N_MAX;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) ok = ok && fabsf(t[k]) < INFINITY;
+    return ok;
+}
+
+// g of eq. (4) from p = pow_arg(M, n), M = A + R + D >= A0 >= 1
+__device__ __forceinline__ double force_f64(PowArg p, double a0, double al, const Math64& tab)
+{
+#pragma clang fp contract(off)
+    return a0 + div_mid(al, 1.0 + pow_exp(p, tab));
 }
 
 template <int NOISE>
-__device__ __forceinline__ int32_t draw_f64(double h, double z, int32_t avail, double scale)
+__device__ __forceinline__ double sd_f64(double h, double scale)
+{
+    return NOISE == 0 ? scale * sqrt_mid(h) : scale * sqrt_mid(sqrt_mid(h));
+}
+
+// Integer part of x, limited to int32 (NaN: 0), as the conversion instruction
+// gives it; in C++ the cast of a value out of range has no result.
+__device__ __forceinline__ int32_t cvt_i32_sat(double x)
+{
+    int32_t r;
+    asm("v_cvt_i32_f64_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// floor(h + sd z) limited to [0, 2^31 - 1] (NaN: 0); the caller limits it to
+// what the source holds
+template <int NOISE>
+__device__ __forceinline__ int32_t draw_f64(double h, double z, double scale)
 {
 #pragma clang fp contract(off)
-    double sd = NOISE == 0 ? scale * sqrt(h) : scale * sqrt(sqrt(h));
-    const double x = h + sd * z;
-    const double f = floor(x);
-    if (!(f > 0.0)) return 0;
-    if (f >= (double)avail) return avail;
-    return (int32_t)f;
+    const double x = h + sd_f64<NOISE>(h, scale) * z;
+    return max(cvt_i32_sat(x), 0);  // truncation is the floor of x >= 0
 }
 
 template <int NOISE>
-__device__ __forceinline__ void day_step_f64(State& s, const Theta& t, double P, double scale,
-                                             const double z[5])
+__device__ __forceinline__ void day_step_f64(State& s, const Theta& t, bool mid, double P, double rP,
+                                             double scale, const double z[5], const Math64& tab)
 {
 #pragma clang fp contract(off)
-    const double M = (double)(s.A + s.R + s.D);
-    const double g = (double)t.a0 + (double)t.al / (1.0 + pow(M, (double)t.n));
-    const double h1 = g * (double)s.S * (double)s.I / P;
-    const double h2 = (double)t.ga * (double)s.I;
-    const double h3 = (double)t.be * (double)s.A;
-    const double h4 = (double)t.de * (double)s.A;
-    const double h5 = (double)t.be * (double)t.et * (double)s.I;
-    const int32_t n1 = draw_f64<NOISE>(h1, z[0], s.S, scale);
-    const int32_t n2 = draw_f64<NOISE>(h2, z[1], s.I, scale);
-    const int32_t n3 = draw_f64<NOISE>(h3, z[2], s.A, scale);
-    const int32_t n4 = draw_f64<NOISE>(h4, z[3], s.A - n3, scale);
-    const int32_t n5 = draw_f64<NOISE>(h5, z[4], s.I - n2, scale);
+    const double M = (double)(s.A + s.R + s.D), n = (double)t.n, a0 = (double)t.a0, al = (double)t.al;
+    const double g = mid ? force_f64(pow_arg(M, n, tab), a0, al, tab) : force_general(M, n, a0, al);
+    const double If = (double)s.I, Af = (double)s.A;
+    const double h0 = g * (double)s.S * If;
+    const double h1 = mid ? div_by(h0, P, rP) : div_general(h0, P);
+    const int32_t n1 = min(draw_f64<NOISE>(h1, z[0], scale), s.S);
+    const int32_t n2 = min(draw_f64<NOISE>((double)t.ga * If, z[1], scale), s.I);
+    const int32_t n3 = min(draw_f64<NOISE>((double)t.be * Af, z[2], scale), s.A);
+    const int32_t n4 = min(draw_f64<NOISE>((double)t.de * Af, z[3], scale), s.A - n3);
+    const int32_t n5 = min(draw_f64<NOISE>((double)t.be * (double)t.et * If, z[4], scale), s.I - n2);
     s.S -= n1;
     s.I += n1 - n2 - n5;
     s.A += n2 - n3 - n4;
@@ -243,171 +280,187 @@ __device__ __forceinline__ void day_step_f64(State& s, const Theta& t, double P,
     s.Ru += n5;
 }
 
-// Observed series for the float64 distance: log1p(O), or O for the raw distance.
+// ln(1 + X) of a count (X + 1 is exact in float64)
+__device__ __forceinline__ double log1p_count_f64(int32_t X, const Math64& tab)
+{
+    return log_mid((double)X + 1.0, tab);
+}
+
+// Observed series for the float64 distance: log1p(O), or O for the raw
+// distance. Observed counts below 0 take the library's log1p (NaN or -inf).
 template <int DIST>
-__device__ __forceinline__ void stage_obs_f64(const int32_t* obs, int T, double* lds)
+__device__ __forceinline__ void stage_obs_f64(const int32_t* obs, int T, double* lds, const Math64& tab)
 {
     for (int q = threadIdx.x; q < 3 * T; q += blockDim.x) {
         const int32_t O = obs[q];
-        lds[q] = DIST == 0 ? log1p((double)O) : (double)O;
+        lds[q] = DIST == 0 ? (O >= 0 ? log1p_count_f64(O, tab) : log1p((double)O)) : (double)O;
     }
-}
-
-// One trajectory in float64; returns +INF once the squared distance passes
-// exit_sq.
-template <int NOISE, int DIST>
-__device__ inline double simulate_one_f64(const float thv[8], uint64_t i, Key key, uint32_t series,
-                                   uint32_t domain, int32_t P, int32_t A0, int32_t R0, int32_t D0,
-                                   int T, double scale, const double* lds, double exit_sq)
-{
-#pragma clang fp contract(off)
-    const Theta th = theta_from(thv);
-    State s = init_state(th.ka, P, A0, R0, D0);
-    const double Pd = (double)P;
-    double acc = 0.0;
-    for (int t = 1; t <= T; ++t) {
-        const uint4 w = stream_words(key, i, series, ctr_word3((uint32_t)t, domain, 0));
-        double z[5];
-        normals_f64(w, z);
-        day_step_f64<NOISE>(s, th, Pd, scale, z);
-        const int32_t X[3] = {s.A, s.R, s.D};
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double d;
-            if (DIST == 0)
-                d = log1p((double)X[c]) - lds[c * T + t - 1];
-            else
-                d = (double)X[c] - lds[c * T + t - 1];
-            acc += d * d;
-        }
-        if (acc > exit_sq) return (double)INFINITY;
-    }
-    return sqrt(acc);
 }
 
 // Up to ROWS_PER_WAVE_MAX float64 trajectories run by one wavefront (one
-// wavefront per workgroup), ROW_WINDOW days at a time: the lanes draw the
-// normals of every (row, day) pair of the window in parallel, lane r walks
-// row r through the window's days, the lanes form the window's squared
-// distance terms in parallel, and lane r adds its row's terms in day order
-// (the order of simulate_one_f64, so each result is the same double).
-// A float64 instruction occupies the SIMD for the same cycles whatever its
-// lane mask, so rows walked side by side in lanes cost no more than one.
-// Each row's counts and running sum stay in LDS between the phases, so no
-// phase holds another's registers.
+// wavefront per workgroup), in windows of W = ROW_PAIRS / nr
+// days (at most ROW_DAYS_MAX): the lanes
+// draw the normals of the window's (row, day) pairs in parallel, one pair a
+// lane; then four lanes walk each row through the window's days; the lanes form
+// the window's squared distance terms in parallel, and lane r adds its row's
+// terms in day order (the order of the one-lane-per-sample kernel, so each
+// result is the same double).
+//
+// A walk is a serial chain, so what bounds it is its length in instructions:
+// a float64 instruction occupies the SIMD for the same four cycles whatever
+// its lane mask. Four of a day's five draws need only the counts of the
+// morning, so the four lanes of a row make them as one (each lane its own rate
+// and normal, the counts exchanged within the quad by DPP); the fifth waits
+// for g. A day's M = A + R + D depends on the previous day's recoveries n2
+// alone, so M^n is taken in two halves: its logarithm beside the infections of
+// the day before, its exponential beside the four draws of its own day. With
+// every row within math64.hpp's ranges a day is one basic block, in which the
+// two chains interleave. A day takes 0.46 us with its share of the other
+// phases (49 days of 114 rows: 28 us); with one lane per row, all five draws in
+// turn and the library's functions it took 1.9 us (94 us).
+//
 // Rows r < nr: theta rth[8 r .. 8 r + 7] and sample index rix[r], in LDS.
-// Scratch in LDS: zs [nr][5 ROW_WINDOW] doubles (normals, then the distance
-// terms), xs [nr][3 ROW_WINDOW] int32, rw [nr] walk states. Returns row r's
-// distance on lane r < nr (other lanes return 0).
-constexpr int ROWS_PER_WAVE_MAX = 8;
-constexpr int ROW_WINDOW = 8;
+// Scratch in LDS: zs [5 ROW_PAIRS] doubles (normals, then the distance terms),
+// xs [4 ROW_PAIRS] int32. Returns row r's distance on lane r < nr (other lanes 0).
+constexpr int ROWS_PER_WAVE_MAX = 16;
+constexpr int ROW_PAIRS = 64;
+constexpr int ROW_DAYS_MAX = 32;
 
+// value of lane L of the calling lane's group of four
+template <int L>
+__device__ __forceinline__ int32_t quad_lane(int32_t x)
+{
+    return __builtin_amdgcn_mov_dpp(x, L * 0x55, 0xF, 0xF, true);
+}
+
+// One row's walk state and constants, alike on its four lanes.
 struct RowWalk {
     State s;
-    int32_t pad[2];
-    double acc;
+    int32_t M;
+    PowArg p;              // of M
+    double a0, al, nn, rate;
+    double P, rP, scale;
+    bool mid, ofA;
+    int role;
 };
 
-// The three phases of a window are separate functions: each keeps its own
-// constants and temporaries, so the kernel needs the registers of the largest
-// phase rather than of all three.
-__device__ __attribute__((noinline)) void rows_window_normals(int nr, int nd, int t0,
-                                                              const uint64_t* rix, Key key,
-                                                              uint32_t series, uint32_t domain,
-                                                              double* zs)
-{
-    constexpr int ZW = 5 * ROW_WINDOW;
-    const int lane = threadIdx.x & 63;
-#pragma unroll 1
-    for (int p = lane; p < nr * nd; p += 64) {
-        const int r = p / nd, u = p - r * nd;
-        const uint4 w = stream_words(key, rix[r], series, ctr_word3((uint32_t)(t0 + u), domain, 0));
-        double z[5];
-        normals_f64(w, z);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) zs[r * ZW + 5 * u + k] = z[k];
-    }
-}
-
-template <int NOISE>
-__device__ __attribute__((noinline)) void rows_window_walk(const float* th8, State* sp,
-                                                           const double* zr, int32_t* xr, int nd,
-                                                           int32_t P, double scale)
+// nd days of a row: normals zr [nd][5], counts A, R, D to xr [nd][4]
+template <int NOISE, bool MID>
+__device__ __forceinline__ void walk_window(RowWalk& w, int nd, const double* zr, int32_t* xr, const Math64& tab)
 {
 #pragma clang fp contract(off)
-    float thv[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) thv[k] = th8[k];
-    const Theta th = theta_from(thv);
-    State s = *sp;
+    State& s = w.s;
+    double z1 = zr[0], zq = zr[1 + w.role];
 #pragma unroll 1
     for (int u = 0; u < nd; ++u) {
-        double z[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) z[k] = zr[5 * u + k];
-        day_step_f64<NOISE>(s, th, (double)P, scale, z);
-        xr[3 * u + 0] = s.A;
-        xr[3 * u + 1] = s.R;
-        xr[3 * u + 2] = s.D;
-    }
-    *sp = s;
-}
-
-template <int DIST>
-__device__ __attribute__((noinline)) void rows_window_terms(int nr, int nd, int t0, int T,
-                                                            const int32_t* xs, const double* lobs,
-                                                            double* zs)
-{
-#pragma clang fp contract(off)
-    constexpr int ZW = 5 * ROW_WINDOW, XW = 3 * ROW_WINDOW;
-    const int lane = threadIdx.x & 63;
-#pragma unroll 1
-    for (int p = lane; p < nr * 3 * nd; p += 64) {
-        const int r = p / (3 * nd), q = p - r * 3 * nd;
-        const int u = q / 3, c = q - 3 * u;
-        const int t = t0 - 1 + u;  // 0-based day
-        double d;
-        if (DIST == 0)
-            d = log1p((double)xs[r * XW + q]) - lobs[c * T + t];
-        else
-            d = (double)xs[r * XW + q] - lobs[c * T + t];
-        zs[r * ZW + q] = d * d;
+        const int v = u + 1 < nd ? u + 1 : u;
+        const double z1n = zr[5 * v], zqn = zr[5 * v + 1 + w.role];
+        const double g = MID || w.mid ? force_f64(w.p, w.a0, w.al, tab)
+                                      : force_general((double)w.M, w.nn, w.a0, w.al);
+        const int32_t d4 = draw_f64<NOISE>(w.rate * (double)(w.ofA ? s.A : s.I), zq, w.scale);
+        const int32_t n2 = min(quad_lane<0>(d4), s.I);
+        w.M += n2;
+        if (MID || w.mid) w.p = pow_arg((double)w.M, w.nn, tab);
+        const double h0 = g * (double)s.S * (double)s.I;
+        const double h1 = MID || w.mid ? div_by(h0, w.P, w.rP) : div_general(h0, w.P);
+        const int32_t n1 = min(draw_f64<NOISE>(h1, z1, w.scale), s.S);
+        const int32_t n3 = min(quad_lane<1>(d4), s.A);
+        const int32_t n4 = min(quad_lane<2>(d4), s.A - n3);
+        const int32_t n5 = min(quad_lane<3>(d4), s.I - n2);
+        s.S -= n1;
+        s.I += n1 - n2 - n5;
+        s.A += n2 - n3 - n4;
+        s.R += n3;
+        s.D += n4;
+        const int32_t ar = w.role == 0 ? s.A : s.R;
+        xr[4 * u + w.role] = w.role < 2 ? ar : s.D;  // the fourth is not read
+        z1 = z1n;
+        zq = zqn;
     }
 }
 
 template <int NOISE, int DIST>
-__device__ double simulate_rows_f64_wave(int nr, const float* rth, const uint64_t* rix, Key key,
-                                         uint32_t series, uint32_t domain, int32_t P, int32_t A0,
-                                         int32_t R0, int32_t D0, int T, double scale,
-                                         const double* lobs, double* zs, int32_t* xs, RowWalk* rw)
+__device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rth, const uint64_t* rix,
+                                                         Key key, uint32_t series, uint32_t domain,
+                                                         int32_t P, int32_t A0, int32_t R0, int32_t D0,
+                                                         int T, double scale, const double* lobs,
+                                                         const Math64& tab, double* zs, int32_t* xs)
 {
 #pragma clang fp contract(off)
-    constexpr int ZW = 5 * ROW_WINDOW, XW = 3 * ROW_WINDOW;
     const int lane = threadIdx.x & 63;
-    const bool walker = lane < nr;
-    if (walker) {
-        rw[lane].s = init_state(rth[8 * lane + 7], P, A0, R0, D0);
-        rw[lane].acc = 0.0;
+    const int W = min(ROW_PAIRS / nr, ROW_DAYS_MAX);
+    // the row's walk: lanes 4 r .. 4 r + 3
+    const int row = (lane >> 2) < nr ? (lane >> 2) : 0, role = lane & 3;
+    const bool walker = (lane >> 2) < nr;
+    RowWalk wk;
+    {
+        float th[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) th[k] = rth[8 * row + k];
+        wk.mid = theta_mid(th);
+        wk.P = (double)P;
+        wk.rP = 1.0 / wk.P;
+        wk.scale = scale;
+        wk.a0 = (double)th[0];
+        wk.al = (double)th[1];
+        wk.nn = (double)th[2];
+        // this lane's draw: n2 (gamma I), n3 (beta A), n4 (delta A), n5 (beta eta I)
+        wk.role = role;
+        wk.ofA = role == 1 || role == 2;
+        wk.rate = role == 0 ? (double)th[4]
+                            : (role == 1 ? (double)th[3]
+                                         : (role == 2 ? (double)th[5] : (double)th[3] * (double)th[6]));
+        wk.s = init_state(th[7], P, A0, R0, D0);
+        wk.M = A0 + R0 + D0;
+        wk.p = pow_arg((double)wk.M, wk.nn, tab);  // not used unless mid
     }
-    for (int t0 = 1; t0 <= T; t0 += ROW_WINDOW) {
-        const int nd = T - t0 + 1 < ROW_WINDOW ? T - t0 + 1 : ROW_WINDOW;
-        rows_window_normals(nr, nd, t0, rix, key, series, domain, zs);
-        __syncthreads();
-        if (walker)
-            rows_window_walk<NOISE>(rth + 8 * lane, &rw[lane].s, zs + lane * ZW, xs + lane * XW, nd,
-                                    P, scale);
-        __syncthreads();
-        rows_window_terms<DIST>(nr, nd, t0, T, xs, lobs, zs);
+    const bool all_mid = __ballot(!wk.mid) == 0ull;
+    double acc = 0.0;
+    for (int t0 = 1; t0 <= T; t0 += W) {
+        const int nd = T - t0 + 1 < W ? T - t0 + 1 : W;
+        {
+            const int r = lane / nd, u = lane - r * nd;
+            if (r < nr) {
+                const uint4 w = stream_words(key, rix[r], series, ctr_word3((uint32_t)(t0 + u), domain, 0));
+                double z[5];
+                normals_f64(w, tab, z);
+#pragma unroll
+                for (int k = 0; k < 5; ++k) zs[5 * (r * W + u) + k] = z[k];
+            }
+        }
         __syncthreads();
         if (walker) {
-            const double* tr = zs + lane * ZW;
-            double acc = rw[lane].acc;
-            for (int q = 0; q < 3 * nd; ++q) acc += tr[q];
-            rw[lane].acc = acc;
+            if (all_mid)
+                walk_window<NOISE, true>(wk, nd, zs + 5 * row * W, xs + 4 * row * W, tab);
+            else
+                walk_window<NOISE, false>(wk, nd, zs + 5 * row * W, xs + 4 * row * W, tab);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int p = lane; p < nr * 3 * nd; p += 64) {
+            const int r = p / (3 * nd), q = p - r * 3 * nd;
+            const int u = q / 3, c = q - 3 * u;
+            const int t = t0 - 1 + u;  // 0-based day
+            const int32_t X = xs[4 * (r * W + u) + c];
+            const double d = (DIST == 0 ? log1p_count_f64(X, tab) : (double)X) - lobs[c * T + t];
+            zs[5 * r * W + q] = d * d;
+        }
+        __syncthreads();
+        if (lane < nr) {
+            const double* tr = zs + 5 * lane * W;
+            int q = 0;
+            for (; q + 6 <= 3 * nd; q += 6) {
+                double v[6];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) v[k] = tr[q + k];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) acc += v[k];
+            }
+            for (; q < 3 * nd; ++q) acc += tr[q];
         }
         __syncthreads();  // the window's scratch is reused by the next one
     }
-    return walker ? sqrt(rw[lane].acc) : 0.0;
+    return lane < nr ? sqrt_mid(acc) : 0.0;
 }
 
 }  // namespace abc

@@ -298,27 +298,120 @@ __global__ __launch_bounds__(1024 / SPL) void k_simulate_f32(SimArgs a)
 // float64 simulate + distance (precision study, recheck of borderline samples)
 // ---------------------------------------------------------------------------
 
+// Lane refill as in the float32 kernel: each wavefront walks its share of the
+// 64-sample chunks as a queue, and the idle lanes take the next positions once
+// at least F64_REFILL of them are idle. A sample's parameters are drawn (or
+// read) by the lane that takes it: two Philox blocks are short beside a
+// float64 day. Bound by float64 issue: one day is about 430 instructions of
+// four cycles each. With one lane per sample for the whole launch, early exits
+// left most lanes idle behind the longest trajectory of their wavefront: 1e6
+// samples of T = 100 at the 1e-3 quantile took 3.46 ms (with the library's
+// functions), now 0.73 ms.
+constexpr int F64_BLOCK = 512;
+constexpr int F64_REFILL = 8;
+constexpr int F64_BLOCKS_PER_CU = 1;
+
 template <int NOISE, int DIST, bool PRIOR>
-__global__ __launch_bounds__(SIM_BLOCK) void k_simulate_f64(SimArgs a)
+__global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
 {
-    extern __shared__ double lds_d[];  // [3][T]
-    stage_obs_f64<DIST>(a.obs, a.T, lds_d);
+#pragma clang fp contract(off)
+    // Math64 | [3][T] | future-days bound [2][ntb][LB_Q] f32, then the space that builds it
+    extern __shared__ double lds_d[];
+    Math64& tab = *reinterpret_cast<Math64*>(lds_d);
+    double* lobs = lds_d + sizeof(Math64) / sizeof(double);
+    const int ntb = DIST == 0 ? a.lb_ntb : 0;
+    double* stage = lobs + 3 * a.T;
+    float* lbt = reinterpret_cast<float*>(stage + (ntb > 0 ? 2 * a.T + LB_MAX_SEG * 2 * LB_Q : 0));
+    stage_math64(tab);
     __syncthreads();
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.n) return;
-    const uint64_t i = a.first + (uint64_t)k;
-    float thv[8];
-    load_or_draw_theta(a, PRIOR, k, i, thv);
-    if (!PRIOR && a.box && outside_box(a, thv)) {
-        a.dist[k] = INFINITY;
-        if (a.dist64) a.dist64[k] = (double)INFINITY;
-        return;
+    stage_obs_f64<DIST>(a.obs, a.T, lobs, tab);
+    if (DIST == 0 && ntb > 0) {
+        for (int q = threadIdx.x; q < 2 * a.T; q += blockDim.x)
+            stage[q] = log1p((double)a.obs[a.T + q]) * 1.44269504088896340736;
+        __syncthreads();
+        build_future_bound(stage, a.T, a.lb_sh, ntb, (double)a.exit_f32, lbt);
     }
-    const double dd = simulate_one_f64<NOISE, DIST>(thv, i, a.key, a.series, a.domain, a.P, a.A0,
-                                                    a.R0, a.D0, a.T, (double)a.scale, lds_d,
-                                                    a.exit_f64);
-    a.dist[k] = (float)dd;
-    if (a.dist64) a.dist64[k] = dd;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t wg = (int64_t)blockIdx.x * (F64_BLOCK / 64) + wv;
+    const int64_t nw = (int64_t)gridDim.x * (F64_BLOCK / 64);
+    const int64_t nchunks = (a.n + 63) >> 6;
+    if (wg >= nchunks) return;
+    // queue positions of this wave: its j-th chunk is wg + j nw
+    const int64_t Q = ((nchunks - 1 - wg) / nw + 1) << 6;
+    const int T = a.T;
+    const double Pd = (double)a.P, rP = 1.0 / Pd, scale = (double)a.scale;
+    const PhiloxSeries ps = philox_series(a.series, a.key);
+    constexpr double LOG2E = 1.44269504088896340736;
+
+    int64_t qb = 0, k = 0;
+    PhiloxDays ph{};
+    int t = 0;  // the day simulated next; 0: no sample (idle)
+    State s{};
+    float thv[8];
+    bool mid = true;
+    double acc = 0.0;
+    while (true) {
+        const uint64_t m = __ballot(t == 0);
+        if (qb < Q && __popcll(m) >= F64_REFILL) {
+            const int64_t q = qb + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const int64_t kk = ((wg + (q >> 6) * nw) << 6) + (q & 63);
+            if (t == 0 && q < Q && kk < a.n) {
+                k = kk;
+                load_or_draw_theta(a, PRIOR, k, a.first + (uint64_t)k, thv);
+                if (!PRIOR && a.box && outside_box(a, thv)) {
+                    a.dist[k] = INFINITY;
+                    if (a.dist64) a.dist64[k] = (double)INFINITY;
+                } else {
+                    s = init_state(thv[7], a.P, a.A0, a.R0, a.D0);
+                    mid = theta_mid(thv);
+                    ph.begin(a.first + (uint64_t)k, ps.u0, a.key);
+                    acc = 0.0;
+                    t = 1;
+                }
+            }
+            qb += __popcll(m);
+        }
+        if (__ballot(t != 0) == 0ull) {
+            if (qb >= Q) break;
+            continue;
+        }
+        if (t != 0) {
+            const uint4 w = ph.day(ctr_word3((uint32_t)t, a.domain, 0), ps.b1, a.key);
+            double z[5];
+            normals_f64(w, tab, z);
+            day_step_f64<NOISE>(s, theta_from(thv), mid, Pd, rP, scale, z, tab);
+            const int32_t X[3] = {s.A, s.R, s.D};
+            double lx[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                lx[c] = DIST == 0 ? log1p_count_f64(X[c], tab) : (double)X[c];
+                const double d = lx[c] - lobs[c * T + t - 1];
+                acc += d * d;
+            }
+            // the days still to come, bounded below in float32 with its own
+            // margins: a sample it ends would have passed the exit bound
+            float lb = 0.0f;
+            if (DIST == 0 && ntb > 0) {
+                const float* row = lbt + (t >> a.lb_sh) * LB_Q;
+                const int qr = (int)fmaf((float)(lx[1] * LOG2E), 2.0f, -0x1p-12f);
+                const int qd = (int)fmaf((float)(lx[2] * LOG2E), 2.0f, -0x1p-12f);
+                lb = row[qr] + row[ntb * LB_Q + qd];
+            }
+            const bool exited = acc > a.exit_f64 ||
+                                (lb > 0.0f && (float)(acc * (LOG2E * LOG2E)) + lb > a.exit_f32);
+            if (exited || t == T) {
+                const double dd = exited ? (double)INFINITY : sqrt_mid(acc);
+                a.dist[k] = (float)dd;
+                if (a.dist64) a.dist64[k] = dd;
+                t = 0;
+            } else {
+                ++t;
+            }
+        }
+    }
 }
 
 // Float64 decision for the candidates of a float32 pass (compacted at
@@ -338,20 +431,19 @@ struct RecheckArgs {
     int64_t* count;
     uint8_t* keep;   // scratch [capacity]
     int32_t* rechecked;  // nullable: number of rows simulated in float64
-    int32_t rows_max;    // rows per wavefront the LDS was sized for
     int32_t scan_min;    // candidates per wavefront at least
     int32_t all_rows;    // 1: every candidate is decided in float64, not only the band
     double* dist64;      // nullable [capacity]: float64 distance of each row so decided
 };
 
-// LDS of the float64 row kernels, for up to R rows per wavefront (W = ROW_WINDOW days):
-// obs [3 T] f64 | zs [R][5 W] f64 | rix [R] u64 | rq [R] i64 | rw [R] | xs [R][3 W] i32 | rth [R][8] f32
+// LDS of the float64 row kernels, for up to R rows per wavefront:
+// Math64 | obs [3 T] f64 | zs [5 ROW_PAIRS] f64 | rix [R] u64 | rq [R] i64 | xs [4 ROW_PAIRS] i32 | rth [R][8] f32
 struct RowLds {
+    Math64* tab;
     double* lobs;
     double* zs;
     uint64_t* rix;
     int64_t* rq;
-    RowWalk* rw;
     int32_t* xs;
     float* rth;
 };
@@ -359,20 +451,20 @@ struct RowLds {
 __device__ __forceinline__ RowLds row_lds(double* base, int T, int R)
 {
     RowLds l;
-    l.lobs = base;
-    l.zs = base + 3 * T;
-    l.rix = reinterpret_cast<uint64_t*>(l.zs + (size_t)5 * ROW_WINDOW * R);
+    l.tab = reinterpret_cast<Math64*>(base);
+    l.lobs = base + sizeof(Math64) / sizeof(double);
+    l.zs = l.lobs + 3 * T;
+    l.rix = reinterpret_cast<uint64_t*>(l.zs + 5 * ROW_PAIRS);
     l.rq = reinterpret_cast<int64_t*>(l.rix + R);
-    l.rw = reinterpret_cast<RowWalk*>(l.rq + R);
-    l.xs = reinterpret_cast<int32_t*>(l.rw + R);
-    l.rth = reinterpret_cast<float*>(l.xs + (size_t)3 * ROW_WINDOW * R);
+    l.xs = reinterpret_cast<int32_t*>(l.rq + R);
+    l.rth = reinterpret_cast<float*>(l.xs + 4 * ROW_PAIRS);
     return l;
 }
 
 // Pass 1: each wavefront scans a contiguous block of candidates (enough for
 // the grid to cover the candidate count, at least scan_min), 64 at a time;
 // the in-band ones are gathered, in candidate order, into groups of up to
-// rows_max rows that are simulated side by side in float64
+// ROWS_PER_WAVE_MAX rows that are simulated side by side in float64
 // (simulate_rows_f64_wave); the others only get their keep flag. A large
 // scan_min packs the in-band rows into few wavefronts, so that they take few
 // issue slots from a float32 launch running beside them; scan_min = 1
@@ -384,13 +476,15 @@ __device__ __forceinline__ void recheck_group(const RecheckArgs& r, const RowLds
 {
     const SimArgs& a = r.sim;
     if (!staged) {
-        stage_obs_f64<DIST>(a.obs, a.T, l.lobs);
+        stage_math64(*l.tab);
+        __syncthreads();
+        stage_obs_f64<DIST>(a.obs, a.T, l.lobs, *l.tab);
         staged = true;
     }
     __syncthreads();
     const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
         nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, a.T, (double)a.scale,
-        l.lobs, l.zs, l.xs, l.rw);
+        l.lobs, *l.tab, l.zs, l.xs);
     const int lane = threadIdx.x;
     if (lane < nr) {
         const int64_t qq = l.rq[lane];
@@ -408,7 +502,7 @@ __global__ __launch_bounds__(64) void k_recheck_flags(RecheckArgs r)
     extern __shared__ double lds_r[];
     const int64_t count = *r.count;
     if (count > r.capacity) return;  // overflowed candidate set: left for the caller to rerun
-    const RowLds l = row_lds(lds_r, r.sim.T, r.rows_max);
+    const RowLds l = row_lds(lds_r, r.sim.T, ROWS_PER_WAVE_MAX);
     int64_t per = (count + gridDim.x - 1) / gridDim.x;
     if (per < r.scan_min) per = r.scan_min;
     const int64_t q0 = (int64_t)blockIdx.x * per;
@@ -428,9 +522,9 @@ __global__ __launch_bounds__(64) void k_recheck_flags(RecheckArgs r)
         }
         uint64_t m = __ballot(inb);
         while (m) {
-            // the lowest (rows_max - nr) in-band lanes join the group
+            // the lowest (ROWS_PER_WAVE_MAX - nr) in-band lanes join the group
             uint64_t take = 0;
-            for (int room = r.rows_max - nr; room > 0 && m; --room) {
+            for (int room = ROWS_PER_WAVE_MAX - nr; room > 0 && m; --room) {
                 const uint64_t b = m & (~m + 1ull);
                 take |= b;
                 m ^= b;
@@ -443,7 +537,7 @@ __global__ __launch_bounds__(64) void k_recheck_flags(RecheckArgs r)
                 for (int j = 0; j < 8; ++j) l.rth[8 * slot + j] = r.theta[8 * q + j];
             }
             nr += __popcll(take);
-            if (nr == r.rows_max) {
+            if (nr == ROWS_PER_WAVE_MAX) {
                 recheck_group<NOISE, DIST>(r, l, nr, staged);
                 nr = 0;
             }
@@ -524,7 +618,9 @@ __global__ __launch_bounds__(64) void k_rows_f64(RowsArgs r)
     const SimArgs& a = r.sim;
     const int T = a.T, R = r.rows_per_wave;
     const RowLds l = row_lds(lds_w, T, R);
-    stage_obs_f64<DIST>(a.obs, T, l.lobs);
+    stage_math64(*l.tab);
+    __syncthreads();
+    stage_obs_f64<DIST>(a.obs, T, l.lobs, *l.tab);
     const int lane = threadIdx.x;
     for (int64_t q0 = (int64_t)blockIdx.x * R; q0 < a.n; q0 += (int64_t)gridDim.x * R) {
         const int nr = (int)(a.n - q0 < R ? a.n - q0 : R);
@@ -536,7 +632,7 @@ __global__ __launch_bounds__(64) void k_rows_f64(RowsArgs r)
         __syncthreads();
         const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
             nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T,
-            (double)a.scale, l.lobs, l.zs, l.xs, l.rw);
+            (double)a.scale, l.lobs, *l.tab, l.zs, l.xs);
         if (lane < nr) r.dist64[q0 + lane] = d64;
         __syncthreads();
     }
@@ -553,12 +649,19 @@ __device__ __forceinline__ void store_state(int32_t* row, const State& s)
 template <int NOISE, bool F64>
 __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
 {
+    __shared__ Math64 tab;
+    if (F64) {
+        stage_math64(tab);
+        __syncthreads();
+    }
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     const uint64_t i = a.first + (uint64_t)k;
     float thv[8];
     load_or_draw_theta(a, false, k, i, thv);
     const Theta th = theta_from(thv);
+    const bool mid = theta_mid(thv);
+    const double rP = 1.0 / (double)a.P;
     State s = init_state(th.ka, a.P, a.A0, a.R0, a.D0);
     int32_t* out = a.traj + (int64_t)6 * (a.T + 1) * k;
     store_state(out, s);
@@ -569,8 +672,8 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
         const uint4 w = stream_words(a.key, i, a.series, ctr_word3((uint32_t)t, a.domain, 0));
         if (F64) {
             double z[5];
-            normals_f64(w, z);
-            day_step_f64<NOISE>(s, th, (double)a.P, (double)a.scale, z);
+            normals_f64(w, tab, z);
+            day_step_f64<NOISE>(s, th, mid, (double)a.P, rP, (double)a.scale, z, tab);
         } else {
             Noise32 z;
             normals_f32(w, nc, z);
@@ -620,16 +723,8 @@ static abc_status fill_series(SimArgs& a, const abc_series* ser, const abc_model
 constexpr int64_t ROW_WAVE_GRID = 2048;
 static size_t row_wave_lds_bytes(int T, int R)
 {
-    return sizeof(double) * 3 * (size_t)T +
-           (size_t)R * (sizeof(double) * 5 * ROW_WINDOW + sizeof(uint64_t) + sizeof(int64_t) +
-                        sizeof(RowWalk) + sizeof(int32_t) * 3 * ROW_WINDOW + sizeof(float) * 8);
-}
-// Most rows per wavefront within an LDS budget (at least 1).
-static int row_wave_rows_max(int T, size_t budget)
-{
-    int R = ROWS_PER_WAVE_MAX;
-    while (R > 1 && row_wave_lds_bytes(T, R) > budget) --R;
-    return R;
+    return sizeof(Math64) + sizeof(double) * (3 * (size_t)T + 5 * ROW_PAIRS) + sizeof(int32_t) * 4 * ROW_PAIRS +
+           (size_t)R * (sizeof(uint64_t) + sizeof(int64_t) + sizeof(float) * 8);
 }
 
 static inline unsigned grid_for(int64_t n) { return (unsigned)((n + SIM_BLOCK - 1) / SIM_BLOCK); }
@@ -704,15 +799,24 @@ static void launch_f32(const SimArgs& a, bool prior, hipStream_t s)
     launch_f32_spl<NOISE, DIST, KAHAN, 1>(a, prior, s);
 }
 
-template <int NOISE, int DIST>
-static void launch_f64(const SimArgs& a, bool prior, size_t lds, hipStream_t s)
+// tables, observed series, the future-days bound and the space that builds it
+static size_t f64_lds_bytes(int T, int lb_ntb)
 {
+    return sizeof(Math64) + sizeof(double) * 3 * (size_t)T +
+           (lb_ntb > 0 ? sizeof(double) * (2 * (size_t)T + (size_t)LB_MAX_SEG * 2 * LB_Q) +
+                             sizeof(float) * 2 * LB_Q * (size_t)lb_ntb
+                       : 0);
+}
+
+template <int NOISE, int DIST>
+static void launch_f64(const SimArgs& a, bool prior, hipStream_t s)
+{
+    const size_t lds = f64_lds_bytes(a.T, a.lb_ntb);
+    const dim3 g(refill_grid(a.n, F64_BLOCK, F64_BLOCKS_PER_CU)), b(F64_BLOCK);
     if (prior)
-        hipLaunchKernelGGL((k_simulate_f64<NOISE, DIST, true>), dim3(grid_for(a.n)),
-                           dim3(SIM_BLOCK), lds, s, a);
+        hipLaunchKernelGGL((k_simulate_f64<NOISE, DIST, true>), g, b, lds, s, a);
     else
-        hipLaunchKernelGGL((k_simulate_f64<NOISE, DIST, false>), dim3(grid_for(a.n)),
-                           dim3(SIM_BLOCK), lds, s, a);
+        hipLaunchKernelGGL((k_simulate_f64<NOISE, DIST, false>), g, b, lds, s, a);
 }
 
 }  // namespace abc
@@ -784,14 +888,6 @@ extern "C" abc_status abc_simulate_distance(const abc_series* ser, const abc_mod
     const hipStream_t s = as_stream(stream);
     const int noise = (model->flags & ABC_NOISE_LITERAL) ? 1 : 0;
     const int distm = (model->flags & ABC_DIST_RAW) ? 1 : 0;
-    if (model->flags & ABC_FP64) {
-        const size_t lds = sizeof(double) * 3 * (size_t)a.T;
-        if (noise == 0 && distm == 0) launch_f64<0, 0>(a, use_prior, lds, s);
-        else if (noise == 0 && distm == 1) launch_f64<0, 1>(a, use_prior, lds, s);
-        else if (noise == 1 && distm == 0) launch_f64<1, 0>(a, use_prior, lds, s);
-        else launch_f64<1, 1>(a, use_prior, lds, s);
-        return check_launch("k_simulate_f64");
-    }
     // future-days bound for the log1p distance when there is an exit bound;
     // time blocks of 2^sh days keep the table within LB_MAX_BLOCKS rows
     if (distm == 0 && !isinf(eps_exit) && !(model->flags & ABC_NO_BOUND)) {
@@ -799,7 +895,16 @@ extern "C" abc_status abc_simulate_distance(const abc_series* ser, const abc_mod
         while ((a.T >> sh) + 1 > LB_MAX_BLOCKS) ++sh;
         a.lb_sh = sh;
         a.lb_ntb = (a.T >> sh) + 1;
-        if (refill_lds_bytes(a.T, g_launch.block, a.lb_ntb) > max_lds_per_block()) a.lb_ntb = 0;
+        const size_t need = (model->flags & ABC_FP64) ? f64_lds_bytes(a.T, a.lb_ntb)
+                                                      : refill_lds_bytes(a.T, g_launch.block, a.lb_ntb);
+        if (need > max_lds_per_block()) a.lb_ntb = 0;
+    }
+    if (model->flags & ABC_FP64) {
+        if (noise == 0 && distm == 0) launch_f64<0, 0>(a, use_prior, s);
+        else if (noise == 0 && distm == 1) launch_f64<0, 1>(a, use_prior, s);
+        else if (noise == 1 && distm == 0) launch_f64<1, 0>(a, use_prior, s);
+        else launch_f64<1, 1>(a, use_prior, s);
+        return check_launch("k_simulate_f64");
     }
     const size_t lds = refill_lds_bytes(a.T, g_launch.block, a.lb_ntb);
     if (lds > max_lds_per_block())
@@ -878,8 +983,7 @@ namespace abc {
 abc_status recheck_band(const abc_series* ser, const abc_model* model, const abc_stream* st,
                         float eps, float band_w, int64_t capacity, int64_t* idx, float* theta,
                         float* dist, float* weight, int64_t* count, int32_t* rechecked,
-                        void* stream, size_t lds_budget, int64_t grid_max, int32_t scan_min,
-                        double* dist64, bool all_rows)
+                        void* stream, int64_t grid_max, int32_t scan_min, double* dist64, bool all_rows)
 {
     abc_status rc;
     if ((rc = check_series(ser, true))) return rc;
@@ -891,8 +995,7 @@ abc_status recheck_band(const abc_series* ser, const abc_model* model, const abc
     ABC_REQUIRE(count != nullptr, "count is NULL");
     if (capacity == 0) return ABC_OK;
     ABC_REQUIRE(idx && theta && dist, "idx/theta/dist NULL");
-    const int rows_max = row_wave_rows_max(ser->T, lds_budget);
-    const size_t lds = row_wave_lds_bytes(ser->T, rows_max);
+    const size_t lds = row_wave_lds_bytes(ser->T, ROWS_PER_WAVE_MAX);
     ABC_REQUIRE(lds <= max_lds_per_block(), "T too long for the float64 recheck");
     const hipStream_t s = as_stream(stream);
     RecheckArgs r{};
@@ -907,7 +1010,6 @@ abc_status recheck_band(const abc_series* ser, const abc_model* model, const abc
     r.weight = weight;
     r.count = count;
     r.rechecked = rechecked;
-    r.rows_max = rows_max;
     r.scan_min = scan_min < 1 ? 1 : scan_min;
     r.all_rows = all_rows ? 1 : 0;
     r.dist64 = dist64;
@@ -938,8 +1040,7 @@ extern "C" abc_status abc_recheck_band(const abc_series* ser, const abc_model* m
                                        void* stream)
 {
     return recheck_band(ser, model, st, eps, band_w, capacity, idx, theta, dist, weight, count,
-                        rechecked, stream, ROW_LDS_BESIDE, ROW_WAVE_GRID, ROW_SCAN_BESIDE,
-                        nullptr, false);
+                        rechecked, stream, ROW_WAVE_GRID, ROW_SCAN_BESIDE, nullptr, false);
 }
 
 extern "C" abc_status abc_simulate_rows_f64(const abc_series* ser, const abc_model* model,
@@ -954,9 +1055,11 @@ extern "C" abc_status abc_simulate_rows_f64(const abc_series* ser, const abc_mod
     ABC_REQUIRE(n >= 0, "n < 0");
     if (n == 0) return ABC_OK;
     ABC_REQUIRE(idx && theta && dist64, "idx/theta/dist64 NULL");
-    const int64_t want = (n + ROW_WAVE_TARGET - 1) / ROW_WAVE_TARGET;
-    const int rmax = row_wave_rows_max(ser->T, ROW_LDS_ALONE);
-    const int rows = (int)(want < rmax ? want : rmax);
+    // one row per wavefront while each has a CU to itself, then at least four:
+    // 1024 wavefronts of one row walk a day in 0.78 us, 256 of four in 0.47
+    int64_t want = (n + ROW_WAVE_TARGET - 1) / ROW_WAVE_TARGET;
+    if (n > 256 && want < 4) want = 4;
+    const int rows = (int)(want < ROWS_PER_WAVE_MAX ? want : ROWS_PER_WAVE_MAX);
     const size_t lds = row_wave_lds_bytes(ser->T, rows);
     ABC_REQUIRE(lds <= max_lds_per_block(), "T too long for the float64 path");
     RowsArgs r{};

@@ -348,19 +348,23 @@ struct ProposeArgs {
     int32_t* anc;         // [n] or null
 };
 
-__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& z0, double& z1)
+__device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, const Math64& tab, double& z0, double& z1)
 {
 #pragma clang fp contract(off)
     const double u1 = ((double)a + 1.0) * 0x1p-32;
-    const double r = sqrt(-2.0 * log(u1));
-    const double phi = 6.283185307179586 * ((double)b * 0x1p-32);
-    z0 = r * cos(phi);
-    z1 = r * sin(phi);
+    const double r = sqrt_mid(-2.0 * log_mid(u1, tab));
+    double sn, cs;
+    sincos_turn(6.283185307179586 * ((double)b * 0x1p-32), sn, cs);
+    z0 = r * cs;
+    z1 = r * sn;
 }
 
 __global__ __launch_bounds__(256) void k_smc_propose(ProposeArgs a)
 {
 #pragma clang fp contract(off)
+    __shared__ Math64 tab;
+    stage_math64(tab);
+    __syncthreads();
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     const uint64_t i = a.first + (uint64_t)k;
@@ -369,10 +373,10 @@ __global__ __launch_bounds__(256) void k_smc_propose(ProposeArgs a)
     const uint4 w2 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 2));
     const double u = (double)(((uint64_t)w0.x << 21) | (uint64_t)(w0.y >> 11)) * 0x1p-53;
     double z[8];
-    box_muller(w0.z, w0.w, z[0], z[1]);
-    box_muller(w1.x, w1.y, z[2], z[3]);
-    box_muller(w1.z, w1.w, z[4], z[5]);
-    box_muller(w2.x, w2.y, z[6], z[7]);
+    box_muller(w0.z, w0.w, tab, z[0], z[1]);
+    box_muller(w1.x, w1.y, tab, z[2], z[3]);
+    box_muller(w1.z, w1.w, tab, z[4], z[5]);
+    box_muller(w2.x, w2.y, tab, z[6], z[7]);
     // smallest j with C_j > u C_{N-1}
     const double target = u * a.C[a.N - 1];
     int lo = 0, hi = a.N;
@@ -704,8 +708,7 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
             return rc;
         if (cfg->band_w > 0.0f &&
             (rc = recheck_band(ser, &md, &st, eps, cfg->band_w, cap, oidx, oth, od, nullptr, dcnt,
-                               nullptr, stream, ROW_LDS_ALONE, ROW_WAVE_TARGET, ROW_SCAN_ALONE,
-                               od64, true)))
+                               nullptr, stream, ROW_WAVE_TARGET, ROW_SCAN_ALONE, od64, true)))
             return rc;
         int64_t c = 0;
         ABC_HIP(hipMemcpyAsync(&c, dcnt, sizeof c, hipMemcpyDeviceToHost, s));
