@@ -88,23 +88,134 @@ struct FeatArgs {
     int32_t* TP;           // [n][2] (T, P) or null
 };
 
-__device__ __forceinline__ void feature_days(int T, int d[32])
+// Feature day k = 0..31 of a horizon T: 1 + rint(k (T - 1) / 31), in integers
+// (31 is odd, so the quotient is never halfway between two).
+__device__ __forceinline__ int feature_day(int T, int k)
 {
-#pragma unroll
-    for (int k = 0; k < 32; ++k) d[k] = 1 + (int)rint((double)k * (double)(T - 1) / 31.0);
+    return 1 + (2 * k * (T - 1) + 31) / 62;
 }
 
-__global__ __launch_bounds__(256) void k_mdn_features(FeatArgs a)
+__device__ __forceinline__ int feature_T(const FeatArgs& a, uint32_t w)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.n) return;
+    const int T = a.T_lo + (int)floor((double)(w >> 8) * 0x1p-24 * (double)(a.T_hi - a.T_lo + 1));
+    return T > a.T_hi ? a.T_hi : T;
+}
+
+// Order of the samples, longest horizon first and every horizon's samples
+// padded to whole wavefronts (order -1: no sample): a wavefront's lanes then
+// end together and record their features on the same days. cnt[b] counts
+// horizon T_hi - b; start and fill are its first and next free position.
+constexpr int FEAT_BINS = ABC_T_MAX;
+constexpr int FEAT_BLOCK = 256;
+// Samples from which on the ordering pays (four short launches): with T in
+// [30, 200], 8192 samples take 183 us without and 90 us with it, 1000 samples
+// 179 and 217 us (too few to fill the wavefronts of 171 horizons).
+constexpr int64_t FEAT_SORT_MIN = (int64_t)1 << 13;
+
+struct FeatOrder {
+    uint32_t* cnt;    // [bins]
+    uint32_t* fill;   // [bins]
+    int32_t* order;   // [n + 63 bins]
+    int bins;
+    uint32_t* total;  // positions in use
+};
+
+__global__ __launch_bounds__(FEAT_BLOCK) void k_feat_count(FeatArgs a, FeatOrder o)
+{
+    __shared__ uint32_t h[FEAT_BINS];
+    for (int b = threadIdx.x; b < o.bins; b += FEAT_BLOCK) h[b] = 0u;
+    __syncthreads();
+    for (int64_t k = (int64_t)blockIdx.x * FEAT_BLOCK + threadIdx.x; k < a.n; k += (int64_t)gridDim.x * FEAT_BLOCK) {
+        const uint4 w = stream_words(a.key, a.first + (uint64_t)k, a.series, ctr_word3(0, a.domain, 2));
+        atomicAdd(&h[a.T_hi - feature_T(a, w.x)], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < o.bins; b += FEAT_BLOCK)
+        if (h[b]) atomicAdd(&o.cnt[b], h[b]);
+}
+
+__global__ __launch_bounds__(FEAT_BINS) void k_feat_scan(FeatOrder o)
+{
+    __shared__ uint32_t part[FEAT_BINS];
+    const int b = threadIdx.x;
+    const uint32_t c = b < o.bins ? o.cnt[b] : 0u;
+    const uint32_t padded = (c + 63u) & ~63u;
+    part[b] = padded;
+    __syncthreads();
+    for (int off = 1; off < FEAT_BINS; off <<= 1) {
+        const uint32_t v = b >= off ? part[b - off] : 0u;
+        __syncthreads();
+        part[b] += v;
+        __syncthreads();
+    }
+    const uint32_t end = part[b], start = end - padded;
+    if (b < o.bins) {
+        o.fill[b] = start;
+        for (uint32_t q = start + c; q < end; ++q) o.order[q] = -1;
+    }
+    if (b == FEAT_BINS - 1) *o.total = end;
+}
+
+// each workgroup takes its samples' positions with one addition per horizon
+__global__ __launch_bounds__(FEAT_BLOCK) void k_feat_place(FeatArgs a, FeatOrder o)
+{
+    __shared__ uint32_t h[FEAT_BINS];
+    constexpr int PER = 8;
+    for (int b = threadIdx.x; b < o.bins; b += FEAT_BLOCK) h[b] = 0u;
+    __syncthreads();
+    const int64_t k0 = (int64_t)blockIdx.x * FEAT_BLOCK * PER + threadIdx.x;
+    int bin[PER];
+    uint32_t rank[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int64_t k = k0 + (int64_t)q * FEAT_BLOCK;
+        if (k >= a.n) break;
+        const uint4 w = stream_words(a.key, a.first + (uint64_t)k, a.series, ctr_word3(0, a.domain, 2));
+        bin[q] = a.T_hi - feature_T(a, w.x);
+        rank[q] = atomicAdd(&h[bin[q]], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < o.bins; b += FEAT_BLOCK)
+        if (h[b]) h[b] = atomicAdd(&o.fill[b], h[b]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int64_t k = k0 + (int64_t)q * FEAT_BLOCK;
+        if (k >= a.n) break;
+        o.order[h[bin[q]] + rank[q]] = (int32_t)k;
+    }
+}
+
+// One lane per trajectory. Bound by VALU issue, like the float32 simulation,
+// when the lanes of a wavefront share a horizon (order given); eight recorded
+// days are kept in LDS and stored together, so that every store fills a 32-byte
+// sector (4-byte stores 384 bytes apart, and lanes waiting for the longest
+// horizon of 64 with three float64 logarithms on almost every day, took
+// 3.8 ms for 1e6 pairs of T in [30, 200]; now 0.69 ms).
+constexpr int FEAT_HOLD = 8;
+
+__global__ __launch_bounds__(FEAT_BLOCK) void k_mdn_features(FeatArgs a, const int32_t* order, const uint32_t* total)
+{
+    __shared__ Math64 tab;
+    __shared__ float hold_all[FEAT_BLOCK / 64][3 * FEAT_HOLD][64];
+    stage_math64(tab);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    float (*hold)[64] = hold_all[threadIdx.x >> 6];
+    int64_t k = (int64_t)blockIdx.x * FEAT_BLOCK + threadIdx.x;
+    if (order) {
+        if (k >= (int64_t)*total) return;
+        k = order[k];
+        if (k < 0) return;
+    } else if (k >= a.n) {
+        return;
+    }
     const uint64_t i = a.first + (uint64_t)k;
     float th[8];
     prior_draw(a.key, i, a.series, a.domain, a.lo, a.width, th);
     const uint4 w = stream_words(a.key, i, a.series, ctr_word3(0, a.domain, 2));
-    const double uT = (double)(w.x >> 8) * 0x1p-24, uP = (double)(w.y >> 8) * 0x1p-24;
-    int T = a.T_lo + (int)floor(uT * (double)(a.T_hi - a.T_lo + 1));
-    if (T > a.T_hi) T = a.T_hi;
+    const double uP = (double)(w.y >> 8) * 0x1p-24;
+    const int T = feature_T(a, w.x);
     double P = rint(pow(10.0, a.lp_lo + (a.lp_hi - a.lp_lo) * uP));
     if (P > 2147483647.0) P = 2147483647.0;
     const int32_t Pi = (int32_t)P;
@@ -116,20 +227,36 @@ __global__ __launch_bounds__(256) void k_mdn_features(FeatArgs a)
     const PhiloxSeries ps = philox_series(a.series, a.key);
     PhiloxDays ph;
     ph.begin(i, ps.u0, a.key);
-    int days[32];
-    feature_days(T, days);
     float* f = a.features + 96 * k;
-    int next = 0;
+    const bool vec = (reinterpret_cast<uintptr_t>(a.features) & 15u) == 0;
+    int next = 0, dnext = 1;
     for (int t = 1; t <= T; ++t) {
         const uint4 wd = ph.day(((uint32_t)t << 8) | (a.domain << 4), ps.b1, a.key);
         Noise32 z;
         normals_f32(wd, nc, z);
         day_step_f32<0>(s, r, invP, z);
-        while (next < 32 && days[next] == t) {
-            f[next] = (float)log1p((double)s.A);
-            f[32 + next] = (float)log1p((double)s.R);
-            f[64 + next] = (float)log1p((double)s.D);
+        if (t != dnext) continue;
+        const float v0 = (float)log1p_count_f64(s.A, tab), v1 = (float)log1p_count_f64(s.R, tab),
+                    v2 = (float)log1p_count_f64(s.D, tab);
+        while (dnext == t) {  // short horizons record a day more than once
+            const int j = next & (FEAT_HOLD - 1);
+            hold[j][lane] = v0;
+            hold[FEAT_HOLD + j][lane] = v1;
+            hold[2 * FEAT_HOLD + j][lane] = v2;
             ++next;
+            if (j == FEAT_HOLD - 1) {
+#pragma unroll
+                for (int q = 0; q < 3 * FEAT_HOLD; q += 4) {
+                    const float4 x = make_float4(hold[q][lane], hold[q + 1][lane], hold[q + 2][lane], hold[q + 3][lane]);
+                    float* to = f + 32 * (q / FEAT_HOLD) + (next - FEAT_HOLD) + q % FEAT_HOLD;
+                    if (vec) {
+                        *reinterpret_cast<float4*>(to) = x;
+                    } else {
+                        to[0] = x.x; to[1] = x.y; to[2] = x.z; to[3] = x.w;
+                    }
+                }
+            }
+            dnext = next < 32 ? feature_day(T, next) : 0;
         }
     }
 #pragma unroll
@@ -145,38 +272,92 @@ __global__ void k_obs_features(const int32_t* obs, int T, float* out)
 {
     const int q = threadIdx.x;
     if (q >= 96) return;
-    int days[32];
-    feature_days(T, days);
     const int c = q / 32, k = q % 32;
-    out[q] = (float)log1p((double)obs[c * T + days[k] - 1]);
+    out[q] = (float)log1p((double)obs[c * T + feature_day(T, k) - 1]);
 }
 
-// per-feature mean and sd (float64 two-pass), one workgroup per column
-__global__ __launch_bounds__(256) void k_colstats(const float* x, int64_t n, int cols, float* mean,
-                                                  float* sd)
+// Per-feature mean and sd in float64: the rows are cut into G contiguous
+// ranges (G a function of n alone); a workgroup streams its range, ten rows of
+// 24 float4 per step, each thread keeping sums and squares of its four columns
+// about the first row; one workgroup per column then adds the ranges'
+// partials in a fixed order. Bound by HBM: 1e6 rows (384 MB) take 56 us
+// (one workgroup per column, reading 4 bytes every 384 twice: 4.4 ms).
+constexpr int CS_ROWS = 10, CS_BLOCK = 256, CS_GROUPS = 1024;
+static_assert(NN_IN == 96 && CS_ROWS * (NN_IN / 4) <= CS_BLOCK, "a step of the column sums");
+
+static int64_t colstats_groups(int64_t n)
 {
-    __shared__ double red[4];
-    const int c = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    auto bsum = [&](double v) {
+    const int64_t g = (n + 8 * CS_ROWS - 1) / (8 * CS_ROWS);
+    return g < CS_GROUPS ? g : CS_GROUPS;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(CS_BLOCK) void k_colsums(const float* x, int64_t n, double* part)
+{
+    __shared__ double red[CS_ROWS][2 * NN_IN];
+    const int c4 = threadIdx.x % (NN_IN / 4), sub = threadIdx.x / (NN_IN / 4);
+    const int64_t R = (n + gridDim.x - 1) / gridDim.x;
+    const int64_t r0 = (int64_t)blockIdx.x * R, r1 = r0 + R < n ? r0 + R : n;
+    auto load = [&](int64_t row, float v[4]) {
+        const float* p = x + row * NN_IN + 4 * c4;
+        if (VEC) {
+            const float4 q = load_stream(reinterpret_cast<const float4*>(p));
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        __syncthreads();
-        if (lane == 0) red[wave] = v;
-        __syncthreads();
-        return red[0] + red[1] + red[2] + red[3];
+            for (int j = 0; j < 4; ++j) v[j] = p[j];
+        }
     };
-    double s = 0.0;
-    for (int64_t r = threadIdx.x; r < n; r += blockDim.x) s += (double)x[r * cols + c];
-    const double mu = bsum(s) / (double)n;
-    double v = 0.0;
-    for (int64_t r = threadIdx.x; r < n; r += blockDim.x) {
-        const double d = (double)x[r * cols + c] - mu;
-        v += d * d;
+    if (sub < CS_ROWS) {
+        float c[4];
+        load(0, c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = fabsf(c[j]) < INFINITY ? c[j] : 0.0f;
+        double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int64_t row = r0 + sub; row < r1; row += CS_ROWS) {
+            float v[4];
+            load(row, v);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double d = (double)v[j] - (double)c[j];
+                s1[j] += d;
+                s2[j] += d * d;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            red[sub][4 * c4 + j] = s1[j];
+            red[sub][NN_IN + 4 * c4 + j] = s2[j];
+        }
     }
-    const double var = bsum(v) / (double)(n > 1 ? n - 1 : 1);
-    if (threadIdx.x == 0) {
-        mean[c] = (float)mu;
+    __syncthreads();
+    if (threadIdx.x < 2 * NN_IN) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < CS_ROWS; ++q) t += red[q][threadIdx.x];
+        part[(int64_t)blockIdx.x * 2 * NN_IN + threadIdx.x] = t;
+    }
+}
+
+__global__ __launch_bounds__(64) void k_colstats(const float* x, int64_t n, const double* part, int groups,
+                                                 float* mean, float* sd)
+{
+    const int c = blockIdx.x, lane = threadIdx.x;
+    double s1 = 0.0, s2 = 0.0;
+    for (int g = lane; g < groups; g += 64) {
+        s1 += part[(int64_t)g * 2 * NN_IN + c];
+        s2 += part[(int64_t)g * 2 * NN_IN + NN_IN + c];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        s1 += __shfl_xor(s1, off, 64);
+        s2 += __shfl_xor(s2, off, 64);
+    }
+    if (lane == 0) {
+        const double m = s1 / (double)n;
+        const double var = (s2 - s1 * m) / (double)(n > 1 ? n - 1 : 1);
+        mean[c] = (float)((fabsf(x[c]) < INFINITY ? (double)x[c] : 0.0) + m);
         sd[c] = (float)(sqrt(var) > 1e-6 ? sqrt(var) : 1e-6);
     }
 }
@@ -1201,7 +1382,27 @@ extern "C" abc_status abc_mdn_simulate_features(const abc_prior* prior, uint64_t
     a.features = features;
     a.theta = theta;
     a.TP = TP;
-    hipLaunchKernelGGL(k_mdn_features, dim3(blocks_for(n)), dim3(256), 0, as_stream(stream), a);
+    const hipStream_t s = as_stream(stream);
+    const int bins = T_hi - T_lo + 1;
+    if (n < FEAT_SORT_MIN || n >= ((int64_t)1 << 30) || bins == 1) {
+        hipLaunchKernelGGL(k_mdn_features, dim3(blocks_for(n)), dim3(FEAT_BLOCK), 0, s, a, nullptr, nullptr);
+        return check_launch("k_mdn_features");
+    }
+    FeatOrder o{};
+    o.bins = bins;
+    const int64_t room = n + 63 * (int64_t)bins;
+    void* mem = nullptr;
+    if ((rc = stream_scratch(s, sizeof(uint32_t) * (2 * (size_t)bins + 1) + sizeof(int32_t) * (size_t)room, &mem))) return rc;
+    o.cnt = static_cast<uint32_t*>(mem);
+    o.fill = o.cnt + bins;
+    o.total = o.fill + bins;
+    o.order = reinterpret_cast<int32_t*>(o.total + 1);
+    hipLaunchKernelGGL(k_zero_f32, dim3((bins + 255) / 256), dim3(256), 0, s, reinterpret_cast<float*>(o.cnt), bins);
+    const unsigned count_grid = (unsigned)((n + 8 * FEAT_BLOCK - 1) / (8 * FEAT_BLOCK));
+    hipLaunchKernelGGL(k_feat_count, dim3(count_grid < 1024 ? count_grid : 1024), dim3(FEAT_BLOCK), 0, s, a, o);
+    hipLaunchKernelGGL(k_feat_scan, dim3(1), dim3(FEAT_BINS), 0, s, o);
+    hipLaunchKernelGGL(k_feat_place, dim3(count_grid), dim3(FEAT_BLOCK), 0, s, a, o);
+    hipLaunchKernelGGL(k_mdn_features, dim3(blocks_for(room)), dim3(FEAT_BLOCK), 0, s, a, o.order, o.total);
     return check_launch("k_mdn_features");
 }
 
@@ -1218,7 +1419,16 @@ extern "C" abc_status abc_mdn_fit_standardizer(abc_mdn* net, const float* featur
                                                void* stream)
 {
     ABC_REQUIRE(net && features && n >= 2, "need a net and >= 2 feature rows");
-    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(256), 0, as_stream(stream), features, n, NN_IN,
+    const hipStream_t s = as_stream(stream);
+    const int groups = (int)colstats_groups(n);
+    void* part = nullptr;
+    const abc_status rc = stream_scratch(s, sizeof(double) * 2 * NN_IN * (size_t)groups, &part);
+    if (rc) return rc;
+    if ((reinterpret_cast<uintptr_t>(features) & 15u) == 0)
+        hipLaunchKernelGGL((k_colsums<true>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, static_cast<double*>(part));
+    else
+        hipLaunchKernelGGL((k_colsums<false>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, static_cast<double*>(part));
+    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(64), 0, s, features, n, static_cast<const double*>(part), groups,
                        net->fmean, net->fsd);
     return check_launch("k_colstats");
 }
