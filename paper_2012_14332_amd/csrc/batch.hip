@@ -45,7 +45,7 @@ constexpr int BT_RING = 64;  // ring slots per wave (one chunk)
 
 struct SeriesDesc {         // device, per series, constant over the run
     int32_t T, P, A0, R0, D0;
-    int32_t obs_off;        // offset of [3][T] log2(1 + O) floats in the obs table
+    int32_t obs_off;        // byte offset of the observed rows [T][4] in the obs table
     int32_t room;           // P - A0 - R0 - D0
     uint32_t series_id;     // stream series (counter word 2)
     float invP;
@@ -141,8 +141,9 @@ __global__ void k_batch_obs(const int32_t* const* obs, const SeriesDesc* desc, i
     const int s = blockIdx.x;
     if (s >= m) return;
     const SeriesDesc d = desc[s];
-    for (int q = threadIdx.x; q < 3 * d.T; q += blockDim.x)
-        table[d.obs_off + q] = (float)(log1p((double)obs[s][q]) * 1.44269504088896340736);
+    const int32_t* o = obs[s];
+    float4* to = reinterpret_cast<float4*>(reinterpret_cast<char*>(table) + d.obs_off);
+    for (int q = threadIdx.x; q < d.T; q += blockDim.x) to[q] = obs_row<0>(o[q], o[d.T + q], o[2 * d.T + q], 0u);
 }
 
 __global__ void k_batch_init(BatchArgs a)
@@ -313,22 +314,34 @@ __global__ __launch_bounds__(BT_MAX_SERIES) void k_batch_plan(BatchArgs a)
 // ----------------------------------------------------------------------------
 // one round: persistent grid with lane refill and per-lane series
 // ----------------------------------------------------------------------------
+// One prepared sample (48 bytes); its series and index follow from the chunk in
+// the ring, which is wave-uniform.
 struct alignas(16) BSlot {
     float a0, al, n, be, ga, de, bh;
     int32_t i0;
     uint32_t c1base, g3, h3, f3;  // per-sample part of Philox rounds 1-3
-    int64_t i;                    // sample index
-    int32_t series;               // index into desc, -1 = no sample
+};
+
+// What a lane reads from LDS when it starts a sample (three reads).
+struct alignas(16) BSer {
+    int32_t A0, M0, R1, D1;    // A0, A0 + R0 + D0, R0 + 1, D0 + 1
+    float invP, exit2;
+    uint32_t wend, b1;         // wend: fourth counter word of the last day
+    uint32_t obs;              // byte offset of the first observed row
+    int32_t room;
+    uint32_t u0;
     int32_t pad;
 };
 
 struct BLane {
-    State s;
+    StateD s;
     RatesF r;
     PhiloxDays ph;
     int64_t i;
-    int32_t t;  // the day the slot simulates next; 0: no sample (idle)
-    int32_t T, obs_off, series;
+    uint32_t w;     // fourth counter word of the next day; 0: no sample (idle)
+    uint32_t p;     // byte offset of the day's observed row
+    uint32_t wend;
+    int32_t series;
     float invP, exit2;
     uint32_t b1;
     float acc;
@@ -340,21 +353,23 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
     extern __shared__ float lds_b[];
     __shared__ RoundTable tab_sh;  // copied once per workgroup
     const int nwaves_blk = blockDim.x >> 6;
-    SeriesDesc* desc_sh = reinterpret_cast<SeriesDesc*>(lds_b);
+    BSer* ser = reinterpret_cast<BSer*>(lds_b);
     // the observed rows stay in global memory (read through the caches): in
-    // LDS they would take 12 B per day of every series and leave room for
+    // LDS they would take 16 B per day of every series and leave room for
     // one workgroup per CU
-    BSlot* ring_all = reinterpret_cast<BSlot*>(desc_sh + a.m);
+    BSlot* ring_all = reinterpret_cast<BSlot*>(ser + a.m);
+    const uint32_t wdom = a.domain << 4;
 
-    // stage the round table and the series descriptors
+    // stage the round table and the series
     {
         const int32_t* src = reinterpret_cast<const int32_t*>(a.table);
         int32_t* dst = reinterpret_cast<int32_t*>(&tab_sh);
         for (int q = threadIdx.x; q < (int)(sizeof(RoundTable) / 4); q += blockDim.x) dst[q] = src[q];
-        const int32_t* dsrc = reinterpret_cast<const int32_t*>(a.desc);
-        int32_t* ddst = reinterpret_cast<int32_t*>(desc_sh);
-        for (int q = threadIdx.x; q < a.m * (int)(sizeof(SeriesDesc) / 4); q += blockDim.x)
-            ddst[q] = dsrc[q];
+        for (int q = threadIdx.x; q < a.m; q += blockDim.x) {
+            const SeriesDesc d = a.desc[q];
+            ser[q] = BSer{d.A0, d.A0 + d.R0 + d.D0, d.R0 + 1, d.D0 + 1, d.invP, d.exit2,
+                          ((uint32_t)d.T << 8) | wdom, d.b1, (uint32_t)d.obs_off, d.room, d.u0, 0};
+        }
     }
     __syncthreads();
     const int C = tab_sh.total_chunks;
@@ -366,129 +381,121 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
     // queue arithmetic derived from it
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     BSlot* ring = ring_all + wv * BT_RING;
-    const int64_t wg = (int64_t)blockIdx.x * nwaves_blk + wv;
-    const int64_t nw = (int64_t)gridDim.x * nwaves_blk;
+    const int wg = blockIdx.x * nwaves_blk + wv;
+    const int nw = gridDim.x * nwaves_blk;
     if (wg >= C) return;
-    const int64_t J = (C - 1 - wg) / nw + 1;  // chunks of this wave
-    const int64_t Q = J << 6;
+    // queue positions of this wave: a round has less than 2^31 samples
+    const uint32_t Q = (uint32_t)((C - 1 - wg) / nw + 1) << 6;
 
+    // the chunk in the ring (wave-uniform): its series, the stream index of
+    // its first sample, and how many of its 64 positions hold a sample
+    int cur_s = 0;
+    int64_t cur_first = 0;
+    uint32_t cur_valid = 0;
     // fill the ring with chunk j of this wave (all 64 lanes, one sample each)
-    auto fill = [&](int64_t j) {
-        const int c = (int)(wg + j * nw);
+    auto fill = [&](uint32_t j) {
+        const int c = wg + (int)j * nw;
         int lo = 0, hi = na - 1;  // the active slot r with chunk0[r] <= c < chunk0[r+1]
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (tab_sh.chunk0[mid] <= c) lo = mid; else hi = mid - 1;
         }
-        const int r = lo;
-        const int s = tab_sh.s[r];
-        const int64_t local = (int64_t)(c - tab_sh.chunk0[r]) * 64 + lane;
-        BSlot sl;
-        if (local < tab_sh.n[r]) {
-            const SeriesDesc& d = desc_sh[s];
-            const int64_t i = tab_sh.first[r] + local;
+        const int r = __builtin_amdgcn_readfirstlane(lo);
+        const int s = __builtin_amdgcn_readfirstlane(tab_sh.s[r]);
+        const int32_t local = (c - __builtin_amdgcn_readfirstlane(tab_sh.chunk0[r])) * 64;
+        cur_s = s;
+        cur_first = tab_sh.first[r] + local;
+        cur_valid = (uint32_t)min(__builtin_amdgcn_readfirstlane(tab_sh.n[r]) - local, 64);
+        if ((uint32_t)lane < cur_valid) {
+            const SeriesDesc& d = a.desc[s];
+            const int64_t i = cur_first + lane;
             float th[8];
             (void)batch_theta<MIX>(a, s, d, (uint64_t)i, th);
             const Theta tt = theta_from(th);
             const RatesF rr = rates_f32(tt);
             const State s0 = init_state(tt.ka, d.P, d.A0, d.R0, d.D0);
+            BSlot sl;
             sl.a0 = rr.a0; sl.al = rr.al; sl.n = rr.n; sl.be = rr.be;
             sl.ga = rr.ga; sl.de = rr.de; sl.bh = rr.bh; sl.i0 = s0.I;
             PhiloxDays ph;
             ph.begin((uint64_t)i, d.u0, a.key);
             sl.c1base = ph.c1base; sl.g3 = ph.g3; sl.h3 = ph.h3; sl.f3 = ph.f3;
-            sl.series = s;
-            sl.i = i;
-        } else {
-            sl.series = -1;
-            sl.i = 0;
+            ring[lane] = sl;
         }
-        sl.pad = 0;
-        ring[lane] = sl;
     };
 
-    int64_t q_base = 0;      // next queue position
-    int64_t filled_j = -1;   // chunk currently in the ring
+    uint32_t qb = 0;                // next queue position
+    uint32_t filled = 0xFFFFFFFFu;  // chunk currently in the ring
     BLane L[SPL];
 #pragma unroll
-    for (int k = 0; k < SPL; ++k) L[k].t = 0;
-    uint32_t days_done = 0;
+    for (int k = 0; k < SPL; ++k) L[k].w = 0u;
+    uint64_t days_done = 0;         // of the whole wavefront
 
     while (true) {
-        // refill every idle slot from the wave queue, in queue order; the ring
-        // holds one chunk, so a refill may span the end of one chunk and the
-        // start of the next
+        // refill every idle slot from the wave queue, in queue order, once at
+        // least refill_min lanes are idle; the ring holds one chunk, so a
+        // refill may span the end of one chunk and the start of the next
+        uint64_t any = 0;
 #pragma unroll
         for (int k = 0; k < SPL; ++k) {
-            uint64_t m = __ballot(L[k].t == 0);
-            if (__popcll(m) < a.refill_min) continue;  // let a few more lanes finish first
-            while (m != 0ull && q_base < Q) {
-                const int64_t j = q_base >> 6;
-                if (j != filled_j) {
-                    fill(j);
-                    filled_j = j;
-                }
-                const int avail = 64 - (int)(q_base & 63);
-                const bool inm = (m >> lane) & 1ull;
-                // lanes of m below this one
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                const bool take = inm && rank < avail;
-                if (take) {
-                    const BSlot sl = ring[(q_base & 63) + rank];
-                    if (sl.series >= 0) {
-                        const SeriesDesc& d = desc_sh[sl.series];
+            uint64_t m = __ballot(L[k].w == 0u);
+            if (__popcll(m) >= a.refill_min) {
+                while (m != 0ull && qb < Q) {
+                    const uint32_t j = qb >> 6;
+                    if (j != filled) {
+                        fill(j);
+                        filled = j;
+                    }
+                    const uint32_t off = qb & 63u, avail = 64u - off;
+                    const uint32_t rank = mask_rank(m);
+                    const uint64_t took = m & __ballot(rank < avail);
+                    const uint32_t pos = off + rank;
+                    if (in_mask(took) && pos < cur_valid) {
+                        const BSlot sl = ring[pos];
+                        const BSer e = ser[cur_s];
                         BLane& l = L[k];
                         l.r = RatesF{sl.a0, sl.al, sl.n, sl.be, sl.ga, sl.de, sl.bh};
-                        l.s.A = d.A0; l.s.R = d.R0; l.s.D = d.D0; l.s.Ru = 0;
-                        l.s.I = sl.i0;
-                        l.s.S = d.room - sl.i0;
+                        l.s = StateD{e.room - sl.i0, sl.i0, e.A0, e.M0, e.R1, e.D1};
                         l.ph.c1base = sl.c1base; l.ph.g3 = sl.g3; l.ph.h3 = sl.h3; l.ph.f3 = sl.f3;
-                        l.i = sl.i;
-                        l.t = 1;
-                        l.T = d.T;
-                        l.obs_off = d.obs_off;
-                        l.series = sl.series;
-                        l.invP = d.invP;
-                        l.exit2 = d.exit2;
-                        l.b1 = d.b1;
+                        l.i = cur_first + (int64_t)pos;
+                        l.w = 256u | wdom;
+                        l.p = e.obs;
+                        l.wend = e.wend;
+                        l.series = cur_s;
+                        l.invP = e.invP;
+                        l.exit2 = e.exit2;
+                        l.b1 = e.b1;
                         l.acc = 0.0f;
                     }
+                    qb += (uint32_t)__popcll(took);
+                    m &= ~took;  // lanes still without a position
                 }
-                const int cnt = __popcll(m);
-                q_base += cnt < avail ? cnt : avail;
-                m = __ballot(inm && !take);  // lanes still without a position
+                m = __ballot(L[k].w == 0u);
             }
+            any |= ~m;
+            days_done += (uint64_t)__popcll(~m);
         }
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < SPL; ++k) any |= L[k].t != 0;
         // a refill can land every idle lane on the unused tail of a series'
         // last chunk; the wave ends only when the queue is exhausted too
-        if (__ballot(any) == 0ull && q_base >= Q) break;
+        if (any == 0ull) {
+            if (qb >= Q) break;
+            continue;
+        }
 
 #pragma unroll
         for (int k = 0; k < SPL; ++k) {
             BLane& l = L[k];
-            if (l.t == 0) continue;
-            const int t = l.t;
-            const uint4 w = l.ph.day(((uint32_t)t << 8) | (a.domain << 4), l.b1, a.key);
-            Noise32 z;
-            normals_f32(w, a.nc, z);
-            day_step_f32<0>(l.s, l.r, l.invP, z);
-            const int32_t X[3] = {l.s.A, l.s.R, l.s.D};
-            const float* ob = a.obs_table + l.obs_off + t - 1;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float d = log2p1_count_f32(X[c]) - ob[c * l.T];
-                l.acc = fmaf(d, d, l.acc);
-            }
-            ++days_done;
+            if (l.w == 0u) continue;
+            const float4 ob = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.obs_table) + l.p);
+            const uint4 words = l.ph.day(l.w, l.b1, a.key);
+            float lr, ld, comp = 0.0f;
+            day_distance_f32<0, 0, false>(l.s, l.r, words, l.invP, a.nc, ob, l.acc, comp, lr, ld);
             const bool exited = l.acc > l.exit2;
-            if (exited || t == l.T) {
+            uint32_t wn = l.w + 256u;
+            if (exited | (l.w == l.wend)) {
                 if (!exited) {
                     const float dd = finish_distance_f32(l.acc, 0.693147180559945309417f);
-                    const SeriesDesc& ds = desc_sh[l.series];
+                    const SeriesDesc& ds = a.desc[l.series];
                     if (dd <= ds.eps_hi) {
                         SeriesState& st = a.state[l.series];
                         const int pos = atomicAdd(&st.cand, 1);
@@ -503,18 +510,13 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
                         }
                     }
                 }
-                l.t = 0;
-            } else {
-                l.t = t + 1;
+                wn = 0u;
             }
+            l.w = wn;
+            l.p += (uint32_t)sizeof(float4);
         }
     }
-    if (a.days) {
-        uint64_t v = days_done;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) atomicAdd(a.days, (unsigned long long)v);
-    }
+    if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);
 }
 
 // 1 once every series has reached its target of float32 accepts or used its
@@ -846,7 +848,7 @@ __global__ __launch_bounds__(256) void k_batch_moments(const float* theta, const
 static size_t batch_lds_bytes(int m, int obs_words, int block)
 {
     (void)obs_words;  // the observed rows are read from global memory
-    return sizeof(SeriesDesc) * (size_t)m + sizeof(BSlot) * BT_RING * (size_t)(block / 64);
+    return sizeof(BSer) * (size_t)m + sizeof(BSlot) * BT_RING * (size_t)(block / 64);
 }
 
 }  // namespace abc
@@ -917,7 +919,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
         ABC_REQUIRE(isfinite(b.eps) && b.eps >= 0.0f, "series %d: eps must be finite and >= 0", s);
         SeriesDesc& d = desc[s];
         d.T = b.T; d.P = (int32_t)b.P; d.A0 = b.A0; d.R0 = b.R0; d.D0 = b.D0;
-        d.obs_off = obs_words;
+        d.obs_off = (int32_t)sizeof(float) * obs_words;
         d.room = (int32_t)b.P - (b.A0 + b.R0 + b.D0);
         d.series_id = b.series;
         d.invP = 1.0f / (float)b.P;
@@ -930,7 +932,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
         const uint64_t p1 = (uint64_t)PH_M1 * (uint64_t)b.series;
         d.u0 = (uint32_t)(p1 >> 32) ^ key.k0;
         d.b1 = (uint32_t)p1 ^ (key.k0 + PH_W0);
-        obs_words += 3 * b.T;
+        obs_words += 4 * b.T;
         obs_ptr[s] = b.obs;
         if (b.T > maxT) maxT = b.T;
     }

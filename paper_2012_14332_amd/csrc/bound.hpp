@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include "common.hpp"
+
 namespace abc {
 
 // ---------------------------------------------------------------------------
@@ -33,7 +35,7 @@ constexpr int LB_MAX_BLOCKS = 96; // time blocks per table (48 KB for R and D)
 
 constexpr int LB_MAX_SEG = 8;      // day segments per column while building
 
-// Builds the [2][ntb][LB_Q] table; called by every thread of the workgroup
+// Builds the table [ntb][2][LB_Q], R then D in each row; called by every thread of the workgroup
 // (it synchronises). Column (c, q) is grid point q of table c (0 = R, 1 = D);
 // the days are cut into S = blockDim / 128 segments (at most 8) so that S
 // threads share a column: each sums its segment, the segment sums give every
@@ -70,7 +72,7 @@ __device__ inline void build_future_bound(double* stage, int T, int sh, int ntb,
         const int c = col / LB_Q;
         const double g = 0.5 * (col % LB_Q);
         const double* b = bval + c * T;
-        float* out = tab + c * ntb * LB_Q + (col % LB_Q);
+        float* out = tab + c * LB_Q + (col % LB_Q);
         double F = 0.0;                                // sum over the days after t
         for (int k = S - 1; k > seg; --k) F += segsum[k * 2 * LB_Q + col];
         const int d0 = seg * L + 1, d1 = min((seg + 1) * L, T);
@@ -80,7 +82,7 @@ __device__ inline void build_future_bound(double* stage, int T, int sh, int ntb,
             if (t == min(((tb + 1) << sh) - 1, T)) {
                 double v = F - 2.0 * e * sqrt((double)T * F) - sum_err;
                 v *= 1.0 - 0x1p-20;
-                out[tb * LB_Q] = v > 0.0 ? (float)v : 0.0f;
+                out[2 * tb * LB_Q] = v > 0.0 ? (float)v : 0.0f;
             }
             if (t >= 1) {
                 const double x = g - b[t - 1];
@@ -88,6 +90,14 @@ __device__ inline void build_future_bound(double* stage, int T, int sh, int ntb,
             }
         }
     }
+}
+
+// Bound on the days after the one whose table row has LDS address `row`: grid
+// indexes rounded down, below the float32 error of the logarithms.
+__device__ __forceinline__ float future_bound(uint32_t row, float lr, float ld)
+{
+    const int qr = (int)fmaf(lr, 2.0f, -0x1p-12f), qd = (int)fmaf(ld, 2.0f, -0x1p-12f);
+    return lds_float(row + 4u * (uint32_t)qr) + lds_float(row + 4u * (uint32_t)qd + 4u * LB_Q);
 }
 
 }  // namespace abc

@@ -26,6 +26,10 @@ constexpr int64_t ROW_WAVE_TARGET = 1024;
 constexpr int32_t ROW_SCAN_BESIDE = 8;
 constexpr int32_t ROW_SCAN_ALONE = 4;
 
+// Whether the calling thread has set a launch shape (abc_set_launch_config);
+// otherwise each kernel chooses its own.
+bool launch_shape_chosen();
+
 // abc_recheck_band with a chosen grid cap and candidates per wavefront; with all_rows every candidate (not only those in
 // the band) is decided by its float64 distance, and dist64 (nullable,
 // [capacity]) receives that distance for each row, compacted with the rows.
@@ -65,6 +69,32 @@ __device__ __forceinline__ float4 load_stream(const float4* p)
     return make_float4(t.x, t.y, t.z, t.w);
 }
 __device__ __forceinline__ float load_stream(const float* p) { return __builtin_nontemporal_load(p); }
+
+// LDS by its own 32-bit addresses: a generic pointer into LDS costs an addition
+// of the allocation's base on every access that the day loops cannot spare.
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(const T* p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const T*)p;
+}
+typedef float abc_lds_v4f __attribute__((ext_vector_type(4), aligned(16)));
+__device__ __forceinline__ float4 lds_row(uint32_t address)
+{
+    const abc_lds_v4f v = *(__attribute__((address_space(3))) const abc_lds_v4f*)address;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float lds_float(uint32_t address)
+{
+    return *(__attribute__((address_space(3))) const float*)address;
+}
+
+// Whether this lane is in a wavefront mask (no vector instruction).
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Lanes of m below this one.
+__device__ __forceinline__ uint32_t mask_rank(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
 // Compute units and LDS bytes per workgroup of the current device, queried
 // once per device (attribute queries cost tens of microseconds each, too much

@@ -102,13 +102,21 @@ struct Noise32 {
     float tr[5];
 };
 
+// Uniform (f + 1/2) 2^-21 of the 21-bit field f in the upper bits of x (its
+// lower 11 bits are dropped): one funnel shift puts f under the exponent of
+// 2^23, and the fma takes the 2^23 away again (exact). A shift, a conversion
+// and an fma would be one instruction more.
+__device__ __forceinline__ float field_uniform(uint32_t x)
+{
+    return fmaf(__uint_as_float(__builtin_amdgcn_alignbit(0x258u, x, 11)), 0x1p-21f, 0x1p-22f - 4.0f);
+}
+
 __device__ __forceinline__ void normals_f32(uint4 w, float c, Noise32& z)
 {
-    uint32_t f[6];
-    day_fields(w, f);
-    float u[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) u[k] = fmaf((float)f[k], 0x1p-21f, 0x1p-22f);  // exact
+    // the fifth and sixth field: 11 low bits of one word above 10 of the next
+    const uint32_t x4 = __builtin_amdgcn_alignbit(w.x, w.y << 22, 11), x5 = __builtin_amdgcn_alignbit(w.z, w.w << 22, 11);
+    const float u[6] = {field_uniform(w.x), field_uniform(w.y), field_uniform(w.z),
+                        field_uniform(w.w), field_uniform(x4), field_uniform(x5)};
     z.rr[0] = c * __builtin_amdgcn_logf(u[0]);
     z.rr[1] = c * __builtin_amdgcn_logf(u[2]);
     z.rr[2] = c * __builtin_amdgcn_logf(u[4]);
@@ -124,20 +132,27 @@ __device__ __forceinline__ float noise_c(float scale)
     return -1.38629436111989061883f * scale * scale;
 }
 
+// Integer part of x limited to uint32 (below 0 or NaN: 0), as the conversion
+// instruction gives it; in C++ the cast of a value out of range has no result.
+__device__ __forceinline__ uint32_t cvt_u32_sat(float x)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f32_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // floor(h + sd(h) s z) limited to [0, avail], with s z = sqrt(rr) tr: the
 // standard deviation sqrt(h) (h^(1/4) read literally) and the radius share one
-// square root. For x >= 0 the float->int conversion truncates, which is the
-// floor, and the clamp at 0 absorbs negative x, so no separate floor is
-// needed. The float is limited below 2^31 before the conversion and the
-// integer is then limited to avail, so a float rounding of avail cannot leak
-// into the count. Rates are non-negative, so h >= 0 and the root is finite.
+// square root. The conversion to unsigned truncates, which is the floor for
+// x >= 0, takes negative x to 0 and x above 2^32 to its largest value, which
+// avail then limits: no clamp in float is needed. Rates are non-negative, so
+// h >= 0 and the root is finite.
 template <int NOISE>
 __device__ __forceinline__ int32_t draw_f32(float h, float rr, float tr, int32_t avail)
 {
     const float v = NOISE == 1 ? __builtin_amdgcn_sqrtf(h) * rr : h * rr;
     const float x = fmaf(__builtin_amdgcn_sqrtf(v), tr, h);
-    const float f = __builtin_amdgcn_fmed3f(x, 0.0f, 2147483520.0f);
-    return min((int32_t)f, avail);
+    return (int32_t)min(cvt_u32_sat(x), (uint32_t)avail);
 }
 
 struct RatesF {
@@ -149,38 +164,124 @@ __device__ __forceinline__ RatesF rates_f32(const Theta& t)
     return RatesF{t.a0, t.al, t.n, t.be, t.ga, t.de, t.be * t.et};
 }
 
+// The five transitions of a day from the morning's counts (M = A + R + D).
+struct Moves {
+    int32_t n1, n2, n3, n4, n5;
+};
+
 template <int NOISE>
-__device__ __forceinline__ void day_step_f32(State& s, const RatesF& r, float invP,
-                                             const Noise32& z)
+__device__ __forceinline__ Moves moves_f32(int32_t S, int32_t I, int32_t A, int32_t Mi, const RatesF& r,
+                                           float invP, const Noise32& z)
 {
-    const float M = (float)(s.A + s.R + s.D);
+    const float M = (float)Mi;
     const float pw = __builtin_amdgcn_exp2f(r.n * __builtin_amdgcn_logf(M));
     const float g = fmaf(r.al, __builtin_amdgcn_rcpf(1.0f + pw), r.a0);
-    const float If = (float)s.I;
-    const float Af = (float)s.A;
-    const float h1 = (g * invP) * (float)s.S * If;
+    const float If = (float)I;
+    const float Af = (float)A;
+    const float h1 = (g * invP) * (float)S * If;
     const float h2 = r.ga * If;
     const float h3 = r.be * Af;
     const float h4 = r.de * Af;
     const float h5 = r.bh * If;
-    const int32_t n1 = draw_f32<NOISE>(h1, z.rr[0], z.tr[0], s.S);
-    const int32_t n2 = draw_f32<NOISE>(h2, z.rr[0], z.tr[1], s.I);
-    const int32_t n3 = draw_f32<NOISE>(h3, z.rr[1], z.tr[2], s.A);
-    const int32_t n4 = draw_f32<NOISE>(h4, z.rr[1], z.tr[3], s.A - n3);
-    const int32_t n5 = draw_f32<NOISE>(h5, z.rr[2], z.tr[4], s.I - n2);
-    s.S -= n1;
-    s.I += n1 - n2 - n5;
-    s.A += n2 - n3 - n4;
-    s.R += n3;
-    s.D += n4;
-    s.Ru += n5;
+    Moves m;
+    m.n1 = draw_f32<NOISE>(h1, z.rr[0], z.tr[0], S);
+    m.n2 = draw_f32<NOISE>(h2, z.rr[0], z.tr[1], I);
+    m.n3 = draw_f32<NOISE>(h3, z.rr[1], z.tr[2], A);
+    m.n4 = draw_f32<NOISE>(h4, z.rr[1], z.tr[3], A - m.n3);
+    m.n5 = draw_f32<NOISE>(h5, z.rr[2], z.tr[4], I - m.n2);
+    return m;
 }
 
-// log2(1 + X) of a non-negative count; the float32 distance is accumulated
-// in log2 units and scaled by ln 2 once at the end.
-__device__ __forceinline__ float log2p1_count_f32(int32_t X)
+template <int NOISE>
+__device__ __forceinline__ void day_step_f32(State& s, const RatesF& r, float invP,
+                                             const Noise32& z)
 {
-    return __builtin_amdgcn_logf((float)(X + 1));
+    const Moves m = moves_f32<NOISE>(s.S, s.I, s.A, s.A + s.R + s.D, r, invP, z);
+    s.S -= m.n1;
+    s.I += m.n1 - m.n2 - m.n5;
+    s.A += m.n2 - m.n3 - m.n4;
+    s.R += m.n3;
+    s.D += m.n4;
+    s.Ru += m.n5;
+}
+
+// ---------------------------------------------------------------------------
+// One day of the float32 simulate+distance kernels. They are bound by VALU
+// issue, so the day keeps what it needs in the form it needs it: R and D as
+// R + 1 and D + 1 (the arguments of their logarithms), M = A + R + D as a
+// count of its own (recoveries alone raise it), the counter word of the day
+// and the address of its row counted up instead of formed from the day. The
+// observed days are rows of four words: log2(1 + O) of A, R and D (or, for the
+// raw distance, O of A and O + 1 of R and D), and the LDS address of the day's
+// row in the future-days bound table, so that a day reads one row and its
+// table entries with one address each.
+// ---------------------------------------------------------------------------
+struct StateD {
+    int32_t S, I, A, M, R1, D1;
+};
+
+__device__ __forceinline__ StateD state_d(int32_t room, int32_t A0, int32_t R0, int32_t D0, int32_t I0)
+{
+    return StateD{room - I0, I0, A0, A0 + R0 + D0, R0 + 1, D0 + 1};
+}
+
+// the observed words of one day (the fourth: LDS address of the bound row)
+template <int DIST>
+__device__ __forceinline__ float4 obs_row(int32_t A, int32_t R, int32_t D, uint32_t bound_row)
+{
+    float4 o;
+    if (DIST == 0) {
+        o.x = (float)(log1p((double)A) * 1.44269504088896340736);
+        o.y = (float)(log1p((double)R) * 1.44269504088896340736);
+        o.z = (float)(log1p((double)D) * 1.44269504088896340736);
+    } else {
+        o.x = __int_as_float(A);
+        o.y = __uint_as_float((uint32_t)R + 1u);
+        o.z = __uint_as_float((uint32_t)D + 1u);
+    }
+    o.w = __uint_as_float(bound_row);
+    return o;
+}
+
+// Simulates the day of counter word w, adds its squared distance to acc (comp:
+// the Kahan compensation); lr, ld return log2(1 + R), log2(1 + D) for the
+// log1p distance.
+template <int NOISE, int DIST, bool KAHAN>
+__device__ __forceinline__ void day_distance_f32(StateD& s, const RatesF& r, uint4 words, float invP, float nc,
+                                                 const float4& ob, float& acc, float& comp, float& lr, float& ld)
+{
+    Noise32 z;
+    normals_f32(words, nc, z);
+    const Moves m = moves_f32<NOISE>(s.S, s.I, s.A, s.M, r, invP, z);
+    s.S -= m.n1;
+    s.I = (s.I - m.n2) - m.n5 + m.n1;
+    s.A = (s.A - m.n3) - m.n4 + m.n2;
+    s.M += m.n2;
+    s.R1 += m.n3;
+    s.D1 += m.n4;
+    float d[3];
+    if (DIST == 0) {
+        lr = __builtin_amdgcn_logf((float)s.R1);
+        ld = __builtin_amdgcn_logf((float)s.D1);
+        d[0] = __builtin_amdgcn_logf((float)(s.A + 1)) - ob.x;
+        d[1] = lr - ob.y;
+        d[2] = ld - ob.z;
+    } else {
+        d[0] = (float)(int32_t)((uint32_t)s.A - __float_as_uint(ob.x));
+        d[1] = (float)(int32_t)((uint32_t)s.R1 - __float_as_uint(ob.y));
+        d[2] = (float)(int32_t)((uint32_t)s.D1 - __float_as_uint(ob.z));
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (KAHAN) {
+            const float y = fmaf(d[c], d[c], -comp);
+            const float t = acc + y;
+            comp = (t - acc) - y;
+            acc = t;
+        } else {
+            acc = fmaf(d[c], d[c], acc);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -34,8 +34,8 @@ struct MSeries {
     uint32_t u0, b1;   // its per-series Philox constants
     float invP;
     float exit_f32;    // squared-distance early-exit bound in log2 units (or raw)
-    int32_t obs_off;   // float offset of the observed rows [3][T] in LDS
-    int32_t tab_off;   // float offset of the bound table [2][ntb][LB_Q] in LDS, -1: none
+    int32_t obs_off;   // float offset of the observed rows [T][4] in LDS
+    int32_t tab_off;   // float offset of the bound table [ntb][2][LB_Q] in the tables, -1: none
     int32_t ntb, lb_sh;
     int64_t chunk0;    // first chunk of the series in the launch's queue
     int64_t n;
@@ -56,16 +56,18 @@ struct MultiArgs {
     float scale;
     int32_t obs_words;  // floats of all observed rows (a multiple of 4)
     int32_t tab_words;  // floats of all bound tables (a multiple of 4)
+    int32_t zero_off;   // float offset of a row of zeros among them for series without one, -1: none
     unsigned long long* days;
 };
 
-// What a lane reads from LDS when it starts a sample of series j.
+// What a lane reads from LDS when it starts a sample of series j (three reads).
 struct alignas(16) SerLds {
+    int32_t A0, M0, R1, D1;    // A0, A0 + R0 + D0, R0 + 1, D0 + 1
     float invP, exitb;
-    int32_t T, obs_off, tab_r, tab_d, lb_sh;
-    uint32_t b1;
+    uint32_t wend, b1;         // wend: fourth counter word of the last day
+    uint32_t obs;              // LDS address of the first observed row
+    int32_t room;              // P - A0 - R0 - D0 (S0 + I0)
     float* dist;
-    int32_t A0, R0, D0, room;  // room = P - A0 - R0 - D0 (S0 + I0)
 };
 
 // One prepared sample: rates, I0 and the per-sample Philox words. Its series
@@ -77,24 +79,24 @@ struct alignas(16) MSlot {
     uint32_t c1base, g3, h3, f3;
 };
 
+typedef __attribute__((address_space(1))) float global_float;
+
 struct MLane {
-    State s;
+    StateD s;
     RatesF r;
     PhiloxDays ph;
-    int64_t k;
-    int32_t t;  // the day the lane simulates next; 0: no sample (idle)
+    global_float* out;  // the sample's distance
+    uint32_t w;         // fourth counter word of the next day; 0: no sample (idle)
+    uint32_t p;         // LDS address of the day's observed row
     float acc, comp;
-    int32_t ls;
-    // the lane's series, cached at the start of each sample (tr, td: its
-    // bound tables for R and D, tr null without one)
-    int32_t T, obs_off, lb_sh;
-    const float* tr;
-    const float* td;
+    // the lane's series, cached at the start of each sample
+    uint32_t wend;
     float invP, exitb;
     uint32_t b1;
 };
 
-template <int NOISE, int DIST, bool KAHAN>
+// BOUND: some series of the launch has a future-days bound table.
+template <int NOISE, int DIST, bool KAHAN, bool BOUND>
 __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
 {
     constexpr int RING = 64;
@@ -103,36 +105,37 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
     SerLds* ser = reinterpret_cast<SerLds*>(tabs + a.tab_words);
     MSlot* ring_all = reinterpret_cast<MSlot*>(ser + MS_MAX);
 
-    // observed rows of every series: log2(1 + O) (or O for the raw distance)
+    // observed rows of every series (obs_row)
+    const uint32_t tabs_at = lds_address(tabs);
     for (int j = 0; j < a.m; ++j) {
         const MSeries& sj = a.s[j];
-        for (int q = threadIdx.x; q < 3 * sj.T; q += blockDim.x) {
-            const int32_t O = sj.obs[q];
-            if (DIST == 0)
-                lds_f[sj.obs_off + q] = (float)(log1p((double)O) * 1.44269504088896340736);
-            else
-                lds_f[sj.obs_off + q] = __int_as_float(O);
+        for (int q = threadIdx.x; q < sj.T; q += blockDim.x) {
+            const int row = sj.tab_off >= 0 ? sj.tab_off + 2 * LB_Q * ((q + 1) >> sj.lb_sh) : a.zero_off;
+            *reinterpret_cast<float4*>(lds_f + sj.obs_off + 4 * q) =
+                obs_row<DIST>(sj.obs[q], sj.obs[sj.T + q], sj.obs[2 * sj.T + q],
+                              tabs_at + (uint32_t)sizeof(float) * (uint32_t)row);
         }
     }
+    if (a.zero_off >= 0)
+        for (int q = threadIdx.x; q < 2 * LB_Q; q += blockDim.x) tabs[a.zero_off + q] = 0.0f;
+    const uint32_t wdom = a.domain << 4;
     if (threadIdx.x < (unsigned)a.m) {
         const MSeries& sj = a.s[threadIdx.x];
         SerLds e;
+        e.A0 = sj.A0;
+        e.M0 = sj.A0 + sj.R0 + sj.D0;
+        e.R1 = sj.R0 + 1;
+        e.D1 = sj.D0 + 1;
         e.invP = sj.invP;
         e.exitb = sj.exit_f32;
-        e.T = sj.T;
-        e.obs_off = sj.obs_off;
-        e.tab_r = sj.tab_off;
-        e.tab_d = sj.tab_off + sj.ntb * LB_Q;
-        e.lb_sh = sj.lb_sh;
+        e.wend = ((uint32_t)sj.T << 8) | wdom;
         e.b1 = sj.b1;
+        e.obs = lds_address(lds_f) + (uint32_t)sizeof(float) * (uint32_t)sj.obs_off;
+        e.room = sj.P - e.M0;
         e.dist = sj.dist;
-        e.A0 = sj.A0;
-        e.R0 = sj.R0;
-        e.D0 = sj.D0;
-        e.room = sj.P - (sj.A0 + sj.R0 + sj.D0);
         ser[threadIdx.x] = e;
     }
-    if (DIST == 0) {
+    if (BOUND) {
         // future-days bound tables, one series at a time; b_s of R and D in
         // float64 staged where the ring will live
         double* stage = reinterpret_cast<double*>(ring_all);
@@ -162,8 +165,6 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
     const uint32_t Q = (uint32_t)(((a.nchunks - 1 - wg) / nw + 1) << 6);
     const float nc = noise_c(a.scale);
     const float dscale = DIST == 0 ? 0.693147180559945309417f : 1.0f;
-    const uint32_t wdom = a.domain << 4;
-
     // the chunk in the ring (wave-uniform): its series, the offset of its
     // first sample in that series, and how many of its 64 positions hold a
     // sample (fewer only in a series' last chunk)
@@ -200,15 +201,14 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
     uint32_t qb = 0;
     uint32_t filled = 0xFFFFFFFFu;
     MLane l;
-    l.t = 0;
-    uint32_t days_done = 0;
+    l.w = 0u;
+    uint64_t days_done = 0;  // of the whole wavefront
 
     while (true) {
         // refill: the idle lanes take the next queue positions in lane order,
         // once at least refill_min of them are idle; a pass may span the end
         // of one chunk and the start of the next
-        bool want = l.t == 0;
-        uint64_t m = __ballot(want);
+        uint64_t m = __ballot(l.w == 0u);
         if (__popcll(m) >= a.refill_min) {
             while (m != 0ull && qb < Q) {
                 const uint32_t jc = qb >> 6;
@@ -216,89 +216,51 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
                     fill(wg + (int64_t)jc * nw);
                     filled = jc;
                 }
-                const uint32_t off = qb & 63u;
-                const uint32_t avail = 64u - off;
-                // lanes of m below this one
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                const bool take = want && rank < avail;
+                const uint32_t off = qb & 63u, avail = 64u - off;
+                const uint32_t rank = mask_rank(m);
+                const uint64_t took = m & __ballot(rank < avail);
                 const uint32_t pos = off + rank;
-                if (take && pos < cur_valid) {
+                if (in_mask(took) && pos < cur_valid) {
                     const MSlot sl = ring[pos];
                     const SerLds e = ser[cur_ls];
                     l.r = RatesF{sl.a0, sl.al, sl.n, sl.be, sl.ga, sl.de, sl.bh};
-                    l.s.A = e.A0; l.s.R = e.R0; l.s.D = e.D0; l.s.Ru = 0;
-                    l.s.I = sl.i0;
-                    l.s.S = e.room - sl.i0;
+                    l.s = StateD{e.room - sl.i0, sl.i0, e.A0, e.M0, e.R1, e.D1};
                     l.ph.c1base = sl.c1base; l.ph.g3 = sl.g3; l.ph.h3 = sl.h3; l.ph.f3 = sl.f3;
-                    l.k = cur_base + (int64_t)pos;
-                    l.ls = cur_ls;
-                    l.T = e.T; l.obs_off = e.obs_off;
-                    l.tr = e.tab_r >= 0 ? tabs + e.tab_r : nullptr;
-                    l.td = tabs + e.tab_d;
-                    l.lb_sh = e.lb_sh; l.invP = e.invP; l.exitb = e.exitb; l.b1 = e.b1;
-                    l.t = 1;
+                    l.out = (global_float*)e.dist + (cur_base + (int64_t)pos);
+                    l.wend = e.wend; l.p = e.obs;
+                    l.invP = e.invP; l.exitb = e.exitb; l.b1 = e.b1;
+                    l.w = 256u | wdom;
                     l.acc = 0.0f;
                     l.comp = 0.0f;
                 }
-                want = want && !take;
-                const uint32_t cnt = (uint32_t)__popcll(m);
-                qb += cnt < avail ? cnt : avail;
-                m = __ballot(want);
+                qb += (uint32_t)__popcll(took);
+                m &= ~took;
             }
+            m = __ballot(l.w == 0u);
         }
-        if (__ballot(l.t != 0) == 0ull && qb >= Q) break;
-        if (l.t != 0) {
-            const int t = l.t;
-            const uint4 w = l.ph.day(((uint32_t)t << 8) | wdom, l.b1, a.key);
-            Noise32 z;
-            normals_f32(w, nc, z);
-            day_step_f32<NOISE>(l.s, l.r, l.invP, z);
-            const int32_t X[3] = {l.s.A, l.s.R, l.s.D};
-            float lx[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const int q = l.obs_off + c * l.T + t - 1;
-                float d;
-                if (DIST == 0) {
-                    lx[c] = log2p1_count_f32(X[c]);
-                    d = lx[c] - lds_f[q];
-                } else {
-                    d = (float)(X[c] - __float_as_int(lds_f[q]));
-                }
-                if (KAHAN) {
-                    const float y = fmaf(d, d, -l.comp);
-                    const float tt = l.acc + y;
-                    l.comp = (tt - l.acc) - y;
-                    l.acc = tt;
-                } else {
-                    l.acc = fmaf(d, d, l.acc);
-                }
+        if (m == ~0ull) {
+            if (qb >= Q) break;
+            continue;
+        }
+        days_done += (uint64_t)__popcll(~m);
+        if (l.w != 0u) {
+            const float4 ob = lds_row(l.p);
+            const uint4 words = l.ph.day(l.w, l.b1, a.key);
+            float lr, ld;
+            day_distance_f32<NOISE, DIST, KAHAN>(l.s, l.r, words, l.invP, nc, ob, l.acc, l.comp, lr, ld);
+            float sum = l.acc;
+            if (BOUND) sum += future_bound(__float_as_uint(ob.w), lr, ld);
+            const bool exited = sum > l.exitb;
+            uint32_t wn = l.w + 256u;
+            if (exited | (l.w == l.wend)) {
+                *l.out = exited ? INFINITY : finish_distance_f32(l.acc, dscale);
+                wn = 0u;
             }
-            float lb = 0.0f;
-            if (DIST == 0 && l.tr != nullptr) {
-                const int row = (t >> l.lb_sh) * LB_Q;
-                const int qr = (int)fmaf(lx[1], 2.0f, -0x1p-12f);
-                const int qd = (int)fmaf(lx[2], 2.0f, -0x1p-12f);
-                lb = l.tr[row + qr] + l.td[row + qd];
-            }
-            const bool exited = l.acc + lb > l.exitb;
-            if (exited || t == l.T) {
-                const float dd = exited ? INFINITY : finish_distance_f32(l.acc, dscale);
-                ser[l.ls].dist[l.k] = dd;
-                l.t = 0;
-                days_done += (uint32_t)t;
-            } else {
-                l.t = t + 1;
-            }
+            l.w = wn;
+            l.p += (uint32_t)sizeof(float4);
         }
     }
-    if (a.days) {
-        uint64_t v = days_done;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) atomicAdd(a.days, (unsigned long long)v);
-    }
+    if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);
 }
 
 static size_t multi_lds_bytes(int obs_words, int tab_words, int block, int stage_doubles)
@@ -312,7 +274,13 @@ static size_t multi_lds_bytes(int obs_words, int tab_words, int block, int stage
 template <int NOISE, int DIST, bool KAHAN>
 static void launch_multi(const MultiArgs& a, unsigned grid, int block, size_t lds, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_simulate_multi_f32<NOISE, DIST, KAHAN>), dim3(grid), dim3(block), lds, s, a);
+    if constexpr (DIST == 0) {
+        if (a.tab_words > 0) {
+            hipLaunchKernelGGL((k_simulate_multi_f32<NOISE, DIST, KAHAN, true>), dim3(grid), dim3(block), lds, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_simulate_multi_f32<NOISE, DIST, KAHAN, false>), dim3(grid), dim3(block), lds, s, a);
 }
 
 }  // namespace abc
@@ -366,6 +334,18 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
     a.days = days;
     int32_t spl = 1, block = 512, bpc = 2;
     abc_get_launch_config(&spl, &block, &bpc);
+    // a large launch takes two 1024-thread workgroups per CU, a smaller one
+    // 512-thread workgroups with at least seven chunks per wavefront (as the
+    // one-series launch): three series of 1e7 samples take 1.49 ms instead of
+    // 1.60 ms with two 512-thread workgroups, three of 3e5 samples 0.117 ms
+    // instead of 0.127 ms
+    if (!launch_shape_chosen()) {
+        DeviceInfo di;
+        if ((rc = device_info(&di))) return rc;
+        const int64_t per = (total / 64) / ((int64_t)di.num_cu * 8 * 7);
+        block = per >= 4 ? 1024 : 512;
+        bpc = per >= 2 ? 2 : 1;
+    }
     a.refill_min = abc_get_refill_min();
     int obs_words = 0, maxT = 0;
     int64_t chunk = 0;
@@ -388,7 +368,7 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
         const double unit = distm ? 1.0 : 2.08136898100560809980;
         s.exit_f32 = isinf(jb.eps_exit) ? INFINITY : (float)(e2 * unit * (1.0 + 0x1p-18));
         s.obs_off = obs_words;
-        obs_words += 3 * s.T;
+        obs_words += 4 * s.T;
         s.chunk0 = chunk;
         chunk += (jb.n + 63) >> 6;
         s.n = jb.n;
@@ -402,18 +382,27 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
         }
     }
     a.nchunks = chunk;
-    a.obs_words = (obs_words + 3) & ~3;
+    a.obs_words = obs_words;
     const int stage_doubles = 2 * maxT + LB_MAX_SEG * 2 * LB_Q;
     DeviceInfo info;
     if ((rc = device_info(&info))) return rc;
     const int num_cu = info.num_cu, max_lds = info.max_lds;
+    // where the rows and the rings of a workgroup of this size do not fit, a
+    // smaller workgroup needs fewer rings
+    while (block > 64 && multi_lds_bytes(a.obs_words, 0, block, stage_doubles) > (size_t)max_lds)
+        block = (block / 2 + 63) & ~63;
     // bound tables: coarser time blocks for the series with the most rows until
     // blocks_per_cu workgroups fit a CU's LDS (160 KiB) and one fits the
-    // workgroup limit; without room at all, no tables
+    // workgroup limit; without room at all, no tables. Series without a table
+    // beside others with one look up a row of zeros.
     auto tab_words = [&]() {
         int w = 0;
-        for (int q = 0; q < a.m; ++q) w += 2 * LB_Q * ntb[q];
-        return w;
+        bool with = false, without = false;
+        for (int q = 0; q < a.m; ++q) {
+            w += 2 * LB_Q * ntb[q];
+            (ntb[q] > 0 ? with : without) = true;
+        }
+        return w + (with && without ? 2 * LB_Q : 0);
     };
     const size_t lds_target = std::min((size_t)max_lds, (size_t)(163840 / (bpc > 0 ? bpc : 1)));
     while (multi_lds_bytes(a.obs_words, tab_words(), block, stage_doubles) > lds_target) {
@@ -426,6 +415,8 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
     }
     if (multi_lds_bytes(a.obs_words, tab_words(), block, stage_doubles) > (size_t)max_lds)
         for (int q = 0; q < a.m; ++q) ntb[q] = 0;
+    a.tab_words = tab_words();
+    a.zero_off = -1;
     int tw = 0;
     for (int q = 0; q < a.m; ++q) {
         a.s[q].ntb = ntb[q];
@@ -433,11 +424,11 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
         a.s[q].tab_off = ntb[q] > 0 ? tw : -1;
         tw += 2 * LB_Q * ntb[q];
     }
-    a.tab_words = tw;
+    if (tw < a.tab_words) a.zero_off = tw;
     const size_t lds = multi_lds_bytes(a.obs_words, a.tab_words, block, stage_doubles);
     if (lds > (size_t)max_lds)
         return set_error(ABC_EUNSUPPORTED, "%d series with %d observed days need %zu B of LDS "
-                         "per workgroup of %d (> %d)", a.m, obs_words, lds, block, max_lds);
+                         "per workgroup of %d (> %d)", a.m, obs_words / 4, lds, block, max_lds);
     // resident workgroups: what the LDS allows per CU, at most blocks_per_cu
     int per_cu = (int)(163840 / lds);
     if (per_cu < 1) per_cu = 1;

@@ -3,8 +3,8 @@
 // abc_simulate_record).
 //
 // simulate+distance: one lane per trajectory. The observed series of the
-// launch is staged once per workgroup in LDS as log1p(O) (or O for the raw
-// distance), so the day loop touches no global memory at all: per sample the
+// launch is staged once per workgroup in LDS as rows of one day (log2(1 + O),
+// or O for the raw distance), so the day loop touches no global memory at all: per sample the
 // kernel reads 32 B of theta (or none when theta is drawn in-kernel) and
 // writes 4 B of distance. A sample leaves the day loop as soon as its running
 // squared distance passes the early-exit bound.
@@ -82,13 +82,11 @@ __device__ __forceinline__ bool outside_box(const SimArgs& a, const float th[8])
 // theta, never on the launch shape or on which lane ran it.
 // ---------------------------------------------------------------------------
 // Everything a lane needs to start a sample, prepared by the whole wave so the
-// divergent refill branch only copies 64 bytes out of LDS.
+// divergent refill branch only copies 48 bytes out of LDS.
 struct alignas(16) Slot {
     float a0, al, n, be, ga, de, bh;
-    int32_t i0;
+    int32_t i0;                   // -1: prior density zero (not simulated)
     uint32_t c1base, g3, h3, f3;  // per-sample part of Philox rounds 1-3
-    int64_t k;                    // sample offset in the launch (n = no sample)
-    int64_t pad;
 };
 
 template <bool PRIOR>
@@ -104,40 +102,42 @@ __device__ __forceinline__ void fill_slot(const SimArgs& a, int64_t k, uint32_t 
     out.a0 = r.a0; out.al = r.al; out.n = r.n; out.be = r.be;
     out.ga = r.ga; out.de = r.de; out.bh = r.bh; out.i0 = s0.I;
     out.c1base = ph.c1base; out.g3 = ph.g3; out.h3 = ph.h3; out.f3 = ph.f3;
-    out.k = k;
-    out.pad = (!PRIOR && a.box && outside_box(a, thv)) ? 1 : 0;  // 1: prior density zero
+    if (!PRIOR && a.box && outside_box(a, thv)) out.i0 = -1;
 }
 
 struct Lane {
-    State s;
+    StateD s;
     RatesF r;
     PhiloxDays ph;
     int64_t k;     // sample offset within the launch
-    int32_t t;     // next day to simulate; 0: no sample (idle)
+    uint32_t w;    // fourth counter word of the next day, day << 8 | domain << 4; 0: no sample (idle)
+    uint32_t p;    // LDS address of the day's observed row
     float acc, comp;
 };
 
-template <int NOISE, int DIST, bool KAHAN, bool PRIOR, int SPL>
-__global__ __launch_bounds__(1024 / SPL) void k_simulate_f32(SimArgs a)
+// BOUND: with the future-days bound (log1p distance and an exit bound). With
+// one sample per lane the scheduler is asked for 7 wavefronts per SIMD: left
+// alone it takes 76 registers (6 wavefronts), asked for 8 it takes 53 and
+// orders the day for registers instead of latency; at 62 registers 1e7 samples
+// of T = 100 take 908 us against 924 and 1017.
+template <int NOISE, int DIST, bool KAHAN, bool PRIOR, int SPL, bool BOUND>
+__global__ __launch_bounds__(1024 / SPL, SPL == 1 ? 7 : 1) void k_simulate_f32(SimArgs a)
 {
     constexpr int RING = 64;  // one chunk of 64 queue positions
     extern __shared__ float lds_f[];
     const int T = a.T;
-    const int obs_words = (3 * T + 3) & ~3;
-    const int ntb = DIST == 0 ? a.lb_ntb : 0;
-    float* tab = lds_f + obs_words;  // [2][ntb][LB_Q] future-days bound
+    const int obs_words = 4 * T;
+    const int ntb = BOUND ? a.lb_ntb : 0;
+    float* tab = lds_f + obs_words;  // [ntb][2][LB_Q] future-days bound
     Slot* ring_all = reinterpret_cast<Slot*>(lds_f + obs_words + 2 * LB_Q * ntb);
 
-    // observed series: log2(1 + O) for the log1p distance (accumulated in
-    // log2 units), or the count itself for the raw distance
-    for (int q = threadIdx.x; q < 3 * T; q += blockDim.x) {
-        const int32_t O = a.obs[q];
-        if (DIST == 0)
-            lds_f[q] = (float)(log1p((double)O) * 1.44269504088896340736);
-        else
-            lds_f[q] = __int_as_float(O);
-    }
-    if (DIST == 0 && ntb > 0) {
+    // observed rows (obs_row)
+    const uint32_t tab_at = lds_address(tab);
+    for (int q = threadIdx.x; q < T; q += blockDim.x)
+        reinterpret_cast<float4*>(lds_f)[q] =
+            obs_row<DIST>(a.obs[q], a.obs[T + q], a.obs[2 * T + q],
+                          tab_at + (uint32_t)sizeof(float) * (2 * LB_Q * ((q + 1) >> a.lb_sh)));
+    if (BOUND) {
         // b_s of R and D in float64, staged where the ring will live
         double* stage = reinterpret_cast<double*>(ring_all);
         for (int q = threadIdx.x; q < 2 * T; q += blockDim.x)
@@ -169,16 +169,18 @@ __global__ __launch_bounds__(1024 / SPL) void k_simulate_f32(SimArgs a)
     const float invP = 1.0f / (float)a.P;
     const float nc = noise_c(a.scale);
     const float dscale = DIST == 0 ? 0.693147180559945309417f : 1.0f;
-    const uint32_t wdom = a.domain << 4;
+    const uint32_t w1 = 256u | (a.domain << 4), wend = ((uint32_t)T << 8) | (a.domain << 4);
+    const uint32_t row1 = lds_address(lds_f);
+    const int32_t room = a.P - (a.A0 + a.R0 + a.D0);
 
-    // the ring holds one chunk: sample offsets 64 c + lane
+    // the ring holds one chunk: sample offsets cur_base + lane, of which
+    // cur_valid exist (fewer than 64 only in the last chunk)
+    int64_t cur_base = 0;
+    uint32_t cur_valid = 0;
     auto fill = [&](int64_t c) {
-        const int64_t k = (c << 6) + lane;
-        Slot& sl = ring[lane];
-        if (k < a.n)
-            fill_slot<PRIOR>(a, k, ps.u0, sl);
-        else
-            sl.k = a.n;
+        cur_base = c << 6;
+        cur_valid = (uint32_t)min(a.n - cur_base, (int64_t)64);
+        if ((uint32_t)lane < cur_valid) fill_slot<PRIOR>(a, cur_base + lane, ps.u0, ring[lane]);
     };
 
     // wave-uniform queue state, kept in scalar registers
@@ -186,112 +188,82 @@ __global__ __launch_bounds__(1024 / SPL) void k_simulate_f32(SimArgs a)
     uint32_t filled = 0xFFFFFFFFu; // chunk currently in the ring
     Lane L[SPL];
 #pragma unroll
-    for (int j = 0; j < SPL; ++j) L[j].t = 0;
-    uint32_t days_done = 0;
+    for (int j = 0; j < SPL; ++j) L[j].w = 0u;
+    uint64_t days_done = 0;        // of the whole wavefront
 
     while (true) {
-        // refill every idle slot from the wave queue, in queue order; a refill
-        // may span the end of one chunk and the start of the next
+        // refill every idle slot from the wave queue, in queue order, once at
+        // least refill_min lanes are idle; a refill may span the end of one
+        // chunk and the start of the next
+        uint64_t any = 0;
 #pragma unroll
         for (int j = 0; j < SPL; ++j) {
-            uint64_t m = __ballot(L[j].t == 0);
-            if (__popcll(m) < a.refill_min) continue;  // let a few more lanes finish first
-            while (m != 0ull && qb < Q) {
-                const uint32_t jc = qb >> 6;
-                if (jc != filled) {
-                    fill(wg + (int64_t)jc * nw);
-                    filled = jc;
-                }
-                const uint32_t avail = 64u - (qb & 63u);
-                const bool inm = (m >> lane) & 1ull;
-                // lanes of m below this one
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                const bool take = inm && rank < avail;
-                if (take) {
-                    const Slot sl = ring[(qb & 63u) + rank];
-                    if (!PRIOR && sl.k < a.n && sl.pad != 0) {
-                        a.dist[sl.k] = INFINITY;
-                        if (a.dist64) a.dist64[sl.k] = (double)INFINITY;
-                    } else if (sl.k < a.n) {
-                        Lane& l = L[j];
-                        l.r = RatesF{sl.a0, sl.al, sl.n, sl.be, sl.ga, sl.de, sl.bh};
-                        l.s.A = a.A0; l.s.R = a.R0; l.s.D = a.D0; l.s.Ru = 0;
-                        l.s.I = sl.i0;
-                        l.s.S = a.P - (a.A0 + a.R0 + a.D0) - sl.i0;
-                        l.ph.c1base = sl.c1base; l.ph.g3 = sl.g3; l.ph.h3 = sl.h3; l.ph.f3 = sl.f3;
-                        l.k = sl.k;
-                        l.t = 1;
-                        l.acc = 0.0f;
-                        l.comp = 0.0f;
+            uint64_t m = __ballot(L[j].w == 0u);
+            if (__popcll(m) >= a.refill_min) {
+                while (m != 0ull && qb < Q) {
+                    const uint32_t jc = qb >> 6;
+                    if (jc != filled) {
+                        fill(wg + (int64_t)jc * nw);
+                        filled = jc;
                     }
+                    const uint32_t off = qb & 63u, avail = 64u - off;
+                    const uint32_t rank = mask_rank(m);
+                    const uint64_t took = m & __ballot(rank < avail);
+                    if (in_mask(took) && off + rank < cur_valid) {
+                        const Slot sl = ring[off + rank];
+                        const int64_t k = cur_base + (int64_t)(off + rank);
+                        if (!PRIOR && sl.i0 < 0) {
+                            a.dist[k] = INFINITY;
+                            if (a.dist64) a.dist64[k] = (double)INFINITY;
+                        } else {
+                            Lane& l = L[j];
+                            l.r = RatesF{sl.a0, sl.al, sl.n, sl.be, sl.ga, sl.de, sl.bh};
+                            l.s = state_d(room, a.A0, a.R0, a.D0, sl.i0);
+                            l.ph.c1base = sl.c1base; l.ph.g3 = sl.g3; l.ph.h3 = sl.h3; l.ph.f3 = sl.f3;
+                            l.k = k;
+                            l.w = w1;
+                            l.p = row1;
+                            l.acc = 0.0f;
+                            l.comp = 0.0f;
+                        }
+                    }
+                    qb += (uint32_t)__popcll(took);
+                    m &= ~took;  // lanes still without a position
                 }
-                const uint32_t cnt = (uint32_t)__popcll(m);
-                qb = __builtin_amdgcn_readfirstlane(qb + (cnt < avail ? cnt : avail));
-                m = __ballot(inm && !take);  // lanes still without a position
+                m = __ballot(L[j].w == 0u);
             }
+            any |= ~m;
+            days_done += (uint64_t)__popcll(~m);
         }
-        bool any = false;
-#pragma unroll
-        for (int j = 0; j < SPL; ++j) any |= L[j].t != 0;
-        if (__ballot(any) == 0ull && qb >= Q) break;
+        if (any == 0ull) {
+            if (qb >= Q) break;
+            continue;
+        }
 
         // one day of every active slot
 #pragma unroll
         for (int j = 0; j < SPL; ++j) {
             Lane& l = L[j];
-            if (l.t == 0) continue;
-            const int t = l.t;
-            const uint4 w = l.ph.day(((uint32_t)t << 8) | wdom, ps.b1, a.key);
-            Noise32 z;
-            normals_f32(w, nc, z);
-            day_step_f32<NOISE>(l.s, l.r, invP, z);
-            const int32_t X[3] = {l.s.A, l.s.R, l.s.D};
-            float lx[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                float d;
-                if (DIST == 0) {
-                    lx[c] = log2p1_count_f32(X[c]);
-                    d = lx[c] - lds_f[c * T + t - 1];
-                } else {
-                    d = (float)(X[c] - __float_as_int(lds_f[c * T + t - 1]));
-                }
-                if (KAHAN) {
-                    const float y = fmaf(d, d, -l.comp);
-                    const float tt = l.acc + y;
-                    l.comp = (tt - l.acc) - y;
-                    l.acc = tt;
-                } else {
-                    l.acc = fmaf(d, d, l.acc);
-                }
-            }
-            float lb = 0.0f;
-            if (DIST == 0 && ntb > 0) {
-                // grid index rounded down, below the float32 error of lx
-                const float* row = tab + ((t >> a.lb_sh) * LB_Q);
-                const int qr = (int)fmaf(lx[1], 2.0f, -0x1p-12f);
-                const int qd = (int)fmaf(lx[2], 2.0f, -0x1p-12f);
-                lb = row[qr] + row[ntb * LB_Q + qd];
-            }
-            const bool exited = l.acc + lb > a.exit_f32;
-            if (exited || t == T) {
+            if (l.w == 0u) continue;
+            const float4 ob = lds_row(l.p);
+            const uint4 words = l.ph.day(l.w, ps.b1, a.key);
+            float lr, ld;
+            day_distance_f32<NOISE, DIST, KAHAN>(l.s, l.r, words, invP, nc, ob, l.acc, l.comp, lr, ld);
+            float sum = l.acc;
+            if (BOUND) sum += future_bound(__float_as_uint(ob.w), lr, ld);
+            const bool exited = sum > a.exit_f32;
+            uint32_t wn = l.w + 256u;
+            if (exited | (l.w == wend)) {
                 const float dd = exited ? INFINITY : finish_distance_f32(l.acc, dscale);
                 a.dist[l.k] = dd;
                 if (a.dist64) a.dist64[l.k] = (double)dd;
-                l.t = 0;
-                days_done += (uint32_t)t;
-            } else {
-                l.t = t + 1;
+                wn = 0u;
             }
+            l.w = wn;
+            l.p += (uint32_t)sizeof(float4);
         }
     }
-    if (a.days) {
-        uint64_t v = days_done;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) atomicAdd(a.days, (unsigned long long)v);
-    }
+    if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);
 }
 
 // ---------------------------------------------------------------------------
@@ -315,7 +287,7 @@ template <int NOISE, int DIST, bool PRIOR>
 __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
 {
 #pragma clang fp contract(off)
-    // Math64 | [3][T] | future-days bound [2][ntb][LB_Q] f32, then the space that builds it
+    // Math64 | [3][T] | future-days bound [ntb][2][LB_Q] f32, then the space that builds it
     extern __shared__ double lds_d[];
     Math64& tab = *reinterpret_cast<Math64*>(lds_d);
     double* lobs = lds_d + sizeof(Math64) / sizeof(double);
@@ -344,6 +316,7 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
     const double Pd = (double)a.P, rP = 1.0 / Pd, scale = (double)a.scale;
     const PhiloxSeries ps = philox_series(a.series, a.key);
     constexpr double LOG2E = 1.44269504088896340736;
+    const uint32_t lb_at = lds_address(lbt);
 
     int64_t qb = 0, k = 0;
     PhiloxDays ph{};
@@ -395,10 +368,8 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
             // margins: a sample it ends would have passed the exit bound
             float lb = 0.0f;
             if (DIST == 0 && ntb > 0) {
-                const float* row = lbt + (t >> a.lb_sh) * LB_Q;
-                const int qr = (int)fmaf((float)(lx[1] * LOG2E), 2.0f, -0x1p-12f);
-                const int qd = (int)fmaf((float)(lx[2] * LOG2E), 2.0f, -0x1p-12f);
-                lb = row[qr] + row[ntb * LB_Q + qd];
+                lb = future_bound(lb_at + (uint32_t)sizeof(float) * 2 * LB_Q * (uint32_t)(t >> a.lb_sh),
+                                  (float)(lx[1] * LOG2E), (float)(lx[2] * LOG2E));
             }
             const bool exited = acc > a.exit_f64 ||
                                 (lb > 0.0f && (float)(acc * (LOG2E * LOG2E)) + lb > a.exit_f32);
@@ -732,14 +703,34 @@ static inline unsigned grid_for(int64_t n) { return (unsigned)((n + SIM_BLOCK - 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Launch shape of the float32 refill kernel for the calling thread: samples
-// per lane, workgroup size and resident workgroups per CU (0 = default).
+// per lane, workgroup size and resident workgroups per CU. Until the thread
+// sets one (and again after it sets all three to 0) each kernel chooses its
+// own from the size of the launch.
 struct LaunchConfig {
     int spl = 1;
     int block = 512;
     int blocks_per_cu = 2;
     int refill_min = 8;
+    bool chosen = false;
 };
 static thread_local LaunchConfig g_launch;
+
+bool launch_shape_chosen() { return g_launch.chosen; }
+
+// Resident 512-thread workgroups per CU for a launch of n samples: more
+// wavefronts hide more latency, but every wavefront ends on a few trajectories
+// of its own, so with an early exit each should walk at least seven chunks of
+// 64 samples. Measured on the 3.3e8/T100 series, one / two / four workgroups
+// per CU: 1e6 samples 160 / 172 / 185 us, 1e7 samples 1013 / 908 / 872 us.
+// Without an exit (every trajectory ends on the same day) one chunk each is
+// enough: 1e6 samples of T = 49 250 / 220 / 206 us.
+static int refill_blocks_per_cu(int64_t n, bool exits)
+{
+    DeviceInfo info;
+    const int64_t num_cu = device_info(&info) == ABC_OK && info.num_cu > 0 ? info.num_cu : 256;
+    const int64_t per = ((n + 63) / 64) / (num_cu * (512 / 64) * (exits ? 7 : 1));
+    return per < 1 ? 1 : (per > 4 ? 4 : (int)per);
+}
 
 // Resident-grid size for the refill kernel: enough workgroups to fill every
 // CU several times over, never more than there are 64-sample chunks.
@@ -762,7 +753,7 @@ static size_t refill_lds_bytes(int T, int block, int lb_ntb)
     const size_t ring = sizeof(Slot) * 64 * (size_t)(block / 64);
     const size_t stage =
         lb_ntb > 0 ? sizeof(double) * (2 * (size_t)T + (size_t)LB_MAX_SEG * 2 * LB_Q) : 0;
-    return sizeof(float) * (size_t)((3 * T + 3) & ~3) + sizeof(float) * 2 * LB_Q * (size_t)lb_ntb +
+    return sizeof(float) * 4 * (size_t)T + sizeof(float) * 2 * LB_Q * (size_t)lb_ntb +
            (ring > stage ? ring : stage);
 }
 
@@ -772,16 +763,29 @@ static size_t max_lds_per_block()
     return device_info(&info) == ABC_OK && info.max_lds > 0 ? (size_t)info.max_lds : 65536;
 }
 
-template <int NOISE, int DIST, bool KAHAN, int SPL>
-static void launch_f32_spl(const SimArgs& a, bool prior, hipStream_t s)
+template <int NOISE, int DIST, bool KAHAN, int SPL, bool BOUND>
+static void launch_f32_bound(const SimArgs& a, bool prior, hipStream_t s)
 {
     const int block = g_launch.block;
     const size_t lds = refill_lds_bytes(a.T, block, a.lb_ntb);
-    const dim3 g(refill_grid(a.n, block, g_launch.blocks_per_cu)), b(block);
+    const int bpc = g_launch.chosen ? g_launch.blocks_per_cu : refill_blocks_per_cu(a.n, !isinf(a.exit_f32));
+    const dim3 g(refill_grid(a.n, block, bpc)), b(block);
     if (prior)
-        hipLaunchKernelGGL((k_simulate_f32<NOISE, DIST, KAHAN, true, SPL>), g, b, lds, s, a);
+        hipLaunchKernelGGL((k_simulate_f32<NOISE, DIST, KAHAN, true, SPL, BOUND>), g, b, lds, s, a);
     else
-        hipLaunchKernelGGL((k_simulate_f32<NOISE, DIST, KAHAN, false, SPL>), g, b, lds, s, a);
+        hipLaunchKernelGGL((k_simulate_f32<NOISE, DIST, KAHAN, false, SPL, BOUND>), g, b, lds, s, a);
+}
+
+template <int NOISE, int DIST, bool KAHAN, int SPL>
+static void launch_f32_spl(const SimArgs& a, bool prior, hipStream_t s)
+{
+    if constexpr (DIST == 0) {
+        if (a.lb_ntb > 0) {
+            launch_f32_bound<NOISE, DIST, KAHAN, SPL, true>(a, prior, s);
+            return;
+        }
+    }
+    launch_f32_bound<NOISE, DIST, KAHAN, SPL, false>(a, prior, s);
 }
 
 template <int NOISE, int DIST, bool KAHAN>
@@ -957,6 +961,7 @@ extern "C" abc_status abc_simulate_record(const abc_series* ser, const abc_model
 
 extern "C" abc_status abc_set_launch_config(int32_t spl, int32_t block, int32_t blocks_per_cu)
 {
+    const bool chosen = spl != 0 || block != 0 || blocks_per_cu != 0;
     if (spl == 0) spl = 1;
     if (block == 0) block = 512 / spl < 64 ? 64 : 512 / spl;
     if (blocks_per_cu == 0) blocks_per_cu = 2;
@@ -967,6 +972,7 @@ extern "C" abc_status abc_set_launch_config(int32_t spl, int32_t block, int32_t 
     g_launch.spl = spl;
     g_launch.block = block;
     g_launch.blocks_per_cu = blocks_per_cu;
+    g_launch.chosen = chosen;
     return ABC_OK;
 }
 
