@@ -352,9 +352,9 @@ typedef struct {
  * 0, 1, 2, ... as a prefix (theta drawn from `prior` on stream (seed, domain,
  * series[j].series)). Each round is planned on the device from the counts of
  * the rounds up to two before it, so consecutive rounds overlap (they
- * alternate between two streams of the call); a completion flag follows
- * every round and the host reads the flag of the round rounds_per_graph
- * (clamped to [2, 6]) rounds back. Which samples are simulated, and so every
+ * alternate between two streams of the call); every plan leaves a completion
+ * flag in pinned host memory and the host reads the flag of the plan
+ * rounds_per_graph (clamped to [2, 6]) rounds back. Which samples are simulated, and so every
  * output, does not depend on that setting. At the end the candidates inside the
  * band (eps (1 - band_w), eps (1 + band_w)] are decided in float64, and the
  * first `quota` accepted samples by index are written per series:

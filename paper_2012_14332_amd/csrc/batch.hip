@@ -12,7 +12,9 @@
 //                  sees the counts of rounds up to p - 2 only, so round p - 1 can
 //                  still run while it plans, and round p starts on the
 //                  workgroup slots round p - 1 frees at its end: the rounds
-//                  alternate between two streams and overlap their tails.
+//                  alternate between two streams, each plan on its round's
+//                  stream, and overlap their tails. A plan that finds every
+//                  series at its target says so in pinned host memory.
 //   k_batch_round  persistent grid: every wavefront walks a fixed share of
 //                  the round's 64-sample chunks with lane refill. Lanes carry
 //                  their own series (T, P, tolerance, stream words), and the
@@ -108,7 +110,7 @@ struct BatchArgs {
     const float* obs_table; // [obs_words]
     int64_t* cand_idx;      // [m][cand_cap]
     float* cand_dist;       // [m][cand_cap]
-    int32_t* flag_dev;      // 1 once no series needs more samples
+    int32_t* flag_host;     // pinned host memory: 1 once a plan finds no series in need of samples
     unsigned long long* days;
     float nc;               // -2 ln(2) s^2 of the Box-Muller radius
     float scale;
@@ -308,6 +310,7 @@ __global__ __launch_bounds__(BT_MAX_SERIES) void k_batch_plan(BatchArgs a)
         t->total_chunks = ctot;
         t->chunk0[n_active] = ctot;
         t->done = n_active == 0 ? 1 : 0;
+        __hip_atomic_store(a.flag_host, n_active == 0 ? 1 : 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -347,6 +350,8 @@ struct BLane {
     float acc;
 };
 
+// MIX: the learned proposal is in use; a compile-time switch so that the
+// prior-only round kernel does not carry the proposal's code and registers.
 template <int SPL, bool MIX>
 __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
 {
@@ -413,12 +418,12 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
             (void)batch_theta<MIX>(a, s, d, (uint64_t)i, th);
             const Theta tt = theta_from(th);
             const RatesF rr = rates_f32(tt);
+            PhiloxDays ph;
+            ph.begin((uint64_t)i, d.u0, a.key);
             const State s0 = init_state(tt.ka, d.P, d.A0, d.R0, d.D0);
             BSlot sl;
             sl.a0 = rr.a0; sl.al = rr.al; sl.n = rr.n; sl.be = rr.be;
             sl.ga = rr.ga; sl.de = rr.de; sl.bh = rr.bh; sl.i0 = s0.I;
-            PhiloxDays ph;
-            ph.begin((uint64_t)i, d.u0, a.key);
             sl.c1base = ph.c1base; sl.g3 = ph.g3; sl.h3 = ph.h3; sl.f3 = ph.f3;
             ring[lane] = sl;
         }
@@ -481,6 +486,9 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
             if (qb >= Q) break;
             continue;
         }
+        // the last trajectories of a wavefront's queue are what the next round
+        // but one waits for: they go before the next round's wavefronts
+        if (qb >= Q) __builtin_amdgcn_s_setprio(1);
 
 #pragma unroll
         for (int k = 0; k < SPL; ++k) {
@@ -517,20 +525,6 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
         }
     }
     if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);
-}
-
-// 1 once every series has reached its target of float32 accepts or used its
-// maximum
-__global__ __launch_bounds__(BT_MAX_SERIES) void k_batch_flag(BatchArgs a)
-{
-    __shared__ int open;
-    if (threadIdx.x == 0) open = 0;
-    __syncthreads();
-    const int s = threadIdx.x;
-    if (s < a.m && a.state[s].acc < a.state[s].target && a.state[s].next < a.max_samples)
-        atomicAdd(&open, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) *a.flag_dev = open == 0 ? 1 : 0;
 }
 
 // ----------------------------------------------------------------------------
@@ -941,6 +935,22 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     if (spl != 1 && spl != 2 && spl != 4 && spl != 8)
         return set_error(ABC_EUNSUPPORTED, "the batched round kernel is built for 1, 2, 4 or 8 "
                          "samples per lane, not %d", spl);
+    // A thread that has set no shape gets 256-thread workgroups, two to four per
+    // CU: 24 chunks of 64 samples per wavefront and round. Two rounds are in
+    // flight, so two workgroups already fill a SIMD's issue, and a round ends
+    // sooner with few wavefronts (its samples wait for less of each other's
+    // issue); long rounds want more in flight. 64 series of 1000 rows, ms at
+    // 256 threads x 2 / x 3 / x 4 per CU and at 512 x 2: rounds of 2^22 samples
+    // 24.8 / 24.9 / 25.9 / 27.3, of 2^25 22.5 / 21.1 / 20.7 / 20.9; with a learned
+    // proposal, at x 2 / x 4 and 512 x 2, 2^22 20.3 / 20.0 / 21.0, 2^24 19.3 / 17.4 / 18.1.
+    if (!launch_shape_chosen()) {
+        DeviceInfo di;
+        if ((rc = device_info(&di))) return rc;
+        const int64_t share = (int64_t)di.num_cu * 4 * 24;
+        const int64_t per = ((round_size + 63) / 64 + share - 1) / share;
+        block = 256;
+        bpc = per < 2 ? 2 : (per > 4 ? 4 : (int)per);
+    }
     const int32_t refill_min = abc_get_refill_min();
     const size_t lds = batch_lds_bytes(m, obs_words, block);
     DeviceInfo info;
@@ -986,7 +996,6 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     const size_t o_ptrs = carve.take(sizeof(const int32_t*) * m);
     const size_t o_cidx = carve.take(sizeof(int64_t) * (size_t)m * cand_cap);
     const size_t o_cdist = carve.take(sizeof(float) * (size_t)m * cand_cap);
-    const size_t o_flag = carve.take(sizeof(int32_t) * BT_EVR);
     const size_t o_days = carve.take(sizeof(unsigned long long));
     const size_t o_order = carve.take(sizeof(int32_t) * m);
     const size_t o_mixtab = carve.take(prop ? sizeof(MixTable) * m : 0);
@@ -998,7 +1007,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     char* base = static_cast<char*>(arena);
     struct View { void* p; } b_desc{base + o_desc}, b_state{base + o_state}, b_table{base + o_table},
         b_obs{base + o_obs}, b_ptrs{base + o_ptrs}, b_cidx{base + o_cidx}, b_cdist{base + o_cdist},
-        b_flag{base + o_flag}, b_days{base + o_days}, b_order{base + o_order}, b_mixtab{base + o_mixtab},
+        b_days{base + o_days}, b_order{base + o_order}, b_mixtab{base + o_mixtab},
         b_re{base + o_re}, b_bq{base + o_bq};
     int32_t* flag_host = nullptr;
     if ((rc = stream_pinned(user, sizeof(int32_t) * BT_EVR, reinterpret_cast<void**>(&flag_host)))) return rc;
@@ -1044,7 +1053,6 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     a.obs_table = reinterpret_cast<const float*>(b_obs.p);
     a.cand_idx = reinterpret_cast<int64_t*>(b_cidx.p);
     a.cand_dist = reinterpret_cast<float*>(b_cdist.p);
-    a.flag_dev = reinterpret_cast<int32_t*>(b_flag.p);
     a.days = reinterpret_cast<unsigned long long*>(b_days.p);
     a.nc = -1.38629436111989061883f * model->noise_scale * model->noise_scale;
     a.scale = model->noise_scale;
@@ -1070,40 +1078,34 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     ABC_HIP(hipMemsetAsync(b_days.p, 0, sizeof(unsigned long long), s));
     ABC_HIP(hipMemsetAsync(b_re.p, 0, sizeof(int32_t) * (3 * (size_t)m + 1), s));
 
-    // Rounds alternate between two streams; plan p runs on s after plan
-    // p - 1 and after round p - 2, round p after plan p, so round p - 1 can
-    // still be finishing its last trajectories while round p starts. A
-    // completion flag (every series at quota or at max_samples, from the
-    // counts of all finished samples) follows each round; the host reads the
-    // flag of round p - L (L = rounds_per_graph, at least 2) after enqueueing
-    // round p. A flag that says done was computed after round q finished,
-    // possibly during round q + 1, so the counts were done by the end of
-    // round q + 1 and plans from q + 3 on assign no samples: the rounds up to
-    // q + 2 are all the result depends on, and with L >= 2 they have been
-    // enqueued by then.
+    // Rounds alternate between two streams. Plan p runs on its round's stream,
+    // so after round p - 2, and waits for plan p - 1 on the other one, which
+    // has long run by then: between two rounds of a stream there is one short
+    // launch. (With the plans on a stream of their own, behind a flag kernel
+    // and a copy of the flag after each round, the gap was about 35 us of a
+    // 270 us round.) A plan that finds every series at its target, or at
+    // max_samples, assigns nothing, nor does any later one: the host reads the
+    // flag of plan p - L (L = rounds_per_graph) after enqueueing round p.
     hipStream_t rs[2] = {nullptr, nullptr};
     struct RoundStreams {
         hipStream_t* r;
         ~RoundStreams() { for (int k = 0; k < 2; ++k) if (r[k]) (void)hipStreamDestroy(r[k]); }
     } round_streams{rs};
     for (int k = 0; k < 2; ++k) ABC_HIP(hipStreamCreateWithFlags(&rs[k], hipStreamNonBlocking));
-    hipEvent_t ev_plan[BT_EVR] = {}, ev_round[BT_EVR] = {};
+    hipEvent_t ev_plan[BT_EVR] = {}, ev_end[2] = {};
     struct RoundEvents {
         hipEvent_t* a;
         hipEvent_t* b;
         ~RoundEvents() {
-            for (int k = 0; k < BT_EVR; ++k) {
+            for (int k = 0; k < BT_EVR; ++k)
                 if (a[k]) (void)hipEventDestroy(a[k]);
+            for (int k = 0; k < 2; ++k)
                 if (b[k]) (void)hipEventDestroy(b[k]);
-            }
         }
-    } round_events{ev_plan, ev_round};
-    for (int k = 0; k < BT_EVR; ++k) {
-        ABC_HIP(hipEventCreateWithFlags(&ev_plan[k], hipEventDisableTiming));
-        ABC_HIP(hipEventCreateWithFlags(&ev_round[k], hipEventDisableTiming));
-    }
+    } round_events{ev_plan, ev_end};
+    for (int k = 0; k < BT_EVR; ++k) ABC_HIP(hipEventCreateWithFlags(&ev_plan[k], hipEventDisableTiming));
+    for (int k = 0; k < 2; ++k) ABC_HIP(hipEventCreateWithFlags(&ev_end[k], hipEventDisableTiming));
     RoundTable* tables = reinterpret_cast<RoundTable*>(b_table.p);
-    int32_t* flags_dev = reinterpret_cast<int32_t*>(b_flag.p);
     for (int k = 0; k < BT_EVR; ++k) flag_host[k] = 0;
     const int L = rounds_per_graph < 2 ? 2 : (rounds_per_graph > BT_EVR - 2 ? BT_EVR - 2 : rounds_per_graph);
     const int64_t max_rounds =
@@ -1145,49 +1147,52 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     // adds samples in index order, and the last finalisation decides every
     // candidate, so the rows kept are still the first Q accepts.
     const int32_t margin = std::max(4, quota / 256);  // of every later target
-    int64_t rounds = 0, polls = 0, stop_at = -1, phase0 = 0, rechecked = 0;
+    int64_t rounds = 0, polls = 0, phase0 = 0, rechecked = 0;
+    bool stopped = false;
     int32_t phases = 0;
     std::vector<int64_t> cnt(m), used_h(m);
     std::vector<int32_t> rech(m);
     float rounds_ms = 0.0f;
     for (;;) {
         const int64_t round_cap = rounds + max_rounds;
-        while (rounds < round_cap && (stop_at < 0 || rounds <= stop_at)) {
+        // the rounds start after the set-up (or the finalisation) on s
+        ABC_HIP(hipEventRecord(ev, s));
+        for (int k = 0; k < 2; ++k) ABC_HIP(hipStreamWaitEvent(rs[k], ev, 0));
+        stopped = false;
+        while (rounds < round_cap && !stopped) {
             const int64_t p = rounds;
             const int e = (int)(p % BT_EVR);
             BatchArgs ap = a;
             ap.table = tables + (p & 1);
             ap.round = (int32_t)p;
-            ap.flag_dev = flags_dev + e;
-            if (p >= 2) ABC_HIP(hipStreamWaitEvent(s, ev_round[(p - 2) % BT_EVR], 0));
-            hipLaunchKernelGGL(k_batch_plan, dim3(1), dim3(BT_MAX_SERIES), 0, s, ap);
-            ABC_HIP(hipEventRecord(ev_plan[e], s));
+            ap.flag_host = flag_host + e;
             hipStream_t r = rs[p & 1];
-            ABC_HIP(hipStreamWaitEvent(r, ev_plan[e], 0));
+            if (p > phase0) ABC_HIP(hipStreamWaitEvent(r, ev_plan[(p - 1) % BT_EVR], 0));
+            hipLaunchKernelGGL(k_batch_plan, dim3(1), dim3(BT_MAX_SERIES), 0, r, ap);
+            ABC_HIP(hipEventRecord(ev_plan[e], r));
             switch (spl) {
             case 1: launch_round<1>(ap, grid, block, lds, r); break;
             case 2: launch_round<2>(ap, grid, block, lds, r); break;
             case 4: launch_round<4>(ap, grid, block, lds, r); break;
             case 8: launch_round<8>(ap, grid, block, lds, r); break;
             }
-            hipLaunchKernelGGL(k_batch_flag, dim3(1), dim3(BT_MAX_SERIES), 0, r, ap);
-            ABC_HIP(hipMemcpyAsync(flag_host + e, ap.flag_dev, sizeof(int32_t), hipMemcpyDeviceToHost, r));
-            ABC_HIP(hipEventRecord(ev_round[e], r));
             if ((rc = check_launch("k_batch round"))) return rc;
             ++rounds;
-            if (p >= phase0 + L && stop_at < 0) {
+            if (p >= phase0 + L) {
                 const int64_t q = p - L;
-                ABC_HIP(hipEventSynchronize(ev_round[q % BT_EVR]));
+                ABC_HIP(hipEventSynchronize(ev_plan[q % BT_EVR]));
                 ++polls;
-                if (flag_host[q % BT_EVR]) stop_at = q + 2;
+                stopped = __atomic_load_n(flag_host + q % BT_EVR, __ATOMIC_ACQUIRE) != 0;
             }
         }
-        // the last two rounds are on the two round streams
-        for (int64_t q = rounds - 2; q < rounds; ++q)
-            if (q >= 0) ABC_HIP(hipStreamWaitEvent(s, ev_round[q % BT_EVR], 0));
+        for (int k = 0; k < 2; ++k) {
+            ABC_HIP(hipEventRecord(ev_end[k], rs[k]));
+            ABC_HIP(hipStreamWaitEvent(s, ev_end[k], 0));
+        }
         ABC_HIP(hipEventRecord(t1, s));
         ABC_HIP(hipEventSynchronize(t1));
         ABC_HIP(hipEventElapsedTime(&rounds_ms, t0, t1));
+        if (rounds > 0) stopped = stopped || __atomic_load_n(flag_host + (rounds - 1) % BT_EVR, __ATOMIC_ACQUIRE) != 0;
 
         ABC_HIP(hipMemsetAsync(b_re.p, 0, sizeof(int32_t) * (2 * (size_t)m + 1), s));
         hipLaunchKernelGGL(k_band_collect, dim3((unsigned)m * COLLECT_GROUPS), dim3(256), 0, s, f);
@@ -1208,12 +1213,10 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
             overflow |= cnt[s2] < 0;
             short_q |= cnt[s2] >= 0 && cnt[s2] < quota && used_h[s2] < max_samples;
         }
-        const bool stopped = stop_at >= 0 && rounds > stop_at;
         if (overflow || !short_q || !stopped || phases >= BT_MAX_PHASES) break;
         hipLaunchKernelGGL(k_batch_retarget, dim3((m + 255) / 256), dim3(256), 0, s, a, out_count, margin);
         if ((rc = check_launch("k_batch_retarget"))) return rc;
         phase0 = rounds;
-        stop_at = -1;
     }
     hipLaunchKernelGGL(k_batch_moments, dim3(m), dim3(256), 0, s, out_theta, f.out_w, out_count,
                        quota, out_mean, out_cov);
@@ -1242,16 +1245,15 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
             return set_error(ABC_EOVERFLOW,
                              "series %d: %lld candidates exceed the capacity %d (float32 accepts %d of "
                              "target %d; folded: accepts %d, candidates %d, samples %lld of %lld; "
-                             "%lld rounds, stop %lld)",
+                             "%lld rounds)",
                              s2, (long long)-cnt[s2], cand_cap, st.acc, st.target, st.acc_f, st.cand_f,
-                             (long long)st.done, (long long)st.next, (long long)rounds,
-                             (long long)stop_at);
+                             (long long)st.done, (long long)st.next, (long long)rounds);
         }
         if (cnt[s2] < quota)
             return set_error(ABC_EOVERFLOW, "series %d: %lld of %d accepted within max_samples",
                              s2, (long long)cnt[s2], quota);
     }
-    if (stop_at < 0 && (rounds == 0 || !flag_host[(rounds - 1) % BT_EVR]))
+    if (!stopped)
         return set_error(ABC_EOVERFLOW, "stopped after %lld rounds before every quota was met",
                          (long long)rounds);
     return ABC_OK;

@@ -48,3 +48,26 @@ def test_eight_longest_series_in_one_launch(shape):
     for j, s in enumerate(sers):
         want = abc.simulate_distance(s, 100 + j, 5, series=j, eps_exit=30.0 if j % 2 else float("inf"))
         assert torch.equal(got[j], want)
+
+
+# round sizes at which the chosen number of workgroups per CU changes on 256 CUs
+@pytest.mark.parametrize("round_size", [3_145_728, 3_145_729, 4_718_593])
+@pytest.mark.parametrize("proposal", [False, True])
+def test_batch_own_shape_equals_a_set_shape(round_size, proposal):
+    import torch
+    from paper_2012_14332_amd import abc
+    sers = [_series(40_000_000 + j, 9 + 3 * j, j) for j in range(3)]
+    eps = [float(abc.simulate_distance(s, 40_000, 1).kthvalue(40).values) for s in sers]
+    kw = dict(max_samples=1 << 26)
+    if proposal:
+        rows = torch.randn((3, 136), generator=torch.Generator().manual_seed(2)) * 0.5
+        kw.update(mix=rows.cuda(), lam=0.4, inflate=2.0)
+    got = abc.batch_run(sers, eps, 4, 40, round_size=round_size, **kw)
+    try:
+        abc.set_launch_config(2, 512, 1)
+        want = abc.batch_run(sers, eps, 4, 40, round_size=round_size, **kw)
+    finally:
+        abc.set_launch_config(0, 0, 0)
+    for k in ("idx", "theta", "dist", "count", *(("w",) if proposal else ())):
+        assert torch.equal(got[k], want[k]), k
+    assert int(got["count"].min()) == 40
