@@ -124,13 +124,10 @@ struct BatchArgs {
 
 // theta of sample i of series s (desc d): the prior draw, or the learned
 // proposal's draw with its importance weight
-// (MIX: the learned proposal is in use; a compile-time switch so that the
-// prior-only round kernel does not carry the proposal's code and registers)
-template <bool MIX = true>
 __device__ __forceinline__ float batch_theta(const BatchArgs& a, int s, const SeriesDesc& d, uint64_t i,
                                              float th[8])
 {
-    if (MIX && a.mix) return proposal_draw(a.tables[s], a.prop, a.key, i, d.series_id, a.prop_domain, th);
+    if (a.mix) return proposal_draw(a.tables[s], a.prop, a.key, i, d.series_id, a.prop_domain, th);
     prior_draw(a.key, i, d.series_id, a.domain, a.lo, a.width, th);
     return 1.0f;
 }
@@ -415,7 +412,13 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
             const SeriesDesc& d = a.desc[s];
             const int64_t i = cur_first + lane;
             float th[8];
-            (void)batch_theta<MIX>(a, s, d, (uint64_t)i, th);
+            if (MIX && a.mix) {
+                float* out = reinterpret_cast<float*>(&ring[lane]);
+                proposal_theta(a.tables[s], a.prop, a.key, (uint64_t)i, d.series_id, a.prop_domain, out);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) th[k] = out[k];
+            } else
+                prior_draw(a.key, (uint64_t)i, d.series_id, a.domain, a.lo, a.width, th);
             const Theta tt = theta_from(th);
             const RatesF rr = rates_f32(tt);
             PhiloxDays ph;
@@ -942,7 +945,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     // issue); long rounds want more in flight. 64 series of 1000 rows, ms at
     // 256 threads x 2 / x 3 / x 4 per CU and at 512 x 2: rounds of 2^22 samples
     // 24.8 / 24.9 / 25.9 / 27.3, of 2^25 22.5 / 21.1 / 20.7 / 20.9; with a learned
-    // proposal, at x 2 / x 4 and 512 x 2, 2^22 20.3 / 20.0 / 21.0, 2^24 19.3 / 17.4 / 18.1.
+    // proposal, 2^22 17.7 / 17.2 / 17.5 / 18.4, 2^24 16.8 / 15.4 / 15.0 / 15.1.
     if (!launch_shape_chosen()) {
         DeviceInfo di;
         if ((rc = device_info(&di))) return rc;

@@ -43,6 +43,9 @@ struct MixTable {
     float logw[MIX_K];   // log of the renormalised component weights (-inf: dropped)
     float cum[MIX_K];    // running sums of the renormalised weights
     float logz[MIX_K];
+    // what a draw of (component, dimension) reads: p1, p2 - p1, mu and sigma
+    // with the sign of the interval (kind 1: +, else -)
+    float4 draw[MIX_K * MIX_D];
     int32_t empty;       // every component dropped: the proposal is the prior
 };
 
@@ -74,6 +77,7 @@ __device__ inline void mix_table_entry(const float* o, const ProposalBox& p, int
     t.mu[e] = mu;
     t.sig[e] = sg;
     t.lsig[e] = ls;
+    t.draw[e] = make_float4(t.p1[e], t.p2[e] - t.p1[e], mu, t.kind[e] == 1 ? sg : -sg);
 }
 
 // Truncated mass of entry e.
@@ -142,48 +146,59 @@ __device__ inline float mix_logq_trunc(const MixTable& t, const ProposalBox& p, 
 // component (inverse CDF of the renormalised weights); blocks 1-2 give eight
 // uniforms, used directly (prior) or through the inverse normal CDF of each
 // dimension's truncated interval (mixture), so every draw lies in the box
-// and no draw is repeated. Writes theta, returns prior / q.
+// and no draw is repeated. Writes theta; returns whether the draw is from the
+// prior because no component has mass in the box.
+//
+// One inverse per dimension serves all three kinds of interval: Phi(x) = p1 +
+// u (p2 - p1) with x below the mean and Q(y) = p1 - u (p1 - p2) in a tail have
+// the same argument, and only the sign differs, which the table holds with
+// sigma (a branch per kind made every wavefront run the inverse twice). The
+// dimensions go in two passes of four, a Philox block each, and are written as
+// they are found, so th may lie in LDS: all eight at once held 103 VGPRs in the
+// round kernel, a pass of four holds 73 and half the code. 64 series of 1000
+// rows with rounds of 2^22 / 2^24 samples: 20.2 / 17.4 ms with a branch per
+// kind, 20.4 / 17.7 with one inverse, 17.5 / 15.0 with two passes.
+__device__ inline bool proposal_theta(const MixTable& t, const ProposalBox& p, Key key, uint64_t i,
+                                      uint32_t series, uint32_t domain, float* th)
+{
+    const uint4 w0 = stream_words(key, i, series, ctr_word3(1, domain, 0));
+    const bool empty = t.empty != 0;
+    const bool prior = empty || (float)(w0.x >> 8) * 0x1p-24f < p.lambda;
+    const float u_c = (float)(w0.y >> 8) * 0x1p-24f * t.cum[MIX_K - 1];
+    int comp = MIX_K - 1;  // the first component with u_c < cum
+#pragma unroll
+    for (int c = MIX_K - 2; c >= 0; --c)
+        if (u_c < t.cum[c]) comp = c;
+    const float4* draw = t.draw + comp * MIX_D;
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+        const uint4 w = stream_words(key, i, series, ctr_word3(1, domain, 1 + h));
+        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+        float* out = th + 4 * h;
+        const float *lo = p.lo + 4 * h, *hi = p.hi + 4 * h, *tc = p.tc + 4 * h, *ts = p.ts + 4 * h;
+        if (prior) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) out[j] = fmaf(hi[j] - lo[j], (float)(ww[j] >> 8) * 0x1p-24f, lo[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 d = draw[4 * h + j];
+                const float u = ((float)(ww[j] >> 8) + 0.5f) * 0x1p-24f;  // (0, 1)
+                const float y = 1.41421356237309504880f * erfcinvf(2.0f * fmaf(u, d.y, d.x));
+                out[j] = fminf(fmaxf(fmaf(ts[j], fmaf(d.w, y, d.z), tc[j]), lo[j]), hi[j]);
+            }
+        }
+    }
+    return empty;
+}
+
+// The draw with its importance weight prior / q.
 __device__ inline float proposal_draw(const MixTable& t, const ProposalBox& p, Key key, uint64_t i,
                                       uint32_t series, uint32_t domain, float th[8])
 {
-    const uint4 w0 = stream_words(key, i, series, ctr_word3(1, domain, 0));
-    const uint4 w1 = stream_words(key, i, series, ctr_word3(1, domain, 1));
-    const uint4 w2 = stream_words(key, i, series, ctr_word3(1, domain, 2));
-    const uint32_t ww[8] = {w1.x, w1.y, w1.z, w1.w, w2.x, w2.y, w2.z, w2.w};
+    if (proposal_theta(t, p, key, i, series, domain, th)) return 1.0f;
     float logvol = 0.0f;
     for (int j = 0; j < 8; ++j) logvol += logf(p.hi[j] - p.lo[j]);
-    const float u_sel = (float)(w0.x >> 8) * 0x1p-24f;
-    if (t.empty) {  // no component has mass in the box: the proposal is the prior
-        for (int j = 0; j < 8; ++j)
-            th[j] = fmaf(p.hi[j] - p.lo[j], (float)(ww[j] >> 8) * 0x1p-24f, p.lo[j]);
-        return 1.0f;
-    }
-    if (u_sel < p.lambda) {
-        for (int j = 0; j < 8; ++j)
-            th[j] = fmaf(p.hi[j] - p.lo[j], (float)(ww[j] >> 8) * 0x1p-24f, p.lo[j]);
-    } else {
-        const float u_c = (float)(w0.y >> 8) * 0x1p-24f * t.cum[MIX_K - 1];
-        int comp = MIX_K - 1;
-        for (int c = 0; c < MIX_K; ++c)
-            if (u_c < t.cum[c]) {
-                comp = c;
-                break;
-            }
-        for (int j = 0; j < 8; ++j) {
-            const int e = comp * MIX_D + j;
-            const float u = ((float)(ww[j] >> 8) + 0.5f) * 0x1p-24f;  // (0, 1)
-            const float p1 = t.p1[e], p2 = t.p2[e];
-            float x;
-            if (t.kind[e] == 0) {          // Phi(x) = p1 + u (p2 - p1)
-                x = -1.41421356237309504880f * erfcinvf(2.0f * fmaf(u, p2 - p1, p1));
-            } else {                       // tail: Q(y) = p1 - u (p1 - p2), x = +-y
-                const float y = 1.41421356237309504880f * erfcinvf(2.0f * fmaf(-u, p1 - p2, p1));
-                x = t.kind[e] == 1 ? y : -y;
-            }
-            const float tt = fmaf(t.sig[e], x, t.mu[e]);
-            th[j] = fminf(fmaxf(fmaf(p.ts[j], tt, p.tc[j]), p.lo[j]), p.hi[j]);
-        }
-    }
     const float lq_mix = mix_logq_trunc(t, p, th);
     const float lq_prior = -logvol;
     float lq;
