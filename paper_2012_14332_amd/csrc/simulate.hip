@@ -654,6 +654,63 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
     }
 }
 
+// The float32 recording of few rows. With 64 rows per wavefront a thousand rows
+// are 16 wavefronts, each alone on its SIMD, and a day costs what one wavefront
+// can issue. The noise needs no state, so a workgroup takes 64 rows: three
+// wavefronts draw the noise of a window of days into LDS while the fourth walks
+// the window before it, which leaves it about a third of a day's instructions.
+// It is bound by that wavefront's issue and the chain of a day. 120 days of
+// 1000 rows: 37 -> 25 us.
+constexpr int RECORD_DAYS = 6;
+
+template <int NOISE>
+__global__ __launch_bounds__(256) void k_record_split(SimArgs a)
+{
+    __shared__ float4 zs[2][RECORD_DAYS][2][64];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t k = (int64_t)blockIdx.x * 64 + lane;
+    const bool live = k < a.n;
+    const uint64_t i = a.first + (uint64_t)k;
+    const int windows = (a.T + RECORD_DAYS - 1) / RECORD_DAYS;
+    const float invP = 1.0f / (float)a.P, nc = noise_c(a.scale);
+    RatesF r{};
+    State s{};
+    int32_t* out = a.traj + (int64_t)6 * (a.T + 1) * k;
+    if (wv == 0 && live) {
+        float thv[8];
+        load_or_draw_theta(a, false, k, i, thv);
+        const Theta th = theta_from(thv);
+        r = rates_f32(th);
+        s = init_state(th.ka, a.P, a.A0, a.R0, a.D0);
+        store_state(out, s);
+    }
+    for (int w = 0; w <= windows; ++w) {
+        if (wv > 0) {
+            if (w < windows)
+                for (int d = wv - 1; d < RECORD_DAYS; d += 3) {
+                    const uint4 words = stream_words(a.key, i, a.series, ctr_word3((uint32_t)(w * RECORD_DAYS + d + 1), a.domain, 0));
+                    Noise32 z;
+                    normals_f32(words, nc, z);
+                    zs[w & 1][d][0][lane] = make_float4(z.rr[0], z.rr[1], z.rr[2], z.tr[0]);
+                    zs[w & 1][d][1][lane] = make_float4(z.tr[1], z.tr[2], z.tr[3], z.tr[4]);
+                }
+        } else if (w > 0 && live) {
+            const int t0 = (w - 1) * RECORD_DAYS;
+            const int days = min(RECORD_DAYS, a.T - t0);
+            for (int d = 0; d < days; ++d) {
+                const float4 p = zs[(w - 1) & 1][d][0][lane], q = zs[(w - 1) & 1][d][1][lane];
+                Noise32 z;
+                z.rr[0] = p.x; z.rr[1] = p.y; z.rr[2] = p.z; z.tr[0] = p.w;
+                z.tr[1] = q.x; z.tr[2] = q.y; z.tr[3] = q.z; z.tr[4] = q.w;
+                day_step_f32<NOISE>(s, r, invP, z);
+                store_state(out + 6 * (t0 + d + 1), s);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------
 // prior sampling
 // ---------------------------------------------------------------------------
@@ -948,8 +1005,15 @@ extern "C" abc_status abc_simulate_record(const abc_series* ser, const abc_model
     const hipStream_t s = as_stream(stream);
     const bool f64 = (model->flags & ABC_FP64) != 0;
     const int noise = (model->flags & ABC_NOISE_LITERAL) ? 1 : 0;
-    const dim3 g(grid_for(n)), b(SIM_BLOCK);
-    if (f64) {
+    const dim3 g(grid_for(n)), b(SIM_BLOCK), gs((unsigned)((n + 63) / 64));
+    DeviceInfo info;
+    if ((rc = device_info(&info))) return rc;
+    // up to two workgroups per CU the split is faster (120 days of 16384 rows 28
+    // us against 43, of 32768 46 against 56), from four on it is not (65536: 83, 83)
+    if (!f64 && n <= (int64_t)64 * info.num_cu * 2) {
+        if (noise) hipLaunchKernelGGL((k_record_split<1>), gs, b, 0, s, a);
+        else hipLaunchKernelGGL((k_record_split<0>), gs, b, 0, s, a);
+    } else if (f64) {
         if (noise) hipLaunchKernelGGL((k_record<1, true>), g, b, 0, s, a);
         else hipLaunchKernelGGL((k_record<0, true>), g, b, 0, s, a);
     } else {
