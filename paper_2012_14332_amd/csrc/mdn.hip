@@ -1,6 +1,6 @@
 // Learned mixture-density proposal for rejection ABC: training pairs from the
 // simulator itself, a 96-256-256-136 GELU network trained with hand-written
-// BF16 MFMA GEMMs (FP32 accumulation) and Adam, and a defensive-mixture
+// BF16 MFMA kernels (FP32 accumulation) and Adam, and a defensive-mixture
 // proposal sampler with importance weights. Not part of the paper, whose
 // proposal is the prior (eq. 2); the prior stays both the fallback and the
 // reference for the learned posterior.
@@ -10,8 +10,8 @@
 // -> out = h2 W3 + b3 = (8 logits, 8x8 means, 8x8 log sd clamped to [-7, 3])
 // of a diagonal Gaussian mixture over theta standardised by the prior's mean
 // and sd. Loss: mean negative log-likelihood. Parameters are float32 master
-// copies [W1 96x256 | b1 | W2 256x256 | b2 | W3 256x136 | b3]; the GEMMs read
-// bfloat16 copies refreshed by the Adam kernel.
+// copies [W1 96x256 | b1 | W2 256x256 | b2 | W3 256x136 | b3]; the products read
+// bfloat16 copies refreshed by the Adam update.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -28,8 +28,19 @@ constexpr int NN_IN = 96, NN_H = 256, NN_K = 8, NN_D = 8, NN_OUT = 136;
 constexpr int64_t OFF_W1 = 0, OFF_B1 = OFF_W1 + NN_IN * NN_H, OFF_W2 = OFF_B1 + NN_H,
                   OFF_B2 = OFF_W2 + NN_H * NN_H, OFF_W3 = OFF_B2 + NN_H,
                   OFF_B3 = OFF_W3 + NN_H * NN_OUT, NN_PARAMS = OFF_B3 + NN_OUT;
-// the bf16 copies: every parameter, then W3's transpose W3T [136][256]
-constexpr int64_t OFF_W3T = NN_PARAMS, NN_PB = OFF_W3T + NN_H * NN_OUT;
+
+// The bf16 copies of the weights, one per product that reads them, in the order
+// in which v_mfma_f32_16x16x32_bf16 takes them: a fragment is 16 columns by 32
+// values of k, lane l holding column l & 15 at k = 8 (l >> 4) + 0..7, so a
+// wavefront reads a fragment as 1 KB of consecutive memory. Forward products
+// sum over a layer's inputs (F), the input gradients over its outputs (B). The
+// 136 outputs are padded with zeros to 144 columns and to 160 values of k.
+constexpr int FRAG = 64 * 8;  // elements of a fragment
+constexpr int NF_IN = NN_IN / 16, NF_H = NN_H / 16, NF_OUT = 9;  // fragments of columns
+constexpr int KF_IN = NN_IN / 32, KF_H = NN_H / 32, KF_OUT = 5;  // fragments of k
+constexpr int64_t PB_F1 = 0, PB_F2 = PB_F1 + NF_H * KF_IN * FRAG, PB_F3 = PB_F2 + NF_H * KF_H * FRAG,
+                  PB_B3 = PB_F3 + NF_OUT * KF_H * FRAG, PB_B2 = PB_B3 + NF_H * KF_OUT * FRAG,
+                  NN_PB = PB_B2 + NF_H * KF_H * FRAG;
 constexpr float LOGSIG_LO = -7.0f, LOGSIG_HI = 3.0f;
 static_assert(NN_K == MIX_K && NN_D == MIX_D && NN_OUT == MIX_OUT && LOGSIG_LO == MIX_LOGSIG_LO &&
                   LOGSIG_HI == MIX_LOGSIG_HI,
@@ -48,26 +59,35 @@ __device__ __forceinline__ bf16 f2bf(float x)
 
 __device__ __forceinline__ float bf2f(bf16 h) { return __uint_as_float((uint32_t)h << 16); }
 
-// the bf16 copy of parameter e, and of its W3T entry for W3
-__device__ __forceinline__ void put_bf16(bf16* pb, int64_t e, float p)
+// element (column n, k) of an operand with kf fragments of k per 16 columns
+__device__ __forceinline__ int frag_pos(int n, int k, int kf)
+{
+    return (((n >> 4) * kf + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
+// the bf16 copies of parameter e (biases have none)
+__device__ __forceinline__ void put_bf16(bf16* pb, int e, float p)
 {
     const bf16 h = f2bf(p);
-    pb[e] = h;
-    if (e >= OFF_W3 && e < OFF_B3) {
-        const int64_t q = e - OFF_W3;  // W3 [256][136]: q = k 136 + c
-        pb[OFF_W3T + (q % NN_OUT) * NN_H + q / NN_OUT] = h;
+    if (e < OFF_B1) {
+        pb[PB_F1 + frag_pos(e % NN_H, e / NN_H, KF_IN)] = h;
+    } else if (e >= OFF_W2 && e < OFF_B2) {
+        const int q = e - (int)OFF_W2, i = q / NN_H, o = q % NN_H;
+        pb[PB_F2 + frag_pos(o, i, KF_H)] = h;
+        pb[PB_B2 + frag_pos(i, o, KF_H)] = h;
+    } else if (e >= OFF_W3 && e < OFF_B3) {
+        const int q = e - (int)OFF_W3, i = q / NN_OUT, o = q % NN_OUT;
+        pb[PB_F3 + frag_pos(o, i, KF_H)] = h;
+        pb[PB_B3 + frag_pos(i, o, KF_OUT)] = h;
     }
 }
 
-__device__ __forceinline__ float gelu_f(float z)
+// gelu(z) = z (1 + erf(z / sqrt 2)) / 2, and its derivative from the same erf
+__device__ __forceinline__ float gelu_f(float z, float& grad)
 {
-    return 0.5f * z * (1.0f + erff(z * 0.70710678118654752440f));
-}
-
-__device__ __forceinline__ float gelu_grad_f(float z)
-{
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752440f)) +
-           z * expf(-0.5f * z * z) * 0.39894228040143267794f;
+    const float e = 1.0f + erff(z * 0.70710678118654752440f);
+    grad = 0.5f * e + z * expf(-0.5f * z * z) * 0.39894228040143267794f;
+    return 0.5f * z * e;
 }
 
 // ----------------------------------------------------------------------------
@@ -363,335 +383,81 @@ __global__ __launch_bounds__(64) void k_colstats(const float* x, int64_t n, cons
 }
 
 // ----------------------------------------------------------------------------
-// batch rows: with a step counter, batch row b of training step st is dataset
-// row (a_e j + c_e) mod n of epoch e's affine permutation (e = st / steps per
-// epoch, j = (st mod steps per epoch) batch + b); without one, row b itself.
-// Features are standardised per column, (x - mean) / sd, and theta by the
-// prior's centre and sd, as they are read.
+// batch rows: row b of a training step is dataset row (mul (j0 + b) + add) mod n
+// of its epoch's affine permutation, j0 = (step mod steps per epoch) batch;
+// elsewhere row b itself. Features are standardised per column, (x - mean) / sd,
+// and theta by the prior's centre and sd, as they are read.
 // ----------------------------------------------------------------------------
 struct RowMap {
     const float* features;   // [n][96] raw features
     const float* theta;      // [n][8] or null
-    int64_t n;
-    int batch, steps_per_epoch;
-    const int64_t* perm_ab;  // [epochs][2]
-    const int32_t* step;     // device step counter, or null
+    int64_t n, mul, add, j0;
+    double inv_n;
     const float* fmean;
     const float* fsd;
     float tc[8], ts[8];
 };
 
-__device__ __forceinline__ int64_t map_row(const RowMap& r, int st, int b)
+__device__ __forceinline__ int64_t map_row(const RowMap& r, int b)
 {
-    if (!r.step) return b;
-    const int e = st / r.steps_per_epoch;
-    const int64_t j = (int64_t)(st % r.steps_per_epoch) * r.batch + b;
-    return (r.perm_ab[2 * e] * j + r.perm_ab[2 * e + 1]) % r.n;  // a, j < n < 2^31: no overflow
+    // mul and j0 + b are below n < 2^31: no overflow, and a quotient below 2^31,
+    // which the product with 1 / n misses by one at most
+    const int64_t x = r.mul * (r.j0 + b) + r.add;
+    int64_t m = x - (int64_t)((double)x * r.inv_n) * r.n;
+    if (m < 0) m += r.n;
+    if (m >= r.n) m -= r.n;
+    return m;
 }
-
-// batch row b of step st, assembled by 128 threads (t = 0..127): standardised
-// features to X [batch][96] as bf16, standardised theta to T [batch][8]
-__device__ __forceinline__ void gather_row(const RowMap& rm, int st, int b, int t, bf16* X, float* T)
-{
-    const int64_t row = map_row(rm, st, b);
-    if (t < NN_IN) X[(int64_t)b * NN_IN + t] = f2bf((rm.features[row * NN_IN + t] - rm.fmean[t]) / rm.fsd[t]);
-    if (rm.theta && t < NN_D) T[(int64_t)b * NN_D + t] = (rm.theta[row * NN_D + t] - rm.tc[t]) / rm.ts[t];
-}
-
-// one workgroup of 128 threads per batch row, at the counter's step; clears
-// loss_acc (nullable) for the batch's loss sum
-__global__ __launch_bounds__(128) void k_gather(RowMap rm, bf16* X, float* T, float* loss_acc)
-{
-    if (loss_acc && blockIdx.x == 0 && threadIdx.x == 0) *loss_acc = 0.0f;
-    gather_row(rm, rm.step ? *rm.step : 0, blockIdx.x, threadIdx.x, X, T);
-}
-
-// ----------------------------------------------------------------------------
-// BF16 MFMA GEMM: C[M][N] = op(A)[M][K] op(B)[K][N], float32 accumulation.
-// op(A)[m][k] = A[m lda + k] (TA = false) or A[k lda + m] (TA = true);
-// op(B)[k][n] = B[k ldb + n] (TB = false) or B[n ldb + k] (TB = true).
-// 64x64 workgroup tile, 4 wavefronts of 32x32, v_mfma_f32_16x16x32_bf16
-// fragments, K staged through LDS in tiles of 64. Epilogues:
-//   EPI_STORE    C (float32), optional + bias[n]
-//   EPI_GELU     Z = acc + bias -> C (float32), H = gelu(Z) as bf16
-//   EPI_DGELU    acc * gelu'(Zin) -> H (bf16; Zin has H's row stride)
-// grid.z splits K into equal ranges; split z writes C + z * split_stride.
-// ----------------------------------------------------------------------------
-constexpr int EPI_STORE = 0, EPI_GELU = 1, EPI_DGELU = 2;
-constexpr int G_BM = 64, G_BN = 64, G_BK = 64, G_LD = G_BK + 8;
-constexpr int G_NT = 4, G_KMAX = G_NT * G_BK;  // K range of one workgroup: at most 4 tiles
-// the products that are not split over K (forward, input gradients) reduce
-// over a layer width
-static_assert(NN_IN <= G_KMAX && NN_H <= G_KMAX && NN_OUT <= G_KMAX, "layer widths fit one K range");
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
-
-struct GemmArgs {
-    int M, N, K;
-    const bf16* A;
-    int lda;
-    const bf16* B;
-    int ldb;
-    float* C;
-    int ldc;
-    int64_t split_stride;
-    int k_per_split;
-    const float* bias;
-    bf16* H;
-    int ldh;
-    const float* Zin;
-    float* cs;  // EPI_DGELU: column-sum partials [row tiles][N], or null
-    int gx, gy;          // tile grid (columns, rows); grid.z = splits
-    int32_t* step_inc;   // non-null: tile (0, 0, 0) advances this counter by one
-};
-
-// Staging of one K tile (BK = 64) into registers, then LDS. Each thread holds
-// G_NV = 2 eight-element vectors of A and of B per tile; vector v = tid + 256 h.
-// Where K is contiguous in memory (A untransposed, B transposed) vector v is
-// row v / 8, k = 8 (v % 8); where rows are contiguous it is k = v / 8, rows
-// 8 (v % 8) + 0..7. VEC: every operand row, column count and K range is a
-// multiple of 8 elements and 16-byte aligned, so a vector is one global load;
-// otherwise it is eight scalar loads of the same elements.
+typedef unsigned short us4 __attribute__((ext_vector_type(4)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-constexpr int G_NV = G_BM * G_BK / 8 / 256;
-
-template <bool TA, bool TB, bool VEC>
-struct TileRegs {
-    us8 a[G_NV], b[G_NV];
-
-    // element (r, k) of the tile for a K-contiguous (KC) or row-contiguous operand
-    template <bool KC>
-    __device__ static __forceinline__ void vec_pos(int v, int& r, int& k)
-    {
-        if (KC) { r = v >> 3; k = (v & 7) * 8; }
-        else { k = v >> 3; r = (v & 7) * 8; }
-    }
-
-    template <bool KC>
-    __device__ static __forceinline__ us8 load_vec(const bf16* X, int ld, int rows, int r, int k, int kend)
-    {
-        us8 out = {0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (VEC) {
-            if (r < rows && k < kend)
-                out = KC ? *reinterpret_cast<const us8*>(X + (int64_t)r * ld + k)
-                         : *reinterpret_cast<const us8*>(X + (int64_t)k * ld + r);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int rr = KC ? r : r + q, kk = KC ? k + q : k;
-                if (rr < rows && kk < kend)
-                    out[q] = KC ? reinterpret_cast<const unsigned short*>(X)[(int64_t)rr * ld + kk]
-                                : reinterpret_cast<const unsigned short*>(X)[(int64_t)kk * ld + rr];
-            }
-        }
-        return out;
-    }
-
-    __device__ __forceinline__ void load(const GemmArgs& g, int tid, int m0, int n0, int k0, int kend)
-    {
-#pragma unroll
-        for (int h = 0; h < G_NV; ++h) {
-            const int v = tid + 256 * h;
-            int r, k;
-            vec_pos<!TA>(v, r, k);
-            a[h] = load_vec<!TA>(g.A, g.lda, g.M, m0 + r, k0 + k, kend);
-            vec_pos<TB>(v, r, k);
-            b[h] = load_vec<TB>(g.B, g.ldb, g.N, n0 + r, k0 + k, kend);
-        }
-    }
-
-    template <bool KC>
-    __device__ static __forceinline__ void store_vec(bf16 (*S)[G_LD], int v, const us8& x)
-    {
-        int r, k;
-        vec_pos<KC>(v, r, k);
-        if (KC) {
-            *reinterpret_cast<us8*>(&S[r][k]) = x;
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) reinterpret_cast<unsigned short*>(&S[r + q][k])[0] = x[q];
-        }
-    }
-
-    __device__ __forceinline__ void store(bf16 (*As)[G_LD], bf16 (*Bs)[G_LD], int tid) const
-    {
-#pragma unroll
-        for (int h = 0; h < G_NV; ++h) {
-            store_vec<!TA>(As, tid + 256 * h, a[h]);
-            store_vec<TB>(Bs, tid + 256 * h, b[h]);
-        }
-    }
-};
-
-// One 64 x 64 output tile (bx, by) of K split bz: four wavefronts of 32 x 32,
-// K tiles of 64 (two MFMA steps) on gfx950's v_mfma_f32_16x16x32_bf16: lane l
-// supplies row (l & 15) of A and column (l & 15) of B at k = 8 (l >> 4) + 0..7,
-// one 16-byte LDS read per operand fragment, and receives C[4 (l >> 4) + r][l & 15].
-// The next K tile is loaded into registers while the current one is
-// multiplied. With EPI_DGELU and cs != null, tile (bx, by) also writes the
-// float32 column sums of its 64 output rows to cs[by][n] (the bias gradient's
-// partials).
-template <bool TA, bool TB, int EPI, bool VEC>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz, bf16 (*Ab)[G_BM][G_LD],
-                                          bf16 (*Bb)[G_BN][G_LD], float (*cs_sh)[G_BN])
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = by * G_BM, n0 = bx * G_BN;
-    const int kbeg = bz * g.k_per_split;
-    int kend = kbeg + g.k_per_split;
-    if (kend > g.K) kend = g.K;
-    const int wy = wave >> 1, wx = wave & 1;
-    float4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-    if (g.step_inc && bx == 0 && by == 0 && bz == 0 && tid == 0) *g.step_inc += 1;
-    // every K tile of the range is requested before the first is used: one
-    // memory round trip per workgroup instead of one per tile
-    TileRegs<TA, TB, VEC> regs[G_NT];
-#pragma unroll
-    for (int t = 0; t < G_NT; ++t) regs[t].load(g, tid, m0, n0, kbeg + t * G_BK, kend);
-    // the epilogue's bias and (EPI_DGELU) Zin values are requested with the operands
-    float bias[2] = {0.0f, 0.0f};
-    if (EPI != EPI_DGELU && g.bias) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wx * 32 + j * 16 + (lane & 15);
-            bias[j] = n < g.N ? g.bias[n] : 0.0f;
-        }
-    }
-    float zin[2][2][4];
-    if (EPI == EPI_DGELU) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = m0 + wy * 32 + i * 16 + 4 * (lane >> 4) + r;
-                    const int n = n0 + wx * 32 + j * 16 + (lane & 15);
-                    zin[i][j][r] = (m < g.M && n < g.N) ? g.Zin[(int64_t)m * g.ldh + n] : 0.0f;
-                }
-    }
-#pragma unroll
-    for (int t = 0; t < G_NT; ++t) {
-        if (kbeg + t * G_BK >= kend) break;  // uniform
-        // two LDS buffers: the barrier after this store also orders every
-        // wavefront's reads of buffer t & 1 two tiles ago before it
-        bf16 (*As)[G_LD] = Ab[t & 1];
-        bf16 (*Bs)[G_LD] = Bb[t & 1];
-        regs[t].store(As, Bs, tid);
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < G_BK; kk += 32) {
-            const int kq = kk + 8 * (lane >> 4);
-            bf16x8 a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                a[i] = *reinterpret_cast<const bf16x8*>(&As[wy * 32 + i * 16 + (lane & 15)][kq]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                b[j] = *reinterpret_cast<const bf16x8*>(&Bs[wx * 32 + j * 16 + (lane & 15)][kq]);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    float* C = g.C + (int64_t)bz * g.split_stride;
-    float csum[2] = {0.0f, 0.0f};  // this lane's column sums (j = 0, 1) over its rows
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wy * 32 + i * 16 + 4 * (lane >> 4) + r;
-                const int n = n0 + wx * 32 + j * 16 + (lane & 15);
-                if (m >= g.M || n >= g.N) continue;
-                float v = acc[i][j][r];
-                if (EPI == EPI_STORE) {
-                    v += bias[j];
-                    C[(int64_t)m * g.ldc + n] = v;
-                } else if (EPI == EPI_GELU) {
-                    v += bias[j];
-                    C[(int64_t)m * g.ldc + n] = v;
-                    g.H[(int64_t)m * g.ldh + n] = f2bf(gelu_f(v));
-                } else {
-                    v *= gelu_grad_f(zin[i][j][r]);
-                    g.H[(int64_t)m * g.ldh + n] = f2bf(v);
-                    csum[j] += v;
-                }
-            }
-    if (EPI == EPI_DGELU && g.cs) {
-        // rows of the lane groups l >> 4 (fixed order), then the two wy halves
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            float v = csum[j];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            csum[j] = v;
-        }
-        if (lane < 16) {
-            cs_sh[wy][wx * 32 + lane] = csum[0];
-            cs_sh[wy][wx * 32 + 16 + lane] = csum[1];
-        }
-        __syncthreads();
-        if (tid < G_BN && n0 + tid < g.N)
-            g.cs[(int64_t)by * g.N + n0 + tid] = cs_sh[0][tid] + cs_sh[1][tid];
-    }
-}
-
-template <bool TA, bool TB, int EPI, bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g)
-{
-    __shared__ __align__(16) bf16 As[2][G_BM][G_LD];
-    __shared__ __align__(16) bf16 Bs[2][G_BN][G_LD];  // [n][k]
-    __shared__ float cs_sh[2][G_BN];
-    gemm_tile<TA, TB, EPI, VEC>(g, blockIdx.x, blockIdx.y, blockIdx.z, As, Bs, cs_sh);
-}
-
-// Two independent products in one launch (both VEC): workgroups [0, nb1) take
-// the tiles of the first in (x, y, z) order, the rest those of the second.
-template <bool TA1, bool TB1, int EPI1, bool TA2, bool TB2, int EPI2>
-__global__ __launch_bounds__(256) void k_gemm_pair(GemmArgs g1, GemmArgs g2, int nb1)
-{
-    __shared__ __align__(16) bf16 As[2][G_BM][G_LD];
-    __shared__ __align__(16) bf16 Bs[2][G_BN][G_LD];
-    __shared__ float cs_sh[2][G_BN];
-    int b = blockIdx.x;
-    if (b < nb1) {
-        gemm_tile<TA1, TB1, EPI1, true>(g1, b % g1.gx, (b / g1.gx) % g1.gy, b / (g1.gx * g1.gy), As, Bs, cs_sh);
-    } else {
-        b -= nb1;
-        gemm_tile<TA2, TB2, EPI2, true>(g2, b % g2.gx, (b / g2.gx) % g2.gy, b / (g2.gx * g2.gy), As, Bs, cs_sh);
-    }
-}
 
 // ----------------------------------------------------------------------------
-// Output layer and loss in one pass: out = h2 W3 + b3 for 64 rows per
-// workgroup, kept in LDS, then the mixture negative log-likelihood of each
-// row and its gradient w.r.t. the 136 outputs (divided by the batch size, as
-// bf16: the operand of both products that consume it).
-// The loss (sum of NLL / batch) is accumulated atomically.
+// Everything a step computes per row, in one kernel: the batch row, the three
+// layers, the mixture negative log-likelihood with its gradient w.r.t. the
+// outputs, and the gradients w.r.t. both hidden layers (forward only: the
+// outputs). 16 rows per workgroup stay in LDS and registers from the features
+// to dZ1; sixteen wavefronts split the columns of a layer, so each weight
+// fragment is read by one wavefront, straight from memory into the registers of
+// its product and requested a layer ahead.
+//
+// v_mfma_f32_16x16x32_bf16: lane l supplies row (l & 15) of A and column (l & 15)
+// of B at k = 8 (l >> 4) + 0..7 and receives C[4 (l >> 4) + r][l & 15]. Products
+// sum over k in ascending steps of 32.
+//
+// What the weight gradients read (they sum over rows) is written as fragments
+// too, 16 columns by 32 rows: this workgroup's 16 rows are half a fragment. Rows
+// past the batch are zeros there.
+//
+// What bounds it: the weights of all products, 456 KB per workgroup from the L2
+// (3 us at 64 B a clock), and the error functions and exponentials of two layers
+// (4 us of issue on a full chip at a batch of 4096); 16 rows, not 32 or 64, so
+// that such a batch is a workgroup for each of the 256 CUs, and sixteen
+// wavefronts rather than eight because the error functions branch and their
+// chains want company (20 us then). 18 us at a batch of 4096, 13 at 64; with the
+// weight gradients 31 us a step, where seven kernels with the activations in
+// memory between them took 68.
 // ----------------------------------------------------------------------------
-// Product: the workgroup's 64 rows of h2 and all of W3 (as its bf16
-// transpose W3T [136][256], K contiguous) are loaded in one round trip and
-// staged in LDS; wavefront w multiplies rows 16 w..16 w + 15 by the 9 column
-// fragments (136 columns, padded to 144 with zeros) on
-// v_mfma_f32_16x16x32_bf16 and writes them, plus b3, to its own LDS rows.
-// Loss: 8 rows at a time per wavefront, lane 8 r + k holding row r's mixture
-// component k (its logit, 8 means, 8 log sds, and the row's 8 targets), so
-// the per-row sums over components are 8-lane shuffles and no lane repeats
-// another's transcendentals. cs != null: the workgroup also writes the
-// float32 column sums of its rows' gradient, cs[blockIdx][136] (the output
-// bias's gradient partials).
-constexpr int OL_ROWS = 64, OL_WAVES = 4, OL_LD = NN_H + 8, OL_NP = 144, OL_OLD = NN_OUT + 4;
+constexpr int R_ROWS = 16, R_WAVES = 16, R_BLOCK = 64 * R_WAVES;
+constexpr int R_LX = NN_IN + 8, R_LH = NN_H + 8, R_LO = NN_OUT + 4, R_LD = 32 * KF_OUT + 8;
+static_assert(NF_H == R_WAVES && NF_OUT <= R_WAVES, "one fragment of columns a wavefront");
 static_assert(NN_K == 8 && NN_D == 8 && NN_OUT == 136 && NN_H == 256, "output layer layout");
+
+struct RowArgs {
+    RowMap rm;
+    int n;                // rows of the batch
+    const bf16* pb;
+    const float *b1, *b2, *b3;
+    float* out;           // forward only: [n][136]
+    bf16 *X, *H1, *H2, *dOUT, *dZ2, *dZ1;  // fragments, [blocks of 32 rows][columns / 16]
+    // Bias gradients: what their sums in the order of 64-row tiles need. Of 32
+    // rows, the sums over rows 4 g + 0..3 of the first 16 rows [4][256], then the
+    // second 16 rows themselves [16][256]; of the outputs, the sums over 16 rows.
+    float *cs1, *cs2, *cs3;
+    float* loss;          // the batch's mean NLL is added here (its value only)
+};
 
 __device__ __forceinline__ float sum8(float v)  // over the 8 lanes of a row
 {
@@ -717,267 +483,471 @@ __device__ __forceinline__ float sum_rows(float v)  // over the 8 rows (lane bit
     return v;
 }
 
-// Orders one wavefront's LDS writes before its lanes read what other lanes
-// wrote: a wavefront-scope fence pair around a wave barrier.
-__device__ __forceinline__ void wave_lds_sync()
+// fragments nf KF .. nf KF + KF - 1 of an operand, this lane's 16 bytes of each
+template <int KF>
+__device__ __forceinline__ void load_frags(us8 (&w)[KF], const bf16* base, int nf, int lane)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const us8* p = reinterpret_cast<const us8*>(base) + (nf * KF) * 64 + lane;
+#pragma unroll
+    for (int k = 0; k < KF; ++k) w[k] = p[k * 64];
 }
 
-__global__ __launch_bounds__(64 * OL_WAVES) void k_out_loss(const bf16* H2, const bf16* W3T, const float* b3,
-                                                          const float* T, int n, bf16* dout_b,
-                                                          float* loss_acc, const int32_t* step,
-                                                          float* loss_log, float* cs)
+// one 16 x 16 tile: A from LDS (16 rows of LD elements), B fragments in registers
+template <int KF, int LD>
+__device__ __forceinline__ float4_t tile(const bf16 (&A)[R_ROWS][LD], const us8 (&w)[KF], int lane, float4_t acc)
 {
-    __shared__ __align__(16) bf16 As[OL_ROWS][OL_LD];
-    __shared__ __align__(16) bf16 Bs[OL_NP][OL_LD];    // [n][k]
-    __shared__ __align__(16) float Os[OL_ROWS][OL_OLD];
-    __shared__ float red[OL_WAVES];
-    __shared__ float csh[OL_WAVES][NN_OUT];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int m0 = blockIdx.x * OL_ROWS;
-    constexpr int KV = NN_H / 8;                              // 8-element vectors per row
-    constexpr int NA = OL_ROWS * KV / 256, NB = NN_OUT * KV / 256;  // 8 and 17 per thread
-    static_assert(OL_ROWS * KV % 256 == 0 && NN_OUT * KV % 256 == 0, "whole vectors per thread");
-    const us8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    us8 va[NA], vb[NB];
 #pragma unroll
-    for (int h = 0; h < NA; ++h) {
-        const int v = tid + 256 * h, r = v / KV, kv = v % KV;
-        va[h] = m0 + r < n ? *reinterpret_cast<const us8*>(H2 + (int64_t)(m0 + r) * NN_H + kv * 8) : zero;
+    for (int k = 0; k < KF; ++k) {
+        const us8 x = *reinterpret_cast<const us8*>(&A[lane & 15][32 * k + 8 * (lane >> 4)]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w[k]),
+                                                      acc, 0, 0, 0);
     }
-#pragma unroll
-    for (int h = 0; h < NB; ++h) {
-        const int v = tid + 256 * h;
-        vb[h] = *reinterpret_cast<const us8*>(W3T + (int64_t)(v / KV) * NN_H + (v % KV) * 8);
-    }
-    // the epilogue's biases and the loss's targets are requested with the operands
-    float bias[OL_NP / 16];
-#pragma unroll
-    for (int f = 0; f < OL_NP / 16; ++f) {
-        const int c = 16 * f + (lane & 15);
-        bias[f] = c < NN_OUT ? b3[c] : 0.0f;
-    }
-    const int k = lane & 7;
-    float4 tv[2][2];
-#pragma unroll
-    for (int grp = 0; grp < 2; ++grp) {
-        const int row = m0 + 16 * wv + 8 * grp + (lane >> 3);
-        const float4* t4 = reinterpret_cast<const float4*>(T + (int64_t)(row < n ? row : 0) * NN_D);
-        tv[grp][0] = t4[0];
-        tv[grp][1] = t4[1];
-    }
-#pragma unroll
-    for (int h = 0; h < NA; ++h) {
-        const int v = tid + 256 * h;
-        *reinterpret_cast<us8*>(&As[v / KV][(v % KV) * 8]) = va[h];
-    }
-#pragma unroll
-    for (int h = 0; h < NB; ++h) {
-        const int v = tid + 256 * h;
-        *reinterpret_cast<us8*>(&Bs[v / KV][(v % KV) * 8]) = vb[h];
-    }
-    static_assert((OL_NP - NN_OUT) * KV == 256, "one padding vector per thread");
-    *reinterpret_cast<us8*>(&Bs[NN_OUT + tid / KV][(tid % KV) * 8]) = zero;
-    __syncthreads();
-    float4_t acc[OL_NP / 16];
-#pragma unroll
-    for (int f = 0; f < OL_NP / 16; ++f) acc[f] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kk = 0; kk < NN_H; kk += 32) {
-        const int kq = kk + 8 * (lane >> 4);
-        const bf16x8 af = *reinterpret_cast<const bf16x8*>(&As[16 * wv + (lane & 15)][kq]);
-#pragma unroll
-        for (int f = 0; f < OL_NP / 16; ++f) {
-            const bf16x8 bf = *reinterpret_cast<const bf16x8*>(&Bs[16 * f + (lane & 15)][kq]);
-            acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[f], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int f = 0; f < OL_NP / 16; ++f) {
-        const int c = 16 * f + (lane & 15);
-        if (c < NN_OUT) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Os[16 * wv + 4 * (lane >> 4) + r][c] = acc[f][r] + bias[f];
-        }
-    }
-    wave_lds_sync();  // from here on the wavefront reads only its own rows
+    return acc;
+}
 
-    const float inv_n = 1.0f / (float)n;
-    float nll = 0.0f, ck = 0.0f, cm[8], cl[8];
+// this workgroup's half of fragment nf of its 32 rows: rows 8 q + 0..7, column c
+__device__ __forceinline__ bf16* row_frag(bf16* base, int columns16, int nf, int q, int c)
+{
+    return base + (((int64_t)(blockIdx.x >> 1) * columns16 + nf) * 64 + ((blockIdx.x & 1) * 2 + q) * 16 + c) * 8;
+}
+
+// a tile's four rows of column c = 16 nf + (lane & 15), to LDS rows and the fragment
+template <int LD>
+__device__ __forceinline__ void put_tile(bf16 (&S)[R_ROWS][LD], bf16* base, int nf, const us4& h, int lane)
+{
+    const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) cm[j] = cl[j] = 0.0f;
+    for (int r = 0; r < 4; ++r) S[4 * g + r][16 * nf + c] = h[r];
+    if (base) *reinterpret_cast<us4*>(row_frag(base, NF_H, nf, g >> 1, c) + (g & 1) * 4) = h;
+}
+
+// columns [0, 16 NF) of the workgroup's 16 rows, from LDS to their half fragments,
+// by threads t = 0, 1, ..
+template <int NF, int LD>
+__device__ __forceinline__ void put_columns(const bf16 (&S)[R_ROWS][LD], bf16* base, int t)
+{
+    if (t < 0 || t >= NF * 32) return;
+    const int q = t / (16 * NF), c = t % (16 * NF);
+    us8 x;
 #pragma unroll
-    for (int grp = 0; grp < 2; ++grp) {
-        const int rl = 16 * wv + 8 * grp + (lane >> 3);
-        const int row = m0 + rl;
-        const bool live = row < n;
-        const float* o = &Os[rl][0];
-        const float4* mu4 = reinterpret_cast<const float4*>(o + NN_K + NN_D * k);
-        const float4* raw4 = reinterpret_cast<const float4*>(o + NN_K + NN_K * NN_D + NN_D * k);
-        const float logit = o[k];
-        const float4 m0v = mu4[0], m1v = mu4[1], r0v = raw4[0], r1v = raw4[1], t0v = tv[grp][0], t1v = tv[grp][1];
-        const float mu[8] = {m0v.x, m0v.y, m0v.z, m0v.w, m1v.x, m1v.y, m1v.z, m1v.w};
-        const float raw[8] = {r0v.x, r0v.y, r0v.z, r0v.w, r1v.x, r1v.y, r1v.z, r1v.w};
-        const float t[8] = {t0v.x, t0v.y, t0v.z, t0v.w, t1v.x, t1v.y, t1v.z, t1v.w};
-        // log-softmax of the row's logits
-        const float lmax = max8(logit);
-        const float lse_logits = lmax + logf(sum8(expf(logit - lmax)));
-        // component k's log density: sum over dimensions of -u^2 / 2 - log sd
-        float u[8], si[8], term = 0.0f;
+    for (int r = 0; r < 8; ++r) x[r] = S[8 * q + r][c];
+    *reinterpret_cast<us8*>(row_frag(base, NF, c >> 4, q, c & 15)) = x;
+}
+
+// the gradient of a hidden layer's pre-activations from its product, for one tile
+template <bool LDS, int LD>
+__device__ __forceinline__ void put_gradient(const float4_t& acc, const float (&grad)[4], int row0, int n, int nf,
+                                             bf16 (&S)[R_ROWS][LD], bf16* base, float* cs, int lane)
+{
+    const int g = lane >> 4, c = 16 * nf + (lane & 15);
+    float v[4], sum = 0.0f;
+    us4 h;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float ls = fminf(fmaxf(raw[j], LOGSIG_LO), LOGSIG_HI);
-            si[j] = expf(-ls);
-            u[j] = (t[j] - mu[j]) * si[j];
-            term += -0.5f * u[j] * u[j] - ls;
+    for (int r = 0; r < 4; ++r) {
+        v[r] = row0 + 4 * g + r < n ? acc[r] * grad[r] : 0.0f;
+        h[r] = f2bf(v[r]);
+        sum += v[r];
+    }
+    if (LDS) {
+        put_tile(S, base, nf, h, lane);
+    } else {
+        *reinterpret_cast<us4*>(row_frag(base, NF_H, nf, g >> 1, lane & 15) + (g & 1) * 4) = h;
+    }
+    float* o = cs + (int64_t)(blockIdx.x >> 1) * 20 * NN_H;
+    if ((blockIdx.x & 1) == 0) {
+        o[g * NN_H + c] = sum;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[(4 + 4 * g + r) * NN_H + c] = v[r];
+    }
+}
+
+template <bool TRAIN>
+__global__ __launch_bounds__(R_BLOCK) void k_rows(RowArgs a)
+{
+    __shared__ __align__(16) bf16 Xs[R_ROWS][R_LX];
+    __shared__ __align__(16) bf16 Ha[R_ROWS][R_LH];
+    __shared__ __align__(16) bf16 Hb[R_ROWS][R_LH];
+    __shared__ __align__(16) float Os[R_ROWS][R_LO];
+    __shared__ __align__(16) bf16 Ds[TRAIN ? R_ROWS : 1][R_LD];
+    __shared__ __align__(16) float Ts[TRAIN ? R_ROWS : 1][NN_D];
+    __shared__ float part[TRAIN ? 2 : 1][TRAIN ? 2 * NN_D + 2 : 1][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * R_ROWS;
+    const int g = lane >> 4;
+
+    us8 w1[KF_IN], w2[KF_H];
+    load_frags(w1, a.pb + PB_F1, wv, lane);
+    // the rows: a float4 of features per thread, standardised
+    constexpr int XV = NN_IN / 4;
+    if (tid < R_ROWS * XV) {
+        const int r = tid / XV, c = 4 * (tid % XV);
+        us4 h = {0, 0, 0, 0};
+        if (row0 + r < a.n) {
+            const float4 f = *reinterpret_cast<const float4*>(a.rm.features + map_row(a.rm, row0 + r) * NN_IN + c);
+            const float4 m = *reinterpret_cast<const float4*>(a.rm.fmean + c), d = *reinterpret_cast<const float4*>(a.rm.fsd + c);
+            h[0] = f2bf((f.x - m.x) / d.x);
+            h[1] = f2bf((f.y - m.y) / d.y);
+            h[2] = f2bf((f.z - m.z) / d.z);
+            h[3] = f2bf((f.w - m.w) / d.w);
         }
-        const float Lk = logit - lse_logits - 0.5f * NN_D * 1.83787706640934548356f + term;
-        // log-sum-exp over the components
-        const float Lmax = max8(Lk);
-        const float lse = Lmax + logf(sum8(expf(Lk - Lmax)));
-        const float resp = expf(Lk - lse);
-        const float gk = live ? (expf(logit - lse_logits) - resp) * inv_n : 0.0f;
-        float gmu[8], gls[8];
+        *reinterpret_cast<us4*>(&Xs[r][c]) = h;
+    } else if (TRAIN && tid >= R_BLOCK - R_ROWS * NN_D) {
+        const int t = tid - (R_BLOCK - R_ROWS * NN_D), r = t / NN_D, c = t % NN_D;
+        if (row0 + r < a.n) Ts[r][c] = (a.rm.theta[map_row(a.rm, row0 + r) * NN_D + c] - a.rm.tc[c]) / a.rm.ts[c];
+        else Ts[r][c] = 0.0f;
+    }
+    load_frags(w2, a.pb + PB_F2, wv, lane);
+    const float bias1 = a.b1[16 * wv + (lane & 15)], bias2 = a.b2[16 * wv + (lane & 15)];
+    __syncthreads();
+
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+    // derivatives of both activations, where the input gradients need them
+    float grad1[4], grad2[4];
+    if (TRAIN) put_columns<NF_IN>(Xs, a.X, tid);
+    // h1 = gelu(x W1 + b1)
+    {
+        const float4_t acc = tile(Xs, w1, lane, zero);
+        us4 h;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            gmu[j] = live ? -resp * u[j] * si[j] * inv_n : 0.0f;
-            gls[j] = (live && raw[j] > LOGSIG_LO && raw[j] < LOGSIG_HI) ? -resp * (u[j] * u[j] - 1.0f) * inv_n
-                                                                         : 0.0f;
+        for (int r = 0; r < 4; ++r) {
+            const bf16 y = f2bf(gelu_f(acc[r] + bias1, grad1[r]));
+            h[r] = row0 + 4 * g + r < a.n ? y : (bf16)0;
         }
-        if (live) {
-            bf16* gb = dout_b + (int64_t)row * NN_OUT;
-            gb[k] = f2bf(gk);
+        put_tile(Ha, TRAIN ? a.H1 : nullptr, wv, h, lane);
+    }
+    us8 w3[KF_H];
+    float bias3 = 0.0f;
+    if (wv < NF_OUT) {
+        load_frags(w3, a.pb + PB_F3, wv, lane);
+        if (16 * wv + (lane & 15) < NN_OUT) bias3 = a.b3[16 * wv + (lane & 15)];
+    }
+    __syncthreads();
+    // h2 = gelu(h1 W2 + b2)
+    {
+        const float4_t acc = tile(Ha, w2, lane, zero);
+        us4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bf16 y = f2bf(gelu_f(acc[r] + bias2, grad2[r]));
+            h[r] = row0 + 4 * g + r < a.n ? y : (bf16)0;
+        }
+        put_tile(Hb, TRAIN ? a.H2 : nullptr, wv, h, lane);
+    }
+    us8 w4[KF_OUT];
+    if (TRAIN) load_frags(w4, a.pb + PB_B3, wv, lane);
+    __syncthreads();
+    // out = h2 W3 + b3
+    if (wv < NF_OUT) {
+        const float4_t acc = tile(Hb, w3, lane, zero);
+        if (16 * wv + (lane & 15) < NN_OUT)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Os[4 * g + r][16 * wv + (lane & 15)] = acc[r] + bias3;
+    }
+    if (TRAIN)  // the padding of dOUT's columns
+        for (int t = tid; t < R_ROWS * (R_LD - NN_OUT); t += R_BLOCK)
+            Ds[t / (R_LD - NN_OUT)][NN_OUT + t % (R_LD - NN_OUT)] = 0;
+    __syncthreads();
+    if constexpr (!TRAIN) {
+        for (int t = tid; t < R_ROWS * NN_OUT; t += R_BLOCK) {
+            const int r = t / NN_OUT;
+            if (row0 + r < a.n) a.out[(int64_t)(row0 + r) * NN_OUT + t % NN_OUT] = Os[r][t % NN_OUT];
+        }
+    } else {
+        us8 w5[KF_H];
+        load_frags(w5, a.pb + PB_B2, wv, lane);
+        // The loss: 8 rows in each of the first two wavefronts, lane 8 r + k
+        // holding row r's mixture component k (its logit, 8 means, 8 log sds, and
+        // the row's 8 targets), so the per-row sums over components are 8-lane
+        // shuffles and no lane repeats another's transcendentals.
+        const int k = lane & 7;
+        if (wv < 2) {
+            const int rl = 8 * wv + (lane >> 3);
+            const bool live = row0 + rl < a.n;
+            const float inv_n = 1.0f / (float)a.n;
+            const float* o = &Os[rl][0];
+            const float4* mu4 = reinterpret_cast<const float4*>(o + NN_K + NN_D * k);
+            const float4* raw4 = reinterpret_cast<const float4*>(o + NN_K + NN_K * NN_D + NN_D * k);
+            const float4* t4 = reinterpret_cast<const float4*>(&Ts[rl][0]);
+            const float logit = o[k];
+            const float4 m0v = mu4[0], m1v = mu4[1], r0v = raw4[0], r1v = raw4[1], t0v = t4[0], t1v = t4[1];
+            const float mu[8] = {m0v.x, m0v.y, m0v.z, m0v.w, m1v.x, m1v.y, m1v.z, m1v.w};
+            const float raw[8] = {r0v.x, r0v.y, r0v.z, r0v.w, r1v.x, r1v.y, r1v.z, r1v.w};
+            const float t[8] = {t0v.x, t0v.y, t0v.z, t0v.w, t1v.x, t1v.y, t1v.z, t1v.w};
+            // log-softmax of the row's logits
+            const float lmax = max8(logit);
+            const float lse_logits = lmax + logf(sum8(expf(logit - lmax)));
+            // component k's log density: sum over dimensions of -u^2 / 2 - log sd
+            float u[8], si[8], term = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float ls = fminf(fmaxf(raw[j], LOGSIG_LO), LOGSIG_HI);
+                si[j] = expf(-ls);
+                u[j] = (t[j] - mu[j]) * si[j];
+                term += -0.5f * u[j] * u[j] - ls;
+            }
+            const float Lk = logit - lse_logits - 0.5f * NN_D * 1.83787706640934548356f + term;
+            // log-sum-exp over the components
+            const float Lmax = max8(Lk);
+            const float lse = Lmax + logf(sum8(expf(Lk - Lmax)));
+            const float resp = expf(Lk - lse);
+            const float gk = live ? (expf(logit - lse_logits) - resp) * inv_n : 0.0f;
+            float gmu[8], gls[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                gmu[j] = live ? -resp * u[j] * si[j] * inv_n : 0.0f;
+                gls[j] = (live && raw[j] > LOGSIG_LO && raw[j] < LOGSIG_HI) ? -resp * (u[j] * u[j] - 1.0f) * inv_n
+                                                                             : 0.0f;
+            }
             us8 bm, bl;
 #pragma unroll
             for (int j = 0; j < 8; ++j) { bm[j] = f2bf(gmu[j]); bl[j] = f2bf(gls[j]); }
-            *reinterpret_cast<us8*>(gb + NN_K + NN_D * k) = bm;
-            *reinterpret_cast<us8*>(gb + NN_K + NN_K * NN_D + NN_D * k) = bl;
+            Ds[rl][k] = f2bf(gk);
+            *reinterpret_cast<us8*>(&Ds[rl][NN_K + NN_D * k]) = bm;
+            *reinterpret_cast<us8*>(&Ds[rl][NN_K + NN_K * NN_D + NN_D * k]) = bl;
+            // of the component, by lane: what is summed over the 16 rows
+            float (*own)[64] = part[wv];
+            own[0][lane] = gk;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { own[1 + j][lane] = gmu[j]; own[1 + NN_D + j][lane] = gls[j]; }
+            own[2 * NN_D + 1][lane] = live && k == 0 ? -lse : 0.0f;
         }
-        if (live && k == 0) nll += -lse;
-        ck += gk;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { cm[j] += gmu[j]; cl[j] += gls[j]; }
-    }
-    // the wavefront's loss (rows in lane order) and column sums (8 rows, fixed tree)
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) nll += __shfl_xor(nll, off, 64);
-    if (lane == 0) red[wv] = nll;
-    if (cs) {
-        ck = sum_rows(ck);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { cm[j] = sum_rows(cm[j]); cl[j] = sum_rows(cl[j]); }
-        if (lane < 8) {
-            csh[wv][k] = ck;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                csh[wv][NN_K + NN_D * k + j] = cm[j];
-                csh[wv][NN_K + NN_K * NN_D + NN_D * k + j] = cl[j];
+        __syncthreads();
+        // the output bias's sums over the 16 rows, and the loss
+        for (int q = wv; q < 2 * NN_D + 2; q += R_WAVES) {
+            const float v = sum_rows(part[0][q][lane] + part[1][q][lane]);
+            const int col = q == 0 ? k : (q <= NN_D ? NN_K + NN_D * k + q - 1 : NN_K + NN_K * NN_D + NN_D * k + q - 1 - NN_D);
+            if (q == 2 * NN_D + 1) {  // lane 0's rows: the others of a row hold zeros
+                if (lane == 0 && a.loss && row0 < a.n) atomicAdd(a.loss, v / (float)a.n);
+            } else if (lane < 8) {
+                a.cs3[(int64_t)blockIdx.x * NN_OUT + col] = v;
             }
         }
-    }
-    __syncthreads();
-    // one atomic per workgroup for the loss (its value only): into the log
-    // entry of the counter's step when training, else into loss_acc
-    float* dst = loss_log ? loss_log + *step : loss_acc;
-    if (tid == 0 && dst) {
-        float s = 0.0f;
-        for (int w = 0; w < OL_WAVES; ++w) s += red[w];
-        atomicAdd(dst, s / (float)n);
-    }
-    if (cs && tid < NN_OUT) {
-        float s = 0.0f;
-        for (int w = 0; w < OL_WAVES; ++w) s += csh[w][tid];
-        cs[(int64_t)blockIdx.x * NN_OUT + tid] = s;
+        put_columns<NF_OUT>(Ds, a.dOUT, R_BLOCK - 1 - tid);
+        // dZ2 = (dOUT W3^T) gelu'(z2), then dZ1 = (dZ2 W2^T) gelu'(z1)
+        put_gradient<true>(tile(Ds, w4, lane, zero), grad2, row0, a.n, wv, Ha, a.dZ2, a.cs2, lane);
+        __syncthreads();
+        put_gradient<false>(tile(Ha, w5, lane, zero), grad1, row0, a.n, wv, Ha, a.dZ1, a.cs1, lane);
     }
 }
 
 // ----------------------------------------------------------------------------
-// Adam (Kingma & Ba) on the float32 master parameters, then the bf16 copies
-// of the weights
+// Weight and bias gradients and, with adam, the update (Kingma & Ba) of the
+// float32 master parameters and the bf16 copies of the weights.
+//
+// A workgroup takes a 32 x 16 tile of one weight gradient over the whole batch:
+// dW = A^T B, summed over rows. The rows come in ranges of k_per_split (128 from
+// a batch of 512 on), each range a product of its own and the ranges added in
+// order; eight wavefronts take the ranges in turn, 32 of them at a time, and the
+// partial tiles meet in LDS, where the thread that then updates a parameter adds
+// its ranges. Nothing but the parameters goes back to memory. The last
+// workgroups add the bias gradients, 16 columns each, in the order of 64-row tiles.
+// Bound by the L2: 95 MB of fragments at a batch of 4096 take 13 us with 4 us of
+// it for the chain of one range (batch 64: 4.3 us). Partial products in memory,
+// as tiles of 64 x 64 need them to fill the chip, were 16 MB each way.
 // ----------------------------------------------------------------------------
-// The gradient of every parameter from its partials, added in fixed order:
-// a weight entry from the split-K partials of its layer's product (split
-// order), a bias entry from the column-sum partials of its layer (row-block
-// order). With adam, the same thread then applies Adam to the float32 master
-// parameter, at the update count the step counter holds (the first backward
-// launch has advanced it), and refreshes its bf16 copy. With gather_rows > 0
-// the workgroups after the parameters' assemble the next step's batch (two
-// rows each) while the partials are summed: the step's products are done
-// with X and T.
-constexpr int FIN_PARAM_BLOCKS = (int)((NN_PARAMS + 255) / 256);
+constexpr int W_BLOCK = 512, W_WAVES = W_BLOCK / 64, W_RANGES = 32;
+constexpr int W_TILES1 = NN_IN / 32 * NF_H, W_TILES2 = NN_H / 32 * NF_H, W_TILES3 = NN_H / 32 * NF_OUT;
+constexpr int W_TILES = W_TILES1 + W_TILES2 + W_TILES3;
+static_assert(NN_H / 32 == 8 && NN_IN / 32 == 3 && NF_H == 16, "the split of the tiles over eight XCDs");
+constexpr int W_COLS = 16;  // bias columns of a workgroup
+constexpr int W_BIAS_H = NN_H / W_COLS, W_BIAS_OUT = (NN_OUT + W_COLS - 1) / W_COLS;
+constexpr int W_GRID = W_TILES + 2 * W_BIAS_H + W_BIAS_OUT;
 
-struct FinishArgs {
-    const float* part1;   // [splits][96][256]
-    const float* part2;   // [splits][256][256]
-    const float* part3;   // [splits][256][136]
-    int splits;
-    const float* cs1;     // [row tiles][256]
-    const float* cs2;     // [row tiles][256]
-    const float* cs3;     // [loss blocks][136]
-    int tiles, lblocks;
+struct GradArgs {
+    const bf16 *X, *H1, *H2, *dOUT, *dZ2, *dZ1;
+    const float *cs1, *cs2, *cs3;
+    int n, k_per_split;
     float* g;
     int adam;
     float* p;
     float* m;
     float* v;
     bf16* pb;
-    const int32_t* step;
+    int updates;          // of the parameters, this one included
     float lr, b1, b2, eps;
-    int gather_rows;      // batch rows to assemble for the next step (0: none)
-    int64_t steps_total;  // no batch is assembled once the counter reaches it
-    RowMap rm;
-    bf16* X;
-    float* T;
 };
 
-__global__ __launch_bounds__(256) void k_grad_finish(FinishArgs a)
+__device__ __forceinline__ void finish_param(const GradArgs& a, int e, float gsum, float m0, float v0, float p0,
+                                             const float (&power)[2])
 {
-    if (blockIdx.x >= FIN_PARAM_BLOCKS) {
-        const int st = *a.step;
-        const int b = 2 * (blockIdx.x - FIN_PARAM_BLOCKS) + (threadIdx.x >> 7);
-        if (st < a.steps_total && b < a.gather_rows) gather_row(a.rm, st, b, threadIdx.x & 127, a.X, a.T);
-        return;
-    }
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= NN_PARAMS) return;
-    const float* src;
-    int64_t stride;
-    int cnt;
-    if (e < OFF_B1) { src = a.part1 + e; stride = (int64_t)NN_IN * NN_H; cnt = a.splits; }
-    else if (e < OFF_W2) { src = a.cs1 + (e - OFF_B1); stride = NN_H; cnt = a.tiles; }
-    else if (e < OFF_B2) { src = a.part2 + (e - OFF_W2); stride = (int64_t)NN_H * NN_H; cnt = a.splits; }
-    else if (e < OFF_W3) { src = a.cs2 + (e - OFF_B2); stride = NN_H; cnt = a.tiles; }
-    else if (e < OFF_B3) { src = a.part3 + (e - OFF_W3); stride = (int64_t)NN_H * NN_OUT; cnt = a.splits; }
-    else { src = a.cs3 + (e - OFF_B3); stride = NN_OUT; cnt = a.lblocks; }
-    // Adam's state is requested before the partials are summed
-    float m0 = 0.0f, v0 = 0.0f, p0 = 0.0f;
-    if (a.adam) { m0 = a.m[e]; v0 = a.v[e]; p0 = a.p[e]; }
-    // in order, loads issued eight ahead of the adds
-    float gsum = 0.0f;
-    int z = 0;
-    for (; z + 8 <= cnt; z += 8) {
-        float t[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) t[q] = src[(int64_t)(z + q) * stride];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) gsum += t[q];
-    }
-    for (; z < cnt; ++z) gsum += src[(int64_t)z * stride];
     a.g[e] = gsum;
     if (!a.adam) return;
-    const int st = *a.step;  // updates so far, this one included
     const float m = a.b1 * m0 + (1.0f - a.b1) * gsum;
     const float v = a.b2 * v0 + (1.0f - a.b2) * gsum * gsum;
     a.m[e] = m;
     a.v[e] = v;
-    const float mh = m / (1.0f - powf(a.b1, (float)st));
-    const float vh = v / (1.0f - powf(a.b2, (float)st));
+    const float mh = m / (1.0f - power[0]);
+    const float vh = v / (1.0f - power[1]);
     const float p = p0 - a.lr * mh / (sqrtf(vh) + a.eps);
     a.p[e] = p;
     put_bf16(a.pb, e, p);
+}
+
+// STEPS: products of 32 rows in a range
+template <int STEPS>
+__global__ __launch_bounds__(W_BLOCK) void k_weight_grad(GradArgs a)
+{
+    __shared__ float part[W_RANGES][W_BLOCK];
+    __shared__ float power[2];  // the decay rates to the number of updates
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b = blockIdx.x;
+    if (a.adam && wv == W_WAVES - 1) {
+        const float x = powf((lane & 1) ? a.b2 : a.b1, (float)a.updates);
+        if (lane < 2) power[lane] = x;  // read after a barrier of the sums
+    }
+    if (b < W_TILES) {
+        // Workgroups go to the eight XCDs in turn, and what an XCD reads of the
+        // fragments comes over the fabric: its tiles share rows and columns.
+        const bf16 *A, *B;
+        int ca, cb, cols, off, mt, nt;  // fragments per row block of either operand, columns, first parameter, tile
+        const int xcd = b & 7, q = b >> 3;
+        if (q < W_TILES2 / 8) {
+            A = a.H1; B = a.dZ2; ca = NF_H; cb = NF_H; cols = NN_H; off = (int)OFF_W2;
+            mt = 4 * (xcd & 1) + (q & 3); nt = 4 * (xcd >> 1) + (q >> 2);
+        } else if (q < (W_TILES2 + W_TILES3) / 8) {
+            A = a.H2; B = a.dOUT; ca = NF_H; cb = NF_OUT; cols = NN_OUT; off = (int)OFF_W3;
+            mt = xcd; nt = q - W_TILES2 / 8;
+        } else {
+            const int u = q - (W_TILES2 + W_TILES3) / 8;
+            A = a.X; B = a.dZ1; ca = NF_IN; cb = NF_H; cols = NN_H; off = (int)OFF_W1;
+            mt = u % 3; nt = 2 * xcd + u / 3;
+        }
+        // thread t holds element t of the tile: C[4 (lane >> 4) + (wv & 3)][lane & 15] of half wv >> 2
+        const int col = 16 * nt + (lane & 15);
+        const int e = off + (32 * mt + 16 * (wv >> 2) + 4 * (lane >> 4) + (wv & 3)) * cols + col;
+        const bool mine = col < cols;
+        float m0 = 0.0f, v0 = 0.0f, p0 = 0.0f;
+        if (a.adam && mine) { m0 = a.m[e]; v0 = a.v[e]; p0 = a.p[e]; }
+        const int nblk = (a.n + 31) / 32;
+        const int ranges = (nblk + STEPS - 1) / STEPS;
+        // a range in groups of four products at most
+        constexpr int GROUP = STEPS < 4 ? STEPS : (STEPS == 6 ? 3 : 4), GROUPS = STEPS / GROUP;
+        struct Group { us8 x0[GROUP], x1[GROUP], y[GROUP]; };
+        const us8* pa = reinterpret_cast<const us8*>(A) + (2 * mt) * 64;
+        const us8* pq = reinterpret_cast<const us8*>(B) + nt * 64;
+        float gsum = 0.0f;
+        for (int z0 = 0; z0 < ranges; z0 += W_RANGES) {
+            const int zn = min(W_RANGES, ranges - z0);
+            // this wavefront's ranges wv, wv + 8, .. of the 32, in groups
+            const int items = wv < zn ? ((zn - 1 - wv) / W_WAVES + 1) * GROUPS : 0;
+            auto first = [&](int t) { return (z0 + wv + W_WAVES * (t / GROUPS)) * STEPS + GROUP * (t % GROUPS); };
+            // (blocks past the last are read as block 0, unused, so that no branch
+            // stands between a group's loads and the wait for the group before it)
+            auto load = [&](int t, Group& f) {
+                const int blk0 = first(t);
+#pragma unroll
+                for (int q = 0; q < GROUP; ++q) {
+                    const int blk = blk0 + q < nblk ? blk0 + q : 0;  // uniform
+                    f.x0[q] = pa[(int64_t)(blk * ca) * 64 + lane];
+                    f.x1[q] = pa[(int64_t)(blk * ca) * 64 + 64 + lane];
+                    f.y[q] = pq[(int64_t)(blk * cb) * 64 + lane];
+                }
+            };
+            float4_t acc[2];
+            auto multiply = [&](int t, const Group& f) {
+                if (t >= items) return;
+                const int lim = nblk - first(t);
+                if (t % GROUPS == 0) acc[0] = acc[1] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < GROUP; ++q) {
+                    if (q >= lim) break;
+                    const bf16x8 yb = __builtin_bit_cast(bf16x8, f.y[q]);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.x0[q]), yb, acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.x1[q]), yb, acc[1], 0, 0, 0);
+                }
+                if (t % GROUPS == GROUPS - 1)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) part[wv + W_WAVES * (t / GROUPS)][(4 * i + r) * 64 + lane] = acc[i][r];
+            };
+            // two groups in flight
+            Group f0, f1;
+            load(0, f0);
+            for (int t = 0; t < items; t += 2) {
+                load(t + 1, f1);
+                multiply(t, f0);
+                load(t + 2, f0);
+                multiply(t + 1, f1);
+            }
+            __syncthreads();
+            int z = 0;
+            for (; z + 8 <= zn; z += 8) {
+                float p[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) p[q] = part[z + q][tid];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) gsum += p[q];
+            }
+            for (; z < zn; ++z) gsum += part[z][tid];
+            __syncthreads();
+        }
+        if (mine) finish_param(a, e, gsum, m0, v0, p0, power);
+        return;
+    }
+    b -= W_TILES;
+    // biases: thread (i, c) forms the sum of column c over one 64-row tile
+    constexpr int IN = W_BLOCK / W_COLS;  // tiles side by side
+    const int c = tid % W_COLS, i = tid / W_COLS;
+    const bool hidden = b < 2 * W_BIAS_H;
+    const int cols = hidden ? NN_H : NN_OUT;
+    const int col0 = W_COLS * (hidden ? b % W_BIAS_H : b - 2 * W_BIAS_H) + c;
+    const bool mine = col0 < cols;
+    const int col = mine ? col0 : 0;
+    const int e = (hidden ? (int)(b < W_BIAS_H ? OFF_B1 : OFF_B2) : (int)OFF_B3) + col;
+    const float* cs = b < W_BIAS_H ? a.cs1 : a.cs2;
+    float m0 = 0.0f, v0 = 0.0f, p0 = 0.0f;
+    if (a.adam && mine && i == 0) { m0 = a.m[e]; v0 = a.v[e]; p0 = a.p[e]; }
+    const int tiles = (a.n + 63) / 64, nblk = (a.n + 31) / 32;
+    float gsum = 0.0f;
+    for (int t0 = 0; t0 < tiles; t0 += IN) {
+        const int t = t0 + i;
+        // the blocks of 32 rows of the tile; missing ones count as zeros, and are
+        // read as block 0 so that all loads are in flight together
+        const bool in[2] = {2 * t < nblk, 2 * t + 1 < nblk};
+        const int64_t blk[2] = {in[0] ? 2 * t : 0, in[1] ? 2 * t + 1 : 0};
+        float sum = 0.0f;
+        if (hidden) {
+            float s[2][4], x[2][16];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float* o = cs + blk[h] * 20 * NN_H + col;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) s[h][g] = o[g * NN_H];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x[h][r] = o[(4 + r) * NN_H];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[h][r >> 2] += x[h][r];
+                const float v = (s[h][0] + s[h][1]) + (s[h][2] + s[h][3]);
+                sum = h == 0 ? v : sum + (in[1] ? v : 0.0f);
+            }
+        } else {
+            float x[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) x[w] = a.cs3[(2 * blk[w >> 1] + (w & 1)) * NN_OUT + col];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) sum += in[w >> 1] ? x[w] : 0.0f;
+        }
+        part[0][tid] = sum;
+        __syncthreads();
+        if (i == 0) {
+            const int tn = min(IN, tiles - t0);
+            float p[IN];
+#pragma unroll
+            for (int q = 0; q < IN; ++q) p[q] = part[0][q * W_COLS + c];
+#pragma unroll
+            for (int q = 0; q < IN; ++q)
+                if (q < tn) gsum += p[q];
+        }
+        __syncthreads();
+    }
+    if (mine && i == 0) finish_param(a, e, gsum, m0, v0, p0, power);
 }
 
 __global__ void k_zero_f32(float* p, int64_t n)
@@ -989,7 +959,7 @@ __global__ void k_zero_f32(float* p, int64_t n)
 __global__ void k_params_bf16(const float* p, bf16* pb)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < NN_PARAMS) put_bf16(pb, e, p[e]);
+    if (e < NN_PARAMS) put_bf16(pb, (int)e, p[e]);
 }
 
 // initialisation (domain 3 stream): W ~ U(-1/sqrt(fan_in), 1/sqrt(fan_in)), b = 0
@@ -1047,61 +1017,14 @@ __global__ __launch_bounds__(256) void k_mdn_sample(SampleArgs a)
     a.weight[k] = w;
 }
 
-// K range per split for the weight-gradient products (reduction over the
-// batch): 128 rows per split once K >= 512, else K in ranges of at most
-// G_KMAX.
+// Rows per range of the weight-gradient products: 128 from a batch of 512 on,
+// else ranges of whole 64-row tiles, at most 256 rows each.
 static int k_per_split_for(int K)
 {
     if (K >= 512) return 128;
-    const int tiles = (K + G_BK - 1) / G_BK;
-    const int splits = (tiles + G_NT - 1) / G_NT;
-    return ((tiles + splits - 1) / splits) * G_BK;
-}
-static int splits_for(int K) { const int kps = k_per_split_for(K); return (K + kps - 1) / kps; }
-
-// kps = K range per split (0: the whole K in one split); returns whether the
-// operands allow the vector loads
-template <bool TA, bool TB>
-static bool gemm_prep(GemmArgs& g, int kps)
-{
-    g.k_per_split = kps > 0 ? kps : ((g.K + G_BK - 1) / G_BK) * G_BK;
-    g.split_stride = (int64_t)g.M * g.N;
-    g.gx = (g.N + G_BN - 1) / G_BN;
-    g.gy = (g.M + G_BM - 1) / G_BM;
-    return g.M % 8 == 0 && g.N % 8 == 0 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
-           g.k_per_split % 8 == 0 && (reinterpret_cast<uintptr_t>(g.A) & 15u) == 0 &&
-           (reinterpret_cast<uintptr_t>(g.B) & 15u) == 0;
-}
-
-static int splits_of(const GemmArgs& g) { return (g.K + g.k_per_split - 1) / g.k_per_split; }
-
-template <bool TA, bool TB, int EPI>
-static void gemm(const GemmArgs& g0, int kps, hipStream_t s)
-{
-    GemmArgs g = g0;
-    const bool vec = gemm_prep<TA, TB>(g, kps);
-    const dim3 grid(g.gx, g.gy, splits_of(g));
-    if (vec)
-        hipLaunchKernelGGL((k_gemm_bf16<TA, TB, EPI, true>), grid, dim3(256), 0, s, g);
-    else
-        hipLaunchKernelGGL((k_gemm_bf16<TA, TB, EPI, false>), grid, dim3(256), 0, s, g);
-}
-
-// two independent products in one launch where both allow vector loads
-// (the first one's tiles are dispatched first), else one launch each
-template <bool TA1, bool TB1, int EPI1, bool TA2, bool TB2, int EPI2>
-static void gemm_pair(const GemmArgs& a0, int kps1, const GemmArgs& b0, int kps2, hipStream_t s)
-{
-    GemmArgs a = a0, b = b0;
-    const bool va = gemm_prep<TA1, TB1>(a, kps1), vb = gemm_prep<TA2, TB2>(b, kps2);
-    if (!va || !vb) {
-        gemm<TA1, TB1, EPI1>(a0, kps1, s);
-        gemm<TA2, TB2, EPI2>(b0, kps2, s);
-        return;
-    }
-    const int na = a.gx * a.gy * splits_of(a), nb = b.gx * b.gy * splits_of(b);
-    hipLaunchKernelGGL((k_gemm_pair<TA1, TB1, EPI1, TA2, TB2, EPI2>), dim3(na + nb), dim3(256), 0, s, a, b,
-                       na);
+    const int tiles = (K + 63) / 64;
+    const int splits = (tiles + 3) / 4;
+    return ((tiles + splits - 1) / splits) * 64;
 }
 
 }  // namespace abc
@@ -1116,162 +1039,105 @@ struct abc_mdn {
     float* g = nullptr;
     float* fmean = nullptr;
     float* fsd = nullptr;
-    int32_t* step = nullptr;
     float* loss_acc = nullptr;
     float lo[8], hi[8], tc[8], ts[8];
-    int ws = 0;  // workspace rows
-    bf16 *X = nullptr, *H1 = nullptr, *H2 = nullptr, *dOUTb = nullptr, *dZ2b = nullptr, *dZ1b = nullptr;
-    float *T = nullptr, *Z1 = nullptr, *Z2 = nullptr, *OUT = nullptr;
-    // split-K partials of the three weight gradients, column-sum partials of
-    // the three bias gradients
-    float *part1 = nullptr, *part2 = nullptr, *part3 = nullptr, *cs1 = nullptr, *cs2 = nullptr,
-          *cs3 = nullptr;
-    int64_t* perm = nullptr;
+    int ws = 0;  // workspace: blocks of 32 rows
+    bf16* frags = nullptr;  // fragments of X, H1, H2, dOUT, dZ2, dZ1
+    float* sums = nullptr;  // bias gradients' partials cs1, cs2, cs3
 };
 
 namespace {
 
+constexpr int64_t WS_FRAGS = (int64_t)(NF_IN + 4 * NF_H + NF_OUT) * FRAG;  // of 32 rows
+constexpr int64_t WS_SUMS = 2 * 20 * NN_H + 2 * NN_OUT;
+
 void free_ws(abc_mdn* n)
 {
-    void* ptrs[] = {n->X, n->H1, n->H2, n->dOUTb, n->dZ2b, n->dZ1b, n->T, n->Z1, n->Z2,
-                    n->OUT, n->part1, n->part2, n->part3,
-                    n->cs1, n->cs2, n->cs3};
-    for (void* q : ptrs)
-        if (q) (void)hipFree(q);
-    n->X = n->H1 = n->H2 = n->dOUTb = n->dZ2b = n->dZ1b = nullptr;
-    n->T = n->Z1 = n->Z2 = n->OUT = nullptr;
-    n->part1 = n->part2 = n->part3 = n->cs1 = n->cs2 = n->cs3 = nullptr;
+    if (n->frags) (void)hipFree(n->frags);
+    if (n->sums) (void)hipFree(n->sums);
+    n->frags = nullptr;
+    n->sums = nullptr;
     n->ws = 0;
 }
 
 abc_status ensure_ws(abc_mdn* n, int rows)
 {
-    if (rows <= n->ws) return ABC_OK;
+    const int blocks = (rows + 31) / 32;
+    if (blocks <= n->ws) return ABC_OK;
     free_ws(n);
-    const size_t r = (size_t)rows;
-    const int splits = splits_for(rows);
-#define ALLOC(ptr, bytes) ABC_HIP(hipMalloc((void**)&(ptr), (bytes)))
-    ALLOC(n->X, r * NN_IN * sizeof(bf16));
-    ALLOC(n->T, r * NN_D * sizeof(float));
-    ALLOC(n->Z1, r * NN_H * sizeof(float));
-    ALLOC(n->H1, r * NN_H * sizeof(bf16));
-    ALLOC(n->Z2, r * NN_H * sizeof(float));
-    ALLOC(n->H2, r * NN_H * sizeof(bf16));
-    ALLOC(n->OUT, r * NN_OUT * sizeof(float));
-    ALLOC(n->dOUTb, r * NN_OUT * sizeof(bf16));
-    ALLOC(n->dZ2b, r * NN_H * sizeof(bf16));
-    ALLOC(n->dZ1b, r * NN_H * sizeof(bf16));
-    ALLOC(n->part1, (size_t)splits * NN_IN * NN_H * sizeof(float));
-    ALLOC(n->part2, (size_t)splits * NN_H * NN_H * sizeof(float));
-    ALLOC(n->part3, (size_t)splits * NN_H * NN_OUT * sizeof(float));
-    ALLOC(n->cs1, (size_t)((rows + G_BM - 1) / G_BM) * NN_H * sizeof(float));
-    ALLOC(n->cs2, (size_t)((rows + G_BM - 1) / G_BM) * NN_H * sizeof(float));
-    ALLOC(n->cs3, (size_t)((rows + OL_ROWS - 1) / OL_ROWS) * NN_OUT * sizeof(float));
-#undef ALLOC
-    n->ws = rows;
+    ABC_HIP(hipMalloc((void**)&n->frags, (size_t)blocks * WS_FRAGS * sizeof(bf16)));
+    ABC_HIP(hipMalloc((void**)&n->sums, (size_t)blocks * WS_SUMS * sizeof(float)));
+    n->ws = blocks;
     return ABC_OK;
 }
 
-// the batch's rows: rows 0..batch-1 in order without a step counter
-RowMap row_map(const abc_mdn* net, const float* features, const float* theta, int64_t n_rows,
-               int batch, int steps_per_epoch, const int64_t* perm, const int32_t* step)
+// the batch's rows: rows 0..n-1 in order
+RowMap row_map(const abc_mdn* net, const float* features, const float* theta, int64_t n)
 {
     RowMap r{};
     r.features = features;
     r.theta = theta;
-    r.n = n_rows;
-    r.batch = batch;
-    r.steps_per_epoch = steps_per_epoch;
-    r.perm_ab = perm;
-    r.step = step;
+    r.n = n;
+    r.mul = 1;
+    r.inv_n = 1.0 / (double)n;
     r.fmean = net->fmean;
     r.fsd = net->fsd;
     for (int j = 0; j < 8; ++j) { r.tc[j] = net->tc[j]; r.ts[j] = net->ts[j]; }
     return r;
 }
 
-void launch_gather(abc_mdn* net, const RowMap& rm, int rows, float* loss_acc, hipStream_t s)
+RowArgs row_args(const abc_mdn* net, const RowMap& rm, int n)
 {
-    hipLaunchKernelGGL(k_gather, dim3(rows), dim3(128), 0, s, rm, net->X, net->T, loss_acc);
+    RowArgs a{};
+    a.rm = rm;
+    a.n = n;
+    a.pb = net->pb;
+    a.b1 = net->p + OFF_B1;
+    a.b2 = net->p + OFF_B2;
+    a.b3 = net->p + OFF_B3;
+    if (net->ws) {
+        const int64_t w = net->ws;
+        a.X = net->frags;
+        a.H1 = a.X + w * NF_IN * FRAG;
+        a.H2 = a.H1 + w * NF_H * FRAG;
+        a.dOUT = a.H2 + w * NF_H * FRAG;
+        a.dZ2 = a.dOUT + w * NF_OUT * FRAG;
+        a.dZ1 = a.dZ2 + w * NF_H * FRAG;
+        a.cs1 = net->sums;
+        a.cs2 = a.cs1 + w * 20 * NN_H;
+        a.cs3 = a.cs2 + w * 20 * NN_H;
+    }
+    return a;
 }
 
-// the hidden layers: Z1, H1, Z2, H2 from X
-void forward_hidden(abc_mdn* net, int n, hipStream_t s)
+// a launch covers whole blocks of 32 rows: rows past the batch are zeros
+void launch_rows(const RowArgs& a, bool train, hipStream_t s)
 {
-    GemmArgs g{};
-    g.M = n; g.N = NN_H; g.K = NN_IN;
-    g.A = net->X; g.lda = NN_IN; g.B = net->pb + OFF_W1; g.ldb = NN_H;
-    g.C = net->Z1; g.ldc = NN_H; g.bias = net->p + OFF_B1; g.H = net->H1; g.ldh = NN_H;
-    gemm<false, false, EPI_GELU>(g, 0, s);
-    g = GemmArgs{};
-    g.M = n; g.N = NN_H; g.K = NN_H;
-    g.A = net->H1; g.lda = NN_H; g.B = net->pb + OFF_W2; g.ldb = NN_H;
-    g.C = net->Z2; g.ldc = NN_H; g.bias = net->p + OFF_B2; g.H = net->H2; g.ldh = NN_H;
-    gemm<false, false, EPI_GELU>(g, 0, s);
+    const dim3 grid(2 * ((a.n + 31) / 32)), block(R_BLOCK);
+    if (train) hipLaunchKernelGGL(k_rows<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(k_rows<false>, grid, block, 0, s, a);
 }
 
-// the network outputs OUT (inference)
-void forward_out(abc_mdn* net, int n, hipStream_t s)
+GradArgs grad_args(const abc_mdn* net, const RowArgs& r)
 {
-    GemmArgs g{};
-    g.M = n; g.N = NN_OUT; g.K = NN_H;
-    g.A = net->H2; g.lda = NN_H; g.B = net->pb + OFF_W3; g.ldb = NN_OUT;
-    g.C = net->OUT; g.ldc = NN_OUT; g.bias = net->p + OFF_B3;
-    gemm<false, false, EPI_STORE>(g, 0, s);
+    GradArgs a{};
+    a.X = r.X; a.H1 = r.H1; a.H2 = r.H2; a.dOUT = r.dOUT; a.dZ2 = r.dZ2; a.dZ1 = r.dZ1;
+    a.cs1 = r.cs1; a.cs2 = r.cs2; a.cs3 = r.cs3;
+    a.n = r.n;
+    a.k_per_split = k_per_split_for(r.n);
+    a.g = net->g;
+    return a;
 }
 
-// output layer, loss and the gradient partials of the mean NLL
-// (forward_hidden must have run); the gradient itself is formed by
-// k_grad_finish. The weight gradient of a layer
-// and the next layer's input gradient do not depend on each other and share
-// a launch. Training (step != null): the loss goes to loss_log[step] and the
-// first backward launch advances the step counter (no kernel of this launch
-// reads it).
-void backward(abc_mdn* net, int n, int32_t* step, float* loss_log, hipStream_t s)
+void launch_weight_grad(const GradArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_out_loss, dim3((n + OL_ROWS - 1) / OL_ROWS), dim3(64 * OL_WAVES), 0, s, net->H2,
-                       net->pb + OFF_W3T, net->p + OFF_B3, net->T, n, net->dOUTb, net->loss_acc, step,
-                       step ? loss_log : nullptr, net->cs3);
-    const int kps = k_per_split_for(n);
-    // dZ2 = (dOUT W3^T) gelu'(Z2), with the column partials of db2; dW3 = H2^T dOUT
-    // (db3: the loss kernel's column partials)
-    GemmArgs d{}, w{};
-    d.M = n; d.N = NN_H; d.K = NN_OUT;
-    d.A = net->dOUTb; d.lda = NN_OUT; d.B = net->pb + OFF_W3; d.ldb = NN_OUT;
-    d.Zin = net->Z2; d.H = net->dZ2b; d.ldh = NN_H; d.cs = net->cs2;
-    d.step_inc = step;
-    w.M = NN_H; w.N = NN_OUT; w.K = n;
-    w.A = net->H2; w.lda = NN_H; w.B = net->dOUTb; w.ldb = NN_OUT;
-    w.C = net->part3; w.ldc = NN_OUT;
-    gemm_pair<false, true, EPI_DGELU, true, false, EPI_STORE>(d, 0, w, kps, s);
-    // dZ1 = (dZ2 W2^T) gelu'(Z1), with the column partials of db1; dW2 = H1^T dZ2
-    d = GemmArgs{};
-    w = GemmArgs{};
-    d.M = n; d.N = NN_H; d.K = NN_H;
-    d.A = net->dZ2b; d.lda = NN_H; d.B = net->pb + OFF_W2; d.ldb = NN_H;
-    d.Zin = net->Z1; d.H = net->dZ1b; d.ldh = NN_H; d.cs = net->cs1;
-    w.M = NN_H; w.N = NN_H; w.K = n;
-    w.A = net->H1; w.lda = NN_H; w.B = net->dZ2b; w.ldb = NN_H;
-    w.C = net->part2; w.ldc = NN_H;
-    gemm_pair<false, true, EPI_DGELU, true, false, EPI_STORE>(d, 0, w, kps, s);
-    // dW1 = X^T dZ1
-    w = GemmArgs{};
-    w.M = NN_IN; w.N = NN_H; w.K = n;
-    w.A = net->X; w.lda = NN_IN; w.B = net->dZ1b; w.ldb = NN_H;
-    w.C = net->part1; w.ldc = NN_H;
-    gemm<true, false, EPI_STORE>(w, kps, s);
-}
-
-FinishArgs finish_args(abc_mdn* net, int n)
-{
-    FinishArgs f{};
-    f.part1 = net->part1; f.part2 = net->part2; f.part3 = net->part3;
-    f.splits = splits_for(n);
-    f.cs1 = net->cs1; f.cs2 = net->cs2; f.cs3 = net->cs3;
-    f.tiles = (n + G_BM - 1) / G_BM;
-    f.lblocks = (n + OL_ROWS - 1) / OL_ROWS;
-    f.g = net->g;
-    return f;
+    const dim3 grid(W_GRID), block(W_BLOCK);
+    switch (a.k_per_split / 32) {
+    case 2: hipLaunchKernelGGL(k_weight_grad<2>, grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL(k_weight_grad<4>, grid, block, 0, s, a); break;
+    case 6: hipLaunchKernelGGL(k_weight_grad<6>, grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL(k_weight_grad<8>, grid, block, 0, s, a); break;
+    }
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -1302,20 +1168,20 @@ extern "C" abc_status abc_mdn_create(const abc_prior* prior, uint64_t init_seed,
     e = e ? e : hipMalloc((void**)&n->g, NN_PARAMS * sizeof(float));
     e = e ? e : hipMalloc((void**)&n->fmean, NN_IN * sizeof(float));
     e = e ? e : hipMalloc((void**)&n->fsd, NN_IN * sizeof(float));
-    e = e ? e : hipMalloc((void**)&n->step, sizeof(int32_t));
     e = e ? e : hipMalloc((void**)&n->loss_acc, sizeof(float));
     if (e != hipSuccess) {
         abc_mdn_destroy(n);
         return set_error(ABC_EHIP, "abc_mdn_create: %s", hipGetErrorString(e));
     }
     hipLaunchKernelGGL(k_mdn_init, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, 0, n->p, init_seed);
+    static_assert(NN_PB % 2 == 0, "cleared as float32");
+    hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(NN_PB / 2)), dim3(256), 0, 0, reinterpret_cast<float*>(n->pb), NN_PB / 2);
     hipLaunchKernelGGL(k_params_bf16, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, 0, n->p, n->pb);
     hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, 0, n->m, NN_PARAMS);
     hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, 0, n->v, NN_PARAMS);
     hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(NN_IN), 0, 0, n->fmean, NN_IN);
     std::vector<float> ones(NN_IN, 1.0f);
     e = hipMemcpy(n->fsd, ones.data(), NN_IN * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(n->step, 0, sizeof(int32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         abc_mdn_destroy(n);
@@ -1329,7 +1195,7 @@ extern "C" abc_status abc_mdn_destroy(abc_mdn* n)
 {
     if (!n) return ABC_OK;
     free_ws(n);
-    void* ptrs[] = {n->p, n->pb, n->m, n->v, n->g, n->fmean, n->fsd, n->step, n->loss_acc, n->perm};
+    void* ptrs[] = {n->p, n->pb, n->m, n->v, n->g, n->fmean, n->fsd, n->loss_acc};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete n;
@@ -1438,13 +1304,9 @@ extern "C" abc_status abc_mdn_forward(abc_mdn* net, const float* features, int64
 {
     ABC_REQUIRE(net && features && out && n >= 1 && n <= (1 << 20), "bad forward arguments");
     ABC_REQUIRE((reinterpret_cast<uintptr_t>(features) & 15u) == 0, "features must be 16-byte aligned");
-    abc_status rc = ensure_ws(net, (int)n);
-    if (rc) return rc;
-    const hipStream_t s = as_stream(stream);
-    launch_gather(net, row_map(net, features, nullptr, n, (int)n, 1, nullptr, nullptr), (int)n, nullptr, s);
-    forward_hidden(net, (int)n, s);
-    forward_out(net, (int)n, s);
-    ABC_HIP(hipMemcpyAsync(out, net->OUT, (size_t)n * NN_OUT * sizeof(float), hipMemcpyDeviceToDevice, s));
+    RowArgs a = row_args(net, row_map(net, features, nullptr, n), (int)n);
+    a.out = out;
+    launch_rows(a, false, as_stream(stream));
     return check_launch("abc_mdn_forward");
 }
 
@@ -1456,11 +1318,11 @@ extern "C" abc_status abc_mdn_loss_grad(abc_mdn* net, const float* features, con
     abc_status rc = ensure_ws(net, (int)n);
     if (rc) return rc;
     const hipStream_t s = as_stream(stream);
-    launch_gather(net, row_map(net, features, theta, n, (int)n, 1, nullptr, nullptr), (int)n, net->loss_acc, s);
-    forward_hidden(net, (int)n, s);
-    backward(net, (int)n, nullptr, nullptr, s);
-    const FinishArgs f = finish_args(net, (int)n);
-    hipLaunchKernelGGL(k_grad_finish, dim3(FIN_PARAM_BLOCKS), dim3(256), 0, s, f);
+    hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, s, net->loss_acc, (int64_t)1);
+    RowArgs a = row_args(net, row_map(net, features, theta, n), (int)n);
+    a.loss = net->loss_acc;
+    launch_rows(a, true, s);
+    launch_weight_grad(grad_args(net, a), s);
     if (loss) ABC_HIP(hipMemcpyAsync(loss, net->loss_acc, sizeof(float), hipMemcpyDeviceToDevice, s));
     if (grad) ABC_HIP(hipMemcpyAsync(grad, net->g, NN_PARAMS * sizeof(float), hipMemcpyDeviceToDevice, s));
     return check_launch("abc_mdn_loss_grad");
@@ -1497,61 +1359,41 @@ extern "C" abc_status abc_mdn_train(abc_mdn* net, const float* features, const f
         ab[2 * e] = a;
         ab[2 * e + 1] = (int64_t)(next() % (uint64_t)n);
     }
-    if (net->perm) (void)hipFree(net->perm);
-    net->perm = nullptr;
-    ABC_HIP(hipMalloc((void**)&net->perm, ab.size() * sizeof(int64_t)));
-    const hipStream_t user = as_stream(stream);
-    hipStream_t s;
-    ABC_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    struct SF { hipStream_t s; ~SF() { (void)hipStreamDestroy(s); } } sf{s};
-    hipEvent_t ev, t0, t1;
-    ABC_HIP(hipEventCreate(&ev));
+    const hipStream_t s = as_stream(stream);
+    hipEvent_t t0, t1;
     ABC_HIP(hipEventCreate(&t0));
     ABC_HIP(hipEventCreate(&t1));
-    struct EF { hipEvent_t a, b, c; ~EF() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); (void)hipEventDestroy(c); } } ef{ev, t0, t1};
-    ABC_HIP(hipEventRecord(ev, user));
-    ABC_HIP(hipStreamWaitEvent(s, ev, 0));
-    ABC_HIP(hipMemcpyAsync(net->perm, ab.data(), ab.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-    ABC_HIP(hipMemsetAsync(net->step, 0, sizeof(int32_t), s));
-    if (loss_log) ABC_HIP(hipMemsetAsync(loss_log, 0, (size_t)steps * sizeof(float), s));
+    struct EF { hipEvent_t a, b; ~EF() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); } } ef{t0, t1};
+    if (loss_log) hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(steps)), dim3(256), 0, s, loss_log, steps);
     hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, s, net->m, NN_PARAMS);
     hipLaunchKernelGGL(k_zero_f32, dim3(blocks_for(NN_PARAMS)), dim3(256), 0, s, net->v, NN_PARAMS);
-    // the first batch; every step's finish kernel assembles the next one
-    const RowMap rm = row_map(net, features, theta, n, batch, spe, net->perm, net->step);
-    launch_gather(net, rm, batch, nullptr, s);
-    ABC_HIP(hipStreamSynchronize(s));
 
-    // one training step, captured once and replayed
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    ABC_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    forward_hidden(net, batch, s);
-    backward(net, batch, net->step, loss_log, s);
-    FinishArgs f = finish_args(net, batch);
+    // Two launches a step. They take longer than their launches, so a graph of
+    // them gains nothing over the stream, and its capture took a tenth of a
+    // short training run.
+    RowArgs r = row_args(net, row_map(net, features, theta, n), batch);
+    GradArgs f = grad_args(net, r);
     f.adam = 1;
-    f.p = net->p; f.m = net->m; f.v = net->v; f.pb = net->pb; f.step = net->step;
+    f.p = net->p; f.m = net->m; f.v = net->v; f.pb = net->pb;
     f.lr = lr; f.b1 = 0.9f; f.b2 = 0.999f; f.eps = 1e-8f;
-    f.gather_rows = batch;
-    f.steps_total = steps;
-    f.rm = rm;
-    f.X = net->X;
-    f.T = net->T;
-    hipLaunchKernelGGL(k_grad_finish, dim3(FIN_PARAM_BLOCKS + (batch + 1) / 2), dim3(256), 0, s, f);
-    hipError_t ce = hipStreamEndCapture(s, &graph);
-    if (ce != hipSuccess) return set_error(ABC_EHIP, "training graph capture: %s", hipGetErrorString(ce));
-    struct GF { hipGraph_t g; hipGraphExec_t e; ~GF() { if (e) (void)hipGraphExecDestroy(e); if (g) (void)hipGraphDestroy(g); } } gf{graph, nullptr};
-    ABC_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-    gf.e = exec;
     ABC_HIP(hipEventRecord(t0, s));
-    for (int64_t k = 0; k < steps; ++k) ABC_HIP(hipGraphLaunch(exec, s));
+    for (int64_t k = 0; k < steps; ++k) {
+        const int64_t e = k / spe;
+        r.rm.mul = ab[2 * e];
+        r.rm.add = ab[2 * e + 1];
+        r.rm.j0 = (k % spe) * batch;
+        r.loss = loss_log ? loss_log + k : nullptr;
+        launch_rows(r, true, s);
+        f.updates = (int)(k + 1);
+        launch_weight_grad(f, s);
+    }
+    if ((rc = check_launch("abc_mdn_train"))) return rc;
     ABC_HIP(hipEventRecord(t1, s));
     ABC_HIP(hipEventSynchronize(t1));
     float ms = 0.0f;
     ABC_HIP(hipEventElapsedTime(&ms, t0, t1));
     if (train_ms) *train_ms = ms;
     if (steps_out) *steps_out = steps;
-    ABC_HIP(hipEventRecord(ev, s));
-    ABC_HIP(hipStreamWaitEvent(user, ev, 0));
     return ABC_OK;
 }
 
