@@ -500,10 +500,9 @@ ABC_API abc_status abc_mdn_loss_grad(abc_mdn* net, const float* features, const 
 /* Adam (beta 0.9, 0.999, eps 1e-8, learning rate lr) on the mean NLL over
  * `epochs` passes of n pairs in batches of `batch` (floor(n / batch) steps per
  * epoch; epoch e visits row (a_e j + c_e) mod n, with (a_e, c_e) from
- * shuffle_seed). One training step is captured once as a hipGraph and
- * replayed. loss_log (device float32 [steps], nullable) receives each step's
+ * shuffle_seed). loss_log (device float32 [steps], nullable) receives each step's
  * batch loss; steps_out and train_ms (host, nullable) the step count and the
- * GPU time of the replays. Blocks the host until done. */
+ * GPU time of the steps. Blocks the host until done. */
 ABC_API abc_status abc_mdn_train(abc_mdn* net, const float* features, const float* theta,
                                  int64_t n, int32_t epochs, int32_t batch, float lr,
                                  uint64_t shuffle_seed, float* loss_log, int64_t* steps_out,

@@ -7,12 +7,13 @@
 // One generation t >= 1 on the device:
 //   k_smc_setup     one workgroup: weighted mean and covariance of generation
 //                   t-1 (left-to-right float64 sums), Sigma = 2 cov, its
-//                   Cholesky factor L, running weight sums C_j, whitened
-//                   particles y_j = L^-1 theta_j, and eps_t, the kth smallest
-//                   previous distance, by radix selection.
+//                   Cholesky factor L and running weight sums C_j; another
+//                   beside it: eps_t, the kth smallest previous distance, by
+//                   radix selection.
 //   k_smc_propose   one lane per candidate: ancestor by binary search of
 //                   u C_{N-1} in C, theta* = theta_anc + L z (float64, rounded
-//                   to float32).
+//                   to float32). The first one of a generation also forms the
+//                   whitened particles y_j = L^-1 theta_j.
 //   simulate / compact / float64 decision: the rejection-ABC kernels, with
 //                   the prior-support check (candidates outside the box are
 //                   rejected unsimulated); with a band every candidate is
@@ -50,6 +51,24 @@ struct SmcState {
     int32_t status;   // 0 ok, 1 Sigma not positive definite
 };
 
+// What the host reads back, in pinned memory that the kernels write to: a copy
+// of a few bytes is a launch of its own, 4 us each and 50 of them in a run of
+// eight generations.
+struct FromDevice {
+    float eps;
+    int32_t status;
+    int64_t count;             // accepted candidates of the chunk
+    int64_t last;              // index of the candidate that completes the population
+    unsigned long long inbox;  // candidates inside the prior box
+    double ess;
+};
+
+template <typename T>
+__device__ __forceinline__ void tell(T* host, T v)
+{
+    __hip_atomic_store(host, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct SetupArgs {
     const float* theta;   // [N][8]
     const double* w;      // [N] normalised weights
@@ -59,31 +78,49 @@ struct SetupArgs {
     float eps_min;
     SmcState* st;
     double* C;            // [N]
-    double* y;            // [N][8]
+    FromDevice* host;
 };
 
-// The single-lane ordered sums read the particles from LDS: all threads copy
-// a chunk of SMC_CHUNK particles (weights, then theta) into the distance
-// array before it holds the distances, and the summing lanes load SMC_PF
-// values ahead of their adds. The order of the additions is that of the
-// plainly written definition.
-constexpr int SMC_PF = 16;
-constexpr int SMC_CHUNK = 1024;  // 8 KiB of weights + 32 KiB of theta
-
-__device__ __forceinline__ void smc_stage_chunk(const SetupArgs& a, int c0, int m, double* sw,
-                                                float* sth)
+// s + P[0][c] + P[1][c] + ... + P[m - 1][c], left to right, rows of STRIDE, 16
+// values in registers ahead of their adds; STORE: every running sum replaces
+// the value it was reached with.
+template <int STRIDE, bool STORE>
+__device__ __forceinline__ double ordered_sum(double s, double* P, int c, int m)
 {
-    // one particle per thread: all nine loads are in flight before any store
-    for (int j = threadIdx.x; j < m; j += blockDim.x) {
-        const float* src = a.theta + (int64_t)8 * (c0 + j);
-        float v[8];
+#pragma clang fp contract(off)
+    constexpr int AHEAD = 16, WHOLE = 128;
+    if (m == WHOLE) {
+        double v[2][AHEAD];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = src[k];
-        const double wj = a.w[c0 + j];
-        sw[j] = wj;
+        for (int k = 0; k < AHEAD; ++k) v[0][k] = P[k * STRIDE + c];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) sth[8 * j + k] = v[k];
+        for (int q = 0; q < WHOLE / AHEAD; ++q) {
+            if (q + 1 < WHOLE / AHEAD)
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k) v[(q + 1) & 1][k] = P[((q + 1) * AHEAD + k) * STRIDE + c];
+            __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the adds
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                s = s + v[q & 1][k];
+                if (STORE) P[(q * AHEAD + k) * STRIDE + c] = s;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return s;
     }
+    for (int j = 0; j < m; j += AHEAD) {
+        const int e = min(AHEAD, m - j);
+        double v[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) v[k] = P[(j + (k < e ? k : 0)) * STRIDE + c];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k)
+            if (k < e) {
+                s = s + v[k];
+                if (STORE) P[(j + k) * STRIDE + c] = s;
+            }
+    }
+    return s;
 }
 
 // Keys whose unsigned order is the order of the (non-NaN) doubles.
@@ -101,129 +138,168 @@ __device__ __forceinline__ double key_value(uint64_t k)
 
 constexpr int SMC_SETUP_THREADS = 1024;
 constexpr int SMC_SEL_PER = SMC_MAX_N / SMC_SETUP_THREADS;
+constexpr int SU_CHUNK = 128, SU_PAIRS = 7;     // pairs of wavefronts that form products
+constexpr int SU_SUMS1 = 9, SU_SUMS2 = 37;      // row strides: w and w theta; the 36 covariance products (odd)
 
-// One workgroup of SMC_SETUP_THREADS threads. Sums run left to right over the
-// particles in single lanes so that every rounding matches the plainly written
-// definition.
-__global__ __launch_bounds__(SMC_SETUP_THREADS) void k_smc_setup(SetupArgs a)
+// eps_t, the kth smallest previous distance: radix selection over
+// order-preserving 64-bit keys, 8 bits per pass from the most significant, with
+// one histogram per wavefront in LDS.
+__device__ __forceinline__ void smc_select(const SetupArgs& a, unsigned int* hist)
 {
-#pragma clang fp contract(off)
-    __shared__ double sd[SMC_MAX_N];
-    __shared__ double m_sh[8];
-    __shared__ double v_sh;
-    __shared__ double sig_sh[64];
     __shared__ unsigned long long sel_prefix;
     __shared__ unsigned int sel_rank;
-    __shared__ double l_sh[64];
-    __shared__ int status_sh;
-    static_assert(SMC_CHUNK * 6 <= SMC_MAX_N, "staging chunk exceeds the distance array");
-    double* sw = sd;
-    float* sth = reinterpret_cast<float*>(sd + SMC_CHUNK);
-    double* sC = sd + 5 * SMC_CHUNK;  // running sums of the chunk, stored coalesced
-    const int tid = threadIdx.x;
-    const int N = a.N;
-    // phase A: running weight sums (lane 64), sums of W theta (lanes 0..7)
-    double sc = 0.0, sm = 0.0;
-    for (int c0 = 0; c0 < N; c0 += SMC_CHUNK) {
-        const int m = min(SMC_CHUNK, N - c0);
-        smc_stage_chunk(a, c0, m, sw, sth);
-        __syncthreads();
-        if (tid == 64) {
-            int j = 0;
-            for (; j + SMC_PF <= m; j += SMC_PF) {
-                double wv[SMC_PF];
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) wv[k] = sw[j + k];
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) {
-                    sc = sc + wv[k];
-                    sC[j + k] = sc;
-                }
-            }
-            for (; j < m; ++j) {
-                sc = sc + sw[j];
-                sC[j] = sc;
-            }
-        }
-        if (tid < 8) {
-            int j = 0;
-            for (; j + SMC_PF <= m; j += SMC_PF) {
-                double wv[SMC_PF];
-                float tv[SMC_PF];
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) {
-                    wv[k] = sw[j + k];
-                    tv[k] = sth[8 * (j + k) + tid];
-                }
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) sm = sm + wv[k] * (double)tv[k];
-            }
-            for (; j < m; ++j) sm = sm + sw[j] * (double)sth[8 * j + tid];
-        }
-        __syncthreads();
-        for (int j = tid; j < m; j += blockDim.x) a.C[c0 + j] = sC[j];
-    }
-    if (tid == 64) {
-        v_sh = sc;
-        a.st->total = sc;
-    }
-    __syncthreads();
-    if (tid < 8) {
-        m_sh[tid] = sm / v_sh;
-        a.st->mean[tid] = m_sh[tid];
-    }
-    __syncthreads();
-    // phase B: covariance entries (a >= b), one lane each
-    int r = 0, c = 0;
-    double mr = 0.0, mc = 0.0, sv = 0.0;
-    if (tid < 36) {
-        while ((r + 1) * (r + 2) / 2 <= tid) ++r;
-        c = tid - r * (r + 1) / 2;
-        mr = m_sh[r];
-        mc = m_sh[c];
-    }
-    for (int c0 = 0; c0 < N; c0 += SMC_CHUNK) {
-        const int m = min(SMC_CHUNK, N - c0);
-        smc_stage_chunk(a, c0, m, sw, sth);
-        __syncthreads();
-        if (tid < 36) {
-            int j = 0;
-            for (; j + SMC_PF <= m; j += SMC_PF) {
-                double wv[SMC_PF];
-                float tr[SMC_PF], tc[SMC_PF];
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) {
-                    wv[k] = sw[j + k];
-                    tr[k] = sth[8 * (j + k) + r];
-                    tc[k] = sth[8 * (j + k) + c];
-                }
-#pragma unroll
-                for (int k = 0; k < SMC_PF; ++k) {
-                    const double dr = (double)tr[k] - mr;
-                    const double dc = (double)tc[k] - mc;
-                    sv = sv + wv[k] * (dr * dc);
-                }
-            }
-            for (; j < m; ++j) {
-                const double dr = (double)sth[8 * j + r] - mr;
-                const double dc = (double)sth[8 * j + c] - mc;
-                sv = sv + sw[j] * (dr * dc);
-            }
-        }
-        __syncthreads();  // the chunk is replaced next
-    }
-    if (tid < 36) {
-        const double sg = 2.0 * (sv / v_sh);
-        a.st->sigma[8 * r + c] = sg;
-        a.st->sigma[8 * c + r] = sg;
-        sig_sh[8 * r + c] = sg;
-    }
-    // previous distances as order-preserving 64-bit keys, SMC_SEL_PER per thread
+    const int tid = threadIdx.x, N = a.N;
     uint64_t key[SMC_SEL_PER];
 #pragma unroll
     for (int e = 0; e < SMC_SEL_PER; ++e) {
         const int j = tid + e * SMC_SETUP_THREADS;
         key[e] = j < N ? order_key(a.dist[j]) : 0ull;
+    }
+    uint64_t prefix = 0;
+    unsigned int rank = (unsigned int)a.kth;  // 1-based, among keys matching prefix
+    for (int shift = 56; shift >= 0; shift -= 8) {
+        for (int b = tid; b < 16 * 256; b += SMC_SETUP_THREADS) hist[b] = 0u;
+        __syncthreads();
+        const uint64_t hmask = shift == 56 ? 0ull : (~0ull << (shift + 8));
+        unsigned int* hw = hist + 256 * (tid >> 6);
+#pragma unroll
+        for (int e = 0; e < SMC_SEL_PER; ++e) {
+            const int j = tid + e * SMC_SETUP_THREADS;
+            if (j < N && (key[e] & hmask) == prefix)
+                atomicAdd(&hw[(unsigned)(key[e] >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        if (tid < 64) {
+            unsigned int c[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                unsigned int t = 0;
+                for (int w = 0; w < 16; ++w) t += hist[256 * w + 4 * tid + q];
+                c[q] = t;
+            }
+            const unsigned int tot = c[0] + c[1] + c[2] + c[3];
+            unsigned int incl = tot;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned int v = __shfl_up(incl, o, 64);
+                if (tid >= o) incl += v;
+            }
+            const unsigned int excl = incl - tot;
+            if (excl < rank && rank <= incl) {
+                unsigned int run = excl;
+                int q = 0;
+                while (q < 3 && run + c[q] < rank) run += c[q++];
+                sel_prefix = prefix | ((uint64_t)(4 * tid + q) << shift);
+                sel_rank = rank - run;
+            }
+        }
+        __syncthreads();
+        prefix = sel_prefix;
+        rank = sel_rank;
+    }
+    if (tid == 0) {
+        const double q = key_value(prefix);
+        a.st->eps64 = q;
+        const double f = (double)a.eps_min;
+        a.st->eps = (float)(q > f ? q : f);
+        tell(&a.host->eps, a.st->eps);
+    }
+}
+
+// Workgroup 0: the sums run left to right over the particles in single lanes so
+// that every rounding matches the plainly written definition. Only their adds
+// are serial: pairs of wavefronts form the products of 128 particles each, a
+// particle per lane and loaded seven chunks ahead, into two LDS buffers in turn,
+// and the first wavefront adds the chunk before theirs. Bound by those two
+// chains of N dependent float64 additions. Workgroup 1 selects eps meanwhile.
+// An addition waits 16 cycles for the one before it, so N = 4096 cannot take
+// less than 55 us: 77, and 157 with the loads and products between the adds.
+__global__ __launch_bounds__(SMC_SETUP_THREADS) void k_smc_setup(SetupArgs a)
+{
+#pragma clang fp contract(off)
+    __shared__ double buf[2][SU_CHUNK * SU_SUMS2];
+    __shared__ double m_sh[8];
+    __shared__ double v_sh;
+    __shared__ double sig_sh[64];
+    if (blockIdx.x == 1) {
+        smc_select(a, reinterpret_cast<unsigned int*>(&buf[0][0]));
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = a.N, chunks = (N + SU_CHUNK - 1) / SU_CHUNK;
+    const int pair = wv >= 1 && wv <= 2 * SU_PAIRS ? (wv - 1) >> 1 : -1;
+    const int at = ((wv - 1) & 1) * 64 + lane;  // particle of the pair's chunk
+    if (wv == 0) __builtin_amdgcn_s_setprio(3);
+    float th[8] = {};
+    double w = 0.0;
+    auto load = [&](int chunk) {
+        const int j = chunk * SU_CHUNK + at;
+        if (j < N) {
+            const float* src = a.theta + (int64_t)8 * j;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) th[k] = src[k];
+            w = a.w[j];
+        }
+    };
+    // phase A: running weight sums (lane 0), sums of W theta (lanes 1..8)
+    if (pair >= 0) load(pair);
+    double sum = 0.0;
+    for (int it = 0; it < chunks + 2; ++it) {
+        if (pair == it % SU_PAIRS) {
+            double* row = &buf[it & 1][at * SU_SUMS1];
+            if (it >= 2 && (it - 2) * SU_CHUNK + at < N) a.C[(it - 2) * SU_CHUNK + at] = row[0];
+            if (it < chunks) {
+                row[0] = w;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) row[1 + k] = w * (double)th[k];
+                load(it + SU_PAIRS);
+            }
+        }
+        if (wv == 0 && lane < SU_SUMS1 && it >= 1 && it <= chunks)
+            sum = ordered_sum<SU_SUMS1, true>(sum, buf[(it - 1) & 1], lane, min(SU_CHUNK, N - (it - 1) * SU_CHUNK));
+        __syncthreads();
+    }
+    if (pair >= 0) load(pair);
+    if (tid == 0) {
+        v_sh = sum;
+        a.st->total = sum;
+    }
+    __syncthreads();
+    if (tid >= 1 && tid < SU_SUMS1) {
+        m_sh[tid - 1] = sum / v_sh;
+        a.st->mean[tid - 1] = m_sh[tid - 1];
+    }
+    __syncthreads();
+    // phase B: covariance entries (r >= c), one lane each
+    double mean[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) mean[k] = m_sh[k];
+    sum = 0.0;
+    for (int it = 0; it < chunks + 1; ++it) {
+        if (it < chunks && pair == it % SU_PAIRS) {
+            double* row = &buf[it & 1][at * SU_SUMS2];
+            double d[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) d[k] = (double)th[k] - mean[k];
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int c = 0; c <= r; ++c) row[r * (r + 1) / 2 + c] = w * (d[r] * d[c]);
+            load(it + SU_PAIRS);
+        }
+        if (wv == 0 && lane < 36 && it >= 1)
+            sum = ordered_sum<SU_SUMS2, false>(sum, buf[(it - 1) & 1], lane, min(SU_CHUNK, N - (it - 1) * SU_CHUNK));
+        __syncthreads();
+    }
+    if (tid < 36) {
+        int r = 0;
+        while ((r + 1) * (r + 2) / 2 <= tid) ++r;
+        const int c = tid - r * (r + 1) / 2;
+        const double sg = 2.0 * (sum / v_sh);
+        a.st->sigma[8 * r + c] = sg;
+        a.st->sigma[8 * c + r] = sg;
+        sig_sh[8 * r + c] = sg;
     }
     __syncthreads();
     // phase C: Cholesky-Banachiewicz, row by row (lane 0). Fully unrolled so
@@ -255,83 +331,9 @@ __global__ __launch_bounds__(SMC_SETUP_THREADS) void k_smc_setup(SetupArgs a)
 #pragma unroll
         for (int i = 0; i < 64; ++i) {
             a.st->L[i] = L[i];
-            l_sh[i] = L[i];
         }
         a.st->status = bad;
-        status_sh = bad;
-    }
-    // phase D: eps_t is the kth smallest previous distance: radix selection
-    // over the keys, 8 bits per pass from the most significant, with one
-    // histogram per wavefront in LDS (the distance array is free by now).
-    {
-        unsigned int* hist = reinterpret_cast<unsigned int*>(sd);  // [16][256]
-        uint64_t prefix = 0;
-        unsigned int rank = (unsigned int)a.kth;  // 1-based, among keys matching prefix
-        for (int shift = 56; shift >= 0; shift -= 8) {
-            for (int b = tid; b < 16 * 256; b += SMC_SETUP_THREADS) hist[b] = 0u;
-            __syncthreads();
-            const uint64_t hmask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-            unsigned int* hw = hist + 256 * (tid >> 6);
-#pragma unroll
-            for (int e = 0; e < SMC_SEL_PER; ++e) {
-                const int j = tid + e * SMC_SETUP_THREADS;
-                if (j < N && (key[e] & hmask) == prefix)
-                    atomicAdd(&hw[(unsigned)(key[e] >> shift) & 255u], 1u);
-            }
-            __syncthreads();
-            if (tid < 64) {
-                unsigned int c[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    unsigned int t = 0;
-                    for (int w = 0; w < 16; ++w) t += hist[256 * w + 4 * tid + q];
-                    c[q] = t;
-                }
-                const unsigned int tot = c[0] + c[1] + c[2] + c[3];
-                unsigned int incl = tot;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const unsigned int v = __shfl_up(incl, o, 64);
-                    if (tid >= o) incl += v;
-                }
-                const unsigned int excl = incl - tot;
-                if (excl < rank && rank <= incl) {
-                    unsigned int run = excl;
-                    int q = 0;
-                    while (q < 3 && run + c[q] < rank) run += c[q++];
-                    sel_prefix = prefix | ((uint64_t)(4 * tid + q) << shift);
-                    sel_rank = rank - run;
-                }
-            }
-            __syncthreads();
-            prefix = sel_prefix;
-            rank = sel_rank;
-        }
-        if (tid == 0) {
-            const double q = key_value(prefix);
-            a.st->eps64 = q;
-            const double f = (double)a.eps_min;
-            a.st->eps = (float)(q > f ? q : f);
-        }
-    }
-    __syncthreads();
-    // phase E: whitened particles y_j = L^-1 theta_j (forward substitution)
-    if (status_sh == 0) {
-        double L[64];
-#pragma unroll
-        for (int i = 0; i < 64; ++i) L[i] = l_sh[i];
-        for (int j = tid; j < N; j += blockDim.x) {
-            double yv[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                double s = (double)a.theta[8 * j + r];
-#pragma unroll
-                for (int k = 0; k < r; ++k) s = s - L[8 * r + k] * yv[k];
-                yv[r] = s / L[8 * r + r];
-            }
-#pragma unroll
-            for (int r = 0; r < 8; ++r) a.y[8 * j + r] = yv[r];
-        }
+        tell(&a.host->status, bad);
     }
 }
 
@@ -346,6 +348,8 @@ struct ProposeArgs {
     const SmcState* st;
     float* theta;         // [n][8]
     int32_t* anc;         // [n] or null
+    double* y;            // [N][8]: the whitened particles, or null
+    int32_t blocks;       // workgroups that propose; the ones after them whiten
 };
 
 __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, const Math64& tab, double& z0, double& z1)
@@ -359,45 +363,78 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, const Math64&
     z1 = r * sn;
 }
 
-__global__ __launch_bounds__(256) void k_smc_propose(ProposeArgs a)
+// The running sums lie in LDS, where the search is a chain of 12 or 13 dependent
+// reads, and so does the factor. Workgroups of 1024 threads, one or two on a CU,
+// so that few of them copy the sums; the whitening ones use a wavefront each.
+// 2^20 candidates from 4096 particles: 36 us, 63 with the search and the factor
+// in global memory; float64 issue bounds it.
+constexpr int WHITEN_BLOCK = 64;
+constexpr int PROPOSE_BLOCK = 1024;
+
+__global__ __launch_bounds__(PROPOSE_BLOCK) void k_smc_propose(ProposeArgs a)
 {
 #pragma clang fp contract(off)
+    extern __shared__ double C[];  // [N]
     __shared__ Math64 tab;
+    __shared__ __align__(16) double L[64];
+    if (threadIdx.x < 64) L[threadIdx.x] = a.st->L[threadIdx.x];
+    if ((int)blockIdx.x >= a.blocks) {
+        // y_j = L^-1 theta_j (forward substitution); without a factor the host
+        // stops before this
+        __syncthreads();
+        const int j = ((int)blockIdx.x - a.blocks) * WHITEN_BLOCK + (int)threadIdx.x;
+        if ((int)threadIdx.x >= WHITEN_BLOCK || j >= a.N) return;
+        double yv[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            double s = (double)a.prev[8 * j + r];
+#pragma unroll
+            for (int k = 0; k < r; ++k) s = s - L[8 * r + k] * yv[k];
+            yv[r] = s / L[8 * r + r];
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) a.y[8 * j + r] = yv[r];
+        return;
+    }
     stage_math64(tab);
+    for (int j = threadIdx.x; j < a.N; j += PROPOSE_BLOCK) C[j] = a.C[j];
     __syncthreads();
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.n) return;
-    const uint64_t i = a.first + (uint64_t)k;
-    const uint4 w0 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 0));
-    const uint4 w1 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 1));
-    const uint4 w2 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 2));
-    const double u = (double)(((uint64_t)w0.x << 21) | (uint64_t)(w0.y >> 11)) * 0x1p-53;
-    double z[8];
-    box_muller(w0.z, w0.w, tab, z[0], z[1]);
-    box_muller(w1.x, w1.y, tab, z[2], z[3]);
-    box_muller(w1.z, w1.w, tab, z[4], z[5]);
-    box_muller(w2.x, w2.y, tab, z[6], z[7]);
-    // smallest j with C_j > u C_{N-1}
-    const double target = u * a.C[a.N - 1];
-    int lo = 0, hi = a.N;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a.C[mid] > target) hi = mid;
-        else lo = mid + 1;
-    }
-    const int j = lo < a.N ? lo : a.N - 1;
-    float out[8];
+    for (int64_t k = (int64_t)blockIdx.x * PROPOSE_BLOCK + threadIdx.x; k < a.n; k += (int64_t)a.blocks * PROPOSE_BLOCK) {
+        const uint64_t i = a.first + (uint64_t)k;
+        const uint4 w0 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 0));
+        const uint4 w1 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 1));
+        const uint4 w2 = stream_words(a.key, i, a.series, ctr_word3(0, DOMAIN_SMC, 2));
+        const double u = (double)(((uint64_t)w0.x << 21) | (uint64_t)(w0.y >> 11)) * 0x1p-53;
+        // smallest j with C_j > u C_{N-1}
+        const double target = u * C[a.N - 1];
+        int lo = 0, hi = a.N;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (C[mid] > target) hi = mid;
+            else lo = mid + 1;
+        }
+        const int j = lo < a.N ? lo : a.N - 1;
+        float base[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        double acc = (double)a.prev[8 * j + r];
+        for (int r = 0; r < 8; ++r) base[r] = a.prev[8 * j + r];
+        double z[8];
+        box_muller(w0.z, w0.w, tab, z[0], z[1]);
+        box_muller(w1.x, w1.y, tab, z[2], z[3]);
+        box_muller(w1.z, w1.w, tab, z[4], z[5]);
+        box_muller(w2.x, w2.y, tab, z[6], z[7]);
+        float out[8];
 #pragma unroll
-        for (int c = 0; c <= r; ++c) acc = acc + a.st->L[8 * r + c] * z[c];
-        out[r] = (float)acc;
+        for (int r = 0; r < 8; ++r) {
+            double acc = (double)base[r];
+#pragma unroll
+            for (int c = 0; c <= r; ++c) acc = acc + L[8 * r + c] * z[c];
+            out[r] = (float)acc;
+        }
+        float4* p = reinterpret_cast<float4*>(a.theta + 8 * k);
+        p[0] = make_float4(out[0], out[1], out[2], out[3]);
+        p[1] = make_float4(out[4], out[5], out[6], out[7]);
+        if (a.anc) a.anc[k] = j;
     }
-    float4* p = reinterpret_cast<float4*>(a.theta + 8 * k);
-    p[0] = make_float4(out[0], out[1], out[2], out[3]);
-    p[1] = make_float4(out[4], out[5], out[6], out[7]);
-    if (a.anc) a.anc[k] = j;
 }
 
 __global__ void k_smc_zero_u64(unsigned long long* p)
@@ -407,7 +444,8 @@ __global__ void k_smc_zero_u64(unsigned long long* p)
 
 // Number of rows of theta [m][8] inside the closed box (added to *count).
 // Candidates inside the prior box: grid-stride count, one atomic per workgroup.
-constexpr int BOX_GRID = 1024;
+// (1024 workgroups took 14 us, ten of them for their additions to one word)
+constexpr int BOX_GRID = 256;
 
 __global__ __launch_bounds__(256) void k_smc_count_box(const float* theta, int64_t m, abc_prior box,
                                                        unsigned long long* count)
@@ -435,12 +473,37 @@ __global__ __launch_bounds__(256) void k_smc_count_box(const float* theta, int64
     }
 }
 
-// ancestors of the kept candidate rows (row r is candidate oidx[r] - first of the chunk)
-__global__ __launch_bounds__(256) void k_smc_gather_anc(const int64_t* oidx, int64_t take, int64_t first,
-                                                        const int32_t* anc_chunk, int32_t* out)
+// The accepted rows of a chunk that the population still lacks, to its rows from
+// `got` on (row r is candidate oidx[r] - first of the chunk). A chunk whose rows
+// overflow `cap` gives none: the host reports it.
+struct TakeArgs {
+    const int64_t* count;
+    const int64_t* oidx;
+    const float* oth;
+    const double* od64;      // null: distances come later
+    const int32_t* anc;      // null: no ancestors
+    int64_t first, cap;
+    int32_t got, lack;       // rows the population has, and lacks
+    int64_t* idx;
+    float* theta;
+    double* dist;
+    int32_t* ancestors;
+    FromDevice* host;
+};
+
+__global__ __launch_bounds__(256) void k_smc_take(TakeArgs a)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < take) out[r] = anc_chunk[oidx[r] - first];
+    const int t = blockIdx.x * 256 + threadIdx.x, r = t >> 3, k = t & 7;
+    const int64_t c = *a.count;
+    if (t == 0) tell(&a.host->count, c);
+    if (c > a.cap || r >= c || r >= a.lack) return;
+    a.theta[8 * (int64_t)(a.got + r) + k] = a.oth[8 * (int64_t)r + k];
+    if (k) return;
+    const int64_t i = a.oidx[r];
+    if (r == a.lack - 1) tell(&a.host->last, i);
+    a.idx[a.got + r] = i;
+    if (a.od64) a.dist[a.got + r] = a.od64[r];
+    if (a.anc) a.ancestors[a.got + r] = a.anc[i - a.first];
 }
 
 struct SumsArgs {
@@ -501,7 +564,8 @@ __global__ __launch_bounds__(SUMS_BLOCK) void k_smc_sums(SumsArgs a)
 // w_i = 1 / sum_s partial[s][i]; W = w / (w_0 + ... + w_{N-1}); ESS = 1 / sum W^2.
 // The w_i stay in LDS for the single-lane left-to-right sum.
 __global__ __launch_bounds__(1024) void k_smc_finish(const double* partial, int32_t splits,
-                                                     int32_t N, double* W, double* ess)
+                                                     int32_t N, double* W, const unsigned long long* inbox,
+                                                     FromDevice* host)
 {
 #pragma clang fp contract(off)
     __shared__ double v_sh;
@@ -515,15 +579,7 @@ __global__ __launch_bounds__(1024) void k_smc_finish(const double* partial, int3
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        int i = 0;
-        for (; i + SMC_PF <= N; i += SMC_PF) {
-            double v[SMC_PF];
-#pragma unroll
-            for (int k = 0; k < SMC_PF; ++k) v[k] = wl[i + k];
-#pragma unroll
-            for (int k = 0; k < SMC_PF; ++k) s = s + v[k];
-        }
-        for (; i < N; ++i) s = s + wl[i];
+        for (int i = 0; i < N; i += 128) s = ordered_sum<1, false>(s, wl + i, 0, min(128, N - i));
         v_sh = s;
     }
     __syncthreads();
@@ -541,14 +597,17 @@ __global__ __launch_bounds__(1024) void k_smc_finish(const double* partial, int3
         if ((int)threadIdx.x < s) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *ess = 1.0 / red[0];
+    if (threadIdx.x == 0) {
+        tell(&host->ess, 1.0 / red[0]);
+        tell(&host->inbox, *inbox);
+    }
 }
 
-__global__ __launch_bounds__(256) void k_smc_equal(double* W, int32_t N, double* ess)
+__global__ __launch_bounds__(256) void k_smc_equal(double* W, int32_t N, FromDevice* host)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < N) W[i] = 1.0 / (double)N;
-    if (i == 0) *ess = (double)N;
+    if (i == 0) tell(&host->ess, (double)N);
 }
 
 // ---------------------------------------------------------------------------
@@ -628,8 +687,7 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
     const size_t o_od64 = o_od + up(sizeof(float) * cap);
     const size_t o_cnt = o_od64 + up(sizeof(double) * cap);
     const size_t o_box = o_cnt + 256;
-    const size_t o_ess = o_box + 256;
-    const size_t o_anc = o_ess + 256;
+    const size_t o_anc = o_box + 256;
     const size_t total = o_anc + up(sizeof(int32_t) * cap);
     void* ws = nullptr;
     if ((rc = stream_scratch(s, total, &ws, SCRATCH_SMC_WS))) return rc;
@@ -645,9 +703,12 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
     double* od64 = reinterpret_cast<double*>(base + o_od64);
     int64_t* dcnt = reinterpret_cast<int64_t*>(base + o_cnt);
     unsigned long long* dbox = reinterpret_cast<unsigned long long*>(base + o_box);
-    double* dess = reinterpret_cast<double*>(base + o_ess);
     int32_t* danc = reinterpret_cast<int32_t*>(base + o_anc);
 
+    FromDevice* host = nullptr;
+    if ((rc = stream_pinned(s, sizeof *host, reinterpret_cast<void**>(&host)))) return rc;
+    DeviceInfo info;
+    if ((rc = device_info(&info))) return rc;
     float eps = cfg->eps0;
     if (gen > 0) {
         SetupArgs sa{};
@@ -660,19 +721,14 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
         sa.eps_min = cfg->eps_min;
         sa.st = dstate;
         sa.C = dC;
-        sa.y = dy;
-        hipLaunchKernelGGL(k_smc_setup, dim3(1), dim3(SMC_SETUP_THREADS), 0, s, sa);
+        sa.host = host;
+        hipLaunchKernelGGL(k_smc_setup, dim3(2), dim3(SMC_SETUP_THREADS), 0, s, sa);
         if ((rc = check_launch("k_smc_setup"))) return rc;
-        struct {
-            float eps;
-            int32_t status;
-        } h{};
-        ABC_HIP(hipMemcpyAsync(&h, &dstate->eps, sizeof h, hipMemcpyDeviceToHost, s));
         if ((rc = sync(s))) return rc;
-        if (h.status)
+        if (host->status)
             return set_error(ABC_EINVAL, "generation %d: kernel covariance of the previous population "
                              "is not positive definite", gen);
-        eps = h.eps;
+        eps = host->eps;
     }
     hipLaunchKernelGGL(k_smc_zero_u64, dim3(1), dim3(64), 0, s, dbox);
 
@@ -696,7 +752,11 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
             pa.st = dstate;
             pa.theta = cth;
             pa.anc = ancestors ? danc : nullptr;
-            hipLaunchKernelGGL(k_smc_propose, dim3((unsigned)((chunk + 255) / 256)), dim3(256), 0, s, pa);
+            pa.y = first == 0 ? dy : nullptr;
+            const int64_t blocks = (chunk + PROPOSE_BLOCK - 1) / PROPOSE_BLOCK;
+            pa.blocks = (int32_t)(blocks < 2 * info.num_cu ? blocks : 2 * info.num_cu);
+            const int whiten = pa.y ? (n_prev + WHITEN_BLOCK - 1) / WHITEN_BLOCK : 0;
+            hipLaunchKernelGGL(k_smc_propose, dim3(pa.blocks + whiten), dim3(PROPOSE_BLOCK), sizeof(double) * n_prev, s, pa);
             if ((rc = check_launch("k_smc_propose"))) return rc;
             th_in = cth;
         }
@@ -710,30 +770,30 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
             (rc = recheck_band(ser, &md, &st, eps, cfg->band_w, cap, oidx, oth, od, nullptr, dcnt,
                                nullptr, stream, ROW_WAVE_TARGET, ROW_SCAN_ALONE, od64, true)))
             return rc;
-        int64_t c = 0;
-        ABC_HIP(hipMemcpyAsync(&c, dcnt, sizeof c, hipMemcpyDeviceToHost, s));
+        TakeArgs ta{};
+        ta.count = dcnt;
+        ta.oidx = oidx;
+        ta.oth = oth;
+        ta.od64 = cfg->band_w > 0.0f ? od64 : nullptr;
+        ta.anc = gen > 0 && ancestors ? danc : nullptr;
+        ta.first = first;
+        ta.cap = cap;
+        ta.got = got;
+        ta.lack = N - got;
+        ta.idx = idx;
+        ta.theta = theta;
+        ta.dist = dist;
+        ta.ancestors = ancestors;
+        ta.host = host;
+        hipLaunchKernelGGL(k_smc_take, dim3((unsigned)((8 * (int64_t)ta.lack + 255) / 256)), dim3(256), 0, s, ta);
+        if ((rc = check_launch("k_smc_take"))) return rc;
         if ((rc = sync(s))) return rc;
+        const int64_t c = host->count;
         if (c > cap) return set_error(ABC_EOVERFLOW, "candidate count %lld exceeds chunk_max", (long long)c);
         const int take = (int)(c < (int64_t)(N - got) ? c : (int64_t)(N - got));
         int64_t used = chunk;  // candidates of this chunk that the population consumes
-        if (take > 0) {
-            ABC_HIP(hipMemcpyAsync(idx + got, oidx, sizeof(int64_t) * take, hipMemcpyDeviceToDevice, s));
-            ABC_HIP(hipMemcpyAsync(theta + 8 * (size_t)got, oth, sizeof(float) * 8 * take,
-                                   hipMemcpyDeviceToDevice, s));
-            if (cfg->band_w > 0.0f)
-                ABC_HIP(hipMemcpyAsync(dist + got, od64, sizeof(double) * take,
-                                       hipMemcpyDeviceToDevice, s));
-            if (gen > 0 && ancestors) {
-                hipLaunchKernelGGL(k_smc_gather_anc, dim3((unsigned)((take + 255) / 256)), dim3(256), 0,
-                                   s, oidx, take, first, danc, ancestors + got);
-                if ((rc = check_launch("k_smc_gather_anc"))) return rc;
-            }
-        }
         if (got + take == N) {
-            int64_t last = 0;
-            ABC_HIP(hipMemcpyAsync(&last, oidx + take - 1, sizeof last, hipMemcpyDeviceToHost, s));
-            if ((rc = sync(s))) return rc;
-            samples = last + 1;
+            samples = host->last + 1;
             used = samples - first;
         }
         if (gen > 0) {
@@ -755,7 +815,7 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
         return rc;
     // weights
     if (gen == 0) {
-        hipLaunchKernelGGL(k_smc_equal, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, w, N, dess);
+        hipLaunchKernelGGL(k_smc_equal, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, w, N, host);
         if ((rc = check_launch("k_smc_equal"))) return rc;
     } else {
         const int bx = (N + SUMS_BLOCK - 1) / SUMS_BLOCK;
@@ -778,20 +838,16 @@ extern "C" abc_status abc_smc_generation(const abc_series* ser, const abc_model*
         sa.partial = static_cast<double*>(part);
         hipLaunchKernelGGL(k_smc_sums, dim3(bx, splits), dim3(SUMS_BLOCK), 0, s, sa);
         if ((rc = check_launch("k_smc_sums"))) return rc;
-        hipLaunchKernelGGL(k_smc_finish, dim3(1), dim3(1024), 0, s, sa.partial, splits, N, w, dess);
+        hipLaunchKernelGGL(k_smc_finish, dim3(1), dim3(1024), 0, s, sa.partial, splits, N, w, dbox, host);
         if ((rc = check_launch("k_smc_finish"))) return rc;
     }
-    unsigned long long inbox = 0;
-    double ess = 0.0;
-    ABC_HIP(hipMemcpyAsync(&inbox, dbox, sizeof inbox, hipMemcpyDeviceToHost, s));
-    ABC_HIP(hipMemcpyAsync(&ess, dess, sizeof ess, hipMemcpyDeviceToHost, s));
     if ((rc = sync(s))) return rc;
     stats->eps = eps;
     stats->pad = 0;
     stats->samples = samples;
-    stats->in_support = gen == 0 ? samples : (int64_t)inbox;
+    stats->in_support = gen == 0 ? samples : (int64_t)host->inbox;
     stats->proposed = proposed;
-    stats->ess = ess;
+    stats->ess = host->ess;
     return ABC_OK;
 }
 
