@@ -265,11 +265,21 @@ __device__ __forceinline__ uint64_t step_mask(const CompactArgs& a, int64_t s0, 
             bits |= m << (4 * q);
         }
     } else {
-        for (int q = 0; q < CT_STEPS; ++q)
-            for (int c = 0; c < 4; ++c) {
-                const int64_t k = s0 + 256 * q + 4 * lane + c;
-                if (k < a.n && a.dist[k] <= a.eps) bits |= 1ull << (4 * q + c);
-            }
+        // past the end the last sample is read again, so that sixteen loads are
+        // in flight at a time
+        const float* d = a.dist + s0;
+        const int left = (int)(a.n - s0);  // 1..CT_WAVE_SPAN - 1 samples
+#pragma unroll 1
+        for (int g = 0; g < CT_STEPS; g += 4) {
+            float v[16];
+            uint32_t m = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = d[min(256 * (g + (i >> 2)) + 4 * lane + (i & 3), left - 1)];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                m |= (256 * (g + (i >> 2)) + 4 * lane + (i & 3) < left && v[i] <= a.eps ? 1u : 0u) << i;
+            bits |= (uint64_t)m << (4 * g);
+        }
     }
     return bits;
 }

@@ -67,11 +67,35 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v)
+// Sums of a wavefront's lanes for the 46 values of every lane, by the tree over
+// lane distances 32, 16, .., 1. A lane keeps half of its values at each step and
+// its partner the other half, so a step exchanges half of what the step before
+// did: 48 exchanges in all, not 46 at each of six steps (those took 8 of the 12
+// us that a few rows need). Returns the sum of value `which`, for 46 of the lanes.
+template <int HALF>
+__device__ __forceinline__ void halve(double* s, int off, int lane)
 {
+    const bool upper = (lane & off) != 0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    for (int i = 0; i < HALF; ++i) {
+        const double keep = upper ? s[i + HALF] : s[i], give = upper ? s[i] : s[i + HALF];
+        s[i] = keep + __shfl_xor(give, off, 64);
+    }
+}
+
+__device__ __forceinline__ double wave_sums(double (&s)[48], int lane, int& which)
+{
+    halve<24>(s, 32, lane);
+    halve<12>(s, 16, lane);
+    halve<6>(s, 8, lane);
+    halve<3>(s, 4, lane);
+    s[3] = 0.0;
+    halve<2>(s, 2, lane);
+    halve<1>(s, 1, lane);
+    const int last = lane & 3;  // of three values and a padding one
+    which = ((lane >> 5) & 1) * 24 + ((lane >> 4) & 1) * 12 + ((lane >> 3) & 1) * 6 + ((lane >> 2) & 1) * 3 + last;
+    if (last == 3) which = MOM_NSUM;
+    return s[0];
 }
 
 __global__ __launch_bounds__(MOM_BLOCK) void k_moments_partial(MomArgs a)
@@ -93,9 +117,10 @@ __global__ __launch_bounds__(MOM_BLOCK) void k_moments_partial(MomArgs a)
         c[0] = u.x; c[1] = u.y; c[2] = u.z; c[3] = u.w;
         c[4] = v.x; c[5] = v.y; c[6] = v.z; c[7] = v.w;
     }
-    double s[MOM_NSUM];
+    double s[48];  // MOM_NSUM and two of padding
+    static_assert(MOM_NSUM <= 48, "padded to a multiple of 16 times 3");
 #pragma unroll
-    for (int q = 0; q < MOM_NSUM; ++q) s[q] = 0.0;
+    for (int q = 0; q < 48; ++q) s[q] = 0.0;
     // Thread t sums its rows r0 + t, r0 + t + 256, ... in order. Wavefront w
     // reads the 64 consecutive rows r0 + 64 w + 256 k + [0, 64) of its step k
     // as two fully coalesced 1 KiB streams (row halves side by side), stages
@@ -147,10 +172,10 @@ __global__ __launch_bounds__(MOM_BLOCK) void k_moments_partial(MomArgs a)
         }
         wave_lds_sync();  // the next batch overwrites the staged rows
     }
-#pragma unroll
-    for (int q = 0; q < MOM_NSUM; ++q) {
-        const double v = wave_sum_f64(s[q]);
-        if (lane == 0) red[wave][q] = v;
+    {
+        int which;
+        const double v = wave_sums(s, lane, which);
+        if (which < MOM_NSUM) red[wave][which] = v;
     }
     __syncthreads();
     if (threadIdx.x < MOM_NSUM) {
@@ -197,23 +222,20 @@ __global__ __launch_bounds__(64 * MOM_FINAL_SPLIT) void k_moments_final(MomArgs 
         tot[threadIdx.x] = v;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
+    // thread t: entry (t / 8, t % 8) of the covariance, and mean t
+    const int t = threadIdx.x;
+    if (t >= 64) return;
     if (n == 0) {
-        for (int j = 0; j < 8; ++j) a.mean[j] = NAN;
-        for (int j = 0; j < 64; ++j) a.cov[j] = NAN;
+        if (t < 8) a.mean[t] = NAN;
+        a.cov[t] = NAN;
         return;
     }
     const double v1 = tot[0], v2 = tot[1];
     const double* s1 = tot + 2;
-    for (int j = 0; j < 8; ++j) a.mean[j] = (double)a.theta[j] + s1[j] / v1;
+    if (t < 8) a.mean[t] = (double)a.theta[t] + s1[t] / v1;
     const double denom = v1 - v2 / v1;
-    int q = 10;
-    for (int j = 0; j < 8; ++j)
-        for (int l = j; l < 8; ++l) {
-            const double cj = (tot[q++] - s1[j] * s1[l] / v1) / (denom > 0.0 ? denom : NAN);
-            a.cov[8 * j + l] = cj;
-            a.cov[8 * l + j] = cj;
-        }
+    const int r = min(t >> 3, t & 7), l = max(t >> 3, t & 7);
+    a.cov[t] = (tot[10 + 8 * r - r * (r - 1) / 2 + (l - r)] - s1[r] * s1[l] / v1) / (denom > 0.0 ? denom : NAN);
 }
 
 }  // namespace abc

@@ -9,15 +9,17 @@
 //   k_nk_minmax   min / max key of the distances below +inf and their count;
 //   k_nk_hist     4096 linear bins over a key range (or, for a run of equal
 //                 keys, over the sample index), wavefront-private LDS counts;
-//                 the host narrows the range to the bin holding the k-th key
-//                 until at most NK_CAP samples lie at or below the threshold
-//                 (each pass shrinks the range 4096-fold);
+//                 the last workgroup narrows the range to the bin holding the
+//                 k-th key until at most NK_CAP samples lie at or below the
+//                 threshold (each pass shrinks the range 4096-fold);
 //   k_nk_collect  composite keys (key << 32 | index) of those samples;
-//   k_nk_finish   one workgroup sorts them in LDS (bitonic), keeps the first
-//                 k, re-sorts those by index and writes the rows.
-// Each pass reads the distances once (4 B per sample); the host synchronises
-// once per pass.
+//   k_nk_finish   one workgroup orders them (counted ranks, or a bitonic sort in
+//                 LDS), keeps the first k in index order and writes the rows.
+// Each pass reads the distances once (4 B per sample). The host launches all of
+// them with one histogram pass and synchronises once, for the count of finite
+// distances; a range that needs more passes costs a synchronisation each.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "common.hpp"
@@ -42,13 +44,22 @@ __device__ __forceinline__ uint32_t order_key(float d)
 
 constexpr uint32_t KEY_POS_INF = 0xFF800000u;  // order_key(+inf)
 
+// What the kernels pass on, and the host reads up to hist.
 struct NkCtl {
     uint32_t kmin, kmax;
     unsigned long long finite;
-    uint32_t count;  // collected rows
-    uint32_t pad;
+    uint64_t lo, hi;     // range of the next histogram pass: keys, or indices of a tie
+    uint64_t below;      // rows strictly below it
+    uint64_t tidx;       // threshold: rows with key < tkey, or == tkey and index <= tidx
+    uint32_t tkey;
+    uint32_t mode, tie;  // 0: keys; 1: indices of the rows with key == tie
+    int32_t state;       // NK_OPEN: another pass is needed
+    uint32_t count;      // collected rows
+    uint32_t ticket;     // workgroups of the running pass that have finished
     uint32_t hist[NK_BINS];
 };
+
+constexpr int32_t NK_OPEN = 0, NK_FITS = 1, NK_LOST = 2, NK_STUCK = 3;
 
 __global__ __launch_bounds__(256) void k_nk_init(NkCtl* c)
 {
@@ -57,7 +68,28 @@ __global__ __launch_bounds__(256) void k_nk_init(NkCtl* c)
         c->kmin = 0xFFFFFFFFu;
         c->kmax = 0u;
         c->finite = 0ull;
+        c->below = 0ull;
+        c->mode = 0u;
+        c->tie = 0u;
+        c->state = NK_OPEN;
         c->count = 0u;
+        c->ticket = 0u;
+    }
+}
+
+// calls f(k, order_key(dist[k])) for this thread's samples of a grid-stride
+// pass, four loads at a time; past the end the last sample is read again
+template <typename F>
+__device__ __forceinline__ void nk_each(const float* dist, int64_t n, F f)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k0 < n; k0 += 4 * stride) {
+        float d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) d[u] = dist[k0 + u * stride < n ? k0 + u * stride : n - 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k0 + u * stride < n) f(k0 + u * stride, order_key(d[u]));
     }
 }
 
@@ -65,15 +97,13 @@ __global__ __launch_bounds__(256) void k_nk_minmax(const float* dist, int64_t n,
 {
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;
     uint64_t cnt = 0;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t key = order_key(dist[k]);
+    nk_each(dist, n, [&](int64_t, uint32_t key) {
         if (key < KEY_POS_INF) {  // below +inf (NaN and +inf excluded)
             mn = min(mn, key);
             mx = max(mx, key);
             ++cnt;
         }
-    }
+    });
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
@@ -105,41 +135,100 @@ __global__ __launch_bounds__(256) void k_nk_minmax(const float* dist, int64_t n,
     }
 }
 
+// One histogram pass over the range of the control block (FIRST: all keys):
 // mode 0: keys in [lo, hi], bin = (key - lo) / width;
 // mode 1: key == tie and index in [lo, hi], bin = (index - lo) / width.
+// The workgroup that finishes last finds the bin with the k-th row and leaves
+// the threshold, or the range of the next pass.
 struct HistArgs {
     const float* dist;
     int64_t n;
-    int32_t mode;
-    uint32_t tie;
-    uint64_t lo, hi, width;
+    int32_t k;
+    int32_t first;
     NkCtl* c;
 };
 
 __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
 {
     __shared__ uint32_t h[4][NK_BINS];  // one histogram per wavefront
-    const int wv = threadIdx.x >> 6;
+    __shared__ uint32_t wave_tot[4];
+    __shared__ bool last;
+    NkCtl* c = a.c;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (c->finite < (unsigned long long)a.k) return;  // the host reports it
+    const uint32_t mode = c->mode, tie = c->tie;
+    const uint64_t lo = a.first ? c->kmin : c->lo, hi = a.first ? c->kmax : c->hi;
+    const uint64_t width = (hi - lo + NK_BINS) / NK_BINS;  // ceil of the span over the bins
     for (int b = threadIdx.x; b < 4 * NK_BINS; b += blockDim.x) (&h[0][0])[b] = 0u;
     __syncthreads();
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < a.n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t key = order_key(a.dist[k]);
-        uint64_t v;
-        bool in;
-        if (a.mode == 0) {
-            v = key;
-            in = v >= a.lo && v <= a.hi;
-        } else {
-            v = (uint64_t)k;
-            in = key == a.tie && v >= a.lo && v <= a.hi;
-        }
-        if (in) atomicAdd(&h[wv][(int)((v - a.lo) / a.width)], 1u);
-    }
+    // keys and indices are below 2^32, so are the range and its bins
+    const uint32_t lo32 = (uint32_t)lo, span32 = (uint32_t)(hi - lo), w32 = (uint32_t)width;
+    nk_each(a.dist, a.n, [&](int64_t k, uint32_t key) {
+        const uint32_t v = mode == 0 ? key : (uint32_t)k;
+        if (v >= lo32 && v - lo32 <= span32 && (mode == 0 || key == tie)) atomicAdd(&h[wv][(v - lo32) / w32], 1u);
+    });
     __syncthreads();
     for (int b = threadIdx.x; b < NK_BINS; b += blockDim.x) {
         const uint32_t s = h[0][b] + h[1][b] + h[2][b] + h[3][b];
-        if (s) atomicAdd(&a.c->hist[b], s);
+        if (s) atomicAdd(&c->hist[b], s);
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&c->ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    // thread t holds bins 16 t .. 16 t + 15; the first bin whose running sum
+    // reaches k
+    uint32_t x[NK_BINS / 256], own = 0;
+#pragma unroll
+    for (int q = 0; q < NK_BINS / 256; ++q) {
+        x[q] = __hip_atomic_load(&c->hist[threadIdx.x * (NK_BINS / 256) + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        own += x[q];
+    }
+    uint32_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wave_tot[wv] = incl;
+    __syncthreads();
+    uint32_t excl = incl - own, total = 0;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wv) excl += wave_tot[w];
+        total += wave_tot[w];
+    }
+    const uint64_t below = c->below, want = (uint64_t)a.k;
+    if (threadIdx.x == 0) {
+        c->ticket = 0u;
+        if (below + total < want) c->state = NK_LOST;
+    }
+    if (below + excl < want && want <= below + excl + own) {
+        uint64_t cum = below + excl;
+        int q = 0;
+        while (cum + x[q] < want) cum += x[q++];
+        const uint64_t blo = lo + (uint64_t)(threadIdx.x * (NK_BINS / 256) + q) * width;
+        const uint64_t bhi = blo + width - 1 < hi ? blo + width - 1 : hi;
+        c->tkey = mode == 0 ? (uint32_t)bhi : tie;
+        c->tidx = mode == 0 ? UINT64_MAX : bhi;
+        if (cum + x[q] <= (uint64_t)NK_CAP) {
+            c->state = NK_FITS;
+        } else {
+            c->below = cum;
+            if (width == 1 && mode == 0) {
+                // a run of equal keys: continue on the sample index
+                c->mode = 1u;
+                c->tie = (uint32_t)blo;
+                c->lo = 0;
+                c->hi = (uint64_t)a.n - 1;
+            } else if (width == 1) {
+                c->state = NK_STUCK;
+            } else {
+                c->lo = blo;
+                c->hi = bhi;
+            }
+        }
     }
 }
 
@@ -149,26 +238,32 @@ __global__ __launch_bounds__(256) void k_nk_clear_hist(NkCtl* c)
 }
 
 // rows with key < tkey, or key == tkey and index <= tidx
-__global__ __launch_bounds__(256) void k_nk_collect(const float* dist, int64_t n, uint32_t tkey,
-                                                    uint64_t tidx, NkCtl* c, uint64_t* out)
+__global__ __launch_bounds__(256) void k_nk_collect(const float* dist, int64_t n, NkCtl* c, uint64_t* out)
 {
+    if (c->state != NK_FITS) return;
+    const uint32_t tkey = c->tkey;
+    const uint64_t tidx = c->tidx;
     const int lane = threadIdx.x & 63;
-    for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x; k0 < n; k0 += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = k0 + threadIdx.x;
-        uint32_t key = 0xFFFFFFFFu;
-        bool sel = false;
-        if (k < n) {
-            key = order_key(dist[k]);
-            sel = key < tkey || (key == tkey && (uint64_t)k <= tidx);
-        }
-        const uint64_t m = __ballot(sel);
-        if (m == 0ull) continue;
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&c->count, (uint32_t)__popcll(m));
-        base = (uint32_t)__shfl((int)base, 0, 64);
-        if (sel) {
-            const uint32_t r = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            if (r < (uint32_t)NK_CAP) out[r] = ((uint64_t)key << 32) | (uint64_t)k;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x; b0 < n; b0 += 4 * stride) {
+        const int64_t k0 = b0 + threadIdx.x;
+        float d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) d[u] = dist[k0 + u * stride < n ? k0 + u * stride : n - 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t k = k0 + u * stride;
+            const uint32_t key = order_key(d[u]);
+            const bool sel = k < n && (key < tkey || (key == tkey && (uint64_t)k <= tidx));
+            const uint64_t m = __ballot(sel);
+            if (m == 0ull) continue;
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&c->count, (uint32_t)__popcll(m));
+            base = (uint32_t)__shfl((int)base, 0, 64);
+            if (sel) {
+                const uint32_t r = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                if (r < (uint32_t)NK_CAP) out[r] = ((uint64_t)key << 32) | (uint64_t)k;
+            }
         }
     }
 }
@@ -213,10 +308,55 @@ __device__ __forceinline__ float key_to_float(uint32_t key)
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
+__device__ __forceinline__ void finish_row(const FinishArgs& a, int r, int64_t loc)
+{
+    const uint64_t i = a.first + (uint64_t)loc;
+    a.out_idx[r] = (int64_t)i;
+    if (a.out_dist) a.out_dist[r] = a.dist[loc];
+    if (a.out_theta) {
+        float th[8];
+        if (a.theta) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) th[j] = a.theta[8 * loc + j];
+        } else {
+            prior_draw(a.key, i, a.series, a.domain, a.lo, a.width, th);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a.out_theta[8 * r + j] = th[j];
+    }
+}
+
+// Up to this many rows are ranked by counting the smaller ones (110 rows: 6 us);
+// the two sorts of more rows are 20 or more barriers each (110 rows: 14 us).
+constexpr int NK_RANK_MAX = 512;
+
 __global__ __launch_bounds__(1024) void k_nk_finish(FinishArgs a)
 {
     extern __shared__ uint64_t v[];  // [NK_CAP]
+    __shared__ uint32_t chosen[NK_RANK_MAX];  // indices of the first k, else all ones
+    if (a.c->state != NK_FITS) return;
     const int cnt = (int)min(a.c->count, (uint32_t)NK_CAP);
+    if (cnt <= NK_RANK_MAX) {
+        const int t = threadIdx.x;
+        const uint64_t own = t < cnt ? a.cand[t] : 0ull;
+        if (t < cnt) v[t] = own;
+        __syncthreads();
+        int r = 0;  // the composite keys are distinct
+        if (t < cnt) {
+#pragma unroll 8
+            for (int j = 0; j < cnt; ++j) r += v[j] < own ? 1 : 0;
+            chosen[t] = r < a.k ? (uint32_t)own : 0xFFFFFFFFu;
+            if (r == a.k - 1 && a.out_kth) *a.out_kth = key_to_float((uint32_t)(own >> 32));
+        }
+        __syncthreads();
+        if (t < cnt && r < a.k) {
+            int pos = 0;
+#pragma unroll 8
+            for (int j = 0; j < cnt; ++j) pos += chosen[j] < (uint32_t)own ? 1 : 0;
+            finish_row(a, pos, (int64_t)(uint32_t)own);
+        }
+        return;
+    }
     int npow = 1;
     while (npow < cnt) npow <<= 1;
     for (int t = threadIdx.x; t < npow; t += blockDim.x) v[t] = t < cnt ? a.cand[t] : ~0ull;
@@ -234,23 +374,7 @@ __global__ __launch_bounds__(1024) void k_nk_finish(FinishArgs a)
     for (int t = threadIdx.x; t < kpow; t += blockDim.x) v[t] = mine[nm++];
     __syncthreads();
     bitonic_u64(v, kpow);
-    for (int r = threadIdx.x; r < a.k; r += blockDim.x) {
-        const int64_t loc = (int64_t)v[r];
-        const uint64_t i = a.first + (uint64_t)loc;
-        a.out_idx[r] = (int64_t)i;
-        if (a.out_dist) a.out_dist[r] = a.dist[loc];
-        if (a.out_theta) {
-            float th[8];
-            if (a.theta) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) th[j] = a.theta[8 * loc + j];
-            } else {
-                prior_draw(a.key, i, a.series, a.domain, a.lo, a.width, th);
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) a.out_theta[8 * r + j] = th[j];
-        }
-    }
+    for (int r = threadIdx.x; r < a.k; r += blockDim.x) finish_row(a, r, (int64_t)v[r]);
 }
 
 // ---------------------------------------------------------------------------
@@ -258,11 +382,9 @@ __global__ __launch_bounds__(1024) void k_nk_finish(FinishArgs a)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool row_less(double da, int64_t ia, double db, int64_t ib)
 {
-    // NaN sorts after every number
+    // NaN sorts after every number (no branches: rows are compared in bulk)
     const bool na = da != da, nb = db != db;
-    if (na != nb) return nb;
-    if (!na && da != db) return da < db;
-    return ia < ib;
+    return (nb & !na) | (da < db) | (((da == db) | (na & nb)) & (ia < ib));
 }
 
 __global__ __launch_bounds__(256) void k_rows_rank(const double* d, const int64_t* idx, int64_t n,
@@ -316,11 +438,64 @@ __global__ __launch_bounds__(256) void k_rows_place(const double* d, const int64
         for (int j = 0; j < 8; ++j) out_theta[8 * pos + j] = theta[8 * q + j];
 }
 
-// workgroups of the grid-stride passes: about 16 samples per thread, so a
+// The same for a set that one workgroup's lanes hold, a row each, from LDS and in
+// one launch (114 rows: 11 us; two launches took 11 and 9, each a chain of loads).
+constexpr int ROWS_SMALL = 1024;
+
+__global__ __launch_bounds__(ROWS_SMALL) void k_rows_small(const double* d, const int64_t* idx, const float* theta,
+                                                           int32_t n, int32_t k, int64_t* out_idx, float* out_theta,
+                                                           double* out_d)
+{
+    // rows past n compare as greater than any: the loops run over whole eights
+    __shared__ double ds[ROWS_SMALL];
+    __shared__ int64_t is[ROWS_SMALL];
+    __shared__ int64_t sel[ROWS_SMALL];  // index of a kept row, else the largest
+    const int q = threadIdx.x;
+    const double dq = q < n ? d[q] : NAN;
+    const int64_t iq = q < n ? idx[q] : INT64_MAX;
+    ds[q] = dq;
+    is[q] = iq;
+    __syncthreads();
+    int r = 0;
+    if (q < n)
+        for (int j = 0; j < n; j += 8) {
+            double dj[8];
+            int64_t ij[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { dj[u] = ds[j + u]; ij[u] = is[j + u]; }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r += row_less(dj[u], ij[u], dq, iq) ? 1 : 0;
+        }
+    sel[q] = q < n && r < k ? iq : INT64_MAX;
+    __syncthreads();
+    if (q >= n || r >= k) return;
+    int pos = 0;  // selected rows with a smaller sample index
+    for (int j = 0; j < n; j += 8) {
+        int64_t ij[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ij[u] = sel[j + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) pos += ((ij[u] < iq) | ((ij[u] == iq) & (j + u < q))) ? 1 : 0;
+    }
+    out_idx[pos] = iq;
+    if (out_d) out_d[pos] = dq;
+    if (out_theta)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) out_theta[8 * (int64_t)pos + j] = theta[8 * (int64_t)q + j];
+}
+
+// workgroups of the histogram pass: about 16 samples per thread, so a
 // short input does not pay for hundreds of LDS histogram clears and merges
 static unsigned nk_grid(int64_t n)
 {
     const int64_t g = (n + 4095) / 4096;
+    return (unsigned)(g < NK_GRID ? (g > 0 ? g : 1) : NK_GRID);
+}
+
+// and of the passes without a histogram: four samples per thread
+static unsigned nk_grid_light(int64_t n)
+{
+    const int64_t g = (n + 1023) / 1024;
     return (unsigned)(g < NK_GRID ? (g > 0 ? g : 1) : NK_GRID);
 }
 
@@ -354,77 +529,13 @@ extern "C" abc_status abc_nearest_k(const float* dist, const float* theta, const
     }
     NkCtl* dc = static_cast<NkCtl*>(mem);
     uint64_t* cand = reinterpret_cast<uint64_t*>(static_cast<char*>(mem) + ctl_bytes);
-    const unsigned grid = nk_grid(n);
-    hipLaunchKernelGGL(k_nk_init, dim3(1), dim3(256), 0, s, dc);
-    hipLaunchKernelGGL(k_nk_minmax, dim3(grid), dim3(256), 0, s, dist, n, dc);
-    abc_status rc = check_launch("k_nk_minmax");
-    if (rc) return rc;
-    struct {
-        uint32_t kmin, kmax;
-        unsigned long long finite;
-    } mm{};
-    ABC_HIP(hipMemcpyAsync(&mm, dc, sizeof mm, hipMemcpyDeviceToHost, s));
-    ABC_HIP(hipStreamSynchronize(s));
-    if (mm.finite < (unsigned long long)k)
-        return set_error(ABC_EINVAL, "only %llu of the %lld distances are finite, fewer than k = %d",
-                         mm.finite, (long long)n, k);
-
-    // narrow [lo, hi] on the key until the rows at or below the threshold fit
-    uint32_t tkey = mm.kmax;
-    uint64_t tidx = UINT64_MAX;
-    uint64_t below = 0;  // rows strictly below the current range
-    uint64_t lo = mm.kmin, hi = mm.kmax;
-    uint32_t hist[NK_BINS];
-    int mode = 0;
-    uint32_t tie = 0;
-    bool fits = false;
-    for (int pass = 0; pass < 16 && !fits; ++pass) {
-        const uint64_t span = hi - lo + 1;
-        const uint64_t width = (span + NK_BINS - 1) / NK_BINS;
-        HistArgs ha{dist, n, mode, tie, lo, hi, width, dc};
-        hipLaunchKernelGGL(k_nk_clear_hist, dim3(1), dim3(256), 0, s, dc);
-        hipLaunchKernelGGL(k_nk_hist, dim3(grid), dim3(256), 0, s, ha);
-        if ((rc = check_launch("k_nk_hist"))) return rc;
-        ABC_HIP(hipMemcpyAsync(hist, dc->hist, sizeof hist, hipMemcpyDeviceToHost, s));
-        ABC_HIP(hipStreamSynchronize(s));
-        uint64_t cum = below;
-        int b = 0;
-        for (; b < NK_BINS; ++b) {
-            if (cum + hist[b] >= (uint64_t)k) break;
-            cum += hist[b];
-        }
-        if (b == NK_BINS) return set_error(ABC_EHIP, "nearest-k: histogram lost rows");
-        const uint64_t blo = lo + (uint64_t)b * width;
-        const uint64_t bhi = blo + width - 1 < hi ? blo + width - 1 : hi;
-        const uint64_t at_or_below = cum + hist[b];
-        if (mode == 0) {
-            tkey = (uint32_t)bhi;
-            tidx = UINT64_MAX;
-        } else {
-            tkey = tie;
-            tidx = bhi;
-        }
-        if (at_or_below <= (uint64_t)NK_CAP) {
-            fits = true;
-            break;
-        }
-        below = cum;
-        if (width == 1 && mode == 0) {
-            // a run of equal keys: continue on the sample index
-            mode = 1;
-            tie = (uint32_t)blo;
-            lo = 0;
-            hi = (uint64_t)n - 1;
-        } else if (width == 1) {
-            return set_error(ABC_EHIP, "nearest-k: index refinement did not converge");
-        } else {
-            lo = blo;
-            hi = bhi;
-        }
+    constexpr size_t HEAD = offsetof(NkCtl, hist);
+    void* pinned = nullptr;
+    {
+        const abc_status rs = stream_pinned(s, HEAD, &pinned);
+        if (rs) return rs;
     }
-    if (!fits) return set_error(ABC_EHIP, "nearest-k: threshold search did not converge");
-    hipLaunchKernelGGL(k_nk_collect, dim3(grid), dim3(256), 0, s, dist, n, tkey, tidx, dc, cand);
-    if ((rc = check_launch("k_nk_collect"))) return rc;
+    const NkCtl* h = static_cast<const NkCtl*>(pinned);  // up to hist
     fa.cand = cand;
     fa.c = dc;
     fa.k = k;
@@ -435,8 +546,29 @@ extern "C" abc_status abc_nearest_k(const float* dist, const float* theta, const
     fa.out_theta = out_theta;
     fa.out_dist = out_dist;
     fa.out_kth = out_kth;
-    hipLaunchKernelGGL(k_nk_finish, dim3(1), dim3(1024), sizeof(uint64_t) * NK_CAP, s, fa);
-    return check_launch("k_nk_finish");
+    HistArgs ha{dist, n, k, 1, dc};
+    abc_status rc;
+    hipLaunchKernelGGL(k_nk_init, dim3(1), dim3(256), 0, s, dc);
+    hipLaunchKernelGGL(k_nk_minmax, dim3(nk_grid_light(n)), dim3(256), 0, s, dist, n, dc);
+    for (int pass = 0; pass < 16; ++pass) {
+        // narrow the range until the rows at or below the threshold fit; with a
+        // pass that leaves it open the last two kernels do nothing
+        if (pass > 0) hipLaunchKernelGGL(k_nk_clear_hist, dim3(1), dim3(256), 0, s, dc);
+        ha.first = pass == 0;
+        hipLaunchKernelGGL(k_nk_hist, dim3(nk_grid(n)), dim3(256), 0, s, ha);
+        hipLaunchKernelGGL(k_nk_collect, dim3(nk_grid_light(n)), dim3(256), 0, s, dist, n, dc, cand);
+        hipLaunchKernelGGL(k_nk_finish, dim3(1), dim3(1024), sizeof(uint64_t) * NK_CAP, s, fa);
+        if ((rc = check_launch("k_nk_finish"))) return rc;
+        ABC_HIP(hipMemcpyAsync(pinned, dc, HEAD, hipMemcpyDeviceToHost, s));
+        ABC_HIP(hipStreamSynchronize(s));
+        if (h->finite < (unsigned long long)k)
+            return set_error(ABC_EINVAL, "only %llu of the %lld distances are finite, fewer than k = %d",
+                             h->finite, (long long)n, k);
+        if (h->state == NK_FITS) return ABC_OK;
+        if (h->state == NK_LOST) return set_error(ABC_EHIP, "nearest-k: histogram lost rows");
+        if (h->state == NK_STUCK) return set_error(ABC_EHIP, "nearest-k: index refinement did not converge");
+    }
+    return set_error(ABC_EHIP, "nearest-k: threshold search did not converge");
 }
 
 extern "C" abc_status abc_nearest_k_rows(const double* dist64, const int64_t* idx, const float* theta,
@@ -448,6 +580,11 @@ extern "C" abc_status abc_nearest_k_rows(const double* dist64, const int64_t* id
     ABC_REQUIRE(n >= 1 && n <= 65536, "n must be in [1, 65536]");
     ABC_REQUIRE(k >= 1 && k <= n, "k must be in [1, n]");
     const hipStream_t s = as_stream(stream);
+    if (n <= ROWS_SMALL) {
+        hipLaunchKernelGGL(k_rows_small, dim3(1), dim3(ROWS_SMALL), 0, s, dist64, idx, theta, (int32_t)n, k, out_idx,
+                           out_theta, out_dist);
+        return check_launch("k_rows_small");
+    }
     void* mem = nullptr;
     {
         const abc_status rs = stream_scratch(s, sizeof(int32_t) * (size_t)n, &mem);
