@@ -436,7 +436,10 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
     uint32_t filled = 0xFFFFFFFFu;  // chunk currently in the ring
     BLane L[SPL];
 #pragma unroll
-    for (int k = 0; k < SPL; ++k) L[k].w = 0u;
+    for (int k = 0; k < SPL; ++k) {
+        L[k] = BLane{};  // idle, with a valid state (no people) and the first row
+        L[k].s = state_d(0, 0, 0, 0, 0);
+    }
     uint64_t days_done = 0;         // of the whole wavefront
 
     while (true) {
@@ -485,25 +488,23 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
         }
         // a refill can land every idle lane on the unused tail of a series'
         // last chunk; the wave ends only when the queue is exhausted too
-        if (any == 0ull) {
-            if (qb >= Q) break;
-            continue;
-        }
+        if (any == 0ull && qb >= Q) break;
         // the last trajectories of a wavefront's queue are what the next round
         // but one waits for: they go before the next round's wavefronts
         if (qb >= Q) __builtin_amdgcn_s_setprio(1);
 
 #pragma unroll
         for (int k = 0; k < SPL; ++k) {
+            // idle lanes take the day too and drop it (as in k_simulate_f32)
             BLane& l = L[k];
-            if (l.w == 0u) continue;
+            const bool live = l.w != 0u;
             const float4 ob = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.obs_table) + l.p);
             const uint4 words = l.ph.day(l.w, l.b1, a.key);
             float lr, ld, comp = 0.0f;
             day_distance_f32<0, 0, false>(l.s, l.r, words, l.invP, a.nc, ob, l.acc, comp, lr, ld);
             const bool exited = l.acc > l.exit2;
-            uint32_t wn = l.w + 256u;
-            if (exited | (l.w == l.wend)) {
+            const bool done = exited | (l.w == l.wend);
+            if (done & live) {
                 if (!exited) {
                     const float dd = finish_distance_f32(l.acc, 0.693147180559945309417f);
                     const SeriesDesc& ds = a.desc[l.series];
@@ -521,10 +522,10 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
                         }
                     }
                 }
-                wn = 0u;
             }
-            l.w = wn;
-            l.p += (uint32_t)sizeof(float4);
+            const bool idle = done | !live;
+            l.w = idle ? 0u : l.w + 256u;
+            l.p = idle ? 0u : l.p + (uint32_t)sizeof(float4);
         }
     }
     if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);

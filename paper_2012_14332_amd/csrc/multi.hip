@@ -162,7 +162,7 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
     if (wg >= a.nchunks) return;
     // queue positions of this wave (the host keeps them within 32 bits); its
     // j-th chunk is wg + j nw
-    const uint32_t Q = (uint32_t)(((a.nchunks - 1 - wg) / nw + 1) << 6);
+    const uint32_t Q = __builtin_amdgcn_readfirstlane((uint32_t)(((a.nchunks - 1 - wg) / nw + 1) << 6));
     const float nc = noise_c(a.scale);
     const float dscale = DIST == 0 ? 0.693147180559945309417f : 1.0f;
     // the chunk in the ring (wave-uniform): its series, the offset of its
@@ -200,8 +200,10 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
 
     uint32_t qb = 0;
     uint32_t filled = 0xFFFFFFFFu;
-    MLane l;
-    l.w = 0u;
+    const uint32_t row1 = lds_address(lds_f);
+    MLane l{};  // idle, with a valid state (no people) and row
+    l.s = state_d(0, 0, 0, 0, 0);
+    l.p = row1;
     uint64_t days_done = 0;  // of the whole wavefront
 
     while (true) {
@@ -238,12 +240,11 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
             }
             m = __ballot(l.w == 0u);
         }
-        if (m == ~0ull) {
-            if (qb >= Q) break;
-            continue;
-        }
+        if (m == ~0ull && qb >= Q) break;
         days_done += (uint64_t)__popcll(~m);
-        if (l.w != 0u) {
+        // idle lanes take the day too and drop it (as in k_simulate_f32)
+        const bool live = l.w != 0u;
+        {
             const float4 ob = lds_row(l.p);
             const uint4 words = l.ph.day(l.w, l.b1, a.key);
             float lr, ld;
@@ -251,13 +252,11 @@ __global__ __launch_bounds__(1024) void k_simulate_multi_f32(MultiArgs a)
             float sum = l.acc;
             if (BOUND) sum += future_bound(__float_as_uint(ob.w), lr, ld);
             const bool exited = sum > l.exitb;
-            uint32_t wn = l.w + 256u;
-            if (exited | (l.w == l.wend)) {
-                *l.out = exited ? INFINITY : finish_distance_f32(l.acc, dscale);
-                wn = 0u;
-            }
-            l.w = wn;
-            l.p += (uint32_t)sizeof(float4);
+            const bool done = exited | (l.w == l.wend);
+            if (done & live) *l.out = exited ? INFINITY : finish_distance_f32(l.acc, dscale);
+            const bool idle = done | !live;
+            l.w = idle ? 0u : l.w + 256u;
+            l.p = idle ? row1 : l.p + (uint32_t)sizeof(float4);
         }
     }
     if (a.days && lane == 0) atomicAdd(a.days, (unsigned long long)days_done);
