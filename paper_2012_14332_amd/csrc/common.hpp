@@ -96,6 +96,16 @@ __device__ __forceinline__ uint32_t mask_rank(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Orders one wavefront's LDS writes before its lanes read what other lanes
+// wrote (and reads before the next writes): a wavefront-scope fence pair
+// around a wave barrier, which the compiler does not move accesses across.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Compute units and LDS bytes per workgroup of the current device, queried
 // once per device (attribute queries cost tens of microseconds each, too much
 // for a per-launch path).

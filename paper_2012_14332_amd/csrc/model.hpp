@@ -480,12 +480,13 @@ __device__ __forceinline__ void walk_window(RowWalk& w, int nd, const double* zr
     }
 }
 
-template <int NOISE, int DIST>
+template <int NOISE, int DIST, bool EXIT = false>
 __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rth, const uint64_t* rix,
                                                          Key key, uint32_t series, uint32_t domain,
                                                          int32_t P, int32_t A0, int32_t R0, int32_t D0,
                                                          int T, double scale, const double* lobs,
-                                                         const Math64& tab, double* zs, int32_t* xs)
+                                                         const Math64& tab, double* zs, int32_t* xs,
+                                                         double exit_at = 0.0)
 {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
@@ -529,14 +530,14 @@ __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rt
                 for (int k = 0; k < 5; ++k) zs[5 * (r * W + u) + k] = z[k];
             }
         }
-        __syncthreads();
+        wave_lds_sync();
         if (walker) {
             if (all_mid)
                 walk_window<NOISE, true>(wk, nd, zs + 5 * row * W, xs + 4 * row * W, tab);
             else
                 walk_window<NOISE, false>(wk, nd, zs + 5 * row * W, xs + 4 * row * W, tab);
         }
-        __syncthreads();
+        wave_lds_sync();
 #pragma unroll 1
         for (int p = lane; p < nr * 3 * nd; p += 64) {
             const int r = p / (3 * nd), q = p - r * 3 * nd;
@@ -546,7 +547,7 @@ __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rt
             const double d = (DIST == 0 ? log1p_count_f64(X, tab) : (double)X) - lobs[c * T + t];
             zs[5 * r * W + q] = d * d;
         }
-        __syncthreads();
+        wave_lds_sync();
         if (lane < nr) {
             const double* tr = zs + 5 * lane * W;
             int q = 0;
@@ -559,8 +560,10 @@ __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rt
             }
             for (; q < 3 * nd; ++q) acc += tr[q];
         }
-        __syncthreads();  // the window's scratch is reused by the next one
+        wave_lds_sync();  // the window's scratch is reused by the next one
+        if (EXIT && __ballot(lane < nr && !(acc > exit_at)) == 0ull) break;
     }
+    if (EXIT && acc > exit_at) return INFINITY;  // the sum only grows
     return lane < nr ? sqrt_mid(acc) : 0.0;
 }
 

@@ -57,16 +57,6 @@ __device__ __forceinline__ int64_t rows_used(const MomArgs& a)
     return n;
 }
 
-// Orders one wavefront's LDS writes before its lanes read what other lanes
-// wrote (and reads before the next writes): a wavefront-scope fence pair
-// around a wave barrier, which the compiler does not move accesses across.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Sums of a wavefront's lanes for the 46 values of every lane, by the tree over
 // lane distances 32, 16, .., 1. A lane keeps half of its values at each step and
 // its partner the other half, so a step exchanges half of what the step before

@@ -63,3 +63,25 @@ def test_exit_bound_changes_no_distance(T):
         _, d = abc.simulate_distance(ser, 4000, 3, flags=abc.ABC_FP64 | flags, want64=True, eps_exit=eps)
         inside = full <= eps
         assert torch.equal(d[inside], full[inside]) and bool(torch.isinf(d[~inside]).all())
+
+
+@pytest.mark.parametrize("n", [1, 3, 64, 700, 5000, 40_000])
+@pytest.mark.parametrize("T", [7, 33, 49, 300])
+@pytest.mark.parametrize("flags", [0x1, 0x1 | 0x8, 0x1 | 0x4])
+def test_last_samples_walked_as_rows(n, T, flags):
+    """Exits leave few samples to a wavefront, which then walks them again side by
+    side: same distances as a pass without exits, infinite past the bound."""
+    import torch
+    from paper_2012_14332_amd import abc
+    P = 60_000_000
+    obs = O.observe(O.make_model(P, T), np.array([0.3, 15, 0.4, 0.01, 0.4, 0.01, 0.5, 0.6], np.float32), 4)
+    ser = abc.DeviceSeries(P, T, torch.tensor(obs))
+    full = abc.simulate_distance(ser, n, 11, flags=flags, want64=True)[1]
+    for q in (0.0, 0.02, 0.5, 1.0):
+        eps = float(torch.quantile(full, q))
+        d32, got = abc.simulate_distance(ser, n, 11, flags=flags, eps_exit=eps, want64=True)
+        inside = full <= float(np.float32(eps))
+        assert torch.equal(got[inside], full[inside]), (q, n)
+        # beyond the tolerance a sample is either ended or finished
+        assert torch.all(torch.isinf(got[~inside]) | (got[~inside] == full[~inside]))
+        assert torch.equal(d32, got.float())
