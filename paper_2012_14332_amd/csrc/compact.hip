@@ -214,7 +214,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_compact(CompactArgs a)
 
 // ---------------------------------------------------------------------------
 // Two-pass compaction (abc_accept_compact). Each wavefront owns a unit of
-// consecutive samples (16 steps of 4096; fewer below CP_STEP_EMIT samples). Pass 1 streams the unit's distances once and,
+// consecutive samples (1 to 16 steps of 4096). Pass 1 streams the unit's distances once and,
 // with no dependency on any other wavefront, counts its accepted samples and
 // keeps the unit offsets of the first CP_SLOTS of them in sample order. A
 // single workgroup then forms the exclusive prefix of the unit counts, and
@@ -223,19 +223,15 @@ __global__ __launch_bounds__(64 * WAVES) void k_compact(CompactArgs a)
 // again. Rows come out in sample-index order, exactly as from the look-back
 // kernel above; the streaming pass has no ticket and no look-back to wait on.
 // ---------------------------------------------------------------------------
-constexpr int CP_CHUNKS = 16;                        // 4096-sample steps per unit
+constexpr int CP_CHUNKS = 16;                        // 4096-sample steps per unit, at most
+constexpr int CP_UNITS = 4096;                       // units per input, at least, while steps last
 constexpr int CP_SLOTS = 64;                         // accepted offsets kept per unit
 constexpr int CP_WAVES = 4;                          // wavefronts per workgroup
-// Below this many samples the units shrink to about 256 per input (down to
-// one step), so that a short input spreads over many wavefronts instead of a
-// few walking 16 steps each, and pass 1 also keeps each step's count so that
-// pass 2 runs one wavefront per step: a unit with more accepts than kept
-// offsets is then written by all its steps at once instead of one wavefront
-// streaming it again (high acceptance, as in the SMC generations). Larger
-// inputs keep 16-step units and one emit wavefront per unit, as most extra
-// wavefronts would find nothing. The order of the rows does not depend on
-// either choice.
-constexpr int64_t CP_STEP_EMIT = (int64_t)1 << 22;
+// An input is cut into about CP_UNITS units, of one step to CP_CHUNKS, so that it
+// spreads over many wavefronts and a unit that holds more accepts than kept
+// offsets is short to stream again. With 16 steps above 2^22 samples the count of
+// 1e7 was 152 wavefronts, 27 us (now 11), and the whole compaction of 1e7 samples
+// with 5e4 accepts 320 us (now 34).
 
 struct CpArgs {
     CompactArgs a;
@@ -245,7 +241,6 @@ struct CpArgs {
     uint32_t* cnt;   // [units]
     uint32_t* slot;  // [units][CP_SLOTS]
     int64_t* pref;   // [units]
-    uint32_t* scnt;  // [units][chunks] accepts per step, or null (one emit wavefront per unit)
 };
 
 // Accept mask of one 4096-sample step of a unit: bit 4 q + c for sample
@@ -323,7 +318,6 @@ __global__ __launch_bounds__(64 * CP_WAVES) void k_cp_count(CpArgs p)
                 if (r < CP_SLOTS) slot[r] = (uint32_t)(k - start);
             });
         total += c;
-        if (p.scnt && lane == 0) p.scnt[u * p.chunks + j] = (uint32_t)c;
     }
     if (lane == 0) p.cnt[u] = (uint32_t)total;
 }
@@ -381,38 +375,6 @@ __global__ __launch_bounds__(64 * CP_WAVES) void k_cp_emit(CpArgs p)
             emit_row(p.a, k, base + r);
         });
     }
-}
-
-// Pass 2 with one wavefront per step (inputs below CP_STEP_EMIT): a unit
-// within its kept offsets is written by its first step's wavefront; otherwise
-// each step's wavefront writes that step's accepts after those of the unit's
-// earlier steps.
-__global__ __launch_bounds__(64 * CP_WAVES) void k_cp_emit_steps(CpArgs p)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * CP_WAVES + (threadIdx.x >> 6);
-    const int64_t u = w / p.chunks;
-    const int j = (int)(w - u * p.chunks);
-    if (u >= p.units) return;
-    const uint32_t c = p.cnt[u];
-    if (c == 0) return;
-    const int64_t base = p.pref[u];
-    if (base >= p.a.capacity) return;
-    const int64_t start = u * p.span;
-    if (c <= (uint32_t)CP_SLOTS) {
-        if (j != 0) return;
-        for (uint32_t q = lane; q < c; q += 64)
-            emit_row(p.a, start + p.slot[u * CP_SLOTS + q], base + q);
-        return;
-    }
-    const int64_t s0 = start + (int64_t)j * CT_WAVE_SPAN;
-    if (s0 >= p.a.n) return;
-    const uint32_t* sc = p.scnt + u * p.chunks;
-    int64_t off = 0;
-    for (int q = 0; q < j; ++q) off += sc[q];
-    if (sc[j] == 0u || base + off >= p.a.capacity) return;
-    const uint64_t bits = step_mask(p.a, s0, lane);
-    step_visit(bits, s0, lane, 0, [&](int64_t k, int64_t r) { emit_row(p.a, k, base + off + r); });
 }
 
 }  // namespace abc
@@ -543,24 +505,18 @@ extern "C" abc_status abc_accept_compact(const float* dist, const float* theta,
     // stream's buffer
     CpArgs p{};
     p.a = a;
-    p.chunks = CP_CHUNKS;
-    if (n < CP_STEP_EMIT) {
-        const int64_t c = (n + CT_WAVE_SPAN * 256 - 1) / (CT_WAVE_SPAN * 256);  // about 256 units
-        p.chunks = c < 1 ? 1 : (int32_t)c;
-    }
+    const int64_t c = (n + (int64_t)CT_WAVE_SPAN * CP_UNITS - 1) / ((int64_t)CT_WAVE_SPAN * CP_UNITS);
+    p.chunks = c < 1 ? 1 : (c < CP_CHUNKS ? (int32_t)c : CP_CHUNKS);
     p.span = (int64_t)CT_WAVE_SPAN * p.chunks;
     p.units = (n + p.span - 1) / p.span;
     const int64_t units = p.units > 0 ? p.units : 1;
-    const bool steps = n < CP_STEP_EMIT;
     void* mem = nullptr;
     const size_t bytes = sizeof(int64_t) * (size_t)units + sizeof(uint32_t) * (size_t)units +
-                         sizeof(uint32_t) * (size_t)CP_SLOTS * (size_t)units +
-                         (steps ? sizeof(uint32_t) * (size_t)p.chunks * (size_t)units : 0);
+                         sizeof(uint32_t) * (size_t)CP_SLOTS * (size_t)units;
     if ((rc = stream_scratch(s, bytes, &mem))) return rc;
     p.pref = static_cast<int64_t*>(mem);
     p.cnt = reinterpret_cast<uint32_t*>(p.pref + units);
     p.slot = p.cnt + units;
-    p.scnt = steps ? p.slot + (size_t)CP_SLOTS * (size_t)units : nullptr;
     const unsigned grid = (unsigned)((units + CP_WAVES - 1) / CP_WAVES);
     if (p.units > 0) {
         hipLaunchKernelGGL(k_cp_count, dim3(grid), dim3(64 * CP_WAVES), 0, s, p);
@@ -569,15 +525,8 @@ extern "C" abc_status abc_accept_compact(const float* dist, const float* theta,
     hipLaunchKernelGGL(k_cp_scan, dim3(1), dim3(1024), 0, s, p);  // also writes the count
     if ((rc = check_launch("k_cp_scan"))) return rc;
     if (p.units > 0 && capacity > 0) {
-        if (steps) {
-            const int64_t waves = p.units * p.chunks;
-            hipLaunchKernelGGL(k_cp_emit_steps, dim3((unsigned)((waves + CP_WAVES - 1) / CP_WAVES)),
-                               dim3(64 * CP_WAVES), 0, s, p);
-            rc = check_launch("k_cp_emit_steps");
-        } else {
-            hipLaunchKernelGGL(k_cp_emit, dim3(grid), dim3(64 * CP_WAVES), 0, s, p);
-            rc = check_launch("k_cp_emit");
-        }
+        hipLaunchKernelGGL(k_cp_emit, dim3(grid), dim3(64 * CP_WAVES), 0, s, p);
+        rc = check_launch("k_cp_emit");
     }
     return rc;
 }

@@ -100,3 +100,17 @@ def test_moments_of_a_few_rows(n, weighted):
     c = x - m
     want = (v[:, None, None] * c[:, :, None] * c[:, None, :]).sum(0) / (v.sum() - (v * v).sum() / v.sum())
     assert np.max(np.abs(cov - want)) <= 1e-12 and np.array_equal(cov, cov.T)
+
+
+# a unit of one step, of two, and of the most; accepts none, few and more than its kept offsets
+@pytest.mark.parametrize("n", [16_777_216, 16_777_217, 40_000_001, 300_000_000])
+@pytest.mark.parametrize("q", [0.0, 1e-5, 1e-3])
+def test_compaction_units(n, q):
+    import torch
+    from paper_2012_14332_amd import abc
+    d = torch.rand(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    d[n // 3: n // 3 + 9000] = 0.0 if q else 0.5  # a run of accepts across steps
+    idx, _, dd, _, count = abc.accept_compact(d, q, 1 << 20, seed=3)
+    want = torch.nonzero(d <= q).flatten()
+    c = int(count)
+    assert c == want.numel() and torch.equal(idx[:c], want) and torch.equal(dd[:c], d[want])
