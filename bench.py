@@ -26,14 +26,14 @@ sys.path.insert(0, ROOT)
 METRIC = "accepted ABC samples/s at fixed ε (sim-days/s, VALU %); plain vs learned proposal"
 # Algorithmic work of the float32 simulate kernel, counted class by class in
 # its gfx950 assembly (the blocks of one simulated day, and the block that
-# prepares one sample in a wave's ring). One simulated day: 158 VALU
-# instructions -- 22 transcendental, 16 v_mad_u64_u32 (Philox), 18
-# conversions, 54 integer/bit, 15 FMA, 16 multiplies, 5 adds, 8
-# compares/selects, 4 moves -- not counting the 10 of the lower-bound lookup
-# (an optimisation, not the method's work). One sample: 120 (the prior draw's
-# two Philox calls, theta, the rates, the initial state, the hoisted Philox
-# words; 13 register moves not counted).
-FP32_FLOP_PER_SAMPLE_DAY = 73     # FMA 2, add / multiply / transcendental 1
+# prepares one sample in a wave's ring). One simulated day: 132 VALU
+# instructions -- 19 transcendental, 16 v_mad_u64_u32 (Philox), 12
+# conversions, 48 integer/bit, 15 FMA, 16 multiplies, 4 adds, 2 compares --
+# not counting the 8 of the lower-bound lookup (an optimisation, not the
+# method's work) and the 3 that keep idle lanes idle. One sample: 125 (the
+# prior draw's two Philox calls, theta, the rates, the initial state, the
+# hoisted Philox words; 13 register moves not counted).
+FP32_FLOP_PER_SAMPLE_DAY = 69     # FMA 2, add / multiply / transcendental 1
 FP32_FLOP_PER_SAMPLE = 25
 # VALU issue in instruction slots: a SIMD issues one wave64 VALU instruction
 # per quad-cycle. A transcendental occupies its wave for 2 quad-cycles (a
@@ -42,8 +42,8 @@ FP32_FLOP_PER_SAMPLE = 25
 # beside it (SQ_ACTIVE_INST_VALU, which counts it twice, exceeds the SIMD's
 # quad-cycles at eight waves per SIMD), so the issue model counts every
 # instruction once and the transcendental unit as a resource of its own.
-ISSUE_PER_SAMPLE_DAY = 158
-ISSUE_PER_SAMPLE = 120
+ISSUE_PER_SAMPLE_DAY = 132
+ISSUE_PER_SAMPLE = 125
 # The batched round kernel's day step has no bound lookup either.
 BATCH_ISSUE_PER_SAMPLE_DAY = ISSUE_PER_SAMPLE_DAY
 # Issue peak in lane-instructions/s: 256 CUs x 4 SIMDs x 64 lanes x 2.4e9 / 4.
