@@ -480,7 +480,7 @@ ABC_API abc_status abc_mdn_simulate_features(const abc_prior* prior, uint64_t se
 /* The 96 unstandardised features of an observed series (ser->obs device). */
 ABC_API abc_status abc_series_features(const abc_series* ser, float* out96, void* stream);
 
-/* Per-feature mean and sd (float64 two-pass, sd floored at 1e-6) of
+/* Per-feature mean and sd (float64 sums about the first row, sd floored at 1e-6) of
  * features [n][96] (device), kept in the net for every later call. */
 ABC_API abc_status abc_mdn_fit_standardizer(abc_mdn* net, const float* features, int64_t n,
                                             void* stream);
@@ -673,7 +673,7 @@ ABC_API abc_status abc_smc_run(const abc_series* ser, const abc_model* model,
 
 /* Library scratch. Calls that need device scratch (compaction tiles, moment
  * partials, band flags, selection histograms, SMC work space, the batched
- * quota run's buffers) or a small pinned host buffer take it from
+ * quota run's buffers, the order of many training pairs) or a small pinned host buffer take it from
  * library-owned buffers kept per (device, stream): the first calls on a stream
  * allocate it (growing it synchronises that stream once), later calls reuse it
  * without allocating, so a steady-state call never waits for the device.

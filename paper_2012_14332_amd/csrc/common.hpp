@@ -128,6 +128,7 @@ constexpr int SCRATCH_LEAF = 0;
 constexpr int SCRATCH_SMC_WS = 1;
 constexpr int SCRATCH_SMC_SUMS = 2;
 constexpr int SCRATCH_BATCH = 3;  // the batched quota run's buffers (its work runs on a stream of its own, ordered after and before s)
+constexpr int SCRATCH_PAIRS = 4;  // order of the training pairs
 abc_status stream_scratch(hipStream_t s, size_t bytes, void** out, int slot = SCRATCH_LEAF);
 // The same for pinned host memory (one buffer per (device, stream)), for
 // small results a call reads back on the host.

@@ -16,6 +16,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <vector>
 
 #include "common.hpp"
@@ -1040,6 +1041,7 @@ struct abc_mdn {
     float* fmean = nullptr;
     float* fsd = nullptr;
     float* loss_acc = nullptr;
+    double* colpart = nullptr;  // partials of the column sums
     float lo[8], hi[8], tc[8], ts[8];
     int ws = 0;  // workspace: blocks of 32 rows
     bf16* frags = nullptr;  // fragments of X, H1, H2, dOUT, dZ2, dZ1
@@ -1169,6 +1171,7 @@ extern "C" abc_status abc_mdn_create(const abc_prior* prior, uint64_t init_seed,
     e = e ? e : hipMalloc((void**)&n->fmean, NN_IN * sizeof(float));
     e = e ? e : hipMalloc((void**)&n->fsd, NN_IN * sizeof(float));
     e = e ? e : hipMalloc((void**)&n->loss_acc, sizeof(float));
+    e = e ? e : hipMalloc((void**)&n->colpart, sizeof(double) * 2 * NN_IN * CS_GROUPS);
     if (e != hipSuccess) {
         abc_mdn_destroy(n);
         return set_error(ABC_EHIP, "abc_mdn_create: %s", hipGetErrorString(e));
@@ -1195,7 +1198,7 @@ extern "C" abc_status abc_mdn_destroy(abc_mdn* n)
 {
     if (!n) return ABC_OK;
     free_ws(n);
-    void* ptrs[] = {n->p, n->pb, n->m, n->v, n->g, n->fmean, n->fsd, n->loss_acc};
+    void* ptrs[] = {n->p, n->pb, n->m, n->v, n->g, n->fmean, n->fsd, n->loss_acc, n->colpart};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete n;
@@ -1250,15 +1253,34 @@ extern "C" abc_status abc_mdn_simulate_features(const abc_prior* prior, uint64_t
     a.TP = TP;
     const hipStream_t s = as_stream(stream);
     const int bins = T_hi - T_lo + 1;
-    if (n < FEAT_SORT_MIN || n >= ((int64_t)1 << 30) || bins == 1) {
+    // The order needs scratch, which a captured call must not take (a replay
+    // would use it after it was grown or released) and a full device may not
+    // have: the samples then go unordered, with the same results. Calls of
+    // several threads on one stream share the scratch, so each enqueues its
+    // launches before the next one's.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    bool ordered = n >= FEAT_SORT_MIN && n < ((int64_t)1 << 30) && bins > 1;
+    if (ordered && (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        ordered = false;
+    }
+    static std::mutex enqueue;
+    std::unique_lock<std::mutex> lock(enqueue, std::defer_lock);
+    const int64_t room = n + 63 * (int64_t)bins;
+    void* mem = nullptr;
+    if (ordered) {
+        lock.lock();
+        if (stream_scratch(s, sizeof(uint32_t) * (2 * (size_t)bins + 1) + sizeof(int32_t) * (size_t)room, &mem, SCRATCH_PAIRS)) {
+            (void)hipGetLastError();
+            ordered = false;
+        }
+    }
+    if (!ordered) {
         hipLaunchKernelGGL(k_mdn_features, dim3(blocks_for(n)), dim3(FEAT_BLOCK), 0, s, a, nullptr, nullptr);
         return check_launch("k_mdn_features");
     }
     FeatOrder o{};
     o.bins = bins;
-    const int64_t room = n + 63 * (int64_t)bins;
-    void* mem = nullptr;
-    if ((rc = stream_scratch(s, sizeof(uint32_t) * (2 * (size_t)bins + 1) + sizeof(int32_t) * (size_t)room, &mem))) return rc;
     o.cnt = static_cast<uint32_t*>(mem);
     o.fill = o.cnt + bins;
     o.total = o.fill + bins;
@@ -1287,14 +1309,11 @@ extern "C" abc_status abc_mdn_fit_standardizer(abc_mdn* net, const float* featur
     ABC_REQUIRE(net && features && n >= 2, "need a net and >= 2 feature rows");
     const hipStream_t s = as_stream(stream);
     const int groups = (int)colstats_groups(n);
-    void* part = nullptr;
-    const abc_status rc = stream_scratch(s, sizeof(double) * 2 * NN_IN * (size_t)groups, &part);
-    if (rc) return rc;
     if ((reinterpret_cast<uintptr_t>(features) & 15u) == 0)
-        hipLaunchKernelGGL((k_colsums<true>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, static_cast<double*>(part));
+        hipLaunchKernelGGL((k_colsums<true>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, net->colpart);
     else
-        hipLaunchKernelGGL((k_colsums<false>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, static_cast<double*>(part));
-    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(64), 0, s, features, n, static_cast<const double*>(part), groups,
+        hipLaunchKernelGGL((k_colsums<false>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, net->colpart);
+    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(64), 0, s, features, n, net->colpart, groups,
                        net->fmean, net->fsd);
     return check_launch("k_colstats");
 }

@@ -35,3 +35,27 @@ def test_column_statistics(n, aligned):
     x = x.astype(np.float64)
     np.testing.assert_allclose(m, x.mean(0), rtol=1.2e-7, atol=1e-12)
     np.testing.assert_allclose(s, np.maximum(x.std(0, ddof=1), 1e-6), rtol=1.2e-7)
+
+
+def test_pairs_and_statistics_in_a_captured_graph():
+    """Captured calls take no scratch of the library's; each replay gives the eager call's values."""
+    import torch
+    from paper_2012_14332_amd import abc
+    want = abc.simulate_features(9001, 11, first=5)
+    net = abc.Mdn(0)
+    net.fit_standardizer(want[0])
+    stats = net.standardizer()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = abc.simulate_features(9001, 11, first=5)
+        net.fit_standardizer(got[0])
+        got_stats = net.standardizer()
+    for _ in range(3):
+        for t in got + got_stats:
+            t.zero_()
+        abc.simulate_features(20000, 3)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(got + got_stats, want + stats):
+            assert torch.equal(a, b)
