@@ -158,6 +158,7 @@ __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
     if (c->finite < (unsigned long long)a.k) return;  // the host reports it
     const uint32_t mode = c->mode, tie = c->tie;
     const uint64_t lo = a.first ? c->kmin : c->lo, hi = a.first ? c->kmax : c->hi;
+    const uint64_t below = c->below;  // read before any thread of the last workgroup can write it
     const uint64_t width = (hi - lo + NK_BINS) / NK_BINS;  // ceil of the span over the bins
     for (int b = threadIdx.x; b < 4 * NK_BINS; b += blockDim.x) (&h[0][0])[b] = 0u;
     __syncthreads();
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
         if (w < wv) excl += wave_tot[w];
         total += wave_tot[w];
     }
-    const uint64_t below = c->below, want = (uint64_t)a.k;
+    const uint64_t want = (uint64_t)a.k;
     if (threadIdx.x == 0) {
         c->ticket = 0u;
         if (below + total < want) c->state = NK_LOST;
