@@ -450,7 +450,7 @@ __global__ __launch_bounds__(ROWS_SMALL) void k_rows_small(const double* d, cons
     // rows past n compare as greater than any: the loops run over whole eights
     __shared__ double ds[ROWS_SMALL];
     __shared__ int64_t is[ROWS_SMALL];
-    __shared__ int64_t sel[ROWS_SMALL];  // index of a kept row, else the largest
+    __shared__ alignas(8) uint8_t keep[ROWS_SMALL];  // 1: one of the k
     const int q = threadIdx.x;
     const double dq = q < n ? d[q] : NAN;
     const int64_t iq = q < n ? idx[q] : INT64_MAX;
@@ -467,16 +467,18 @@ __global__ __launch_bounds__(ROWS_SMALL) void k_rows_small(const double* d, cons
 #pragma unroll
             for (int u = 0; u < 8; ++u) r += row_less(dj[u], ij[u], dq, iq) ? 1 : 0;
         }
-    sel[q] = q < n && r < k ? iq : INT64_MAX;
+    keep[q] = q < n && r < k ? 1 : 0;
     __syncthreads();
     if (q >= n || r >= k) return;
     int pos = 0;  // selected rows with a smaller sample index
     for (int j = 0; j < n; j += 8) {
+        const uint64_t kept = *reinterpret_cast<const uint64_t*>(&keep[j]);
         int64_t ij[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ij[u] = sel[j + u];
+        for (int u = 0; u < 8; ++u) ij[u] = is[j + u];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) pos += ((ij[u] < iq) | ((ij[u] == iq) & (j + u < q))) ? 1 : 0;
+        for (int u = 0; u < 8; ++u)
+            pos += (((kept >> (8 * u)) & 1u) != 0u) & ((ij[u] < iq) | ((ij[u] == iq) & (j + u < q))) ? 1 : 0;
     }
     out_idx[pos] = iq;
     if (out_d) out_d[pos] = dq;

@@ -65,6 +65,18 @@ def test_nearest_k_rows(n, k, kind):
     assert np.array_equal(dd.cpu().numpy(), d[want], equal_nan=True)
 
 
+@pytest.mark.parametrize("n", [9, 1025])
+def test_nearest_k_rows_of_one_index(n):
+    """Rows that share the largest index: only kept rows count for a kept row's place."""
+    import torch
+    from paper_2012_14332_amd import abc
+    d = np.arange(n, 0, -1).astype(np.float64)
+    i = np.full(n, np.iinfo(np.int64).max)
+    th = torch.zeros((n, 8), device="cuda")
+    idx, _, dd = abc.nearest_k_rows(torch.tensor(d).cuda(), torch.tensor(i).cuda(), th, 4)
+    assert np.array_equal(idx.cpu().numpy(), i[:4]) and dd.cpu().tolist() == [4.0, 3.0, 2.0, 1.0]
+
+
 @pytest.mark.parametrize("n", [1, 3, 63, 1023, 1024, 4095, 4096, 4097, 8191, 65_537])
 def test_compaction_of_a_partial_step(n):
     import torch
