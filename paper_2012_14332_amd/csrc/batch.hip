@@ -1156,6 +1156,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     int32_t phases = 0;
     std::vector<int64_t> cnt(m), used_h(m);
     std::vector<int32_t> rech(m);
+    std::vector<SeriesState> state_h(m);
     float rounds_ms = 0.0f;
     for (;;) {
         const int64_t round_cap = rounds + max_rounds;
@@ -1196,7 +1197,14 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
         ABC_HIP(hipEventRecord(t1, s));
         ABC_HIP(hipEventSynchronize(t1));
         ABC_HIP(hipEventElapsedTime(&rounds_ms, t0, t1));
-        if (rounds > 0) stopped = stopped || __atomic_load_n(flag_host + (rounds - 1) % BT_EVR, __ATOMIC_ACQUIRE) != 0;
+        if (!stopped) {
+            // the round limit came first; the last plans have not seen the last
+            // rounds' accepts, so the host looks whether any series is short
+            ABC_HIP(hipMemcpyAsync(state_h.data(), a.state, sizeof(SeriesState) * m, hipMemcpyDeviceToHost, s));
+            ABC_HIP(hipStreamSynchronize(s));
+            stopped = true;
+            for (const SeriesState& st : state_h) stopped &= st.acc >= st.target || st.next >= max_samples;
+        }
 
         ABC_HIP(hipMemsetAsync(b_re.p, 0, sizeof(int32_t) * (2 * (size_t)m + 1), s));
         hipLaunchKernelGGL(k_band_collect, dim3((unsigned)m * COLLECT_GROUPS), dim3(256), 0, s, f);
