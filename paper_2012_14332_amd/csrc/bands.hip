@@ -148,9 +148,10 @@ __global__ __launch_bounds__(768) void k_bands(BandArgs a)
             y = least_above(v, x);
         }
         if (lane == 0) {
-            const double t = h - (double)lo;
+            // what the rounding of h took away stays in the fraction: (n - 1) q - lo, rounded once
+            const double t = fma((double)(a.n - 1), a.q[k], -(double)lo);
             const double p = (double)(int32_t)(x ^ 0x80000000u), q = (double)(int32_t)(y ^ 0x80000000u);
-            a.out[((int64_t)k * (a.T + 1) + day) * 6 + half * 3 + c] = (float)(p + (q - p) * t);
+            a.out[((int64_t)k * (a.T + 1) + day) * 6 + half * 3 + c] = (float)fma(q - p, t, p);
         }
     }
 }
