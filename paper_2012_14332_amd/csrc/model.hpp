@@ -358,7 +358,15 @@ __device__ __forceinline__ int32_t draw_f64(double h, double z, double scale)
     return max(cvt_i32_sat(x), 0);  // truncation is the floor of x >= 0
 }
 
-template <int NOISE>
+// What the source gives of a draw d >= 0: all it holds at most. It holds less than
+// nothing (NEG) only after a negative kappa; then any draw but 0 takes that.
+template <bool NEG>
+__device__ __forceinline__ int32_t taken(int32_t d, int32_t avail)
+{
+    return !NEG || d > 0 ? min(d, avail) : 0;
+}
+
+template <int NOISE, bool NEG = false>
 __device__ __forceinline__ void day_step_f64(State& s, const Theta& t, bool mid, double P, double rP,
                                              double scale, const double z[5], const Math64& tab)
 {
@@ -368,11 +376,11 @@ __device__ __forceinline__ void day_step_f64(State& s, const Theta& t, bool mid,
     const double If = (double)s.I, Af = (double)s.A;
     const double h0 = g * (double)s.S * If;
     const double h1 = mid ? div_by(h0, P, rP) : div_general(h0, P);
-    const int32_t n1 = min(draw_f64<NOISE>(h1, z[0], scale), s.S);
-    const int32_t n2 = min(draw_f64<NOISE>((double)t.ga * If, z[1], scale), s.I);
-    const int32_t n3 = min(draw_f64<NOISE>((double)t.be * Af, z[2], scale), s.A);
-    const int32_t n4 = min(draw_f64<NOISE>((double)t.de * Af, z[3], scale), s.A - n3);
-    const int32_t n5 = min(draw_f64<NOISE>((double)t.be * (double)t.et * If, z[4], scale), s.I - n2);
+    const int32_t n1 = taken<NEG>(draw_f64<NOISE>(h1, z[0], scale), s.S);
+    const int32_t n2 = taken<NEG>(draw_f64<NOISE>((double)t.ga * If, z[1], scale), s.I);
+    const int32_t n3 = taken<NEG>(draw_f64<NOISE>((double)t.be * Af, z[2], scale), s.A);
+    const int32_t n4 = taken<NEG>(draw_f64<NOISE>((double)t.de * Af, z[3], scale), s.A - n3);
+    const int32_t n5 = taken<NEG>(draw_f64<NOISE>((double)t.be * (double)t.et * If, z[4], scale), s.I - n2);
     s.S -= n1;
     s.I += n1 - n2 - n5;
     s.A += n2 - n3 - n4;
@@ -396,6 +404,38 @@ __device__ __forceinline__ void stage_obs_f64(const int32_t* obs, int T, double*
         const int32_t O = obs[q];
         lds[q] = DIST == 0 ? (O >= 0 ? log1p_count_f64(O, tab) : log1p((double)O)) : (double)O;
     }
+}
+
+// A sample with a negative kappa, whose counts can be negative, from its first day
+// to its last, out of line: the loops of the float64 kernels have no room for its
+// conditions (2 % of a row walk, 5 % of k_simulate_f64), and no prior draws it.
+__device__ __forceinline__ bool negative_start(const float t[8]) { return t[7] < 0.0f; }
+
+template <int NOISE, int DIST>
+__device__ __attribute__((noinline)) double simulate_negative_f64(Theta th, uint64_t i, Key key, uint32_t series,
+                                                                  uint32_t domain, int32_t P, int32_t A0, int32_t R0,
+                                                                  int32_t D0, int T, double scale, const double* lobs,
+                                                                  const Math64* tab, double exit_at)
+{
+#pragma clang fp contract(off)
+    const float t8[8] = {th.a0, th.al, th.n, th.be, th.ga, th.de, th.et, th.ka};
+    const bool mid = theta_mid(t8);
+    const double Pd = (double)P, rP = 1.0 / Pd;
+    State s = init_state(th.ka, P, A0, R0, D0);
+    double acc = 0.0;
+    for (int t = 1; t <= T; ++t) {
+        double z[5];
+        normals_f64(stream_words(key, i, series, ctr_word3((uint32_t)t, domain, 0)), *tab, z);
+        // the power's logarithm is of a count of one or more
+        day_step_f64<NOISE, true>(s, th, mid && s.A + s.R + s.D > 0, Pd, rP, scale, z, *tab);
+        const int32_t X[3] = {s.A, s.R, s.D};
+        for (int c = 0; c < 3; ++c) {
+            const double d = (DIST == 0 ? log1p((double)X[c]) : (double)X[c]) - lobs[c * T + t - 1];
+            acc += d * d;
+        }
+        if (acc > exit_at) return (double)INFINITY;
+    }
+    return sqrt(acc);
 }
 
 // Up to ROWS_PER_WAVE_MAX float64 trajectories run by one wavefront (one

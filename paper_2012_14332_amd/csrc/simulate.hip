@@ -383,6 +383,12 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
                 if (!PRIOR && a.box && outside_box(a, thv)) {
                     a.dist[k] = INFINITY;
                     if (a.dist64) a.dist64[k] = (double)INFINITY;
+                } else if (!PRIOR && negative_start(thv)) {
+                    const double dd = simulate_negative_f64<NOISE, DIST>(
+                        theta_from(thv), a.first + (uint64_t)k, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T,
+                        scale, lobs, &tab, a.exit_f64);
+                    a.dist[k] = (float)dd;
+                    if (a.dist64) a.dist64[k] = dd;
                 } else {
                     s = init_state(thv[7], a.P, a.A0, a.R0, a.D0);
                     mid = theta_mid(thv);
@@ -494,6 +500,23 @@ __device__ __forceinline__ RowLds row_lds(double* base, int T, int R)
     return l;
 }
 
+// Distances of the nr rows gathered in LDS, row r's on lane r.
+template <int NOISE, int DIST>
+__device__ __forceinline__ double rows_f64(const SimArgs& a, const RowLds& l, int nr)
+{
+    double d = simulate_rows_f64_wave<NOISE, DIST>(nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0,
+                                                   a.T, (double)a.scale, l.lobs, *l.tab, l.zs, l.xs);
+    const int lane = threadIdx.x;
+    if (lane < nr && negative_start(l.rth + 8 * lane)) {
+        float th[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) th[k] = l.rth[8 * lane + k];
+        d = simulate_negative_f64<NOISE, DIST>(theta_from(th), l.rix[lane], a.key, a.series, a.domain, a.P, a.A0, a.R0,
+                                               a.D0, a.T, (double)a.scale, l.lobs, l.tab, (double)INFINITY);
+    }
+    return d;
+}
+
 // Pass 1: each wavefront scans a contiguous block of candidates (enough for
 // the grid to cover the candidate count, at least scan_min), 64 at a time;
 // the in-band ones are gathered, in candidate order, into groups of up to
@@ -515,9 +538,7 @@ __device__ __forceinline__ void recheck_group(const RecheckArgs& r, const RowLds
         staged = true;
     }
     __syncthreads();
-    const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
-        nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, a.T, (double)a.scale,
-        l.lobs, *l.tab, l.zs, l.xs);
+    const double d64 = rows_f64<NOISE, DIST>(a, l, nr);
     const int lane = threadIdx.x;
     if (lane < nr) {
         const int64_t qq = l.rq[lane];
@@ -670,9 +691,7 @@ __global__ __launch_bounds__(64) void k_rows_f64(RowsArgs r)
             for (int j = 0; j < 8; ++j) l.rth[8 * lane + j] = a.theta[8 * (q0 + lane) + j];
         }
         __syncthreads();
-        const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
-            nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T,
-            (double)a.scale, l.lobs, *l.tab, l.zs, l.xs);
+        const double d64 = rows_f64<NOISE, DIST>(a, l, nr);
         if (lane < nr) r.dist64[q0 + lane] = d64;
         __syncthreads();
     }
@@ -713,7 +732,8 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
         if (F64) {
             double z[5];
             normals_f64(w, tab, z);
-            day_step_f64<NOISE>(s, th, mid, (double)a.P, rP, (double)a.scale, z, tab);
+            // (the power's logarithm is of a count of one or more)
+            day_step_f64<NOISE, true>(s, th, mid && s.A + s.R + s.D > 0, (double)a.P, rP, (double)a.scale, z, tab);
         } else {
             Noise32 z;
             normals_f32(w, nc, z);
