@@ -9,9 +9,9 @@
 //   k_nk_minmax   min / max key of the distances below +inf and their count;
 //   k_nk_hist     4096 linear bins over a key range (or, for a run of equal
 //                 keys, over the sample index), wavefront-private LDS counts;
-//                 the last workgroup narrows the range to the bin holding the
-//                 k-th key until at most NK_CAP samples lie at or below the
-//                 threshold (each pass shrinks the range 4096-fold);
+//   k_nk_narrow   narrows the range to the bin holding the k-th key until at
+//                 most NK_CAP samples lie at or below the threshold (each pass
+//                 shrinks the range 4096-fold);
 //   k_nk_collect  composite keys (key << 32 | index) of those samples;
 //   k_nk_finish   one workgroup orders them (counted ranks, or a bitonic sort in
 //                 LDS), keeps the first k in index order and writes the rows.
@@ -55,7 +55,6 @@ struct NkCtl {
     uint32_t mode, tie;  // 0: keys; 1: indices of the rows with key == tie
     int32_t state;       // NK_OPEN: another pass is needed
     uint32_t count;      // collected rows
-    uint32_t ticket;     // workgroups of the running pass that have finished
     uint32_t hist[NK_BINS];
 };
 
@@ -73,7 +72,6 @@ __global__ __launch_bounds__(256) void k_nk_init(NkCtl* c)
         c->tie = 0u;
         c->state = NK_OPEN;
         c->count = 0u;
-        c->ticket = 0u;
     }
 }
 
@@ -138,8 +136,6 @@ __global__ __launch_bounds__(256) void k_nk_minmax(const float* dist, int64_t n,
 // One histogram pass over the range of the control block (FIRST: all keys):
 // mode 0: keys in [lo, hi], bin = (key - lo) / width;
 // mode 1: key == tie and index in [lo, hi], bin = (index - lo) / width.
-// The workgroup that finishes last finds the bin with the k-th row and leaves
-// the threshold, or the range of the next pass.
 struct HistArgs {
     const float* dist;
     int64_t n;
@@ -151,14 +147,11 @@ struct HistArgs {
 __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
 {
     __shared__ uint32_t h[4][NK_BINS];  // one histogram per wavefront
-    __shared__ uint32_t wave_tot[4];
-    __shared__ bool last;
     NkCtl* c = a.c;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wv = threadIdx.x >> 6;
     if (c->finite < (unsigned long long)a.k) return;  // the host reports it
     const uint32_t mode = c->mode, tie = c->tie;
     const uint64_t lo = a.first ? c->kmin : c->lo, hi = a.first ? c->kmax : c->hi;
-    const uint64_t below = c->below;  // read before any thread of the last workgroup can write it
     const uint64_t width = (hi - lo + NK_BINS) / NK_BINS;  // ceil of the span over the bins
     for (int b = threadIdx.x; b < 4 * NK_BINS; b += blockDim.x) (&h[0][0])[b] = 0u;
     __syncthreads();
@@ -173,18 +166,27 @@ __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
         const uint32_t s = h[0][b] + h[1][b] + h[2][b] + h[3][b];
         if (s) atomicAdd(&c->hist[b], s);
     }
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(&c->ticket, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
+}
+
+// What the counts of a pass leave: the threshold, or the range of the next pass, from
+// the bin with the k-th row. A launch of its own: narrowing in the histogram's
+// last workgroup takes two fences of every workgroup, each of which writes back and
+// invalidates an L2 (1e7 distances 198 us, here 153; 1e3 to 1e5 alike).
+__global__ __launch_bounds__(256) void k_nk_narrow(HistArgs a)
+{
+    __shared__ uint32_t wave_tot[4];
+    NkCtl* c = a.c;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (c->finite < (unsigned long long)a.k) return;
+    const uint32_t mode = c->mode, tie = c->tie;
+    const uint64_t lo = a.first ? c->kmin : c->lo, hi = a.first ? c->kmax : c->hi, below = c->below;
+    const uint64_t width = (hi - lo + NK_BINS) / NK_BINS;
     // thread t holds bins 16 t .. 16 t + 15; the first bin whose running sum
     // reaches k
     uint32_t x[NK_BINS / 256], own = 0;
 #pragma unroll
     for (int q = 0; q < NK_BINS / 256; ++q) {
-        x[q] = __hip_atomic_load(&c->hist[threadIdx.x * (NK_BINS / 256) + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x[q] = c->hist[threadIdx.x * (NK_BINS / 256) + q];
         own += x[q];
     }
     uint32_t incl = own;
@@ -194,17 +196,14 @@ __global__ __launch_bounds__(256) void k_nk_hist(HistArgs a)
         if (lane >= o) incl += v;
     }
     if (lane == 63) wave_tot[wv] = incl;
-    __syncthreads();
+    __syncthreads();  // and every thread has read the range before one writes the next
     uint32_t excl = incl - own, total = 0;
     for (int w = 0; w < 4; ++w) {
         if (w < wv) excl += wave_tot[w];
         total += wave_tot[w];
     }
     const uint64_t want = (uint64_t)a.k;
-    if (threadIdx.x == 0) {
-        c->ticket = 0u;
-        if (below + total < want) c->state = NK_LOST;
-    }
+    if (threadIdx.x == 0 && below + total < want) c->state = NK_LOST;
     if (below + excl < want && want <= below + excl + own) {
         uint64_t cum = below + excl;
         int q = 0;
@@ -559,6 +558,7 @@ extern "C" abc_status abc_nearest_k(const float* dist, const float* theta, const
         if (pass > 0) hipLaunchKernelGGL(k_nk_clear_hist, dim3(1), dim3(256), 0, s, dc);
         ha.first = pass == 0;
         hipLaunchKernelGGL(k_nk_hist, dim3(nk_grid(n)), dim3(256), 0, s, ha);
+        hipLaunchKernelGGL(k_nk_narrow, dim3(1), dim3(256), 0, s, ha);
         hipLaunchKernelGGL(k_nk_collect, dim3(nk_grid_light(n)), dim3(256), 0, s, dist, n, dc, cand);
         hipLaunchKernelGGL(k_nk_finish, dim3(1), dim3(1024), sizeof(uint64_t) * NK_CAP, s, fa);
         if ((rc = check_launch("k_nk_finish"))) return rc;
