@@ -2,8 +2,8 @@
 // samples with the 5th-95th percentile band): per day and compartment, the
 // requested quantiles of n recorded trajectories, and its C-ABI entry point
 // abc_trajectory_bands. Each quantile interpolates linearly between order
-// statistics h = (n - 1) q in float64; the order statistics are found by
-// bisection on the value, not by sorting.
+// statistics h = (n - 1) q in float64; the order statistics of few rows are found
+// by sorting them in registers, of many by bisection on the value.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -25,6 +25,15 @@ struct BandArgs {
 
 // unsigned image of an int32 that keeps its order
 __device__ __forceinline__ uint32_t ordered(int32_t x) { return (uint32_t)x ^ 0x80000000u; }
+
+// Quantile k between the order statistics lo (x) and lo + 1 (y). What the rounding of
+// (n - 1) q took away stays in the fraction: (n - 1) q - lo, rounded once.
+__device__ __forceinline__ void store_quantile(const BandArgs& a, int k, int day, int c, int lo, uint32_t x, uint32_t y)
+{
+    const double t = fma((double)(a.n - 1), a.q[k], -(double)lo);
+    const double p = (double)(int32_t)(x ^ 0x80000000u), q = (double)(int32_t)(y ^ 0x80000000u);
+    a.out[((int64_t)k * (a.T + 1) + day) * 6 + c] = (float)fma(q - p, t, p);
+}
 
 constexpr int BANDS_CAND = 4;  // values per lane once few are left
 
@@ -89,7 +98,7 @@ __global__ __launch_bounds__(768) void k_bands(BandArgs a)
         }
     }
     __syncthreads();
-    if ((wv & 3) >= a.nq) return;
+    if (4 * (int)blockIdx.z + (wv & 3) >= a.nq) return;
     uint32_t v[V], vmin = 0xFFFFFFFFu, vmax = 0u;
 #pragma unroll
     for (int e = 0; e < V; ++e) {
@@ -104,7 +113,7 @@ __global__ __launch_bounds__(768) void k_bands(BandArgs a)
     }
     vmin = __builtin_amdgcn_readfirstlane(vmin);
     vmax = __builtin_amdgcn_readfirstlane(vmax);
-    for (int k = wv & 3; k < a.nq; k += 4) {
+    for (int k = 4 * blockIdx.z + (wv & 3); k < a.nq; k += 4 * gridDim.z) {
         const double h = (double)(a.n - 1) * a.q[k];
         int lo = (int)floor(h);
         if (lo > n - 1) lo = n - 1;
@@ -148,18 +157,83 @@ __global__ __launch_bounds__(768) void k_bands(BandArgs a)
             y = least_above(v, x);
         }
         if (lane == 0) {
-            // what the rounding of h took away stays in the fraction: (n - 1) q - lo, rounded once
-            const double t = fma((double)(a.n - 1), a.q[k], -(double)lo);
-            const double p = (double)(int32_t)(x ^ 0x80000000u), q = (double)(int32_t)(y ^ 0x80000000u);
-            a.out[((int64_t)k * (a.T + 1) + day) * 6 + half * 3 + c] = (float)fma(q - p, t, p);
+            store_quantile(a, k, day, half * 3 + c, lo, x, y);
         }
     }
+}
+
+// Ascending bitonic sort of a wavefront's 64 V values; value e of lane l is number
+// 64 e + l.
+template <int V>
+__device__ __forceinline__ void sort_values(uint32_t (&v)[V], int lane)
+{
+#pragma unroll
+    for (int k = 2; k <= 64 * V; k <<= 1)
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1)
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const bool up = k < 64 ? (lane & k) == 0 : (e & (k >> 6)) == 0;
+                if (j >= 64) {
+                    const int p = e | (j >> 6);
+                    if (p != e) {
+                        const uint32_t x = min(v[e], v[p]), y = max(v[e], v[p]);
+                        v[e] = up ? x : y;
+                        v[p] = up ? y : x;
+                    }
+                } else {
+                    const uint32_t o = (uint32_t)__shfl_xor((int)v[e], j, 64);
+                    v[e] = ((lane & j) == 0) == up ? min(v[e], o) : max(v[e], o);
+                }
+            }
+}
+
+// Few rows: a wavefront sorts the values of a (day, compartment) in its registers,
+// without a barrier, and a lane forms each quantile. Bisection is a search a
+// quantile: of 121 days, with 1 / 3 / 16 quantiles, the whole call, 10 rows took
+// 29 / 29 / 44 us, now 26; 256 rows 29 / 29 / 45, now 26; 512 rows 34 / 34 / 61, now
+// 30 (from 1000 on bisection is ahead with few quantiles).
+template <int V>
+__global__ __launch_bounds__(192) void k_bands_few(BandArgs a)
+{
+    __shared__ uint32_t sorted[3][64 * V];
+    const int day = blockIdx.x, half = blockIdx.y;
+    const int n = (int)a.n, lane = threadIdx.x & 63;
+    const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t* src = a.traj + (int64_t)day * 6 + half * 3 + c;
+    uint32_t v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        const int r = e * 64 + lane;
+        v[e] = ordered(src[(int64_t)(r < n ? r : 0) * (a.T + 1) * 6]);
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = e * 64 + lane < n ? v[e] : 0xFFFFFFFFu;
+    sort_values(v, lane);
+#pragma unroll
+    for (int e = 0; e < V; ++e) sorted[c][e * 64 + lane] = v[e];
+    wave_lds_sync();
+    if (lane < a.nq) {
+        const double h = (double)(a.n - 1) * a.q[lane];
+        int lo = (int)floor(h);
+        if (lo > n - 1) lo = n - 1;
+        store_quantile(a, lane, day, half * 3 + c, lo, sorted[c][lo], sorted[c][lo + 1 < n ? lo + 1 : lo]);
+    }
+}
+
+template <int V>
+static void launch_bands_few(const BandArgs& a, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_bands_few<V>), dim3(a.T + 1, 2), dim3(192), 0, s, a);
 }
 
 template <int V>
 static void launch_bands(const BandArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_bands<V>), dim3(a.T + 1, 2), dim3(768), 0, s, a);
+    // more than four quantiles: workgroups of their own, unless the values fill half
+    // a CU's LDS (16 quantiles of 1000 rows 63 -> 56 us, of 8192 rows 244 and 322)
+    const unsigned z = V <= 32 ? (unsigned)(a.nq + 3) / 4 : 1u;
+    hipLaunchKernelGGL((k_bands<V>), dim3(a.T + 1, 2, z), dim3(768), 0, s, a);
 }
 
 }  // namespace abc
@@ -184,7 +258,9 @@ extern "C" abc_status abc_trajectory_bands(const int32_t* traj, int64_t n, int32
     }
     a.out = out;
     const hipStream_t s = as_stream(stream);
-    if (n <= 64 * 4) launch_bands<4>(a, s);
+    if (n <= 64) launch_bands_few<1>(a, s);
+    else if (n <= 64 * 4) launch_bands_few<4>(a, s);
+    else if (n <= 64 * 8) launch_bands_few<8>(a, s);
     else if (n <= 64 * 16) launch_bands<16>(a, s);
     else if (n <= 64 * 32) launch_bands<32>(a, s);
     else if (n <= 64 * 64) launch_bands<64>(a, s);

@@ -24,7 +24,7 @@ def _bands(x, qs):
     return out
 
 
-@pytest.mark.parametrize("n", [2, 10, 64, 65, 256, 257, 1000, 1025, 4096, 8192])
+@pytest.mark.parametrize("n", [2, 10, 64, 65, 256, 257, 512, 513, 1000, 1025, 2048, 4096, 8192])
 @pytest.mark.parametrize("kind", ["few", "edge"])
 def test_fraction_of_the_exact_product(n, kind):
     import torch
