@@ -919,16 +919,16 @@ def main():
         "per_country": per_country,
     }
     if not args.no_batched:
-        # the batched legs tune their own shapes; the float32 simulate kernel
-        # of the later legs gets the main step's shape back
-        main_shape, main_refill = abc.get_launch_config(), abc.get_refill_min()
+        # the batched legs tune their own shapes; the later legs run with what a
+        # thread gets that sets none
+        main_refill = abc.get_refill_min()
         out["batched"] = batched_leg(args)
         note("batched leg done")
         if not args.no_learned:
             out["learned"] = learned_leg(args, out["batched"])
             note("learned leg done")
         out["batched"].pop("_eps", None)
-        abc.set_launch_config(*main_shape)
+        abc.set_launch_config(0, 0, 0)
         abc.set_refill_min(main_refill)
         out["batched"].pop("_used", None)
     if not args.no_smc:

@@ -299,8 +299,9 @@ ABC_API abc_status abc_posterior_moments(const float* theta, const float* weight
  * blocks_per_cu = resident workgroups per compute unit (1..64). A 0 selects
  * that argument's default: spl 1, block 512 / spl (at least 64), blocks_per_cu
  * 2. Until a thread calls this, and after it sets all three to 0, each kernel
- * chooses workgroups from the size of its launch (abc_get_launch_config then
- * reports the defaults). Results never depend on these settings, only speed.
+ * chooses workgroups from the size of its launch; abc_get_launch_config then
+ * reports three zeros, so that setting what it reported restores the state.
+ * Results never depend on these settings, only speed.
  */
 ABC_API abc_status abc_set_launch_config(int32_t spl, int32_t block, int32_t blocks_per_cu);
 ABC_API abc_status abc_get_launch_config(int32_t* spl, int32_t* block, int32_t* blocks_per_cu);

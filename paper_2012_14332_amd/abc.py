@@ -376,11 +376,14 @@ def posterior_moments(theta: torch.Tensor, weight: Optional[torch.Tensor] = None
 
 
 def set_launch_config(spl: int = 0, block: int = 0, blocks_per_cu: int = 0):
-    """Launch shape of the float32 simulate kernel for this thread (0 = default)."""
+    """Launch shape of the float32 simulate kernels for this thread (a 0: that argument's
+    default; all three 0: each kernel chooses by the size of its launch)."""
     _check(lib().abc_set_launch_config(int(spl), int(block), int(blocks_per_cu)))
 
 
 def get_launch_config():
+    """This thread's launch shape, (0, 0, 0) while none is set; set_launch_config of it
+    restores the state."""
     v = [ctypes.c_int32() for _ in range(3)]
     _check(lib().abc_get_launch_config(*[ctypes.byref(x) for x in v]))
     return tuple(x.value for x in v)

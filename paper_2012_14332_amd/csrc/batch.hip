@@ -934,8 +934,9 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
         obs_ptr[s] = b.obs;
         if (b.T > maxT) maxT = b.T;
     }
-    int32_t spl = 1, block = 1024, bpc = 1;
-    abc_get_launch_config(&spl, &block, &bpc);
+    const LaunchShape shape = launch_shape();
+    const int32_t spl = shape.spl;
+    int32_t block = shape.block, bpc = shape.blocks_per_cu;
     if (spl != 1 && spl != 2 && spl != 4 && spl != 8)
         return set_error(ABC_EUNSUPPORTED, "the batched round kernel is built for 1, 2, 4 or 8 "
                          "samples per lane, not %d", spl);
@@ -947,7 +948,7 @@ static abc_status batch_run(const abc_batch_series* series, int32_t m, const abc
     // 256 threads x 2 / x 3 / x 4 per CU and at 512 x 2: rounds of 2^22 samples
     // 24.8 / 24.9 / 25.9 / 27.3, of 2^25 22.5 / 21.1 / 20.7 / 20.9; with a learned
     // proposal, 2^22 17.7 / 17.2 / 17.5 / 18.4, 2^24 16.8 / 15.4 / 15.0 / 15.1.
-    if (!launch_shape_chosen()) {
+    if (!shape.chosen) {
         DeviceInfo di;
         if ((rc = device_info(&di))) return rc;
         const int64_t share = (int64_t)di.num_cu * 4 * 24;

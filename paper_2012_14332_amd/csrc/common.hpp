@@ -26,9 +26,15 @@ constexpr int64_t ROW_WAVE_TARGET = 1024;
 constexpr int32_t ROW_SCAN_BESIDE = 8;
 constexpr int32_t ROW_SCAN_ALONE = 4;
 
-// Whether the calling thread has set a launch shape (abc_set_launch_config);
-// otherwise each kernel chooses its own.
-bool launch_shape_chosen();
+// Launch shape of the calling thread (abc_set_launch_config). Until it has chosen one
+// each kernel takes its own, with the defaults here where it does not.
+struct LaunchShape {
+    int32_t spl = 1;
+    int32_t block = 512;
+    int32_t blocks_per_cu = 2;
+    bool chosen = false;
+};
+LaunchShape launch_shape();
 
 // abc_recheck_band with a chosen grid cap and candidates per wavefront; with all_rows every candidate (not only those in
 // the band) is decided by its float64 distance, and dist64 (nullable,

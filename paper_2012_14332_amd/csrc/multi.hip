@@ -331,14 +331,14 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
     a.domain = domain;
     a.scale = model->noise_scale;
     a.days = days;
-    int32_t spl = 1, block = 512, bpc = 2;
-    abc_get_launch_config(&spl, &block, &bpc);
+    const LaunchShape shape = launch_shape();
+    int block = shape.block, bpc = shape.blocks_per_cu;
     // a large launch takes two 1024-thread workgroups per CU, a smaller one
     // 512-thread workgroups with at least seven chunks per wavefront (as the
     // one-series launch): three series of 1e7 samples take 1.49 ms instead of
     // 1.60 ms with two 512-thread workgroups, three of 3e5 samples 0.117 ms
     // instead of 0.127 ms
-    if (!launch_shape_chosen()) {
+    if (!shape.chosen) {
         DeviceInfo di;
         if ((rc = device_info(&di))) return rc;
         const int64_t per = (total / 64) / ((int64_t)di.num_cu * 8 * 7);

@@ -852,16 +852,12 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // per lane, workgroup size and resident workgroups per CU. Until the thread
 // sets one (and again after it sets all three to 0) each kernel chooses its
 // own from the size of the launch.
-struct LaunchConfig {
-    int spl = 1;
-    int block = 512;
-    int blocks_per_cu = 2;
+struct LaunchConfig : LaunchShape {
     int refill_min = 8;
-    bool chosen = false;
 };
 static thread_local LaunchConfig g_launch;
 
-bool launch_shape_chosen() { return g_launch.chosen; }
+LaunchShape launch_shape() { return g_launch; }
 
 // Resident 512-thread workgroups per CU for a launch of n samples: more
 // wavefronts hide more latency, but every wavefront ends on a few trajectories
@@ -1139,9 +1135,10 @@ extern "C" abc_status abc_set_launch_config(int32_t spl, int32_t block, int32_t 
 extern "C" abc_status abc_get_launch_config(int32_t* spl, int32_t* block, int32_t* blocks_per_cu)
 {
     ABC_REQUIRE(spl && block && blocks_per_cu, "NULL output pointer");
-    *spl = g_launch.spl;
-    *block = g_launch.block;
-    *blocks_per_cu = g_launch.blocks_per_cu;
+    // what sets the same state again: zeros while the thread has chosen no shape
+    *spl = g_launch.chosen ? g_launch.spl : 0;
+    *block = g_launch.chosen ? g_launch.block : 0;
+    *blocks_per_cu = g_launch.chosen ? g_launch.blocks_per_cu : 0;
     return ABC_OK;
 }
 
