@@ -859,19 +859,30 @@ static thread_local LaunchConfig g_launch;
 
 LaunchShape launch_shape() { return g_launch; }
 
-// Resident 512-thread workgroups per CU for a launch of n samples: more
-// wavefronts hide more latency, but every wavefront ends on a few trajectories
-// of its own, so with an early exit each should walk at least seven chunks of
-// 64 samples. Measured on the 3.3e8/T100 series, one / two / four workgroups
-// per CU: 1e6 samples 160 / 172 / 185 us, 1e7 samples 1013 / 908 / 872 us.
-// Without an exit (every trajectory ends on the same day) one chunk each is
-// enough: 1e6 samples of T = 49 250 / 220 / 206 us.
-static int refill_blocks_per_cu(int64_t n, bool exits)
+// Resident 512-thread workgroups per CU for a launch of n samples over T days: more
+// wavefronts hide more latency, but every wavefront ends on a few trajectories of
+// its own, up to T days after its queue is empty, and early exits make its queue
+// short. So what a wavefront has to itself (chunks of 64 samples, were there one
+// workgroup per CU) is measured against T; raw distances exit late in a
+// trajectory, which counts like seven times the samples; without exits every
+// trajectory ends on the same day and one chunk each is enough. One / two / three /
+// four workgroups per CU, us:
+//   T =  49, exits: 1e6 samples 110 / 114 / 118 / 129, 3e6 237 / 220 / 226 / 230, 1e7 699 / 614 / 590 / 590
+//   T =  95, exits: 1e6 175 / 181 / 211 / 237, 4e6 479 / 447 / 465 / 481, 2e7 2126 / 1859 / 1812 / 1802
+//   T = 200, exits: 2e6 433 / 455 / 500 / 536, 4e6 719 / 706 / 737 / 779, 1e7 1596 / 1461 / 1459 / 1522
+//   T = 400, exits: 4e6 997 / 1068 / 1133 / 1207, 1e7 2110 / 1996 / 2076 / 2160
+//   T =  49, raw, exits: 3e5 93 / 84 / 85 / 84, 1e6 204 / 200 / 192 / 193
+//   T =  49, no exits: 1e6 245 / 229 / 219 / 217
+static int refill_blocks_per_cu(int64_t n, int T, bool exits, bool raw)
 {
     DeviceInfo info;
     const int64_t num_cu = device_info(&info) == ABC_OK && info.num_cu > 0 ? info.num_cu : 256;
-    const int64_t per = ((n + 63) / 64) / (num_cu * (512 / 64) * (exits ? 7 : 1));
-    return per < 1 ? 1 : (per > 4 ? 4 : (int)per);
+    const double share = (double)((n + 63) / 64) / (double)(num_cu * (512 / 64)) * (exits && raw ? 7.0 : 1.0);
+    if (!exits) return share < 2.0 ? 1 : (share >= 4.0 ? 4 : (int)share);
+    const double days = T > 50 ? T : 50;
+    if (share >= 1.12 * days) return 4;
+    if (share >= 0.56 * days) return 3;
+    return share >= 14.0 && share >= 0.094 * T ? 2 : 1;
 }
 
 // Resident-grid size for the refill kernel: enough workgroups to fill every
@@ -910,7 +921,7 @@ static void launch_f32_bound(const SimArgs& a, bool prior, hipStream_t s)
 {
     const int block = g_launch.block;
     const size_t lds = refill_lds_bytes(a.T, block, a.lb_ntb);
-    const int bpc = g_launch.chosen ? g_launch.blocks_per_cu : refill_blocks_per_cu(a.n, !isinf(a.exit_f32));
+    const int bpc = g_launch.chosen ? g_launch.blocks_per_cu : refill_blocks_per_cu(a.n, a.T, !isinf(a.exit_f32), DIST == 1);
     const dim3 g(refill_grid(a.n, block, bpc)), b(block);
     if (prior)
         hipLaunchKernelGGL((k_simulate_f32<NOISE, DIST, KAHAN, true, SPL, BOUND>), g, b, lds, s, a);
