@@ -333,17 +333,24 @@ extern "C" abc_status abc_simulate_distance_multi(const abc_sim_job* jobs, int32
     a.days = days;
     const LaunchShape shape = launch_shape();
     int block = shape.block, bpc = shape.blocks_per_cu;
-    // a large launch takes two 1024-thread workgroups per CU, a smaller one
-    // 512-thread workgroups with at least seven chunks per wavefront (as the
-    // one-series launch): three series of 1e7 samples take 1.49 ms instead of
-    // 1.60 ms with two 512-thread workgroups, three of 3e5 samples 0.117 ms
-    // instead of 0.127 ms
+    // With early exits a large launch takes two 1024-thread workgroups per CU, a
+    // smaller one 512-thread workgroups with at least seven chunks per wavefront:
+    // three series of 1e7 samples take 1.49 ms instead of 1.60 ms with two
+    // 512-thread workgroups, three of 3e5 samples 0.117 ms instead of 0.127 ms.
+    // Where a job has none, its trajectories are most of the work and end together:
+    // 512-thread workgroups with one chunk per wavefront, up to four per CU. Three
+    // series of T = 100 without exits, one / two / three / four per CU: 1e5 samples each
+    // 206 / 176 / 174 / 171 us, 3e5 441 / 386 / 368 / 353, 1e6 1386 / 1205 / 1152 /
+    // 1131. So it is with raw distances over short horizons, whose exits come late (T =
+    // 100: 1e5 169 / 155 / 158 / 158, T = 400: 359 / 407 / 468 / 466).
     if (!shape.chosen) {
         DeviceInfo di;
         if ((rc = device_info(&di))) return rc;
-        const int64_t per = (total / 64) / ((int64_t)di.num_cu * 8 * 7);
-        block = per >= 4 ? 1024 : 512;
-        bpc = per >= 2 ? 2 : 1;
+        bool late = distm == 1 && jobs[order[0]].ser->T <= 150;  // the longest
+        for (int j : order) late = late || isinf(jobs[j].eps_exit);
+        const int64_t per = (total / 64) / ((int64_t)di.num_cu * 8 * (late ? 1 : 7));
+        block = !late && per >= 4 ? 1024 : 512;
+        bpc = late ? (per < 1 ? 1 : (per > 4 ? 4 : (int)per)) : (per >= 2 ? 2 : 1);
     }
     a.refill_min = abc_get_refill_min();
     int obs_words = 0, maxT = 0;
