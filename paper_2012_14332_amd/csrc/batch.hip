@@ -315,10 +315,10 @@ __global__ __launch_bounds__(BT_MAX_SERIES) void k_batch_plan(BatchArgs a)
 // one round: persistent grid with lane refill and per-lane series
 // ----------------------------------------------------------------------------
 // One prepared sample (48 bytes); its series and index follow from the chunk in
-// the ring, which is wave-uniform.
+// the ring, which is wave-uniform. The first eight words are floats throughout: the
+// learned proposal leaves theta there while it draws.
 struct alignas(16) BSlot {
-    float a0, al, n, be, ga, de, bh;
-    int32_t i0;
+    float v[8];                   // the rates a0, al, n, be, ga, de, bh, and the bits of I0
     uint32_t c1base, g3, h3, f3;  // per-sample part of Philox rounds 1-3
 };
 
@@ -413,10 +413,9 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
             const int64_t i = cur_first + lane;
             float th[8];
             if (MIX && a.mix) {
-                float* out = reinterpret_cast<float*>(&ring[lane]);
-                proposal_theta(a.tables[s], a.prop, a.key, (uint64_t)i, d.series_id, a.prop_domain, out);
+                proposal_theta(a.tables[s], a.prop, a.key, (uint64_t)i, d.series_id, a.prop_domain, ring[lane].v);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) th[k] = out[k];
+                for (int k = 0; k < 8; ++k) th[k] = ring[lane].v[k];
             } else
                 prior_draw(a.key, (uint64_t)i, d.series_id, a.domain, a.lo, a.width, th);
             const Theta tt = theta_from(th);
@@ -425,8 +424,8 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
             ph.begin((uint64_t)i, d.u0, a.key);
             const State s0 = init_state(tt.ka, d.P, d.A0, d.R0, d.D0);
             BSlot sl;
-            sl.a0 = rr.a0; sl.al = rr.al; sl.n = rr.n; sl.be = rr.be;
-            sl.ga = rr.ga; sl.de = rr.de; sl.bh = rr.bh; sl.i0 = s0.I;
+            sl.v[0] = rr.a0; sl.v[1] = rr.al; sl.v[2] = rr.n; sl.v[3] = rr.be;
+            sl.v[4] = rr.ga; sl.v[5] = rr.de; sl.v[6] = rr.bh; sl.v[7] = __int_as_float(s0.I);
             sl.c1base = ph.c1base; sl.g3 = ph.g3; sl.h3 = ph.h3; sl.f3 = ph.f3;
             ring[lane] = sl;
         }
@@ -465,8 +464,9 @@ __global__ __launch_bounds__(1024 / SPL) void k_batch_round(BatchArgs a)
                         const BSlot sl = ring[pos];
                         const BSer e = ser[cur_s];
                         BLane& l = L[k];
-                        l.r = RatesF{sl.a0, sl.al, sl.n, sl.be, sl.ga, sl.de, sl.bh};
-                        l.s = StateD{e.room - sl.i0, sl.i0, e.A0, e.M0, e.R1, e.D1};
+                        const int32_t i0 = __float_as_int(sl.v[7]);
+                        l.r = RatesF{sl.v[0], sl.v[1], sl.v[2], sl.v[3], sl.v[4], sl.v[5], sl.v[6]};
+                        l.s = StateD{e.room - i0, i0, e.A0, e.M0, e.R1, e.D1};
                         l.ph.c1base = sl.c1base; l.ph.g3 = sl.g3; l.ph.h3 = sl.h3; l.ph.f3 = sl.f3;
                         l.i = cur_first + (int64_t)pos;
                         l.w = 256u | wdom;
