@@ -481,7 +481,7 @@ ABC_API abc_status abc_mdn_simulate_features(const abc_prior* prior, uint64_t se
 /* The 96 unstandardised features of an observed series (ser->obs device). */
 ABC_API abc_status abc_series_features(const abc_series* ser, float* out96, void* stream);
 
-/* Per-feature mean and sd (float64 sums about the first row, sd floored at 1e-6) of
+/* Per-feature mean and sd (float64, about the means of row ranges, sd floored at 1e-6) of
  * features [n][96] (device), kept in the net for every later call. */
 ABC_API abc_status abc_mdn_fit_standardizer(abc_mdn* net, const float* features, int64_t n,
                                             void* stream);

@@ -300,9 +300,12 @@ __global__ void k_obs_features(const int32_t* obs, int T, float* out)
 // Per-feature mean and sd in float64: the rows are cut into G contiguous
 // ranges (G a function of n alone); a workgroup streams its range, ten rows of
 // 24 float4 per step, each thread keeping sums and squares of its four columns
-// about the first row; one workgroup per column then adds the ranges'
-// partials in a fixed order. Bound by HBM: 1e6 rows (384 MB) take 56 us
-// (one workgroup per column, reading 4 bytes every 384 twice: 4.4 ms).
+// about a value of the range, the median of three of its rows. What is left of a
+// range is its sum and its squares about its own mean, which one workgroup per
+// column joins in a fixed order. (Sums about the first of all rows lost up to a
+// unit of float32 where that row was the column's only other value: 1e7 rows.)
+// Bound by HBM: 1e6 rows (384 MB) take 56 us (one workgroup per column, reading 4
+// bytes every 384 twice: 4.4 ms).
 constexpr int CS_ROWS = 10, CS_BLOCK = 256, CS_GROUPS = 1024;
 static_assert(NN_IN == 96 && CS_ROWS * (NN_IN / 4) <= CS_BLOCK, "a step of the column sums");
 
@@ -312,13 +315,56 @@ static int64_t colstats_groups(int64_t n)
     return g < CS_GROUPS ? g : CS_GROUPS;
 }
 
+__device__ __forceinline__ void store_colstats(int c, double m, double squares, int64_t n, float* mean, float* sd)
+{
+    const double s = sqrt(squares / (double)(n > 1 ? n - 1 : 1));
+    mean[c] = (float)m;
+    sd[c] = (float)(s > 1e-6 ? s : 1e-6);
+}
+
+// Few rows: one workgroup per column, whose threads hold their rows between the sum
+// and the squares; one launch (1000 rows: 21 us a call, two launches 24).
+constexpr int CS_FEW = 16;  // rows per thread, at most
+
+__global__ __launch_bounds__(CS_BLOCK) void k_colstats_few(const float* x, int n, float* mean, float* sd)
+{
+    __shared__ double red[2][CS_BLOCK / 64];
+    const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto total = [&](double v, int k) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) red[k][wave] = v;
+        __syncthreads();
+        return red[k][0] + red[k][1] + red[k][2] + red[k][3];
+    };
+    float v[CS_FEW];
+#pragma unroll
+    for (int q = 0; q < CS_FEW; ++q) {
+        const int r = q * CS_BLOCK + threadIdx.x;
+        v[q] = x[(int64_t)(r < n ? r : 0) * NN_IN + c];
+    }
+    double s = 0.0, squares = 0.0;
+#pragma unroll
+    for (int q = 0; q < CS_FEW; ++q) s += q * CS_BLOCK + (int)threadIdx.x < n ? (double)v[q] : 0.0;
+    const double m = total(s, 0) / (double)n;
+#pragma unroll
+    for (int q = 0; q < CS_FEW; ++q) {
+        const double d = (double)v[q] - m;
+        squares += q * CS_BLOCK + (int)threadIdx.x < n ? d * d : 0.0;
+    }
+    squares = total(squares, 1);
+    if (threadIdx.x == 0) store_colstats(c, m, squares, n, mean, sd);
+}
+
 template <bool VEC>
 __global__ __launch_bounds__(CS_BLOCK) void k_colsums(const float* x, int64_t n, double* part)
 {
     __shared__ double red[CS_ROWS][2 * NN_IN];
+    __shared__ float centre[NN_IN];
     const int c4 = threadIdx.x % (NN_IN / 4), sub = threadIdx.x / (NN_IN / 4);
     const int64_t R = (n + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = (int64_t)blockIdx.x * R, r1 = r0 + R < n ? r0 + R : n;
+    if (r0 >= n) return;  // k_colstats counts no row of this range
     auto load = [&](int64_t row, float v[4]) {
         const float* p = x + row * NN_IN + 4 * c4;
         if (VEC) {
@@ -330,10 +376,16 @@ __global__ __launch_bounds__(CS_BLOCK) void k_colsums(const float* x, int64_t n,
         }
     };
     if (sub < CS_ROWS) {
-        float c[4];
-        load(0, c);
+        float c[4], first[4], last[4];
+        load(r0, first);
+        load(r0 + (r1 - r0) / 2, c);
+        load(r1 - 1, last);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[j] = fabsf(c[j]) < INFINITY ? c[j] : 0.0f;
+        for (int j = 0; j < 4; ++j) {
+            c[j] = fmaxf(fminf(first[j], c[j]), fminf(fmaxf(first[j], c[j]), last[j]));
+            c[j] = fabsf(c[j]) < INFINITY ? c[j] : 0.0f;
+            if (sub == 0) centre[4 * c4 + j] = c[j];
+        }
         double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
         for (int64_t row = r0 + sub; row < r1; row += CS_ROWS) {
@@ -353,34 +405,49 @@ __global__ __launch_bounds__(CS_BLOCK) void k_colsums(const float* x, int64_t n,
         }
     }
     __syncthreads();
-    if (threadIdx.x < 2 * NN_IN) {
-        double t = 0.0;
+    if (threadIdx.x < NN_IN) {
+        const int c = threadIdx.x;
+        double s1 = 0.0, s2 = 0.0;
 #pragma unroll
-        for (int q = 0; q < CS_ROWS; ++q) t += red[q][threadIdx.x];
-        part[(int64_t)blockIdx.x * 2 * NN_IN + threadIdx.x] = t;
+        for (int q = 0; q < CS_ROWS; ++q) {
+            s1 += red[q][c];
+            s2 += red[q][NN_IN + c];
+        }
+        const double rows = (double)(r1 - r0);
+        const double sum = rows * (double)centre[c] + s1, squares = s2 - s1 * s1 / rows;
+        part[(int64_t)blockIdx.x * 2 * NN_IN + c] = sum;
+        part[(int64_t)blockIdx.x * 2 * NN_IN + NN_IN + c] = squares;
     }
 }
 
-__global__ __launch_bounds__(64) void k_colstats(const float* x, int64_t n, const double* part, int groups,
-                                                 float* mean, float* sd)
+__global__ __launch_bounds__(64) void k_colstats(int64_t n, const double* part, int groups, float* mean, float* sd)
 {
+    constexpr int PER = CS_GROUPS / 64;
     const int c = blockIdx.x, lane = threadIdx.x;
-    double s1 = 0.0, s2 = 0.0;
-    for (int g = lane; g < groups; g += 64) {
-        s1 += part[(int64_t)g * 2 * NN_IN + c];
-        s2 += part[(int64_t)g * 2 * NN_IN + NN_IN + c];
+    const int64_t R = (n + groups - 1) / groups;
+    double sum[PER], squares[PER], rows[PER], s = 0.0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int g = q * 64 + lane;
+        const int64_t r0 = g * R, left = g < groups && r0 < n ? n - r0 : 0;
+        rows[q] = (double)(left < R ? left : R);
+        sum[q] = left ? part[(int64_t)g * 2 * NN_IN + c] : 0.0;
+        squares[q] = left ? part[(int64_t)g * 2 * NN_IN + NN_IN + c] : 0.0;
+        s += sum[q];
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        s1 += __shfl_xor(s1, off, 64);
-        s2 += __shfl_xor(s2, off, 64);
-    }
-    if (lane == 0) {
-        const double m = s1 / (double)n;
-        const double var = (s2 - s1 * m) / (double)(n > 1 ? n - 1 : 1);
-        mean[c] = (float)((fabsf(x[c]) < INFINITY ? (double)x[c] : 0.0) + m);
-        sd[c] = (float)(sqrt(var) > 1e-6 ? sqrt(var) : 1e-6);
-    }
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    const double m = s / (double)n;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (rows[q] > 0.0) {
+            const double d = sum[q] / rows[q] - m;
+            v += squares[q] + rows[q] * d * d;
+        }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) store_colstats(c, m, v, n, mean, sd);
 }
 
 // ----------------------------------------------------------------------------
@@ -1308,13 +1375,16 @@ extern "C" abc_status abc_mdn_fit_standardizer(abc_mdn* net, const float* featur
 {
     ABC_REQUIRE(net && features && n >= 2, "need a net and >= 2 feature rows");
     const hipStream_t s = as_stream(stream);
+    if (n <= CS_FEW * CS_BLOCK) {
+        hipLaunchKernelGGL(k_colstats_few, dim3(NN_IN), dim3(CS_BLOCK), 0, s, features, (int)n, net->fmean, net->fsd);
+        return check_launch("k_colstats_few");
+    }
     const int groups = (int)colstats_groups(n);
     if ((reinterpret_cast<uintptr_t>(features) & 15u) == 0)
         hipLaunchKernelGGL((k_colsums<true>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, net->colpart);
     else
         hipLaunchKernelGGL((k_colsums<false>), dim3(groups), dim3(CS_BLOCK), 0, s, features, n, net->colpart);
-    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(64), 0, s, features, n, net->colpart, groups,
-                       net->fmean, net->fsd);
+    hipLaunchKernelGGL(k_colstats, dim3(NN_IN), dim3(64), 0, s, n, net->colpart, groups, net->fmean, net->fsd);
     return check_launch("k_colstats");
 }
 
