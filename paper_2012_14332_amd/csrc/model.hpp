@@ -406,9 +406,13 @@ __device__ __forceinline__ void stage_obs_f64(const int32_t* obs, int T, double*
     }
 }
 
-// A sample with a negative kappa, whose counts can be negative, from its first day
-// to its last, out of line: the loops of the float64 kernels have no room for its
-// conditions (2 % of a row walk, 5 % of k_simulate_f64), and no prior draws it.
+// Logarithm of one plus a count below 0, out of line.
+__device__ __attribute__((noinline)) double log1p_general(double x) { return log1p(x); }
+
+// A sample with a negative kappa, whose counts can be negative. No prior draws it, and
+// the loops of the float64 kernels have no room for its conditions (5 % of
+// k_simulate_f64): a lane that takes one runs it from its first day to its last, out
+// of line, and a row walk takes its form for parameters outside the ranges.
 __device__ __forceinline__ bool negative_start(const float t[8]) { return t[7] < 0.0f; }
 
 template <int NOISE, int DIST>
@@ -499,15 +503,15 @@ __device__ __forceinline__ void walk_window(RowWalk& w, int nd, const double* zr
         const double g = MID || w.mid ? force_f64(w.p, w.a0, w.al, tab)
                                       : force_general((double)w.M, w.nn, w.a0, w.al);
         const int32_t d4 = draw_f64<NOISE>(w.rate * (double)(w.ofA ? s.A : s.I), zq, w.scale);
-        const int32_t n2 = min(quad_lane<0>(d4), s.I);
+        const int32_t n2 = taken<!MID>(quad_lane<0>(d4), s.I);
         w.M += n2;
         if (MID || w.mid) w.p = pow_arg((double)w.M, w.nn, tab);
         const double h0 = g * (double)s.S * (double)s.I;
         const double h1 = MID || w.mid ? div_by(h0, w.P, w.rP) : div_general(h0, w.P);
-        const int32_t n1 = min(draw_f64<NOISE>(h1, z1, w.scale), s.S);
-        const int32_t n3 = min(quad_lane<1>(d4), s.A);
-        const int32_t n4 = min(quad_lane<2>(d4), s.A - n3);
-        const int32_t n5 = min(quad_lane<3>(d4), s.I - n2);
+        const int32_t n1 = taken<!MID>(draw_f64<NOISE>(h1, z1, w.scale), s.S);
+        const int32_t n3 = taken<!MID>(quad_lane<1>(d4), s.A);
+        const int32_t n4 = taken<!MID>(quad_lane<2>(d4), s.A - n3);
+        const int32_t n5 = taken<!MID>(quad_lane<3>(d4), s.I - n2);
         s.S -= n1;
         s.I += n1 - n2 - n5;
         s.A += n2 - n3 - n4;
@@ -539,7 +543,7 @@ __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rt
         float th[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) th[k] = rth[8 * row + k];
-        wk.mid = theta_mid(th);
+        wk.mid = theta_mid(th) && !negative_start(th);
         wk.P = (double)P;
         wk.rP = 1.0 / wk.P;
         wk.scale = scale;
@@ -578,15 +582,21 @@ __device__ __forceinline__ double simulate_rows_f64_wave(int nr, const float* rt
                 walk_window<NOISE, false>(wk, nd, zs + 5 * row * W, xs + 4 * row * W, tab);
         }
         wave_lds_sync();
+        auto terms = [&](auto logarithm) {
 #pragma unroll 1
-        for (int p = lane; p < nr * 3 * nd; p += 64) {
-            const int r = p / (3 * nd), q = p - r * 3 * nd;
-            const int u = q / 3, c = q - 3 * u;
-            const int t = t0 - 1 + u;  // 0-based day
-            const int32_t X = xs[4 * (r * W + u) + c];
-            const double d = (DIST == 0 ? log1p_count_f64(X, tab) : (double)X) - lobs[c * T + t];
-            zs[5 * r * W + q] = d * d;
-        }
+            for (int p = lane; p < nr * 3 * nd; p += 64) {
+                const int r = p / (3 * nd), q = p - r * 3 * nd;
+                const int u = q / 3, c = q - 3 * u;
+                const int t = t0 - 1 + u;  // 0-based day
+                const int32_t X = xs[4 * (r * W + u) + c];
+                const double d = (DIST == 0 ? logarithm(X) : (double)X) - lobs[c * T + t];
+                zs[5 * r * W + q] = d * d;
+            }
+        };
+        if (DIST == 1 || all_mid)
+            terms([&](int32_t X) { return log1p_count_f64(X, tab); });
+        else
+            terms([&](int32_t X) { return X >= 0 ? log1p_count_f64(X, tab) : log1p_general((double)X); });
         wave_lds_sync();
         if (lane < nr) {
             const double* tr = zs + 5 * lane * W;

@@ -12,6 +12,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "bound.hpp"
 #include "common.hpp"
 #include "model.hpp"
@@ -500,23 +502,6 @@ __device__ __forceinline__ RowLds row_lds(double* base, int T, int R)
     return l;
 }
 
-// Distances of the nr rows gathered in LDS, row r's on lane r.
-template <int NOISE, int DIST>
-__device__ __forceinline__ double rows_f64(const SimArgs& a, const RowLds& l, int nr)
-{
-    double d = simulate_rows_f64_wave<NOISE, DIST>(nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0,
-                                                   a.T, (double)a.scale, l.lobs, *l.tab, l.zs, l.xs);
-    const int lane = threadIdx.x;
-    if (lane < nr && negative_start(l.rth + 8 * lane)) {
-        float th[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) th[k] = l.rth[8 * lane + k];
-        d = simulate_negative_f64<NOISE, DIST>(theta_from(th), l.rix[lane], a.key, a.series, a.domain, a.P, a.A0, a.R0,
-                                               a.D0, a.T, (double)a.scale, l.lobs, l.tab, (double)INFINITY);
-    }
-    return d;
-}
-
 // Pass 1: each wavefront scans a contiguous block of candidates (enough for
 // the grid to cover the candidate count, at least scan_min), 64 at a time;
 // the in-band ones are gathered, in candidate order, into groups of up to
@@ -538,7 +523,9 @@ __device__ __forceinline__ void recheck_group(const RecheckArgs& r, const RowLds
         staged = true;
     }
     __syncthreads();
-    const double d64 = rows_f64<NOISE, DIST>(a, l, nr);
+    const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
+        nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, a.T, (double)a.scale,
+        l.lobs, *l.tab, l.zs, l.xs);
     const int lane = threadIdx.x;
     if (lane < nr) {
         const int64_t qq = l.rq[lane];
@@ -691,7 +678,9 @@ __global__ __launch_bounds__(64) void k_rows_f64(RowsArgs r)
             for (int j = 0; j < 8; ++j) l.rth[8 * lane + j] = a.theta[8 * (q0 + lane) + j];
         }
         __syncthreads();
-        const double d64 = rows_f64<NOISE, DIST>(a, l, nr);
+        const double d64 = simulate_rows_f64_wave<NOISE, DIST>(
+            nr, l.rth, l.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T,
+            (double)a.scale, l.lobs, *l.tab, l.zs, l.xs);
         if (lane < nr) r.dist64[q0 + lane] = d64;
         __syncthreads();
     }
@@ -727,20 +716,25 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
     const RatesF r = rates_f32(th);
     const float invP = 1.0f / (float)a.P;
     const float nc = noise_c(a.scale);
-    for (int t = 1; t <= a.T; ++t) {
-        const uint4 w = stream_words(a.key, i, a.series, ctr_word3((uint32_t)t, a.domain, 0));
-        if (F64) {
-            double z[5];
-            normals_f64(w, tab, z);
-            // (the power's logarithm is of a count of one or more)
-            day_step_f64<NOISE, true>(s, th, mid && s.A + s.R + s.D > 0, (double)a.P, rP, (double)a.scale, z, tab);
-        } else {
-            Noise32 z;
-            normals_f32(w, nc, z);
-            day_step_f32<NOISE>(s, r, invP, z);
+    auto days = [&](auto negative) {
+        for (int t = 1; t <= a.T; ++t) {
+            const uint4 w = stream_words(a.key, i, a.series, ctr_word3((uint32_t)t, a.domain, 0));
+            if (F64) {
+                double z[5];
+                normals_f64(w, tab, z);
+                // (the power's logarithm is of a count of one or more)
+                const bool in_range = negative ? mid && s.A + s.R + s.D > 0 : mid;
+                day_step_f64<NOISE, negative>(s, th, in_range, (double)a.P, rP, (double)a.scale, z, tab);
+            } else {
+                Noise32 z;
+                normals_f32(w, nc, z);
+                day_step_f32<NOISE>(s, r, invP, z);
+            }
+            store_state(out + 6 * t, s);
         }
-        store_state(out + 6 * t, s);
-    }
+    };
+    if (F64 && __ballot(negative_start(thv)) != 0ull) days(std::true_type{});
+    else days(std::false_type{});
 }
 
 // The float32 recording of few rows. With 64 rows per wavefront a thousand rows
