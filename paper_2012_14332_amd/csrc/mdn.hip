@@ -132,6 +132,10 @@ constexpr int FEAT_BLOCK = 256;
 // [30, 200], 8192 samples take 183 us without and 90 us with it, 1000 samples
 // 179 and 217 us (too few to fill the wavefronts of 171 horizons).
 constexpr int64_t FEAT_SORT_MIN = (int64_t)1 << 13;
+// And the longest horizon from which on: a trajectory has 32 recorded days, so below it
+// lanes in any order record on almost every day alike. 2e4 samples, without / with: T in
+// [5, 10] 53 / 68 us, [5, 20] 64 / 71, [5, 40] 83 / 79, [30, 100] 122 / 93.
+constexpr int32_t FEAT_SORT_T = 40;
 
 struct FeatOrder {
     uint32_t* cnt;    // [bins]
@@ -1326,7 +1330,7 @@ extern "C" abc_status abc_mdn_simulate_features(const abc_prior* prior, uint64_t
     // several threads on one stream share the scratch, so each enqueues its
     // launches before the next one's.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    bool ordered = n >= FEAT_SORT_MIN && n < ((int64_t)1 << 30) && bins > 1;
+    bool ordered = n >= FEAT_SORT_MIN && T_hi >= FEAT_SORT_T && n < ((int64_t)1 << 30) && bins > 1;
     if (ordered && (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
         (void)hipGetLastError();
         ordered = false;
