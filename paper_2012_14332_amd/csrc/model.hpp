@@ -358,14 +358,17 @@ __device__ __forceinline__ int32_t draw_f64(double h, double z, double scale)
     return max(cvt_i32_sat(x), 0);  // truncation is the floor of x >= 0
 }
 
-// What the source gives of a draw d >= 0: all it holds at most. It holds less than
-// nothing (NEG) only after a negative kappa; then any draw but 0 takes that.
-template <bool NEG>
-__device__ __forceinline__ int32_t taken(int32_t d, int32_t avail)
-{
-    return !NEG || d > 0 ? min(d, avail) : 0;
-}
+// What the source gives of a draw d >= 0 if it may hold less than nothing, after a
+// negative kappa: then any draw but 0 takes that.
+__device__ __forceinline__ int32_t taken(int32_t d, int32_t avail) { return d > 0 ? min(d, avail) : 0; }
 
+template <bool MID>
+__device__ __forceinline__ int32_t give(int32_t d, int32_t avail) { return MID ? min(d, avail) : taken(d, avail); }
+
+// NEG: some lane's kappa may be negative (mid is false for those). Their draws are taken
+// again behind a branch that a wavefront without them skips: a condition in each of the
+// five cost the kernel with given parameters 5 %, the branch costs 1 to 2 (200000 samples
+// of 100 days: 300 -> 303 us where 1 in 1000 reaches the last day, 608 -> 621 where half do).
 template <int NOISE, bool NEG = false>
 __device__ __forceinline__ void day_step_f64(State& s, const Theta& t, bool mid, double P, double rP,
                                              double scale, const double z[5], const Math64& tab)
@@ -376,11 +379,17 @@ __device__ __forceinline__ void day_step_f64(State& s, const Theta& t, bool mid,
     const double If = (double)s.I, Af = (double)s.A;
     const double h0 = g * (double)s.S * If;
     const double h1 = mid ? div_by(h0, P, rP) : div_general(h0, P);
-    const int32_t n1 = taken<NEG>(draw_f64<NOISE>(h1, z[0], scale), s.S);
-    const int32_t n2 = taken<NEG>(draw_f64<NOISE>((double)t.ga * If, z[1], scale), s.I);
-    const int32_t n3 = taken<NEG>(draw_f64<NOISE>((double)t.be * Af, z[2], scale), s.A);
-    const int32_t n4 = taken<NEG>(draw_f64<NOISE>((double)t.de * Af, z[3], scale), s.A - n3);
-    const int32_t n5 = taken<NEG>(draw_f64<NOISE>((double)t.be * (double)t.et * If, z[4], scale), s.I - n2);
+    const int32_t d1 = draw_f64<NOISE>(h1, z[0], scale), d2 = draw_f64<NOISE>((double)t.ga * If, z[1], scale),
+                  d3 = draw_f64<NOISE>((double)t.be * Af, z[2], scale), d4 = draw_f64<NOISE>((double)t.de * Af, z[3], scale),
+                  d5 = draw_f64<NOISE>((double)t.be * (double)t.et * If, z[4], scale);
+    int32_t n1 = min(d1, s.S), n2 = min(d2, s.I), n3 = min(d3, s.A), n4 = min(d4, s.A - n3), n5 = min(d5, s.I - n2);
+    if (NEG && !mid) {
+        n1 = taken(d1, s.S);
+        n2 = taken(d2, s.I);
+        n3 = taken(d3, s.A);
+        n4 = taken(d4, s.A - n3);
+        n5 = taken(d5, s.I - n2);
+    }
     s.S -= n1;
     s.I += n1 - n2 - n5;
     s.A += n2 - n3 - n4;
@@ -409,38 +418,9 @@ __device__ __forceinline__ void stage_obs_f64(const int32_t* obs, int T, double*
 // Logarithm of one plus a count below 0, out of line.
 __device__ __attribute__((noinline)) double log1p_general(double x) { return log1p(x); }
 
-// A sample with a negative kappa, whose counts can be negative. No prior draws it, and
-// the loops of the float64 kernels have no room for its conditions (5 % of
-// k_simulate_f64): a lane that takes one runs it from its first day to its last, out
-// of line, and a row walk takes its form for parameters outside the ranges.
+// A sample with a negative kappa, whose counts can be negative. No prior draws it. It is
+// taken as parameters outside the ranges are: not mid.
 __device__ __forceinline__ bool negative_start(const float t[8]) { return t[7] < 0.0f; }
-
-template <int NOISE, int DIST>
-__device__ __attribute__((noinline)) double simulate_negative_f64(Theta th, uint64_t i, Key key, uint32_t series,
-                                                                  uint32_t domain, int32_t P, int32_t A0, int32_t R0,
-                                                                  int32_t D0, int T, double scale, const double* lobs,
-                                                                  const Math64* tab, double exit_at)
-{
-#pragma clang fp contract(off)
-    const float t8[8] = {th.a0, th.al, th.n, th.be, th.ga, th.de, th.et, th.ka};
-    const bool mid = theta_mid(t8);
-    const double Pd = (double)P, rP = 1.0 / Pd;
-    State s = init_state(th.ka, P, A0, R0, D0);
-    double acc = 0.0;
-    for (int t = 1; t <= T; ++t) {
-        double z[5];
-        normals_f64(stream_words(key, i, series, ctr_word3((uint32_t)t, domain, 0)), *tab, z);
-        // the power's logarithm is of a count of one or more
-        day_step_f64<NOISE, true>(s, th, mid && s.A + s.R + s.D > 0, Pd, rP, scale, z, *tab);
-        const int32_t X[3] = {s.A, s.R, s.D};
-        for (int c = 0; c < 3; ++c) {
-            const double d = (DIST == 0 ? log1p((double)X[c]) : (double)X[c]) - lobs[c * T + t - 1];
-            acc += d * d;
-        }
-        if (acc > exit_at) return (double)INFINITY;
-    }
-    return sqrt(acc);
-}
 
 // Up to ROWS_PER_WAVE_MAX float64 trajectories run by one wavefront (one
 // wavefront per workgroup), in windows of W = ROW_PAIRS / nr
@@ -503,15 +483,15 @@ __device__ __forceinline__ void walk_window(RowWalk& w, int nd, const double* zr
         const double g = MID || w.mid ? force_f64(w.p, w.a0, w.al, tab)
                                       : force_general((double)w.M, w.nn, w.a0, w.al);
         const int32_t d4 = draw_f64<NOISE>(w.rate * (double)(w.ofA ? s.A : s.I), zq, w.scale);
-        const int32_t n2 = taken<!MID>(quad_lane<0>(d4), s.I);
+        const int32_t n2 = give<MID>(quad_lane<0>(d4), s.I);
         w.M += n2;
         if (MID || w.mid) w.p = pow_arg((double)w.M, w.nn, tab);
         const double h0 = g * (double)s.S * (double)s.I;
         const double h1 = MID || w.mid ? div_by(h0, w.P, w.rP) : div_general(h0, w.P);
-        const int32_t n1 = taken<!MID>(draw_f64<NOISE>(h1, z1, w.scale), s.S);
-        const int32_t n3 = taken<!MID>(quad_lane<1>(d4), s.A);
-        const int32_t n4 = taken<!MID>(quad_lane<2>(d4), s.A - n3);
-        const int32_t n5 = taken<!MID>(quad_lane<3>(d4), s.I - n2);
+        const int32_t n1 = give<MID>(draw_f64<NOISE>(h1, z1, w.scale), s.S);
+        const int32_t n3 = give<MID>(quad_lane<1>(d4), s.A);
+        const int32_t n4 = give<MID>(quad_lane<2>(d4), s.A - n3);
+        const int32_t n5 = give<MID>(quad_lane<3>(d4), s.I - n2);
         s.S -= n1;
         s.I += n1 - n2 - n5;
         s.A += n2 - n3 - n4;

@@ -44,7 +44,7 @@ struct SimArgs {
     int32_t* traj;       // record mode: [n][T+1][6]
     int32_t refill_min;  // refill a wave's idle lanes once at least this many are idle
     int32_t lb_ntb;      // future-days bound table: time blocks (0 = no bound)
-    int32_t walk_at;     // float64: byte offset of the wavefronts' row arrays in LDS (0: none)
+    int32_t walk_at;     // float64: byte offset of the wavefronts' row arrays in LDS
     int32_t lb_sh;       // days per time block = 2^lb_sh
 };
 
@@ -373,6 +373,13 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
     float thv[8];
     bool mid = true;
     double acc = 0.0;
+    int rows = 0;  // gathered for a walk
+    auto put_row = [&](int slot, int64_t sample) {
+        walk.rq[slot] = sample;
+        walk.rix[slot] = a.first + (uint64_t)sample;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) walk.rth[8 * slot + j] = thv[j];
+    };
     while (true) {
         const uint64_t m = __ballot(t == 0);
         if (qb < Q && __popcll(m) >= F64_REFILL) {
@@ -385,15 +392,9 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
                 if (!PRIOR && a.box && outside_box(a, thv)) {
                     a.dist[k] = INFINITY;
                     if (a.dist64) a.dist64[k] = (double)INFINITY;
-                } else if (!PRIOR && negative_start(thv)) {
-                    const double dd = simulate_negative_f64<NOISE, DIST>(
-                        theta_from(thv), a.first + (uint64_t)k, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T,
-                        scale, lobs, &tab, a.exit_f64);
-                    a.dist[k] = (float)dd;
-                    if (a.dist64) a.dist64[k] = dd;
                 } else {
                     s = init_state(thv[7], a.P, a.A0, a.R0, a.D0);
-                    mid = theta_mid(thv);
+                    mid = theta_mid(thv) && (PRIOR || !negative_start(thv));
                     ph.begin(a.first + (uint64_t)k, ps.u0, a.key);
                     acc = 0.0;
                     t = 1;
@@ -407,27 +408,13 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
             continue;
         }
         const int nr = __popcll(live);
-        if (qb >= Q && nr <= F64_WALK_ROWS && a.walk_at > 0) {
+        if (qb >= Q && nr <= F64_WALK_ROWS) {
             int left = t != 0 ? T - t + 1 : 0;
 #pragma unroll
             for (int off = 32; off; off >>= 1) left = max(left, __shfl_xor(left, off, 64));
             if (left * F64_WALK_GAIN > T + F64_WALK_GAIN * 4) {
-                if (t != 0) {
-                    const int slot = mask_rank(live);
-                    walk.rq[slot] = k;
-                    walk.rix[slot] = a.first + (uint64_t)k;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) walk.rth[8 * slot + j] = thv[j];
-                }
-                wave_lds_sync();
-                const double dd = simulate_rows_f64_wave<NOISE, DIST, true>(
-                    nr, walk.rth, walk.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T, scale, lobs, tab,
-                    walk.zs, walk.xs, a.exit_f64);
-                if (lane < nr) {
-                    const int64_t q = walk.rq[lane];
-                    a.dist[q] = (float)dd;
-                    if (a.dist64) a.dist64[q] = dd;
-                }
+                if (t != 0) put_row(mask_rank(live), k);
+                rows = nr;
                 break;
             }
         }
@@ -435,19 +422,20 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
             const uint4 w = ph.day(ctr_word3((uint32_t)t, a.domain, 0), ps.b1, a.key);
             double z[5];
             normals_f64(w, tab, z);
-            day_step_f64<NOISE>(s, theta_from(thv), mid, Pd, rP, scale, z, tab);
+            day_step_f64<NOISE, !PRIOR>(s, theta_from(thv), mid, Pd, rP, scale, z, tab);
             const int32_t X[3] = {s.A, s.R, s.D};
             double lx[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 lx[c] = DIST == 0 ? log1p_count_f64(X[c], tab) : (double)X[c];
+                if (DIST == 0 && !PRIOR && !mid && X[c] < 0) lx[c] = log1p_general((double)X[c]);
                 const double d = lx[c] - lobs[c * T + t - 1];
                 acc += d * d;
             }
             // the days still to come, bounded below in float32 with its own
             // margins: a sample it ends would have passed the exit bound
             float lb = 0.0f;
-            if (DIST == 0 && ntb > 0) {
+            if (DIST == 0 && ntb > 0 && (PRIOR || mid)) {  // (counts of 0 or more)
                 lb = future_bound(lb_at + (uint32_t)sizeof(float) * 2 * LB_Q * (uint32_t)(t >> a.lb_sh),
                                   (float)(lx[1] * LOG2E), (float)(lx[2] * LOG2E));
             }
@@ -462,6 +450,16 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
                 ++t;
             }
         }
+    }
+    if (rows == 0) return;
+    wave_lds_sync();
+    const double dd = simulate_rows_f64_wave<NOISE, DIST, true>(
+        rows, walk.rth, walk.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T, scale, lobs, tab, walk.zs,
+        walk.xs, a.exit_f64);
+    if (lane < rows) {
+        const int64_t q = walk.rq[lane];
+        a.dist[q] = (float)dd;
+        if (a.dist64) a.dist64[q] = dd;
     }
 }
 
@@ -708,7 +706,7 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
     float thv[8];
     load_or_draw_theta(a, false, k, i, thv);
     const Theta th = theta_from(thv);
-    const bool mid = theta_mid(thv);
+    const bool mid = theta_mid(thv) && !negative_start(thv);
     const double rP = 1.0 / (double)a.P;
     State s = init_state(th.ka, a.P, a.A0, a.R0, a.D0);
     int32_t* out = a.traj + (int64_t)6 * (a.T + 1) * k;
@@ -722,9 +720,7 @@ __global__ __launch_bounds__(SIM_BLOCK) void k_record(SimArgs a)
             if (F64) {
                 double z[5];
                 normals_f64(w, tab, z);
-                // (the power's logarithm is of a count of one or more)
-                const bool in_range = negative ? mid && s.A + s.R + s.D > 0 : mid;
-                day_step_f64<NOISE, negative>(s, th, in_range, (double)a.P, rP, (double)a.scale, z, tab);
+                day_step_f64<NOISE, negative>(s, th, mid, (double)a.P, rP, (double)a.scale, z, tab);
             } else {
                 Noise32 z;
                 normals_f32(w, nc, z);
@@ -950,7 +946,10 @@ static void launch_f32(const SimArgs& a, bool prior, hipStream_t s)
     launch_f32_spl<NOISE, DIST, KAHAN, 1>(a, prior, s);
 }
 
-// tables, observed series, the future-days bound and the space that builds it
+// tables, observed series, the future-days bound and the space that builds it; the
+// row arrays of the wavefronts come after them (60 KB together for the longest series
+// without the bound)
+constexpr size_t F64_WALK_LDS = (F64_BLOCK / 64) * F64_WALK_BYTES;
 static size_t f64_lds_bytes(int T, int lb_ntb)
 {
     return sizeof(Math64) + sizeof(double) * 3 * (size_t)T +
@@ -963,13 +962,8 @@ template <int NOISE, int DIST>
 static void launch_f64(const SimArgs& args, bool prior, hipStream_t s)
 {
     SimArgs a = args;
-    size_t lds = f64_lds_bytes(a.T, a.lb_ntb);
-    // the walk's arrays where they fit beside a long series' tables
-    const size_t walk = (F64_BLOCK / 64) * F64_WALK_BYTES;
-    if (lds + walk <= max_lds_per_block()) {
-        a.walk_at = (int32_t)lds;
-        lds += walk;
-    }
+    a.walk_at = (int32_t)f64_lds_bytes(a.T, a.lb_ntb);
+    const size_t lds = (size_t)a.walk_at + F64_WALK_LDS;
     const dim3 g(refill_grid(a.n, F64_BLOCK, F64_BLOCKS_PER_CU)), b(F64_BLOCK);
     if (prior)
         hipLaunchKernelGGL((k_simulate_f64<NOISE, DIST, true>), g, b, lds, s, a);
@@ -1053,7 +1047,7 @@ extern "C" abc_status abc_simulate_distance(const abc_series* ser, const abc_mod
         while ((a.T >> sh) + 1 > LB_MAX_BLOCKS) ++sh;
         a.lb_sh = sh;
         a.lb_ntb = (a.T >> sh) + 1;
-        const size_t need = (model->flags & ABC_FP64) ? f64_lds_bytes(a.T, a.lb_ntb)
+        const size_t need = (model->flags & ABC_FP64) ? f64_lds_bytes(a.T, a.lb_ntb) + F64_WALK_LDS
                                                       : refill_lds_bytes(a.T, g_launch.block, a.lb_ntb);
         if (need > max_lds_per_block()) a.lb_ntb = 0;
     }
