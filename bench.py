@@ -670,10 +670,12 @@ def main():
         abc.set_launch_config(*[int(x) for x in args.launch.split(",")])
     elif not args.per_series_launches:
         # two 1024-thread workgroups per CU (eight wavefronts per SIMD at the
-        # kernel's 57 VGPRs); each gets half the LDS, so the bound tables are
+        # kernel's registers); each gets half the LDS, so the bound tables are
         # coarser in time than at one workgroup per CU, but the step is
         # fastest here (same-box sweep of (spl, block, workgroups/CU): ms per
-        # step 1.73 at (1, 1024, 2), 1.78 at (1, 512, 2), 1.99 at (1, 1024, 1))
+        # step 1.45 at (1, 1024, 2), 1.51 at (1, 512, 2) and (1, 1024, 1), 1.47
+        # to 1.55 at (1, 512, 4)). It is also what the library chooses by itself
+        # (1.45); stated here so that the committed counters name their shape
         abc.set_launch_config(1, 1024, 2)
     if args.refill_min:
         abc.set_refill_min(args.refill_min)

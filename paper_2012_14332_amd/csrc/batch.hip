@@ -581,10 +581,10 @@ __device__ void bitonic_sort(int64_t* key, float* val, int n_pow2)
 // own). k_batch_band is a persistent grid of one-wavefront workgroups that
 // take chunks of up to rows_max rows of one series from a global counter and
 // simulate them in float64 side by side (simulate_rows_f64_wave: each row's
-// distance is the double simulate_one_f64 gives), so every walk but the last
-// of a series is full and no wavefront waits on another's series. A decided
-// row keeps its float64 distance (as float); a rejected one gets idx
-// INT64_MAX, which sorts it last.
+// distance is the double that k_simulate_f64's days, day_step_f64, give), so
+// every walk but the last of a series is full and no wavefront waits on
+// another's series. A decided row keeps its float64 distance (as float); a
+// rejected one gets idx INT64_MAX, which sorts it last.
 constexpr int COLLECT_GROUPS = 4;  // workgroups of 256 per series in the collection
 
 __global__ __launch_bounds__(256) void k_band_collect(FinalArgs f)

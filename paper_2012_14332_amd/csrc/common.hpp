@@ -21,7 +21,7 @@ constexpr int64_t ROW_WAVE_TARGET = 1024;
 // Candidates a band-decision wavefront scans at least: beside a float32
 // launch a few in-band rows (about a quarter of the candidates) share a
 // wavefront; larger blocks (16, 32) slowed the float32 launches beside them
-// (packed wavefronts live longer); alone the rows are spread for the
+// (packed wavefronts live longer); alone about one row a wavefront, for the
 // shortest latency.
 constexpr int32_t ROW_SCAN_BESIDE = 8;
 constexpr int32_t ROW_SCAN_ALONE = 4;

@@ -224,12 +224,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_compact(CompactArgs a)
 // kernel above; the streaming pass has no ticket and no look-back to wait on.
 // ---------------------------------------------------------------------------
 constexpr int CP_CHUNKS = 16;                        // 4096-sample steps per unit, at most
-constexpr int CP_UNITS = 4096;                       // units per input, at least, while steps last
+constexpr int CP_UNITS = 4096;                       // units per input, at most, while steps last
 constexpr int CP_SLOTS = 64;                         // accepted offsets kept per unit
 constexpr int CP_WAVES = 4;                          // wavefronts per workgroup
-// An input is cut into about CP_UNITS units, of one step to CP_CHUNKS, so that it
-// spreads over many wavefronts and a unit that holds more accepts than kept
-// offsets is short to stream again. With 16 steps above 2^22 samples the count of
+// Up to CP_UNITS * 4096 samples a unit is one step; from there to CP_CHUNKS steps an
+// input is 2049 to 4096 units, so that it spreads over many wavefronts and a unit that
+// holds more accepts than kept offsets is short to stream again. With 16 steps above 2^22 samples the count of
 // 1e7 was 152 wavefronts, 27 us (now 11), and the whole compaction of 1e7 samples
 // with 5e4 accepts 320 us (now 34).
 

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(FEAT_BLOCK) void k_feat_place(FeatArgs a, FeatOrder
 // days are kept in LDS and stored together, so that every store fills a 32-byte
 // sector (4-byte stores 384 bytes apart, and lanes waiting for the longest
 // horizon of 64 with three float64 logarithms on almost every day, took
-// 3.8 ms for 1e6 pairs of T in [30, 200]; now 0.69 ms).
+// 3.8 ms for 1e6 pairs of T in [30, 200]; now 0.65 ms).
 constexpr int FEAT_HOLD = 8;
 
 __global__ __launch_bounds__(FEAT_BLOCK) void k_mdn_features(FeatArgs a, const int32_t* order, const uint32_t* total)
@@ -508,9 +508,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // (4 us of issue on a full chip at a batch of 4096); 16 rows, not 32 or 64, so
 // that such a batch is a workgroup for each of the 256 CUs, and sixteen
 // wavefronts rather than eight because the error functions branch and their
-// chains want company (20 us then). 18 us at a batch of 4096, 13 at 64; with the
-// weight gradients 31 us a step, where seven kernels with the activations in
-// memory between them took 68.
+// chains want company (at least 20 us then, 18.1 so). 19.4 us in the mean at a batch
+// of 4096, 12 at 64; with the weight gradients 33.6 us a step, where seven kernels
+// with the activations in memory between them took 70.5.
 // ----------------------------------------------------------------------------
 constexpr int R_ROWS = 16, R_WAVES = 16, R_BLOCK = 64 * R_WAVES;
 constexpr int R_LX = NN_IN + 8, R_LH = NN_H + 8, R_LO = NN_OUT + 4, R_LD = 32 * KF_OUT + 8;

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(1024 / SPL, SPL == 1 ? 7 : 1) void k_simulate_f32(S
 // four cycles each. With one lane per sample for the whole launch, early exits
 // left most lanes idle behind the longest trajectory of their wavefront: 1e6
 // samples of T = 100 at the 1e-3 quantile took 3.46 ms (with the library's
-// functions), now 0.73 ms.
+// functions), now 0.66 ms.
 constexpr int F64_BLOCK = 512;
 constexpr int F64_REFILL = 8;
 constexpr int F64_BLOCKS_PER_CU = 1;
@@ -296,8 +296,9 @@ constexpr int F64_BLOCKS_PER_CU = 1;
 // again from their first day, four lanes each as the rows of a band decision, if
 // that is sooner than their days to come: a day takes a lane 3 us, whose
 // instructions wait for each other, and eight rows 0.7. T = 100 at the 1e-3
-// quantile, with all that follows: 1e4 samples 310 -> 205 us, 1e5 308 -> 220, 1e6
-// 765 -> 715; with four rows 225, 267 and 726, with sixteen 196, 224 and 723.
+// quantile, when the walk came: 1e4 samples 310 -> 205 us, 1e5 308 -> 220, 1e6
+// 765 -> 715 (the last is 664 now); with four rows 225, 267 and 726, with sixteen
+// 196, 224 and 723.
 constexpr int F64_WALK_ROWS = 8;
 
 constexpr int F64_WALK_GAIN = 4;  // days of a row in the time of a lane's day
@@ -506,9 +507,10 @@ __device__ __forceinline__ RowLds row_lds(double* base, int T, int R)
 // ROWS_PER_WAVE_MAX rows that are simulated side by side in float64
 // (simulate_rows_f64_wave); the others only get their keep flag. A large
 // scan_min packs the in-band rows into few wavefronts, so that they take few
-// issue slots from a float32 launch running beside them; scan_min = 1
-// spreads them for the shortest latency. Workgroups that meet no in-band row
-// never stage the observed series.
+// issue slots from a float32 launch running beside them; ROW_SCAN_ALONE
+// gives a wavefront about one of them, for the shortest latency (a quarter of the
+// candidates is in the band). Workgroups that meet no in-band row never stage the
+// observed series.
 template <int NOISE, int DIST>
 __device__ __forceinline__ void recheck_group(const RecheckArgs& r, const RowLds& l, int nr,
                                               bool& staged)
