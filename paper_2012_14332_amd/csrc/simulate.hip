@@ -288,7 +288,7 @@ __global__ __launch_bounds__(1024 / SPL, SPL == 1 ? 7 : 1) void k_simulate_f32(S
 // four cycles each. With one lane per sample for the whole launch, early exits
 // left most lanes idle behind the longest trajectory of their wavefront: 1e6
 // samples of T = 100 at the 1e-3 quantile took 3.46 ms (with the library's
-// functions), now 0.66 ms.
+// functions), now 0.67 ms.
 constexpr int F64_BLOCK = 512;
 constexpr int F64_REFILL = 8;
 constexpr int F64_BLOCKS_PER_CU = 1;
@@ -297,7 +297,7 @@ constexpr int F64_BLOCKS_PER_CU = 1;
 // that is sooner than their days to come: a day takes a lane 3 us, whose
 // instructions wait for each other, and eight rows 0.7. T = 100 at the 1e-3
 // quantile, when the walk came: 1e4 samples 310 -> 205 us, 1e5 308 -> 220, 1e6
-// 765 -> 715 (the last is 664 now); with four rows 225, 267 and 726, with sixteen
+// 765 -> 715 (the last is 672 now); with four rows 225, 267 and 726, with sixteen
 // 196, 224 and 723.
 constexpr int F64_WALK_ROWS = 8;
 
@@ -381,6 +381,17 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
 #pragma unroll
         for (int j = 0; j < 8; ++j) walk.rth[8 * slot + j] = thv[j];
     };
+    auto walk_rows = [&](int nr) {
+        wave_lds_sync();
+        const double dd = simulate_rows_f64_wave<NOISE, DIST, true>(
+            nr, walk.rth, walk.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T, scale, lobs, tab, walk.zs,
+            walk.xs, a.exit_f64);
+        if (lane < nr) {
+            const int64_t q = walk.rq[lane];
+            a.dist[q] = (float)dd;
+            if (a.dist64) a.dist64[q] = dd;
+        }
+    };
     while (true) {
         const uint64_t m = __ballot(t == 0);
         if (qb < Q && __popcll(m) >= F64_REFILL) {
@@ -415,7 +426,11 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
             for (int off = 32; off; off >>= 1) left = max(left, __shfl_xor(left, off, 64));
             if (left * F64_WALK_GAIN > T + F64_WALK_GAIN * 4) {
                 if (t != 0) put_row(mask_rank(live), k);
-                rows = nr;
+                // where the walk's code stands decides the registers of the days: behind
+                // the loop it is 2 to 3 % sooner with given parameters, where many reach the
+                // last day; prior draws with exits 1 to 3 % sooner with it here
+                if (PRIOR) walk_rows(nr);
+                else rows = nr;
                 break;
             }
         }
@@ -452,16 +467,7 @@ __global__ __launch_bounds__(F64_BLOCK) void k_simulate_f64(SimArgs a)
             }
         }
     }
-    if (rows == 0) return;
-    wave_lds_sync();
-    const double dd = simulate_rows_f64_wave<NOISE, DIST, true>(
-        rows, walk.rth, walk.rix, a.key, a.series, a.domain, a.P, a.A0, a.R0, a.D0, T, scale, lobs, tab, walk.zs,
-        walk.xs, a.exit_f64);
-    if (lane < rows) {
-        const int64_t q = walk.rq[lane];
-        a.dist[q] = (float)dd;
-        if (a.dist64) a.dist64[q] = dd;
-    }
+    if (rows > 0) walk_rows(rows);
 }
 
 // Float64 decision for the candidates of a float32 pass (compacted at
